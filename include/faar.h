@@ -534,13 +534,13 @@ int faar_rope(const void* x, int64_t T, int64_t H, int64_t dh, const float* cos_
  *   q in bf16 [T * n_q * dh], k, v in bf16 [T * n_kv * dh], T = n_seq * S tokens, sequence b = rows b*S .. (b+1)*S - 1;
  *   o out bf16 [T * n_q * dh]; lse out float [n_q * T]: log of the softmax denominator per head and query (for the backward).
  *   S % 32 == 0, dh 64 or 128, n_q % n_kv == 0, scale > 0.  float32 arithmetic, probabilities rounded to bf16 as matrix-core
- *   operands.  ws: FAAR_OP_ATTENTION_FWD (a transposed copy of v). */
+ *   operands.  ws: FAAR_OP_ATTENTION_FWD (required; its contents are not used). */
 int faar_attention_fwd(const void* q, const void* k, const void* v, int64_t n_seq, int64_t S, int64_t n_q, int64_t n_kv,
                        int64_t dh, float scale, void* o, float* lse, void* ws, size_t ws_bytes, void* stream);
 
 /* (dq, dk, dv) of the above for the output gradient d_o (bf16 [T * n_q * dh]); o and lse from the forward call.
  *   dq out bf16 [T * n_q * dh]; dk, dv out bf16 [T * n_kv * dh] (summed over the query heads of a group in a fixed order).
- *   ws: FAAR_OP_ATTENTION_BWD (transposed copies of q, k, d_o and one float per head and query). */
+ *   ws: FAAR_OP_ATTENTION_BWD (one float per head and query is used). */
 int faar_attention_bwd(const void* d_o, const void* q, const void* k, const void* v, const void* o, const float* lse,
                        int64_t n_seq, int64_t S, int64_t n_q, int64_t n_kv, int64_t dh, float scale, void* dq, void* dk,
                        void* dv, void* ws, size_t ws_bytes, void* stream);

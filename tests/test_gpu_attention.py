@@ -118,6 +118,24 @@ def test_attention_forward_and_backward(n_seq, S, n_q, n_kv, dh):
     near(dk, dk_w, "dk", norm=5e-3, elem=8e-2)
 
 
+# a last key block of 32 instead of 64 and a short last group of 128 positions, at either head width; and more than 256
+# workgroups of several ranks, so that the second round of resident workgroups (taken from light to heavy) is entered
+@pytest.mark.parametrize("n_seq,S,n_q,n_kv,dh", [(1, 224, 2, 1, 128), (2, 288, 4, 4, 64), (8, 1184, 4, 4, 64)])
+def test_attention_at_the_edges_of_its_blocks(n_seq, S, n_q, n_kv, dh):
+    q, k, v, do = _attn_inputs(n_seq, S, n_q, n_kv, dh, 3)
+    o, lse = faar.faar_attention_fwd(dev(q), dev(k), dev(v), n_seq, n_q, n_kv)
+    dq, dk, dv = faar.faar_attention_bwd(dev(do), dev(q), dev(k), dev(v), o, lse, n_seq, n_q, n_kv)
+    o_want, P = bo.attention(q, k, v, n_seq, n_q, n_kv, dh, dh ** -0.5)
+    dq_w, dk_w, dv_w = bo.attention_backward(do, q, k, v, P, n_seq, n_q, n_kv, dh, dh ** -0.5)
+    # norm-wise, over everything and over the last 32 positions of the sequences alone (where the short blocks are): a misplaced
+    # row or mask is an error of order one there.  The norms are those of the test above: at most three bf16 roundings of rms
+    # 2^-9 / sqrt(3) each, on terms that cancel by up to a factor of two in dq and dk.
+    last = (np.arange(n_seq * S) % S) >= S - 32
+    for got, want, name, norm in ((o, o_want, "o", 2.5e-3), (dv, dv_w, "dv", 3e-3), (dq, dq_w, "dq", 5e-3), (dk, dk_w, "dk", 5e-3)):
+        near(got, want, name, norm=norm, elem=np.inf)
+        near(host(got)[last], want[last], name + " at the end", norm=norm, elem=np.inf)
+
+
 def test_attention_is_causal_and_sequences_are_independent():
     """Properties that hold at any size: later tokens and other sequences do not influence an output row."""
     n_seq, S, n_q, n_kv, dh = 2, 96, 4, 2, 128
