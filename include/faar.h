@@ -114,14 +114,12 @@ enum {
   FAAR_K_GEMM_GRAM = 14      /* (W_q - W) (X_q^T X_q), loss, gradient   (faar_layer_step_gram) */
 };
 
-/* GEMM kernel variants, as reported by faar_gemm_plan */
+/* GEMM kernel variants (output tiles), as reported by faar_gemm_plan */
 enum {
-  FAAR_GEMM_GENERIC = 0,  /* register-staged 128x128 tile, any contraction length */
-  FAAR_GEMM_L = 1,        /* contraction % 32 == 0: direct-to-LDS ring of 32-wide slices, 256x256 tile */
-  FAAR_GEMM_M = 2,        /*   256x128 tile */
-  FAAR_GEMM_S = 3,        /*   128x128 tile */
-  FAAR_GEMM_L64 = 4,      /* contraction % 64 == 0: 64-wide slices, 256x256 tile */
-  FAAR_GEMM_M64 = 5       /*   256x128 tile */
+  FAAR_GEMM_L64 = 0, /* 256x256 tile */
+  FAAR_GEMM_M64 = 1, /* 256x128 tile */
+  FAAR_GEMM_S64 = 2, /* 128x128 tile */
+  FAAR_GEMM_N64 = 3  /* 128x64 tile */
 };
 
 /* Library version, MAJOR*10000 + MINOR*100 + PATCH.  Pure host function. */

@@ -10,21 +10,14 @@
 // token-major form (acc[m][n] = sum_t A[t][m] B[t][n], LDS transposing reads) that takes dY and X_q as
 // they are.
 //
-// Three main loops:
-//  * k_gemm_dma64 (contraction length a multiple of 64 -- every GEMM of an LLM-shaped layer): 256x256 or
-//    256x128 output tile per 512-thread workgroup (8 wavefronts, 2 per SIMD), BK = 64 slices copied
-//    global -> LDS by global_load_lds_dwordx4 (no VGPR staging) into two or three stages, 128-byte LDS rows,
-//    v_mfma_f32_16x16x32_bf16, one workgroup barrier per slice.  Described at the kernel.
-//  * k_gemm_dma (contraction length a multiple of 32, and all 128x128 tiles): BK = 32 slices in a 4-stage
-//    ring; LDS rows are 64 B, un-padded, with the 16-byte chunk index XOR-swizzled by (row / 4) % 4 so that the
-//    fragment reads of 16 consecutive rows hit 16 distinct bank groups (measured: zero LDS bank conflicts);
-//    fragments are prefetched one MFMA phase ahead, also across the slice boundary, and the ds_reads / DMA
-//    issues are interleaved one by one between the v_mfma_f32_32x32x16_bf16 instructions.
-//    In both, workgroups are dealt to the 8 XCDs in contiguous chunks of a grouped tile order so that each
-//    XCD's L2 sees a compact sub-grid.
-//  * k_gemm_nt (generic fallback for ragged contraction lengths): 128x128 tile, register-staged,
-//    padded LDS, bounds-checked loads.
+// One main loop, k_gemm_dma64: slices of 64 of the contraction copied global -> LDS by global_load_lds_dwordx4 (no VGPR
+// staging) into a ring of stages, 128-byte LDS rows, v_mfma_f32_16x16x32_bf16, one workgroup barrier per slice.  Described at
+// the kernel.  Four tile shapes (plan_gemm): 256x256 and 256x128 with 8 wavefronts for products that fill the chip with them,
+// 128x128 and 128x64 with a deep ring and the contraction shared out inside the workgroup for those that do not.  A contraction that is not a multiple of 64 ends
+// in a slice whose missing chunks are copied from zeros.  Workgroups are dealt to the 8 XCDs in contiguous chunks of a grouped
+// tile order so that each XCD's L2 sees a compact sub-grid.
 #include <algorithm>
+#include <type_traits>
 
 #include "faar_internal.h"
 
@@ -32,132 +25,7 @@ namespace faar {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int BK = 64;            // contraction slice per stage
-constexpr int LDS_LD = BK + 8;    // padded LDS row, elements (144 B)
-constexpr int GEMM_THREADS = 256;
-
-template <int BM_, int BN_>
-struct Tile {
-  static constexpr int BM = BM_, BN = BN_;
-  static constexpr int WM = BM / 2, WN = BN / 2;   // 2 x 2 wavefronts
-  static constexpr int TM = WM / 32, TN = WN / 32; // 32x32 MFMA tiles per wavefront
-  static constexpr int A_CHUNKS = BM * (BK / 8) / GEMM_THREADS;  // 16-byte chunks per thread
-  static constexpr int B_CHUNKS = BN * (BK / 8) / GEMM_THREADS;
-  static constexpr int STAGE = (BM + BN) * LDS_LD;               // elements per LDS stage
-};
-
-// Output coordinates held by one lane for accumulator register v of a 32x32 tile:
-// column = lane % 32, row = 8 * (v / 4) + 4 * (lane / 32) + v % 4.
-struct Out {
-  int64_t M, N;
-};
-
-template <class T, class Epi>
-__global__ void __launch_bounds__(GEMM_THREADS)
-k_gemm_nt(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d, int tiles_m, int tiles_n,
-          int64_t k_per_split, Epi epi) {
-  __shared__ __attribute__((aligned(16))) bf16_t lds[2 * T::STAGE];
-  epi.once();
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * T::WM, wn = (wave & 1) * T::WN;
-
-  int pid = blockIdx.x;
-  const int split = pid / (tiles_m * tiles_n);
-  pid -= split * tiles_m * tiles_n;
-  const int tm = pid % tiles_m, tn = pid / tiles_m;   // consecutive workgroups share the B panel
-  const int64_t m0 = (int64_t)tm * T::BM, n0 = (int64_t)tn * T::BN;
-  const int64_t k_begin = split * k_per_split;
-  const int64_t k_end = k_begin + k_per_split < d.Kd ? k_begin + k_per_split : d.Kd;
-  const int nk = static_cast<int>((k_end - k_begin + BK - 1) / BK);
-
-  uint4 ra[T::A_CHUNKS], rb[T::B_CHUNKS];
-  auto g_load = [&](int kt) {
-    const int64_t k0 = k_begin + (int64_t)kt * BK;
-#pragma unroll
-    for (int j = 0; j < T::A_CHUNKS; ++j) {
-      const int c = tid + j * GEMM_THREADS, row = c >> 3, kc = (c & 7) * 8;
-      const int64_t m = m0 + row, k = k0 + kc;
-      ra[j] = (m < d.M && k < k_end) ? *reinterpret_cast<const uint4*>(A + m * d.lda + k) : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < T::B_CHUNKS; ++j) {
-      const int c = tid + j * GEMM_THREADS, row = c >> 3, kc = (c & 7) * 8;
-      const int64_t n = n0 + row, k = k0 + kc;
-      rb[j] = (n < d.N && k < k_end) ? *reinterpret_cast<const uint4*>(B + n * d.ldb + k) : make_uint4(0, 0, 0, 0);
-    }
-  };
-  auto s_store = [&](int stage) {
-    bf16_t* sa = lds + stage * T::STAGE;
-    bf16_t* sb = sa + T::BM * LDS_LD;
-#pragma unroll
-    for (int j = 0; j < T::A_CHUNKS; ++j) {
-      const int c = tid + j * GEMM_THREADS, row = c >> 3, kc = (c & 7) * 8;
-      *reinterpret_cast<uint4*>(sa + row * LDS_LD + kc) = ra[j];
-    }
-#pragma unroll
-    for (int j = 0; j < T::B_CHUNKS; ++j) {
-      const int c = tid + j * GEMM_THREADS, row = c >> 3, kc = (c & 7) * 8;
-      *reinterpret_cast<uint4*>(sb + row * LDS_LD + kc) = rb[j];
-    }
-  };
-
-  f32x16 acc[T::TM][T::TN];
-#pragma unroll
-  for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < T::TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  if (nk > 0) {
-    g_load(0);
-    s_store(0);
-  }
-  __syncthreads();
-  const int frag_row = lane & 31, frag_k = (lane >> 5) * 8;
-  for (int kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) g_load(kt + 1);
-    const bf16_t* sa = lds + (kt & 1) * T::STAGE;
-    const bf16_t* sb = sa + T::BM * LDS_LD;
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 16) {
-      bf16x8 fa[T::TM], fb[T::TN];
-#pragma unroll
-      for (int i = 0; i < T::TM; ++i)
-        fa[i] = *reinterpret_cast<const bf16x8*>(sa + (wm + i * 32 + frag_row) * LDS_LD + kk + frag_k);
-#pragma unroll
-      for (int j = 0; j < T::TN; ++j)
-        fb[j] = *reinterpret_cast<const bf16x8*>(sb + (wn + j * 32 + frag_row) * LDS_LD + kk + frag_k);
-#pragma unroll
-      for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < T::TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nk) s_store((kt + 1) & 1);
-    __syncthreads();
-  }
-
-  // epilogue: hand every group of 4 consecutive rows (one column) to the functor
-  epi.begin();
-  const int col = lane & 31, hi = lane >> 5;
-#pragma unroll
-  for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < T::TN; ++j) {
-      const int64_t n = n0 + wn + j * 32 + col;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int64_t m = m0 + wm + i * 32 + 8 * g + 4 * hi;
-        const float r[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-        epi.rows4(r, m, n, split, d);
-      }
-    }
-  epi.finish(blockIdx.x);
-}
 
 // ---- epilogues -----------------------------------------------------------------------------
 
@@ -186,6 +54,7 @@ struct EpiResidualT {
   static constexpr bool kRowStaged = false;
   static constexpr bool kTransposedOut = true;  // the fast kernel stages dYt through LDS for full-line stores
   static constexpr int kMode = 0;               // 0: the whole main loop (1, 2: measurement variants, see EpiProbe)
+  static constexpr bool kPaddedContraction = false;
   // The GEMM that follows (dW = dY^T X_q) reads X_q^T, which the pass that updates V has meanwhile pushed out of the
   // last-level cache; with either operand coming from HBM that GEMM runs ~25 % slower.  The BK = 64 main loop of this
   // kernel therefore reads `warm` (X_q^T, warm_chunks KB) on the side, 1 KB per wavefront and slice, and keeps nothing.
@@ -256,6 +125,7 @@ struct EpiPerturbationRows {
   static constexpr bool kRowStaged = true;
   static constexpr bool kWarm = false;
   static constexpr int kMode = 0;
+  static constexpr bool kPaddedContraction = false;
   const float* x_scale;
   float xs;
   ForwardGuard guard;
@@ -303,6 +173,7 @@ struct EpiSumSq {
   static constexpr bool kWarm = false;
   static constexpr bool kTransposedOut = false;
   static constexpr int kMode = 0;
+  static constexpr bool kPaddedContraction = false;
   const float* x_scale;
   float xs;
   ForwardGuard guard;
@@ -332,9 +203,10 @@ struct EpiSumSq {
 // out[split][m][n] = acc
 struct EpiF32 {
   static constexpr bool kWarm = false;
-  static constexpr bool kRowStaged = true;   // the BK = 64 kernel hands it runs of 8 columns of a row (run8)
+  static constexpr bool kRowStaged = true;   // the main loop hands it runs of 8 columns of a row (run8)
   static constexpr bool kTransposedOut = false;
   static constexpr int kMode = 0;
+  static constexpr bool kPaddedContraction = true;   // its contractions are padded token counts, multiples of 64
   float* out;
   __device__ __forceinline__ void once() {}
   __device__ __forceinline__ void begin() {}
@@ -365,6 +237,7 @@ struct EpiSub {
   static constexpr bool kWarm = false;
   static constexpr bool kTransposedOut = false;
   static constexpr int kMode = 0;
+  static constexpr bool kPaddedContraction = false;
   const void* Y;
   bool first;
   float* C_out;
@@ -397,10 +270,11 @@ struct EpiSub {
 
 // out[m][n] = bf16(scale * acc)
 struct EpiBf16 {
-  static constexpr bool kRowStaged = true;    // the DMA kernels hand it runs of 8 columns of a row (run8)
+  static constexpr bool kRowStaged = true;    // the main loop hands it runs of 8 columns of a row (run8)
   static constexpr bool kWarm = false;
   static constexpr bool kTransposedOut = false;
   static constexpr int kMode = 0;
+  static constexpr bool kPaddedContraction = false;
   bf16_t* out;
   const float* scale;   // device scalar multiplying the product (activations stored in units of it); null = 1
   float sc;
@@ -437,6 +311,7 @@ struct EpiGram {
   static constexpr bool kRowStaged = true;
   static constexpr bool kTransposedOut = false;
   static constexpr int kMode = 0;
+  static constexpr bool kPaddedContraction = false;
   const bf16_t* delta;     // the A operand, [M, N] row-major
   const float* diag_lo;    // [N]
   const float* x_scale;
@@ -505,6 +380,7 @@ struct EpiProbe {
   static constexpr bool kWarm = false;
   static constexpr bool kRowStaged = false;
   static constexpr int kMode = MODE;
+  static constexpr bool kPaddedContraction = false;
   unsigned long long* clocks;   // [items][2]
   float* sink;
   long long t0, w0;
@@ -523,27 +399,7 @@ struct EpiProbe {
   }
 };
 
-// ---- fast path: direct-to-LDS ring, swizzled LDS, interleaved schedule ------------------------------
-
-constexpr int DBK = 32;   // contraction slice per stage
-constexpr int DNS = 4;    // ring stages
-
-template <int BM_, int BN_, int WGM_, int WGN_>
-struct DmaCfg {
-  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
-  static constexpr int NW = WGM * WGN, THREADS = 64 * NW;
-  static constexpr int WM = BM / WGM, WN = BN / WGN;
-  static constexpr int TM = WM / 32, TN = WN / 32;
-  static constexpr int CPR = DBK / 8;            // 16-byte chunks per LDS row (4)
-  static constexpr int RPI = 64 / CPR;           // rows written by one wave-wide DMA instruction (16)
-  static constexpr int RB = 16 / CPR;            // rows per 256-byte bank cycle (4)
-  static constexpr int STAGE = (BM + BN) * DBK;  // elements per stage
-  static constexpr int P = (BM + BN) / RPI / NW; // DMA instructions per wavefront per stage
-  static constexpr int KK = DBK / 16;            // MFMA phases per stage
-  static constexpr int NF = TM + TN, NM = TM * TN;
-  static_assert(NF <= NM, "every phase must have room to prefetch the next phase's fragments");
-  static_assert((BM + BN) % (RPI * NW) == 0 && (KK * NM) / P >= 1, "DMA schedule");
-};
+// ---- main loop: direct-to-LDS ring, swizzled LDS, interleaved schedule ------------------------------
 
 // 16 bytes per lane from global memory straight into LDS at lds_addr + 16 * lane (lds_addr wave-uniform).
 // Written as inline assembly so that the compiler's wait-count bookkeeping for ordinary LDS reads stays
@@ -578,207 +434,20 @@ __device__ __forceinline__ bool item_coords(int pid, int tiles_m, int tiles_n, i
   return true;
 }
 
-template <class C, class Epi>
-__global__ void __launch_bounds__(C::THREADS)
-k_gemm_dma(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d, int tiles_m, int tiles_n, int n_split,
-           int ksteps_per_split, Epi epi) {
-  __shared__ __attribute__((aligned(1024))) bf16_t lds[DNS * C::STAGE];
-  epi.once();
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave / C::WGN) * C::WM, wn = (wave % C::WGN) * C::WN;
-  int tm, tn, split, item;
-  if (!item_coords(blockIdx.x, tiles_m, tiles_n, n_split, tm, tn, split, item)) return;
-  const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
-  const int ksteps = static_cast<int>(d.Kd / DBK);
-  const int kbeg = split * ksteps_per_split;
-  const int kend = kbeg + ksteps_per_split < ksteps ? kbeg + ksteps_per_split : ksteps;
-  const int nk = kend - kbeg;
-  constexpr int P = C::P, KK = C::KK, NF = C::NF, NM = C::NM;
-
-  f32x16 acc[C::TM][C::TN];
-#pragma unroll
-  for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  if (nk > 0) {
-    // DMA instruction q of this wavefront fills rows [(wave*P + q)*RPI, +RPI) of the stacked [A rows; B rows]
-    // stage: lane -> row = base + lane / CPR, LDS slot = lane % CPR, global chunk = slot ^ ((row / RB) % CPR).
-    // Rows beyond M (or N) are clamped to the last valid row: their products are never stored.
-    const bf16_t* gsrc[P];
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      const int trow = (wave * P + q) * C::RPI + lane / C::CPR;
-      const int chunk = (lane % C::CPR) ^ ((trow / C::RB) % C::CPR);
-      if (trow < C::BM) {
-        const int64_t m = m0 + trow < d.M ? m0 + trow : d.M - 1;
-        gsrc[q] = A + m * d.lda + chunk * 8;
-      } else {
-        const int64_t n = n0 + (trow - C::BM) < d.N ? n0 + (trow - C::BM) : d.N - 1;
-        gsrc[q] = B + n * d.ldb + chunk * 8;
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < DNS - 1; ++s) {
-      const int t = kbeg + (s < nk ? s : nk - 1);
-#pragma unroll
-      for (int q = 0; q < P; ++q)
-        dma16(gsrc[q] + (int64_t)t * DBK,
-              __builtin_amdgcn_readfirstlane(lds_addr_of(lds + s * C::STAGE + (wave * P + q) * C::RPI * DBK)));
-    }
-
-    // fragment addresses: row = w? + i*32 + lane % 32, chunk = 2*kk + lane / 32, slot = chunk ^ ((row / RB) % CPR)
-    const int fr = lane & 31, hi = lane >> 5;
-    const int sw = (fr / C::RB) % C::CPR;
-    int a_off[KK], b_off[KK];
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const int slot = ((2 * kk + hi) ^ sw) * 8;
-      a_off[kk] = (wm + fr) * DBK + slot;
-      b_off[kk] = C::BM * DBK + (wn + fr) * DBK + slot;
-    }
-    bf16x8 fa[2][C::TM], fb[2][C::TN];
-
-    FAAR_WAIT_VMCNT(P * (DNS - 2));  // slice 0 has landed (mine); barrier: everybody's
-    __builtin_amdgcn_s_barrier();
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(lds + a_off[0] + i * 32 * DBK);
-#pragma unroll
-    for (int j = 0; j < C::TN; ++j) fb[0][j] = *reinterpret_cast<const bf16x8*>(lds + b_off[0] + j * 32 * DBK);
-
-    for (int it = 0; it < nk; ++it) {
-      // slice it+1 must have landed before its first fragments are prefetched at the end of this iteration;
-      // the barrier also guarantees that every wavefront has finished reading the stage refilled below.
-      FAAR_WAIT_VMCNT(P * (DNS - 3));
-      __builtin_amdgcn_s_barrier();
-      const bf16_t* st = lds + (it % DNS) * C::STAGE;
-      const bf16_t* st_next = lds + ((it + 1) % DNS) * C::STAGE;
-      const int dma_k = kbeg + (it + DNS - 1 < nk ? it + DNS - 1 : nk - 1);  // past the end: a harmless reload
-      const bf16_t* dma_base = lds + ((it + DNS - 1) % DNS) * C::STAGE + wave * P * C::RPI * DBK;
-      constexpr int DSTEP = (KK * NM) / P;
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        const int cur = kk & 1;
-        const bf16_t* src = (kk + 1 < KK) ? st : st_next;
-        const int nkk = (kk + 1 < KK) ? kk + 1 : 0;
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-          const int mi = m / C::TN, mj = m % C::TN;
-          acc[mi][mj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][mi], fb[cur][mj], acc[mi][mj], 0, 0, 0);
-          if (m < NF) {  // fragment m of the next phase, in the order A0, B0..B(TN-1), A1..A(TM-1)
-            if (m == 0) fa[cur ^ 1][0] = *reinterpret_cast<const bf16x8*>(src + a_off[nkk]);
-            else if (m <= C::TN) fb[cur ^ 1][m - 1] = *reinterpret_cast<const bf16x8*>(src + b_off[nkk] + (m - 1) * 32 * DBK);
-            else fa[cur ^ 1][m - C::TN] = *reinterpret_cast<const bf16x8*>(src + a_off[nkk] + (m - C::TN) * 32 * DBK);
-          }
-          const int g = kk * NM + m;
-          if (g % DSTEP == DSTEP / 2 && g / DSTEP < P) {
-            const int q = g / DSTEP;
-            dma16(gsrc[q] + (int64_t)dma_k * DBK, __builtin_amdgcn_readfirstlane(lds_addr_of(dma_base + q * C::RPI * DBK)));
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-    FAAR_WAIT_VMCNT(0);  // no copy may still be in flight into this workgroup's LDS when it retires
-  }
-
-  epi.begin();
-  const int col = lane & 31, hi2 = lane >> 5;
-  if constexpr (Epi::kTransposedOut) {
-    // Output is wanted transposed ([n][m], m contiguous) while a lane holds 4 consecutive m of one n: stage
-    // one 32-column slab per wavefront column through LDS and write whole 2*BM-byte rows with 16 B per lane.
-    // staging row: BM elements + 4, i.e. a pitch of 2 words more than a multiple of 32: the 16 lanes that write one
-    // 8-byte group of four rows each then fall into 32 distinct LDS banks (a pitch of BM + 8 made rows r and r + 8 collide)
-    constexpr int LDT = C::BM + 4;
-    constexpr int ROWS = C::WGN * 32;       // staged n-rows per pass
-    constexpr int CPRW = C::BM / 8;         // 16-byte chunks per staged row
-    static_assert(ROWS * LDT <= DNS * C::STAGE, "staging buffer fits in the ring");
-    bf16_t* stg = lds;
-    const int wc = wave % C::WGN;
-#pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      __syncthreads();                      // ring (or previous slab) no longer read by anybody
-      const int64_t n = n0 + wn + j * 32 + col;
-      float4 cv[C::TM][4];
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) cv[i][g] = epi.load4(m0 + wm + i * 32 + 8 * g + 4 * hi2, n, d);
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int ml = wm + i * 32 + 8 * g + 4 * hi2;
-          const float r[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-          *reinterpret_cast<uint2*>(stg + (wc * 32 + col) * LDT + ml) = epi.value4(r, cv[i][g], m0 + ml, n, d);
-        }
-      __syncthreads();
-      for (int idx = tid; idx < ROWS * CPRW; idx += C::THREADS) {
-        const int row = idx / CPRW, ch = idx % CPRW;
-        const uint2* src = reinterpret_cast<const uint2*>(stg + row * LDT + ch * 8);   // 8-byte aligned
-        const uint2 lo = src[0], hi = src[1];
-        epi.store_chunk(make_uint4(lo.x, lo.y, hi.x, hi.y), m0 + ch * 8, n0 + (row / 32) * C::WN + j * 32 + (row % 32), d);
-      }
-    }
-  } else if constexpr (Epi::kRowStaged) {
-    // as in k_gemm_dma64: one 32 x WN row of accumulator tiles per wavefront at a time through its own piece of LDS, handed
-    // to the epilogue as runs of 8 consecutive columns of a row
-    constexpr int PITCH = C::WN + 4;
-    constexpr int RUNS = 32 * (C::WN / 8) / 64;
-    static_assert(C::NW * 32 * PITCH * 4 <= DNS * C::STAGE * 2 && (32 * (C::WN / 8)) % 64 == 0, "staging fits in the ring");
-    float* stg = reinterpret_cast<float*>(lds) + wave * 32 * PITCH;
-    __syncthreads();                                 // nobody reads the ring any more
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i) {
-#pragma unroll
-      for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) stg[(8 * g + 4 * hi2 + v) * PITCH + j * 32 + col] = acc[i][j][4 * g + v];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-      for (int t = 0; t < RUNS; ++t) {
-        const int idx = lane + 64 * t, row = idx / (C::WN / 8), cg = idx % (C::WN / 8);
-        const float4 a = *reinterpret_cast<const float4*>(stg + row * PITCH + cg * 8);
-        const float4 b = *reinterpret_cast<const float4*>(stg + row * PITCH + cg * 8 + 4);
-        const float r[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        epi.run8(r, m0 + wm + i * 32 + row, n0 + wn + cg * 8, split, d);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < C::TN; ++j) {
-        const int64_t n = n0 + wn + j * 32 + col;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int64_t m = m0 + wm + i * 32 + 8 * g + 4 * hi2;
-          const float r[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-          epi.rows4(r, m, n, split, d);
-        }
-      }
-  }
-  epi.finish(item);
-}
-
-// ---- fast path for contractions that are a multiple of 64: 128-byte LDS rows, two stages, 16x16x32 MFMAs ----
-//
-// The chip runs this loop power-limited, and two things lower the energy per flop: global->LDS copies whose
+// The chip runs this loop power-limited on large products, and two things lower the energy per flop: global->LDS copies whose
 // eight lanes per row make one 128-byte request (BK = 64) instead of two 64-byte ones, and the 16x16x32 MFMA,
 // which reads and writes a quarter of the accumulator values per instruction of the 32x32x16 form for half
 // its flops.  With BK = 64 only two stages fit next to a 256x256 tile (2 x 64 KB; three for 256x128), so a stage
 // is refilled as soon as the workgroup has read it: ONE barrier per slice, placed before the slice's last MFMA phase, at
 // which point every wavefront holds the last fragments of the slice in registers and the copies of the next
 // slice (issued NS - 1 slices earlier, right after a barrier) have landed.
+// Small tiles are bound by latencies: the time goes with the slices one workgroup walks, not with the bytes or the flops.  They
+// use the LDS that their size leaves for a ring of four or six stages, and a second group of four wavefronts (WGK = 2): each
+// group takes one of a slice's two MFMA phases on the whole tile, so that every SIMD has two wavefronts to switch between
+// without a byte more read from LDS; the groups' sums meet once, at the end.  Measured per slice with about half of the compute
+// units busy, against four wavefronts: 128x128 0.53-0.62 -> 0.31 us, 128x64 0.37 -> 0.21 us.  Against the former
+// kernels for these shapes (BK = 32 slices in a 4-stage ring; register-staged where the contraction was not a multiple of 32):
+// residual GEMM of a 512x2048 layer at 4096 tokens 25.2 -> 16.3 us, of 1000x1488 at 3001 tokens 30.4 -> 21 us.
 
 constexpr int DBK64 = 64;
 
@@ -786,13 +455,14 @@ constexpr int DBK64 = 64;
 // acc[m][n] = sum_t A[t][m] B[t][n]) -- activations and their gradients as the layers produce them, token-major.  A stage then
 // holds 64 rows (tokens) of BM + BN columns, and a wavefront gathers the 8 tokens x 1 column an MFMA lane needs with two of the
 // LDS transposing reads of this architecture (ds_read_b64_tr_b16) instead of one 16-byte read.
-template <int BM_, int BN_, int WGM_, int WGN_, int NS_, bool kTokenMajor_ = false>
+template <int BM_, int BN_, int WGM_, int WGN_, int NS_, bool kTokenMajor_ = false, int WGK_ = 1>
 struct Dma64Cfg {
-  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NS = NS_;  // NS ring stages (2 or 3)
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NS = NS_;  // NS ring stages
   static constexpr bool kTokenMajor = kTokenMajor_;
   static_assert(!kTokenMajor_ || ((BM_ == 256 || BM_ == 192) && (BN_ == 256 || BN_ == 192)),
                 "the token-major stage layout is written for 256 and 192 columns per operand");
-  static constexpr int NW = WGM * WGN, THREADS = 64 * NW;
+  static constexpr int WGK = WGK_;                 // groups of wavefronts that share out a slice's MFMA phases
+  static constexpr int NW = WGM * WGN * WGK, THREADS = 64 * NW;
   static constexpr int WM = BM / WGM, WN = BN / WGN;
   static constexpr int TM = WM / 16, TN = WN / 16;
   static constexpr int CPR = DBK64 / 8;            // 16-byte chunks per LDS row (8)
@@ -800,12 +470,13 @@ struct Dma64Cfg {
   static constexpr int RB = 2;                     // rows per 256-byte bank cycle
   static constexpr int STAGE = (BM + BN) * DBK64;  // elements per stage
   static constexpr int P = (BM + BN) / RPI / NW;   // DMA instructions per wavefront per stage
-  static constexpr int KK = DBK64 / 32;            // MFMA phases per stage (2)
+  static constexpr int KK = DBK64 / 32 / WGK;      // MFMA phases per stage and wavefront (2, or 1 of the two)
   static constexpr int NF = TM + TN, NM = TM * TN;
   static constexpr int FSTEP = NM / NF >= 2 ? 2 : 1;  // one fragment prefetch every FSTEP MFMAs
   static constexpr int DSTEP = NM / P;                // one DMA issue every DSTEP MFMAs of the last phase
   static_assert(NF * FSTEP <= NM && P * DSTEP <= NM && DSTEP >= 1, "phase schedule");
-  static_assert((BM + BN) % (RPI * NW) == 0 && TN % 2 == 0 && (NS == 2 || NS == 3), "tile shape");
+  static_assert((WGK == 1 || (WGK == 2 && TM % 2 == 0)) && !(kTokenMajor_ && WGK != 1), "contraction groups");
+  static_assert((BM + BN) % (RPI * NW) == 0 && TN % 2 == 0 && NS >= 2 && STAGE * NS * 2 <= 160 * 1024, "tile shape");
 };
 
 // Eight consecutive tokens of one column for every lane, from a token-major stage: two transposing reads of 4 tokens each.
@@ -835,7 +506,91 @@ __device__ __forceinline__ int token_key(int t) {
   return COLS == 256 ? (t & 3) | (((t >> 3) & 1) << 2) : ((t >> 1) & 1) | (((t >> 3) & 1) << 1);
 }
 
-template <class C, class Epi>
+// Hands a wavefront's TMW x TN accumulator tiles (rows wm .., columns wn .. of the output tile at m0, n0) to the epilogue
+template <class C, int TMW, class Epi>
+__device__ __forceinline__ void epilogue(Epi& epi, f32x4 (&acc)[TMW][C::TN], bf16_t* lds, int64_t m0, int64_t n0, int wm, int wn,
+                                         int split, const GemmDims& d, int tid, int lane, int wave, int wc) {
+  constexpr int TN = C::TN;
+  const int col = lane & 15, rq = lane >> 4;
+  if constexpr (Epi::kTransposedOut) {
+    // Output is wanted transposed ([n][m], m contiguous) while a lane holds 4 consecutive m of one n: stage a 32-column slab
+    // (two 16-column tiles) per wavefront column through LDS and write whole rows with 16 B per lane
+    constexpr int LDT = C::BM + 4;          // pitch of 2 words beyond a multiple of 32: conflict-free 8-byte writes
+    constexpr int ROWS = C::WGN * 32;
+    constexpr int CPRW = C::BM / 8;
+    static_assert(ROWS * LDT <= C::NS * C::STAGE, "staging buffer fits in the ring");
+    bf16_t* stg = lds;
+#pragma unroll
+    for (int jj = 0; jj < TN / 2; ++jj) {
+      __syncthreads();
+      float4 cv[TMW][2];
+#pragma unroll
+      for (int i = 0; i < TMW; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          cv[i][h] = epi.load4(m0 + wm + i * 16 + 4 * rq, n0 + wn + (2 * jj + h) * 16 + col, d);
+#pragma unroll
+      for (int i = 0; i < TMW; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int ml = wm + i * 16 + 4 * rq;
+          const float r[4] = {acc[i][2 * jj + h][0], acc[i][2 * jj + h][1], acc[i][2 * jj + h][2], acc[i][2 * jj + h][3]};
+          *reinterpret_cast<uint2*>(stg + (wc * 32 + h * 16 + col) * LDT + ml) =
+              epi.value4(r, cv[i][h], m0 + ml, n0 + wn + (2 * jj + h) * 16 + col, d);
+        }
+      __syncthreads();
+      for (int idx = tid; idx < ROWS * CPRW; idx += C::THREADS) {
+        const int row = idx / CPRW, ch = idx % CPRW;
+        const uint2* src = reinterpret_cast<const uint2*>(stg + row * LDT + ch * 8);   // 8-byte aligned
+        const uint2 lo = src[0], hi = src[1];
+        epi.store_chunk(make_uint4(lo.x, lo.y, hi.x, hi.y), m0 + ch * 8, n0 + (row / 32) * C::WN + jj * 32 + (row % 32), d);
+      }
+    }
+  } else if constexpr (Epi::kRowStaged) {
+    // every wavefront stages one 16 x WN row of its accumulator tiles at a time through its own piece of LDS and hands the
+    // epilogue runs of 8 consecutive columns of a row: 16-byte operand loads and stores, a quarter of the instructions
+    constexpr int PITCH = C::WN + 4;                 // floats; 4 * PITCH = 16 mod 32: the two row groups of a half-wave miss each other
+    constexpr int RUNS = 16 * (C::WN / 8) / 64;      // runs per lane and staged row
+    static_assert(C::NW * 16 * PITCH * 4 <= C::NS * C::STAGE * 2 && (16 * (C::WN / 8)) % 64 == 0, "staging fits in the ring");
+    float* stg = reinterpret_cast<float*>(lds) + wave * 16 * PITCH;
+    __syncthreads();                                 // nobody reads the ring any more
+#pragma unroll
+    for (int i = 0; i < TMW; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) stg[(4 * rq + v) * PITCH + j * 16 + col] = acc[i][j][v];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int t = 0; t < RUNS; ++t) {
+        const int idx = lane + 64 * t, row = idx / (C::WN / 8), cg = idx % (C::WN / 8);
+        const float4 a = *reinterpret_cast<const float4*>(stg + row * PITCH + cg * 8);
+        const float4 b = *reinterpret_cast<const float4*>(stg + row * PITCH + cg * 8 + 4);
+        const float r[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        epi.run8(r, m0 + wm + i * 16 + row, n0 + wn + cg * 8, split, d);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TMW; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const float r[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+        epi.rows4(r, m0 + wm + i * 16 + 4 * rq, n0 + wn + j * 16 + col, split, d);
+      }
+  }
+}
+
+// what the chunks beyond the end of a contraction are copied from
+__device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
+
+// kTail: the contraction (a multiple of 8) ends inside its last slice
+template <class C, bool kTail, class Epi>
 __global__ void __launch_bounds__(C::THREADS)
 k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d, int tiles_m, int tiles_n, int n_split,
              int ksteps_per_split, Epi epi) {
@@ -844,11 +599,12 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
   __shared__ __attribute__((aligned(1024))) uint32_t warm_sink[Epi::kWarm ? C::NW * 256 : 4];
   epi.once();
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave / C::WGN) * C::WM, wn = (wave % C::WGN) * C::WN;
+  const int kg = wave / (C::WGM * C::WGN), wxy = wave % (C::WGM * C::WGN);   // contraction group, position in the tile
+  const int wm = (wxy / C::WGN) * C::WM, wn = (wxy % C::WGN) * C::WN;
   int tm, tn, split, item;
   if (!item_coords(blockIdx.x, tiles_m, tiles_n, n_split, tm, tn, split, item)) return;
   const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
-  const int ksteps = static_cast<int>(d.Kd / DBK64);
+  const int ksteps = static_cast<int>((d.Kd + DBK64 - 1) / DBK64);
   const int kbeg = split * ksteps_per_split;
   const int kend = kbeg + ksteps_per_split < ksteps ? kbeg + ksteps_per_split : ksteps;
   const int nk = kend - kbeg;
@@ -920,12 +676,23 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
     const bool in_ = epi.warm != nullptr && (REL) < nk && chunk_ < epi.warm_chunks;                                      \
     dma16(in_ ? static_cast<const char*>(epi.warm) + chunk_ * 1024 + lane * 16 : reinterpret_cast<const char*>(A), warm_dst); \
   }
+    // source of copy q of slice t
+    static_assert(!(kTail && C::kTokenMajor), "a token-major contraction is a multiple of the slice");
+    const int tail = static_cast<int>(d.Kd - (int64_t)(ksteps - 1) * DBK64);
+    auto source = [&](int q, int64_t t) -> const bf16_t* {
+      const bf16_t* g = gsrc[q] + t * gstep[q];
+      if constexpr (kTail) {
+        const int chunk = (lane % C::CPR) ^ ((((wave * P + q) * C::RPI + lane / C::CPR) / C::RB) % C::CPR);
+        if (t == ksteps - 1 && chunk * 8 >= tail) g = reinterpret_cast<const bf16_t*>(&kZeroChunk);
+      }
+      return g;
+    };
 #pragma unroll
     for (int s = 0; s < C::NS; ++s) {
       const int t = kbeg + (s < nk ? s : nk - 1);
 #pragma unroll
       for (int q = 0; q < P; ++q)
-        dma16(gsrc[q] + (int64_t)t * gstep[q],
+        dma16(source(q, t),
               __builtin_amdgcn_readfirstlane(lds_addr_of(lds + s * C::STAGE + (wave * P + q) * C::RPI * DBK64)));
       FAAR_SIDE_READ(s)
     }
@@ -937,7 +704,7 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
     int a_off[KK], b_off[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      const int slot = ((4 * kk + kc) ^ sw) * 8;
+      const int slot = ((4 * (kg * KK + kk) + kc) ^ sw) * 8;
       a_off[kk] = (wm + fr) * DBK64 + slot;
       b_off[kk] = C::BM * DBK64 + (wn + fr) * DBK64 + slot;
     }
@@ -975,14 +742,16 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
       fb[1][j] = fb[0][j];
     }
 
-    for (int it = 0; it < nk; ++it) {
+    // one slice; kOdd: which of the two fragment sets holds its first phase (with two phases a slice, always the first set)
+    auto slice = [&](int it, auto kOdd) {
       bf16_t* st = lds + (it % C::NS) * C::STAGE;
       const bf16_t* sn = lds + ((it + 1) % C::NS) * C::STAGE;
       const bool more = it + C::NS < nk;
       const int64_t gslice = kbeg + it + C::NS;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
-        const int cur = kk & 1;
+        constexpr int kFirst = decltype(kOdd)::value;
+        const int cur = (kFirst + kk) & 1;
         if (kk == KK - 1) {
           // this wavefront's copies of slice it+1 have landed and its reads of slice it are complete;
           // after the barrier that holds for the workgroup: stage `st` may be refilled, `sn` may be read
@@ -1033,7 +802,7 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
           if (Epi::kMode != 1 && kk == KK - 1 && m % C::DSTEP == 0 && m / C::DSTEP < P) {
             // slice it+NS into the stage just released; past the end every lane re-reads one valid address
             const int q = m / C::DSTEP;
-            const bf16_t* g = more ? gsrc[q] + gslice * gstep[q] : A;
+            const bf16_t* g = more ? source(q, gslice) : A;
             dma16(g, __builtin_amdgcn_readfirstlane(lds_addr_of(st + (wave * P + q) * C::RPI * DBK64)));
           }
           if (Epi::kMode != 1 && kk == KK - 1 && m == (P - 1) * C::DSTEP + 1) {   // right after the slice's last copy
@@ -1041,6 +810,14 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
           }
           __builtin_amdgcn_sched_barrier(0);
         }
+      }
+    };
+    if constexpr (KK == 2) {
+      for (int it = 0; it < nk; ++it) slice(it, std::integral_constant<int, 0>{});
+    } else {
+      for (int it = 0; it < nk; it += 2) {
+        slice(it, std::integral_constant<int, 0>{});
+        if (it + 1 < nk) slice(it + 1, std::integral_constant<int, 1>{});
       }
     }
     FAAR_WAIT_VMCNT(0);  // no copy may still be in flight into this workgroup's LDS when it retires
@@ -1051,89 +828,37 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
 
   // accumulator layout of the 16x16 tile: lane -> column lane % 16, rows 4 * (lane / 16) + 0..3
   epi.begin();
-  const int col = lane & 15, rq = lane >> 4;
-  if constexpr (Epi::kTransposedOut) {
-    // as in k_gemm_dma: stage a 32-column slab (two 16-column tiles) per wavefront column through LDS and
-    // write whole rows of the transposed output with 16 B per lane
-    constexpr int LDT = C::BM + 4;          // pitch of 2 words beyond a multiple of 32: conflict-free 8-byte writes
-    constexpr int ROWS = C::WGN * 32;
-    constexpr int CPRW = C::BM / 8;
-    static_assert(ROWS * LDT <= C::NS * C::STAGE, "staging buffer fits in the ring");
-    bf16_t* stg = lds;
-    const int wc = wave % C::WGN;
+  if constexpr (C::WGK == 2) {
+    // the two groups exchange halves of their accumulators through LDS: each ends up with the sums of half the tile's rows
+    constexpr int HT = TM / 2;
+    f32x4* ex = reinterpret_cast<f32x4*>(lds) + (size_t)wave * HT * TN * 64 + lane;
+    const f32x4* ex_in = reinterpret_cast<const f32x4*>(lds) + (size_t)(wave ^ (C::WGM * C::WGN)) * HT * TN * 64 + lane;
+    static_assert(C::NW * HT * TN * 64 * 16 <= C::NS * C::STAGE * 2, "exchange fits in the ring");
+    __syncthreads();
+    f32x4 half[HT][TN];
 #pragma unroll
-    for (int jj = 0; jj < TN / 2; ++jj) {
-      __syncthreads();
-      float4 cv[TM][2];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          cv[i][h] = epi.load4(m0 + wm + i * 16 + 4 * rq, n0 + wn + (2 * jj + h) * 16 + col, d);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int ml = wm + i * 16 + 4 * rq;
-          const float r[4] = {acc[i][2 * jj + h][0], acc[i][2 * jj + h][1], acc[i][2 * jj + h][2], acc[i][2 * jj + h][3]};
-          *reinterpret_cast<uint2*>(stg + (wc * 32 + h * 16 + col) * LDT + ml) =
-              epi.value4(r, cv[i][h], m0 + ml, n0 + wn + (2 * jj + h) * 16 + col, d);
-        }
-      __syncthreads();
-      for (int idx = tid; idx < ROWS * CPRW; idx += C::THREADS) {
-        const int row = idx / CPRW, ch = idx % CPRW;
-        const uint2* src = reinterpret_cast<const uint2*>(stg + row * LDT + ch * 8);   // 8-byte aligned
-        const uint2 lo = src[0], hi = src[1];
-        epi.store_chunk(make_uint4(lo.x, lo.y, hi.x, hi.y), m0 + ch * 8, n0 + (row / 32) * C::WN + jj * 32 + (row % 32), d);
-      }
-    }
-  } else if constexpr (Epi::kRowStaged) {
-    // every wavefront stages one 16 x WN row of its accumulator tiles at a time through its own piece of LDS and hands the
-    // epilogue runs of 8 consecutive columns of a row: 16-byte operand loads and stores, a quarter of the instructions
-    constexpr int PITCH = C::WN + 4;                 // floats; 4 * PITCH = 16 mod 32: the two row groups of a half-wave miss each other
-    constexpr int RUNS = 16 * (C::WN / 8) / 64;      // runs per lane and staged row
-    static_assert(C::NW * 16 * PITCH * 4 <= C::NS * C::STAGE * 2 && (16 * (C::WN / 8)) % 64 == 0, "staging fits in the ring");
-    float* stg = reinterpret_cast<float*>(lds) + wave * 16 * PITCH;
-    __syncthreads();                                 // nobody reads the ring any more
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) stg[(4 * rq + v) * PITCH + j * 16 + col] = acc[i][j][v];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-      for (int t = 0; t < RUNS; ++t) {
-        const int idx = lane + 64 * t, row = idx / (C::WN / 8), cg = idx % (C::WN / 8);
-        const float4 a = *reinterpret_cast<const float4*>(stg + row * PITCH + cg * 8);
-        const float4 b = *reinterpret_cast<const float4*>(stg + row * PITCH + cg * 8 + 4);
-        const float r[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        epi.run8(r, m0 + wm + i * 16 + row, n0 + wn + cg * 8, split, d);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < HT; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        const float r[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-        epi.rows4(r, m0 + wm + i * 16 + 4 * rq, n0 + wn + j * 16 + col, split, d);
+        half[i][j] = kg == 0 ? acc[i][j] : acc[HT + i][j];
+        ex[(i * TN + j) * 64] = kg == 0 ? acc[HT + i][j] : acc[i][j];
       }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < HT; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) half[i][j] += ex_in[(i * TN + j) * 64];
+    epilogue<C, HT>(epi, half, lds, m0, n0, wm + kg * (C::WM / 2), wn, split, d, tid, lane, wave, wxy % C::WGN);
+  } else {
+    epilogue<C, TM>(epi, acc, lds, m0, n0, wm, wn, split, d, tid, lane, wave, wxy % C::WGN);
   }
   epi.finish(item);
 }
 
-typedef Tile<128, 128> T128;
-typedef DmaCfg<256, 256, 2, 4> CfgL;  // large problems
-typedef DmaCfg<256, 128, 4, 2> CfgM;  // one tile per compute unit at ~256 tiles
-typedef DmaCfg<128, 128, 2, 2> CfgS;  // small outputs, two workgroups per compute unit
 typedef Dma64Cfg<256, 256, 2, 4, 2> CfgL64;  // 2 x 64 KB
 typedef Dma64Cfg<256, 128, 4, 2, 3> CfgM64;  // 3 x 48 KB: copies stay in flight for two slices
+typedef Dma64Cfg<128, 128, 2, 2, 4, false, 2> CfgS64;  // 4 x 32 KB, two contraction groups
+typedef Dma64Cfg<128, 64, 2, 2, 6, false, 2> CfgN64;   // 6 x 24 KB, two contraction groups
 typedef Dma64Cfg<256, 256, 2, 4, 2, true> CfgT64;  // CfgL64 on token-major operands
 // ... and with 192 rows (columns) per tile: 6144 x 2048 is 24 x 8 = 192 tiles of 256 x 256 -- a quarter of the 256 compute units
 // idle -- but 32 x 8 = 256 tiles of 192 x 256
@@ -1142,21 +867,17 @@ typedef Dma64Cfg<256, 192, 4, 2, 2, true> CfgT64B;
 
 inline int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
-enum { KIND_GENERIC = 0, KIND_L = 1, KIND_M = 2, KIND_S = 3, KIND_L64 = 4, KIND_M64 = 5 };
+enum { KIND_L64 = 0, KIND_M64 = 1, KIND_S64 = 2, KIND_N64 = 3, KINDS = 4 };   // FAAR_GEMM_*
+constexpr int kTileRows[KINDS] = {256, 256, 128, 128}, kTileCols[KINDS] = {256, 128, 128, 64};
 
 struct Plan {
   int kind, tiles_m, tiles_n, n_split;
   int64_t items() const { return (int64_t)tiles_m * tiles_n * n_split; }
 };
 
-inline Plan make_plan(int kind, const GemmDims& d, int n_split) {
-  const int bm = kind == KIND_S || kind == KIND_GENERIC ? 128 : 256;
-  const int bn = kind == KIND_L || kind == KIND_L64 ? 256 : 128;
-  return Plan{kind, ceil_div(d.M, bm), ceil_div(d.N, bn), n_split};
-}
-
 // Tile shape and contraction split, chosen by a small cost model (all times in microseconds, calibrated on
-// MI355X with every compute unit busy).  A compute unit works through one BK-slice of a tile in c_kind;
+// MI355X with every compute unit busy).  A compute unit works through one 64-wide slice of a tile in slice_us;
+// (0.66 and 0.42 are the small tiles' values with the chip full of them; alone they take half that, but then the rounds decide);
 // an item's epilogue costs a fixed part plus its global traffic (reads count fully, writes half: they do not
 // stall the wave) at one compute unit's share of the memory bandwidth.  Items are dealt in rounds of 256.
 // Large tiles cut LDS and L2 traffic per flop but quantise badly on small outputs; splitting the contraction
@@ -1165,32 +886,23 @@ inline Plan make_plan(int kind, const GemmDims& d, int n_split) {
 struct EpiCost { float read_bytes, write_bytes; };  // per output element
 
 Plan plan_gemm(const GemmDims& d, bool may_split, EpiCost epi) {
-  if (d.Kd % DBK != 0) {
-    Plan p = make_plan(KIND_GENERIC, d, 1);
-    if (may_split)
-      while (p.items() < 256 && d.Kd / (p.n_split * 2) >= 512 && p.n_split < 16) p.n_split *= 2;
-    return p;
-  }
-  // contractions that are a multiple of 64 take the 128-byte-row kernels for the two large shapes
-  const bool k64 = d.Kd % DBK64 == 0;
-  const int kinds[3] = {k64 ? KIND_L64 : KIND_L, k64 ? KIND_M64 : KIND_M, KIND_S};
-  const double slice_us[3] = {k64 ? 0.833 : 0.985, k64 ? 0.552 : 0.63, 0.36};  // per 32 of the contraction
-  const double tile_outputs[3] = {256.0 * 256.0, 256.0 * 128.0, 128.0 * 128.0};
+  constexpr double slice_us[KINDS] = {1.666, 1.104, 0.66, 0.42};
   const double cu_bytes_per_us = 17600.0;   // ~4.5 TB/s over 256 compute units
-  Plan best{};
+  const int64_t ksteps = (d.Kd + DBK64 - 1) / DBK64;
+  Plan best{-1, 0, 0, 0};
   double best_cost = 0.0;
-  for (int i = 0; i < 3; ++i) {
+  for (int kind = 0; kind < KINDS; ++kind) {
     for (int sp = 1; sp <= (may_split ? 8 : 1); ++sp) {
       if (sp > 1 && d.Kd / sp < 512) break;
-      const int64_t ksteps = d.Kd / (i < 2 && k64 ? DBK64 : DBK), per = (ksteps + sp - 1) / sp;
+      const int64_t per = (ksteps + sp - 1) / sp;
       if ((sp - 1) * per >= ksteps) continue;  // the last split would be empty
-      const Plan p = make_plan(kinds[i], d, sp);
+      const Plan p{kind, ceil_div(d.M, kTileRows[kind]), ceil_div(d.N, kTileCols[kind]), sp};
       const double rounds = static_cast<double>((p.items() + 255) / 256);
-      const double epilogue = 3.0 + tile_outputs[i] * (epi.read_bytes + 0.5 * epi.write_bytes) / cu_bytes_per_us;
-      double cost = rounds * (static_cast<double>(per) * (i < 2 && k64 ? 2.0 : 1.0) * slice_us[i] + epilogue);
+      const double epilogue = 3.0 + kTileRows[kind] * kTileCols[kind] * (epi.read_bytes + 0.5 * epi.write_bytes) / cu_bytes_per_us;
+      double cost = rounds * (static_cast<double>(per) * slice_us[kind] + epilogue);
       // every extra split is one more float32 partial written here and read back by the consumer
       cost += (sp - 1) * static_cast<double>(d.M) * static_cast<double>(d.N) * 8.0 / 5.0e6;
-      if (best.kind == 0 || cost < best_cost) {
+      if (best.kind < 0 || cost < best_cost) {
         best = p;
         best_cost = cost;
       }
@@ -1203,23 +915,24 @@ constexpr EpiCost kEpiGram{2.0f, 4.0f}, kEpiResidual{4.0f, 2.0f}, kEpiF32{0.0f, 
 
 template <class Epi>
 hipError_t run(const bf16_t* A, const bf16_t* B, GemmDims d, Plan p, Epi epi, hipStream_t st) {
-  if (p.kind == KIND_GENERIC) {
-    const int64_t k_per_split = round_up((d.Kd + p.n_split - 1) / p.n_split, BK);
-    const dim3 grid(static_cast<unsigned>(p.items()));
-    hipLaunchKernelGGL((k_gemm_nt<T128, Epi>), grid, dim3(GEMM_THREADS), 0, st, A, B, d, p.tiles_m, p.tiles_n, k_per_split, epi);
-    return hipGetLastError();
-  }
-  const bool k64 = p.kind == KIND_L64 || p.kind == KIND_M64;
-  const int ksteps = static_cast<int>(d.Kd / (k64 ? DBK64 : DBK));
+  const bool tail = d.Kd % DBK64 != 0;
+  const int ksteps = static_cast<int>((d.Kd + DBK64 - 1) / DBK64);
   const int per_split = (ksteps + p.n_split - 1) / p.n_split;
   const dim3 grid(static_cast<unsigned>((p.items() + 7) / 8 * 8));
-#define FAAR_LAUNCH(KERNEL, CFG) \
-  hipLaunchKernelGGL((KERNEL<CFG, Epi>), grid, dim3(CFG::THREADS), 0, st, A, B, d, p.tiles_m, p.tiles_n, p.n_split, per_split, epi)
-  if (p.kind == KIND_L64) FAAR_LAUNCH(k_gemm_dma64, CfgL64);
-  else if (p.kind == KIND_M64) FAAR_LAUNCH(k_gemm_dma64, CfgM64);
-  else if (p.kind == KIND_L) FAAR_LAUNCH(k_gemm_dma, CfgL);
-  else if (p.kind == KIND_M) FAAR_LAUNCH(k_gemm_dma, CfgM);
-  else FAAR_LAUNCH(k_gemm_dma, CfgS);
+#define FAAR_LAUNCH(CFG)                                                                                                      \
+  do {                                                                                                                        \
+    if (!tail)                                                                                                                \
+      hipLaunchKernelGGL((k_gemm_dma64<CFG, false, Epi>), grid, dim3(CFG::THREADS), 0, st, A, B, d, p.tiles_m, p.tiles_n,     \
+                         p.n_split, per_split, epi);                                                                          \
+    else if constexpr (!Epi::kPaddedContraction)                                                                              \
+      hipLaunchKernelGGL((k_gemm_dma64<CFG, true, Epi>), grid, dim3(CFG::THREADS), 0, st, A, B, d, p.tiles_m, p.tiles_n,      \
+                         p.n_split, per_split, epi);                                                                          \
+    else return hipErrorInvalidValue;                                                                                         \
+  } while (0)
+  if (p.kind == KIND_L64) FAAR_LAUNCH(CfgL64);
+  else if (p.kind == KIND_M64) FAAR_LAUNCH(CfgM64);
+  else if (p.kind == KIND_S64) FAAR_LAUNCH(CfgS64);
+  else FAAR_LAUNCH(CfgN64);
 #undef FAAR_LAUNCH
   return hipGetLastError();
 }
@@ -1276,9 +989,7 @@ GemmPlanInfo gemm_plan_info(int epilogue, int64_t M, int64_t N, int64_t Kd) {
                : epilogue == kGemmEpiNone   ? plan_gemm(d, false, kEpiNone)
                : epilogue == kGemmEpiGram   ? plan_gemm(d, true, kEpiGram)
                                             : plan_gemm(d, false, kEpiBf16);
-  const int bm = p.kind == KIND_S || p.kind == KIND_GENERIC ? 128 : 256;
-  const int bn = p.kind == KIND_L || p.kind == KIND_L64 ? 256 : 128;
-  return GemmPlanInfo{p.kind, bm, bn, p.n_split};
+  return GemmPlanInfo{p.kind, kTileRows[p.kind], kTileCols[p.kind], p.n_split};
 }
 
 hipError_t launch_gemm_f32(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split,
@@ -1332,7 +1043,7 @@ static hipError_t run_tn(const bf16_t* A, const bf16_t* B, const GemmDims& d, in
   const int per_split = (ksteps + n_split - 1) / n_split;
   const int64_t items = (int64_t)tiles_m * tiles_n * n_split;
   const dim3 grid(static_cast<unsigned>((items + 7) / 8 * 8));
-  hipLaunchKernelGGL((k_gemm_dma64<C, Epi>), grid, dim3(C::THREADS), 0, st, A, B, d, tiles_m, tiles_n, n_split, per_split, epi);
+  hipLaunchKernelGGL((k_gemm_dma64<C, false, Epi>), grid, dim3(C::THREADS), 0, st, A, B, d, tiles_m, tiles_n, n_split, per_split, epi);
   return hipGetLastError();
 }
 
@@ -1347,12 +1058,23 @@ hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, floa
   return run_tn<CfgT64>(A, B, d, n_split, EpiF32{out}, st);
 }
 
+template <class Epi>
+static hipError_t run_probe(const bf16_t* A, const bf16_t* B, const GemmDims& d, const Plan& p, Epi epi, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>((p.items() + 7) / 8 * 8));
+  const int ksteps = static_cast<int>(d.Kd / DBK64);
+  if (p.kind == KIND_L64)
+    hipLaunchKernelGGL((k_gemm_dma64<CfgL64, false, Epi>), grid, dim3(CfgL64::THREADS), 0, st, A, B, d, p.tiles_m, p.tiles_n, 1, ksteps, epi);
+  else
+    hipLaunchKernelGGL((k_gemm_dma64<CfgM64, false, Epi>), grid, dim3(CfgM64::THREADS), 0, st, A, B, d, p.tiles_m, p.tiles_n, 1, ksteps, epi);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_probe(int mode, const bf16_t* A, const bf16_t* B, GemmDims d, unsigned long long* clocks,
                              int64_t capacity, float* sink, int* kind, int64_t* items, hipStream_t st) {
   const Plan p = plan_gemm(d, false, kEpiF32);
   *kind = p.kind;
   *items = p.items();
-  if (p.kind != KIND_L64 && p.kind != KIND_M64) return hipErrorNotSupported;   // only the BK = 64 loop has the variants
+  if (p.kind != KIND_L64 && p.kind != KIND_M64) return hipErrorNotSupported;   // the variants exist for the two large tiles
   if (p.items() > capacity) return hipErrorInvalidValue;
   if (mode & 4) {   // the same loops on token-major operands: the buffers are read as A [Kd, M], B [Kd, N]
     if (!gemm_tn_usable(d.M, d.N, d.Kd)) return hipErrorNotSupported;
@@ -1370,9 +1092,9 @@ hipError_t launch_gemm_probe(int mode, const bf16_t* A, const bf16_t* B, GemmDim
     return run_tn<CfgT64>(A, B, t, 1, EpiProbe<2>{clocks, sink, 0, 0, 0.0f}, st);
   }
   if (mode & 8) return hipErrorNotSupported;
-  if (mode == 0) return run(A, B, d, p, EpiProbe<0>{clocks, sink, 0, 0, 0.0f}, st);
-  if (mode == 1) return run(A, B, d, p, EpiProbe<1>{clocks, sink, 0, 0, 0.0f}, st);
-  return run(A, B, d, p, EpiProbe<2>{clocks, sink, 0, 0, 0.0f}, st);
+  if (mode == 0) return run_probe(A, B, d, p, EpiProbe<0>{clocks, sink, 0, 0, 0.0f}, st);
+  if (mode == 1) return run_probe(A, B, d, p, EpiProbe<1>{clocks, sink, 0, 0, 0.0f}, st);
+  return run_probe(A, B, d, p, EpiProbe<2>{clocks, sink, 0, 0, 0.0f}, st);
 }
 
 hipError_t launch_gemm_sub(const bf16_t* A, const bf16_t* B, GemmDims d, const void* Y, bool y_bf16,

@@ -176,7 +176,7 @@ struct GemmDims { int64_t M, N, Kd, lda, ldb; };
 // C == nullptr: the V-dependent part alone -- A = x_scale * acc, sum A^2 per tile, dYt = bf16(two_alpha * A) (dY must
 // be null); with dYt == nullptr too, only the sums are produced.
 // guard: when its slot is set, workgroup 0 first compares the stored forward tag with guard.expect (see ForwardTag)
-// warm (nullable), warm_bytes: a buffer the BK = 64 kernels read on the side during the main loop and discard, so that the
+// warm (nullable), warm_bytes: a buffer the kernel reads on the side during the main loop and discard, so that the
 // next kernel finds it in the last-level cache (X_q^T for the dW GEMM); 16-byte aligned, whole KB are read
 hipError_t launch_gemm_residual(const bf16_t* A, const bf16_t* B, GemmDims d, const float* C, const float* x_scale,
                                 float two_alpha, bf16_t* dYt, int64_t ldt, bf16_t* dY,
@@ -202,8 +202,7 @@ int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device);
 hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split, bool fill_device,
                               hipStream_t st);
 // The kernel variant, tile shape and contraction split the launchers above pick for an M x N x Kd product
-// (kind: 0 generic, 1 / 2 / 3 the BK = 32 kernels with 256x256 / 256x128 / 128x128 tiles, 4 / 5 the BK = 64
-// kernels with 256x256 / 256x128 tiles).  Pure host function.
+// (kind: 0 / 1 / 2 / 3 for 256x256 / 256x128 / 128x128 / 128x64 tiles).  Pure host function.
 enum { kGemmEpiResidual = 0, kGemmEpiF32 = 1, kGemmEpiSub = 2, kGemmEpiBf16 = 3, kGemmEpiNone = 4, kGemmEpiGram = 5 };
 struct GemmPlanInfo { int kind, bm, bn, n_split; };
 GemmPlanInfo gemm_plan_info(int epilogue, int64_t M, int64_t N, int64_t Kd);

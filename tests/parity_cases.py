@@ -49,10 +49,17 @@ STEP_CASES = [
     StepCase("dw_token_major_256x192", 8088, 1312, 512, 35, chained=True, whole_device=True),
     StepCase("dw_token_major_192x256_split", 528, 6576, 2048, 36, whole_device=True),
     StepCase("dw_token_major_256x192_split", 6576, 528, 2048, 37, whole_device=True),
+    StepCase("dw_token_major_256x192_split_long", 6576, 528, 4096, 38, whole_device=True),
+    StepCase("dw_split_256x128", 6576, 272, 2048, 39),           # dW GEMM: 256x128 tiles, contraction split
+    # residual contractions that end inside a slice: 16 and 48 of 64 on 128x64 tiles, 16 on 128x128 (config-sized ones above: 32)
+    StepCase("tail_16", 272, 80, 192, 45, chained=True),
+    StepCase("tail_48", 136, 624, 520, 46, chained=True),
+    StepCase("tail_128x128", 1000, 208, 3001, 47),
     # token-major dY out of the residual GEMM (with H) on 256x256 tiles with 32-wide slices: K a multiple of 32 only
     StepCase("rows_k160", 12288, 160, 4096, 33),
     # the shapes the benchmark times, at full size
     StepCase("llama_q_proj", 2048, 2048, 4096, 0, full_size=True),
+    StepCase("llama_k_proj", 512, 2048, 4096, 8, full_size=True),
     StepCase("llama_gate_proj", 8192, 2048, 4096, 1, chained=True, full_size=True),
     StepCase("llama_down_proj", 2048, 8192, 4096, 2, gated_input=True, chained=True, full_size=True),
     StepCase("qwen_k_proj", 1024, 2048, 8192, 3, quantised_acts=True, chained=True, full_size=True),
@@ -68,6 +75,7 @@ GRAM_CASES = [
     StepCase("gram_256x128_split", 1024, 2112, 256, 41),          # 256x128 tiles, 64-wide slices, contraction split
     StepCase("gram_256x128_k64", 4096, 1088, 192, 42),            # 256x128 tiles, 64-wide slices, whole
     StepCase("gram_256x128_k32", 4096, 1056, 192, 43),            # 256x128 tiles, 32-wide slices
+    StepCase("gram_256x128_split_k3072", 656, 3072, 256, 44),
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}
