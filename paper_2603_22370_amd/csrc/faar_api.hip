@@ -70,15 +70,14 @@ struct Carver {
 };
 
 struct StepLayout {
-  size_t guard, delta, dYt, G, mse_partials, round_partials, cross_partials, wq_full, wqt, dY, total;
+  size_t guard, delta, dYt, G, mse_partials, round_partials, cross_partials, wq_full, dY, total;
   int n_split;
-  int64_t Tp, Op;
+  int64_t Tp;
 };
 
 StepLayout step_layout(int64_t O, int64_t K, int64_t T, bool chained) {
   StepLayout L{};
   L.Tp = padded_tokens(T);
-  L.Op = round_up(O, 64);
   L.n_split = choose_split(O, K, L.Tp);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t r = off; off += align256(bytes); return r; };
@@ -91,7 +90,6 @@ StepLayout step_layout(int64_t O, int64_t K, int64_t T, bool chained) {
   L.cross_partials = take((size_t)2 * kStepBwdMaxBlocks * 8);  // likewise; used when the layer carries H
   if (chained) {
     L.wq_full = take((size_t)O * K * 2);
-    L.wqt = take((size_t)K * L.Op * 2);
     L.dY = take((size_t)T * O * 2);
   }
   L.total = off;
@@ -543,7 +541,6 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
   // from the locally derived dY, which then must contain the constant
   const float* Hs = (H && !(dX && !dY_ext)) ? H : nullptr;
   bf16_t* wq_full = chained && dX ? reinterpret_cast<bf16_t*>(base + L.wq_full) : nullptr;
-  bf16_t* wqt = chained ? reinterpret_cast<bf16_t*>(base + L.wqt) : nullptr;
   bf16_t* dY = chained ? reinterpret_cast<bf16_t*>(base + L.dY) : nullptr;
   const bf16_t* xq = static_cast<const bf16_t*>(Xq);
 
@@ -590,9 +587,9 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
       if (int e = hip_status(launch_gemm_residual_rows(xq, delta, d1, x_scale, 2.0f * mse_scale, dYt, mse_p, &n_mse, guard, st)))
         return e;
     } else if (int e = hip_status(launch_gemm_residual(xq, delta, d1, Hs ? nullptr : C, x_scale, 2.0f * mse_scale,
-                                                       (Hs && dY_ext) ? nullptr : dYt, L.Tp, need_local_dY ? dY : nullptr, mse_p,
+                                                       dY_ext ? nullptr : dYt, L.Tp, need_local_dY ? dY : nullptr, mse_p,
                                                        &n_mse, guard, warm_xt ? Xt : nullptr, xt_bytes, st))) {
-      // with H: no constant in the epilogue, and no dY^T at all when the gradient comes from upstream
+      // with H: no constant in the epilogue; no dY^T at all when the gradient comes from upstream (only the loss is wanted)
       return e;
     }
   }
@@ -617,10 +614,9 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
   }
   // s4: dX = dY W_q
   if (dX) {
-    if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, wqt, L.Op, st))) return e;
-    const GemmDims d3{T, K, O, O, L.Op};
+    const GemmDims d3{T, K, O, O, K};
     Bracket b(FAAR_K_GEMM_DX, st);
-    if (int e = hip_status(launch_gemm_bf16(dY_used, wqt, d3, static_cast<bf16_t*>(dX), nullptr, st))) return e;
+    if (int e = hip_status(launch_gemm_bf16_nn(dY_used, wq_full, d3, static_cast<bf16_t*>(dX), st))) return e;
   }
   // s5 + s6: dV, Adam, clip; the same launch sums the losses (both kinds of partials are complete by now:
   // they come from earlier kernels) and, when asked, runs s1 of the next step on the updated V

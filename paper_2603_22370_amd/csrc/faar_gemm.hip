@@ -167,13 +167,16 @@ struct EpiPerturbationRows {
   __device__ __forceinline__ void finish(int item) { finish_sum(sum, partials, item); }
 };
 
-// sum of (x_scale * acc)^2 per work item and nothing else: the loss of a step whose dY comes from upstream
+// The loss of a step whose dY comes from upstream, and nothing else: per work item the sum of (x_scale * acc - C)^2, or without C
+// of (x_scale * acc)^2
+template <bool kWithC>
 struct EpiSumSq {
   static constexpr bool kRowStaged = false;
   static constexpr bool kWarm = false;
   static constexpr bool kTransposedOut = false;
   static constexpr int kMode = 0;
   static constexpr bool kPaddedContraction = false;
+  const float* C;        // as in EpiResidualT
   const float* x_scale;
   float xs;
   ForwardGuard guard;
@@ -189,11 +192,14 @@ struct EpiSumSq {
   }
   __device__ __forceinline__ void begin() { xs = x_scale ? *x_scale : 1.0f; }
   __device__ __forceinline__ void rows4(const float (&acc)[4], int64_t m, int64_t n, int, const GemmDims& d) {
-    if (n >= d.N) return;
+    if (n >= d.N || m >= d.M) return;   // m is a multiple of 4
+    float4 c4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (kWithC) c4 = *reinterpret_cast<const float4*>(C + ((m >> 2) * d.N + n) * 4);
+    const float c[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if (m + q < d.M) {
-        const float r = xs * acc[q];
+        const float r = xs * acc[q] - c[q];
         sum += r * r;
       }
   }
@@ -451,16 +457,17 @@ __device__ __forceinline__ bool item_coords(int pid, int tiles_m, int tiles_n, i
 
 constexpr int DBK64 = 64;
 
-// kTokenMajor_: both operands are stored with the contraction index as the ROW index (A [Kd, lda], B [Kd, ldb]; "TN" product
-// acc[m][n] = sum_t A[t][m] B[t][n]) -- activations and their gradients as the layers produce them, token-major.  A stage then
-// holds 64 rows (tokens) of BM + BN columns, and a wavefront gathers the 8 tokens x 1 column an MFMA lane needs with two of the
-// LDS transposing reads of this architecture (ds_read_b64_tr_b16) instead of one 16-byte read.
-template <int BM_, int BN_, int WGM_, int WGN_, int NS_, bool kTokenMajor_ = false, int WGK_ = 1>
+// How the operands are stored.  kNT: both with the contraction index contiguous.  kTN: both with the contraction index as the
+// ROW index (A [Kd, lda], B [Kd, ldb]; acc[m][n] = sum_t A[t][m] B[t][n]) -- activations and their gradients as the layers
+// produce them, token-major.  kNN: B alone that way (the input gradient dY W_q on W_q as the forward product reads it).  Of an
+// operand with the contraction index as the row index a stage holds 64 rows (tokens) of BM or BN columns, and a wavefront gathers
+// the 8 tokens x 1 column an MFMA lane needs with two of the LDS transposing reads of this architecture (ds_read_b64_tr_b16)
+// instead of one 16-byte read.
+enum { kNT = 0, kTN = 1, kNN = 2 };
+template <int BM_, int BN_, int WGM_, int WGN_, int NS_, int kOperands_ = kNT, int WGK_ = 1>
 struct Dma64Cfg {
   static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NS = NS_;  // NS ring stages
-  static constexpr bool kTokenMajor = kTokenMajor_;
-  static_assert(!kTokenMajor_ || ((BM_ == 256 || BM_ == 192) && (BN_ == 256 || BN_ == 192)),
-                "the token-major stage layout is written for 256 and 192 columns per operand");
+  static constexpr bool kTokenA = kOperands_ == kTN, kTokenB = kOperands_ != kNT;
   static constexpr int WGK = WGK_;                 // groups of wavefronts that share out a slice's MFMA phases
   static constexpr int NW = WGM * WGN * WGK, THREADS = 64 * NW;
   static constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -475,7 +482,7 @@ struct Dma64Cfg {
   static constexpr int FSTEP = NM / NF >= 2 ? 2 : 1;  // one fragment prefetch every FSTEP MFMAs
   static constexpr int DSTEP = NM / P;                // one DMA issue every DSTEP MFMAs of the last phase
   static_assert(NF * FSTEP <= NM && P * DSTEP <= NM && DSTEP >= 1, "phase schedule");
-  static_assert((WGK == 1 || (WGK == 2 && TM % 2 == 0)) && !(kTokenMajor_ && WGK != 1), "contraction groups");
+  static_assert((WGK == 1 || (WGK == 2 && TM % 2 == 0)) && !(kTokenA && WGK != 1), "contraction groups");
   static_assert((BM + BN) % (RPI * NW) == 0 && TN % 2 == 0 && NS >= 2 && STAGE * NS * 2 <= 160 * 1024, "tile shape");
 };
 
@@ -497,13 +504,14 @@ __device__ __forceinline__ bf16x8 read_tokens8(const bf16_t* p) {
 // XOR key of a token row's pairs of 16-byte chunks (32 bytes = the 16 columns one transposing read takes from a token) in a
 // token-major stage of COLS columns per token.  One read touches 16 token rows -- 4 consecutive tokens in each of 4 groups 8
 // apart -- and they must fall into the 8 different 32-byte bank groups, two rows each (the two cycles 512 bytes take anyway).
-// 256 columns: a row is 512 bytes, every row starts at bank 0, so the key has 3 bits (token bits 0, 1, 3) and permutes a row's
-// pairs within aligned groups of 8.  192 columns: a row is 384 bytes, odd rows start half-way round the banks, so token bit 0 is
-// taken care of and the key has 2 bits (token bits 1, 3), permuting pairs within aligned groups of 4 -- which 12 pairs divide into.
+// 256 and 128 columns: a row is 512 or 256 bytes, every row starts at bank 0, so the key has 3 bits (token bits 0, 1, 3) and
+// permutes a row's pairs within aligned groups of 8.  192 and 64 columns: a row is 384 or 128 bytes, odd rows start half-way
+// round the banks, so token bit 0 is taken care of and the key has 2 bits (token bits 1, 3), permuting pairs within aligned groups of
+// 4 -- which 12 pairs divide into.
 template <int COLS>
 __device__ __forceinline__ int token_key(int t) {
-  static_assert(COLS == 256 || COLS == 192, "token-major operand width");
-  return COLS == 256 ? (t & 3) | (((t >> 3) & 1) << 2) : ((t >> 1) & 1) | (((t >> 3) & 1) << 1);
+  static_assert(COLS == 256 || COLS == 128 || COLS == 192 || COLS == 64, "token-major operand width");
+  return COLS % 128 == 0 ? (t & 3) | (((t >> 3) & 1) << 2) : ((t >> 1) & 1) | (((t >> 3) & 1) << 1);
 }
 
 // Hands a wavefront's TMW x TN accumulator tiles (rows wm .., columns wn .. of the output tile at m0, n0) to the epilogue
@@ -598,7 +606,7 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
   // where the side reads of an epilogue with kWarm land: 1 KB per wavefront, never read
   __shared__ __attribute__((aligned(1024))) uint32_t warm_sink[Epi::kWarm ? C::NW * 256 : 4];
   epi.once();
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave / (C::WGM * C::WGN), wxy = wave % (C::WGM * C::WGN);   // contraction group, position in the tile
   const int wm = (wxy / C::WGN) * C::WM, wn = (wxy % C::WGN) * C::WN;
   int tm, tn, split, item;
@@ -630,15 +638,14 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
     int64_t gstep[P];   // elements from one slice to the next
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      if constexpr (C::kTokenMajor) {
-        // instruction u = wave * P + q fills 64 consecutive 16-byte slots of the stage; an operand of COLS columns owns
-        // 64 tokens x COLS / 8 slots (a whole number of instructions), slot -> token = slot / (COLS / 8), LDS chunk =
-        // slot % (COLS / 8), global chunk = that ^ 2 key(token).  Columns beyond M (or N) are clamped to the last whole chunk:
-        // their products are never stored.
-        const int u = wave * P + q;
-        const bool is_a = u < C::BM / 8;
+      const int u = wave * P + q;                 // copy u fills 64 consecutive 16-byte slots of the stage
+      const bool is_a = u < C::BM / 8;
+      if (is_a ? C::kTokenA : C::kTokenB) {
+        // an operand of COLS columns owns 64 tokens x COLS / 8 slots (a whole number of copies), slot -> token =
+        // slot / (COLS / 8), LDS chunk = slot % (COLS / 8), global chunk = that ^ 2 key(token).  Columns beyond M (or N) are
+        // clamped to the last whole chunk: their products are never stored.
         int t, chunk;
-        if constexpr (C::BM == 256 && C::BN == 256) {   // two whole token rows per instruction
+        if constexpr (C::kTokenA && C::BM == 256 && C::BN == 256) {   // two whole token rows per copy
           t = 2 * (is_a ? u : u - C::BM / 8) + lane / 32;
           chunk = (lane % 32) ^ (2 * token_key<256>(t));
         } else {
@@ -651,9 +658,9 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
         gsrc[q] = (is_a ? A : B) + t * ld + col;
         gstep[q] = DBK64 * ld;
       } else {
-        const int trow = (wave * P + q) * C::RPI + lane / C::CPR;
+        const int trow = u * C::RPI + lane / C::CPR;
         const int chunk = (lane % C::CPR) ^ ((trow / C::RB) % C::CPR);
-        if (trow < C::BM) {
+        if (is_a) {
           const int64_t m = m0 + trow < d.M ? m0 + trow : d.M - 1;
           gsrc[q] = A + m * d.lda + chunk * 8;
         } else {
@@ -677,13 +684,18 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
     dma16(in_ ? static_cast<const char*>(epi.warm) + chunk_ * 1024 + lane * 16 : reinterpret_cast<const char*>(A), warm_dst); \
   }
     // source of copy q of slice t
-    static_assert(!(kTail && C::kTokenMajor), "a token-major contraction is a multiple of the slice");
+    static_assert(!(kTail && C::kTokenA), "the dW GEMM's contraction is a multiple of the slice");
     const int tail = static_cast<int>(d.Kd - (int64_t)(ksteps - 1) * DBK64);
     auto source = [&](int q, int64_t t) -> const bf16_t* {
       const bf16_t* g = gsrc[q] + t * gstep[q];
       if constexpr (kTail) {
-        const int chunk = (lane % C::CPR) ^ ((((wave * P + q) * C::RPI + lane / C::CPR) / C::RB) % C::CPR);
-        if (t == ksteps - 1 && chunk * 8 >= tail) g = reinterpret_cast<const bf16_t*>(&kZeroChunk);
+        if (t == ksteps - 1) {
+          const int u = wave * P + q;
+          const int k = u < C::BM / 8 || !C::kTokenB
+                            ? ((lane % C::CPR) ^ (((u * C::RPI + lane / C::CPR) / C::RB) % C::CPR)) * 8   // first of the chunk
+                            : ((u - C::BM / 8) * 64 + lane) / (C::BN / 8);                                // token row
+          if (k >= tail) g = reinterpret_cast<const bf16_t*>(&kZeroChunk);
+        }
       }
       return g;
     };
@@ -712,33 +724,37 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
     // lane points at token 8 (lane / 16) + (lane % 16) / 4 of the phase's 32 and at columns w? + 16 i + 4 (lane % 4); that
     // token's XOR key is the same in every phase and for both reads of a fragment (no key uses token bits 2, 4 or 5)
     int a_tr[TM] = {}, b_tr[TN] = {};
-    if constexpr (C::kTokenMajor) {
-      const int tok = 8 * kc + (fr >> 2);
-      const int key_a = token_key<C::BM>(tok), key_b = token_key<C::BN>(tok);
+    const int tok = 8 * kc + (fr >> 2), phase0 = 32 * kg * KK;
+    if constexpr (C::kTokenA) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a_tr[i] = tok * C::BM + (((wm / 16 + i) ^ key_a) * 16) + (fr & 3) * 4;
+      for (int i = 0; i < TM; ++i) a_tr[i] = (phase0 + tok) * C::BM + (((wm / 16 + i) ^ token_key<C::BM>(tok)) * 16) + (fr & 3) * 4;
+    }
+    if constexpr (C::kTokenB) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) b_tr[j] = C::BM * DBK64 + tok * C::BN + (((wn / 16 + j) ^ key_b) * 16) + (fr & 3) * 4;
+      for (int j = 0; j < TN; ++j)
+        b_tr[j] = C::BM * DBK64 + (phase0 + tok) * C::BN + (((wn / 16 + j) ^ token_key<C::BN>(tok)) * 16) + (fr & 3) * 4;
     }
     // fragment i of the A rows (j of the B rows) for phase kk, from the stage at `src`
-#define FAAR_FRAG_A(SRC, KKI, I)                                                                                         \
-  (C::kTokenMajor ? read_tokens8<C::BM>((SRC) + a_tr[I] + 32 * (KKI) * C::BM)                                            \
-                  : *reinterpret_cast<const bf16x8*>((SRC) + a_off[KKI] + (I) * 16 * DBK64))
-#define FAAR_FRAG_B(SRC, KKI, J)                                                                                         \
-  (C::kTokenMajor ? read_tokens8<C::BN>((SRC) + b_tr[J] + 32 * (KKI) * C::BN)                                            \
-                  : *reinterpret_cast<const bf16x8*>((SRC) + b_off[KKI] + (J) * 16 * DBK64))
+    auto frag_a = [&](const bf16_t* src, int kk, int i) -> bf16x8 {
+      if constexpr (C::kTokenA) return read_tokens8<C::BM>(src + a_tr[i] + 32 * kk * C::BM);
+      else return *reinterpret_cast<const bf16x8*>(src + a_off[kk] + i * 16 * DBK64);
+    };
+    auto frag_b = [&](const bf16_t* src, int kk, int j) -> bf16x8 {
+      if constexpr (C::kTokenB) return read_tokens8<C::BN>(src + b_tr[j] + 32 * kk * C::BN);
+      else return *reinterpret_cast<const bf16x8*>(src + b_off[kk] + j * 16 * DBK64);
+    };
     bf16x8 fa[2][TM], fb[2][TN];
 
     FAAR_WAIT_VMCNT(PW * (C::NS - 1));  // slice 0 has landed (mine); barrier: everybody's
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      fa[0][i] = FAAR_FRAG_A(lds, 0, i);
+      fa[0][i] = frag_a(lds, 0, i);
       fa[1][i] = fa[0][i];
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      fb[0][j] = FAAR_FRAG_B(lds, 0, j);
+      fb[0][j] = frag_b(lds, 0, j);
       fb[1][j] = fb[0][j];
     }
 
@@ -767,7 +783,7 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
           const int mi = m / TN, mj = (mi & 1) ? TN - 1 - m % TN : m % TN;
           if constexpr (Epi::kMode != 2)
             acc[mi][mj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[cur][mi], fb[cur][mj], acc[mi][mj], 0, 0, 0);
-          if constexpr (Epi::kMode != 2 && C::kTokenMajor && C::FSTEP == 2) {
+          if constexpr (Epi::kMode != 2 && C::kTokenA && C::FSTEP == 2) {
             // token-major: a fragment is two transposing reads; one of them per MFMA instead of both every other MFMA
             // (in a slice's last phase, where the copies are issued too, spread over all of the phase's MFMAs: every
             // SKIP-th one goes without; in the others the reads have to be complete at the next barrier, so they go first)
@@ -795,9 +811,9 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
           } else
           if (Epi::kMode != 2 && m % C::FSTEP == 0 && m / C::FSTEP < NF) {  // next phase's fragments: A0, B0..B(TN-1), A1..A(TM-1)
             const int f = m / C::FSTEP;
-            if (f == 0) fa[cur ^ 1][0] = FAAR_FRAG_A(src, nkk, 0);
-            else if (f <= TN) fb[cur ^ 1][f - 1] = FAAR_FRAG_B(src, nkk, f - 1);
-            else fa[cur ^ 1][f - TN] = FAAR_FRAG_A(src, nkk, f - TN);
+            if (f == 0) fa[cur ^ 1][0] = frag_a(src, nkk, 0);
+            else if (f <= TN) fb[cur ^ 1][f - 1] = frag_b(src, nkk, f - 1);
+            else fa[cur ^ 1][f - TN] = frag_a(src, nkk, f - TN);
           }
           if (Epi::kMode != 1 && kk == KK - 1 && m % C::DSTEP == 0 && m / C::DSTEP < P) {
             // slice it+NS into the stage just released; past the end every lane re-reads one valid address
@@ -822,8 +838,6 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
     }
     FAAR_WAIT_VMCNT(0);  // no copy may still be in flight into this workgroup's LDS when it retires
 #undef FAAR_SIDE_READ
-#undef FAAR_FRAG_A
-#undef FAAR_FRAG_B
   }
 
   // accumulator layout of the 16x16 tile: lane -> column lane % 16, rows 4 * (lane / 16) + 0..3
@@ -857,13 +871,17 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
 
 typedef Dma64Cfg<256, 256, 2, 4, 2> CfgL64;  // 2 x 64 KB
 typedef Dma64Cfg<256, 128, 4, 2, 3> CfgM64;  // 3 x 48 KB: copies stay in flight for two slices
-typedef Dma64Cfg<128, 128, 2, 2, 4, false, 2> CfgS64;  // 4 x 32 KB, two contraction groups
-typedef Dma64Cfg<128, 64, 2, 2, 6, false, 2> CfgN64;   // 6 x 24 KB, two contraction groups
-typedef Dma64Cfg<256, 256, 2, 4, 2, true> CfgT64;  // CfgL64 on token-major operands
+typedef Dma64Cfg<128, 128, 2, 2, 4, kNT, 2> CfgS64;  // 4 x 32 KB, two contraction groups
+typedef Dma64Cfg<128, 64, 2, 2, 6, kNT, 2> CfgN64;   // 6 x 24 KB, two contraction groups
+typedef Dma64Cfg<256, 256, 2, 4, 2, kNN> CfgL64N;   // the same four on a token-major B
+typedef Dma64Cfg<256, 128, 4, 2, 3, kNN> CfgM64N;
+typedef Dma64Cfg<128, 128, 2, 2, 4, kNN, 2> CfgS64N;
+typedef Dma64Cfg<128, 64, 2, 2, 6, kNN, 2> CfgN64N;
+typedef Dma64Cfg<256, 256, 2, 4, 2, kTN> CfgT64;  // CfgL64 on token-major operands
 // ... and with 192 rows (columns) per tile: 6144 x 2048 is 24 x 8 = 192 tiles of 256 x 256 -- a quarter of the 256 compute units
 // idle -- but 32 x 8 = 256 tiles of 192 x 256
-typedef Dma64Cfg<192, 256, 2, 4, 2, true> CfgT64A;
-typedef Dma64Cfg<256, 192, 4, 2, 2, true> CfgT64B;
+typedef Dma64Cfg<192, 256, 2, 4, 2, kTN> CfgT64A;
+typedef Dma64Cfg<256, 192, 4, 2, 2, kTN> CfgT64B;
 
 inline int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
@@ -911,9 +929,10 @@ Plan plan_gemm(const GemmDims& d, bool may_split, EpiCost epi) {
   return best;
 }
 
-constexpr EpiCost kEpiGram{2.0f, 4.0f}, kEpiResidual{4.0f, 2.0f}, kEpiF32{0.0f, 4.0f}, kEpiSub{4.0f, 4.0f}, kEpiBf16{0.0f, 2.0f}, kEpiNone{0.0f, 0.0f};
+constexpr EpiCost kEpiGram{2.0f, 4.0f}, kEpiResidual{4.0f, 2.0f}, kEpiF32{0.0f, 4.0f}, kEpiSub{4.0f, 4.0f}, kEpiBf16{0.0f, 2.0f}, kEpiNone{0.0f, 0.0f}, kEpiLoss{4.0f, 0.0f};
 
-template <class Epi>
+// kB: the B operand is [Kd, ldb] (kNN)
+template <bool kB = false, class Epi>
 hipError_t run(const bf16_t* A, const bf16_t* B, GemmDims d, Plan p, Epi epi, hipStream_t st) {
   const bool tail = d.Kd % DBK64 != 0;
   const int ksteps = static_cast<int>((d.Kd + DBK64 - 1) / DBK64);
@@ -929,20 +948,28 @@ hipError_t run(const bf16_t* A, const bf16_t* B, GemmDims d, Plan p, Epi epi, hi
                          p.n_split, per_split, epi);                                                                          \
     else return hipErrorInvalidValue;                                                                                         \
   } while (0)
-  if (p.kind == KIND_L64) FAAR_LAUNCH(CfgL64);
-  else if (p.kind == KIND_M64) FAAR_LAUNCH(CfgM64);
-  else if (p.kind == KIND_S64) FAAR_LAUNCH(CfgS64);
-  else FAAR_LAUNCH(CfgN64);
+  if constexpr (kB) {
+    if (p.kind == KIND_L64) FAAR_LAUNCH(CfgL64N);
+    else if (p.kind == KIND_M64) FAAR_LAUNCH(CfgM64N);
+    else if (p.kind == KIND_S64) FAAR_LAUNCH(CfgS64N);
+    else FAAR_LAUNCH(CfgN64N);
+  } else {
+    if (p.kind == KIND_L64) FAAR_LAUNCH(CfgL64);
+    else if (p.kind == KIND_M64) FAAR_LAUNCH(CfgM64);
+    else if (p.kind == KIND_S64) FAAR_LAUNCH(CfgS64);
+    else FAAR_LAUNCH(CfgN64);
+  }
 #undef FAAR_LAUNCH
   return hipGetLastError();
 }
 
 }  // namespace
 
-int64_t gemm_residual_partials(int64_t M, int64_t N, int64_t Kd) {  // the most any of the three epilogues writes
+int64_t gemm_residual_partials(int64_t M, int64_t N, int64_t Kd) {  // the most any of the epilogues writes
   const GemmDims d{M, N, Kd, Kd, Kd};
-  return std::max(plan_gemm(d, false, kEpiResidual).items(),
-                  std::max(plan_gemm(d, false, kEpiBf16).items(), plan_gemm(d, false, kEpiNone).items()));
+  int64_t most = 0;
+  for (const EpiCost& e : {kEpiResidual, kEpiBf16, kEpiNone, kEpiLoss}) most = std::max(most, plan_gemm(d, false, e).items());
+  return most;
 }
 
 hipError_t launch_gemm_residual_rows(const bf16_t* A, const bf16_t* B, GemmDims d, const float* x_scale, float two_alpha,
@@ -960,6 +987,12 @@ hipError_t launch_gemm_residual(const bf16_t* A, const bf16_t* B, GemmDims d, co
                                 double* mse_partials, int64_t* n_partials, const ForwardGuard& guard, const void* warm,
                                 int64_t warm_bytes, hipStream_t st) {
   const int64_t warm_chunks = warm ? warm_bytes / 1024 : 0;
+  if (!dYt && !dY) {
+    const Plan p = plan_gemm(d, false, C ? kEpiLoss : kEpiNone);
+    *n_partials = p.items();
+    if (C) return run(A, B, d, p, EpiSumSq<true>{C, x_scale, 1.0f, guard, mse_partials, 0.0f}, st);
+    return run(A, B, d, p, EpiSumSq<false>{nullptr, x_scale, 1.0f, guard, mse_partials, 0.0f}, st);
+  }
   if (C) {
     EpiResidual e{C, x_scale, 1.0f, guard, two_alpha, dYt, ldt, dY, mse_partials, 0.0f, warm, warm_chunks};
     const Plan p = plan_gemm(d, false, kEpiResidual);
@@ -967,14 +1000,8 @@ hipError_t launch_gemm_residual(const bf16_t* A, const bf16_t* B, GemmDims d, co
     return run(A, B, d, p, e, st);
   }
   if (dY) return hipErrorInvalidValue;   // the un-transposed dY exists only with the constant
-  if (dYt) {
-    EpiPerturbation e{nullptr, x_scale, 1.0f, guard, two_alpha, dYt, ldt, nullptr, mse_partials, 0.0f, warm, warm_chunks};
-    const Plan p = plan_gemm(d, false, kEpiBf16);
-    *n_partials = p.items();
-    return run(A, B, d, p, e, st);
-  }
-  EpiSumSq e{x_scale, 1.0f, guard, mse_partials, 0.0f};
-  const Plan p = plan_gemm(d, false, kEpiNone);
+  EpiPerturbation e{nullptr, x_scale, 1.0f, guard, two_alpha, dYt, ldt, nullptr, mse_partials, 0.0f, warm, warm_chunks};
+  const Plan p = plan_gemm(d, false, kEpiBf16);
   *n_partials = p.items();
   return run(A, B, d, p, e, st);
 }
@@ -1106,6 +1133,12 @@ hipError_t launch_gemm_sub(const bf16_t* A, const bf16_t* B, GemmDims d, const v
   }
   EpiSub<false> e{Y, first, C_out, x_scale, 1.0f};
   return run(A, B, d, p, e, st);
+}
+
+hipError_t launch_gemm_bf16_nn(const bf16_t* A, const bf16_t* B, GemmDims d, bf16_t* out, hipStream_t st) {
+  if (d.N % 8 != 0 || d.Kd % 8 != 0 || d.lda % 8 != 0 || d.ldb % 8 != 0) return hipErrorInvalidValue;
+  EpiBf16 e{out, nullptr, 1.0f};
+  return run<true>(A, B, d, plan_gemm(d, false, kEpiBf16), e, st);
 }
 
 hipError_t launch_gemm_bf16(const bf16_t* A, const bf16_t* B, GemmDims d, bf16_t* out, const float* scale, hipStream_t st) {

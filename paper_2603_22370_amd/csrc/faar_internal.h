@@ -174,7 +174,7 @@ struct GemmDims { int64_t M, N, Kd, lda, ldb; };
 // dYt[n][m] = bf16(two_alpha * R) with row stride ldt (rows n < N, columns m < ldt, zero for m >= M);
 // dY (nullable) [M, N] the same values un-transposed.
 // C == nullptr: the V-dependent part alone -- A = x_scale * acc, sum A^2 per tile, dYt = bf16(two_alpha * A) (dY must
-// be null); with dYt == nullptr too, only the sums are produced.
+// be null).  With neither dYt nor dY only the sums are produced, with or without C.
 // guard: when its slot is set, workgroup 0 first compares the stored forward tag with guard.expect (see ForwardTag)
 // warm (nullable), warm_bytes: a buffer the kernel reads on the side during the main loop and discard, so that the
 // next kernel finds it in the last-level cache (X_q^T for the dW GEMM); 16-byte aligned, whole KB are read
@@ -224,5 +224,7 @@ hipError_t launch_gemm_gram(const bf16_t* delta, const bf16_t* gram, int64_t O, 
 // out[m][n] = bf16(scale * acc), scale a device scalar (null = 1)
 hipError_t launch_gemm_bf16(const bf16_t* A, const bf16_t* B, GemmDims d, bf16_t* out, const float* scale,
                             hipStream_t st);
+// out[m][n] = bf16(sum_k A[m][k] B[k][n]), B [Kd, ldb] row-major; N, Kd multiples of 8
+hipError_t launch_gemm_bf16_nn(const bf16_t* A, const bf16_t* B, GemmDims d, bf16_t* out, hipStream_t st);
 
 }  // namespace faar
