@@ -51,6 +51,10 @@ STEP_CASES = [
     StepCase("dw_token_major_256x192_split", 6576, 528, 2048, 37, whole_device=True),
     StepCase("dw_token_major_256x192_split_long", 6576, 528, 4096, 38, whole_device=True),
     StepCase("dw_split_256x128", 6576, 272, 2048, 39),           # dW GEMM: 256x128 tiles, contraction split
+    StepCase("dx_256x192", 16, 3072, 4096, 48, chained=True),    # dX GEMM: 256x192 tiles
+    # token-major dY out of the residual GEMM (with H) on 192x256 and 256x192 tiles
+    StepCase("rows_192x256", 14336, 160, 6144, 49),
+    StepCase("rows_256x192", 4416, 544, 8192, 50),
     # residual contractions that end inside a slice: 16 and 48 of 64 on 128x64 tiles, 16 on 128x128 (config-sized ones above: 32)
     StepCase("tail_16", 272, 80, 192, 45, chained=True),
     StepCase("tail_48", 136, 624, 520, 46, chained=True),
@@ -76,6 +80,8 @@ GRAM_CASES = [
     StepCase("gram_256x128_k64", 4096, 1088, 192, 42),            # 256x128 tiles, 64-wide slices, whole
     StepCase("gram_256x128_k32", 4096, 1056, 192, 43),            # 256x128 tiles, 32-wide slices
     StepCase("gram_256x128_split_k3072", 656, 3072, 256, 44),
+    StepCase("gram_256x192_split", 400, 6144, 192, 51),           # 256x192 and 256x256 tiles, contraction split
+    StepCase("gram_256x256_split", 688, 6144, 192, 52),
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}
