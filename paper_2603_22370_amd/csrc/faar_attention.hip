@@ -25,6 +25,7 @@
 // Measured, forward / dq / dk + dv in us, against 16x16x32 products on transposed copies with 32-token blocks (whose dk / dv
 // kernel held one workgroup per compute unit): 2 sequences of 4096 tokens, 16 / 8 heads of 128: 338 / 370 / 1008, and 37 of
 // transposes and 12 for delta -> 158 / 210 / 363; forward and backward of 32 sequences of 512: 112 and 507 (+ 98) -> 77 and 260.
+// dk + dv on 64 instead of 128 keys a workgroup: 2 x 4096 tokens (512 groups of 128) 380 -> 334, 32 x 512 (1024 groups) 118 -> 122.
 #include <algorithm>
 
 #include "faar_internal.h"
@@ -425,8 +426,10 @@ k_attn_bwd_dq(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const 
 }
 
 // dv = P^T dO and dk = scale * dS^T q, summed over the query heads that share the key / value head.  A workgroup owns
-// 128 key positions of a key / value head and sequence (32 per wavefront) and walks the blocks of 64 queries at or after
-// them, for each query head of the group in turn; the block's lse and delta go through LDS beside its tiles.
+// 128 / QW key positions of a key / value head and sequence (32 per wavefront; with QW = 2 the other two wavefronts take the
+// second 32 queries of every block for the same keys, and the two sums meet through LDS at the end) and walks the blocks of
+// 64 queries at or after them, for each query head of the group in turn; the block's lse and delta go through LDS beside its
+// tiles.
 template <int DH>
 __device__ __forceinline__ void dkv_tile(f32x16 (&dk)[DH / 32], f32x16 (&dv)[DH / 32], const bf16x8 (&kf)[DH / 16],
                                          const bf16x8 (&vf)[DH / 16], const float* lse_lds, const float* delta_lds,
@@ -483,17 +486,18 @@ __device__ __forceinline__ void dkv_tile(f32x16 (&dk)[DH / 32], f32x16 (&dv)[DH 
   }
 }
 
-template <int DH>
+template <int DH, int QW>
 __global__ void __launch_bounds__(256, 2)
 k_attn_bwd_dkv(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
                const bf16_t* __restrict__ dO, const float* __restrict__ lse, const float* __restrict__ delta, AttnDims d,
                bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
-  constexpr int KS = DH / 16, DT = DH / 32;
+  constexpr int KS = DH / 16, DT = DH / 32, KW = 4 / QW;   // KW: blocks of 32 keys
   typedef Tile<DH> Tl;
   __shared__ __attribute__((aligned(1024))) bf16_t lds[2][2][Tl::ELEMS];   // [stage][q, dO]
   __shared__ __attribute__((aligned(16))) float stats[2][2][kTok];         // [stage][lse, delta]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, hi = lane >> 5;
-  const int blocks = d.S / 32, groups = (blocks + 3) / 4;
+  const int kw = wave % KW, qw = wave / KW;
+  const int blocks = d.S / 32, groups = (blocks + KW - 1) / KW;
   const int pairs = static_cast<int>(gridDim.x) / groups;
   int grp, pair;
   work_item(blockIdx.x, pairs, groups, grp, pair);   // the first positions are seen by the most queries
@@ -501,7 +505,7 @@ k_attn_bwd_dkv(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const
   const int64_t b = pair / d.n_kv;
   const int rep = d.n_q / d.n_kv;
   const int64_t t0 = b * d.S, ldq = (int64_t)d.n_q * DH, ldk = (int64_t)d.n_kv * DH;
-  const int kb = grp * 4 + wave;                 // this wavefront's block of 32 positions
+  const int kb = grp * KW + kw;                 // this wavefront's block of 32 positions
   const bool active = kb < blocks;
   const int64_t t = t0 + kb * 32 + n;
   const float c = d.scale * kLog2e;
@@ -519,8 +523,8 @@ k_attn_bwd_dkv(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const
     dk[dt] = zero16();
     dv[dt] = zero16();
   }
-  // steps: query head of the group (outer) x 64-query block first .. last (inner); 128-position groups start on such a block
-  const int first = grp * 2, n_blk = (blocks + 1) / 2, steps = rep * (n_blk - first);
+  // steps: query head of the group (outer) x 64-query block first .. last (inner); groups of 128 and of 64 positions start on such a block
+  const int first = grp * KW / 2, n_blk = (blocks + 1) / 2, steps = rep * (n_blk - first);
 #define FAAR_DKV_COPY(STAGE, HEAD, BLK)                                                                  \
   do {                                                                                                  \
     const int q0_ = (BLK) * kTok;                                                                       \
@@ -547,7 +551,7 @@ k_attn_bwd_dkv(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const
     const uint32_t q_lds = lds0 + (it & 1) * (2 * Tl::ELEMS * 2);
     const float *lse_lds = stats[it & 1][0], *delta_lds = stats[it & 1][1];
 #pragma unroll 1
-    for (int qt = 0; qt < 2; ++qt) {
+    for (int qt = qw; qt < 2; qt += QW) {
       const int qb = qb0 + qt;               // block of 32 queries
       if (!active || qb < kb || qb >= blocks) continue;
       const uint32_t tile = q_lds + qt * (32 * DH * 2);
@@ -555,6 +559,27 @@ k_attn_bwd_dkv(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const
     }
   }
 #undef FAAR_DKV_COPY
+  if constexpr (QW == 2) {
+    // the two wavefronts of a block of keys: one hands over its dv and finishes dk, the other the reverse
+    f32x16* give = reinterpret_cast<f32x16*>(lds) + (size_t)wave * DT * 64 + lane;
+    const f32x16* take = reinterpret_cast<const f32x16*>(lds) + (size_t)(wave ^ KW) * DT * 64 + lane;
+    static_assert(4 * DT * 64 * sizeof(f32x16) <= sizeof(lds), "exchange fits in the stages");
+    __syncthreads();
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) give[dt * 64] = qw == 0 ? dv[dt] : dk[dt];
+    __syncthreads();
+    if (!active) return;
+    const float k = qw == 0 ? d.scale : 1.0f;
+    bf16_t* out = qw == 0 ? dK : dV;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const f32x16 r = (qw == 0 ? dk[dt] : dv[dt]) + take[dt * 64];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        store4_bf16(out + t * ldk + kvh * DH + dt * 32 + 8 * j + 4 * hi, r[4 * j] * k, r[4 * j + 1] * k, r[4 * j + 2] * k, r[4 * j + 3] * k);
+    }
+    return;
+  }
   if (!active) return;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -620,14 +645,24 @@ hipError_t launch_attention_bwd(const bf16_t* dO, const bf16_t* Q, const bf16_t*
                                 float scale, bf16_t* dQ, bf16_t* dK, bf16_t* dV, hipStream_t st) {
   const AttnDims d{static_cast<int>(S), static_cast<int>(n_q), static_cast<int>(n_kv), n_seq * S, scale};
   const int64_t groups = (S + 127) / 128;
-  const dim3 gq(static_cast<unsigned>(n_seq * n_q * groups)), gk(static_cast<unsigned>(n_seq * n_kv * groups));
-  if (dh == 128) {
-    hipLaunchKernelGGL(k_attn_bwd_dq<128>, gq, dim3(256), 0, st, Q, K, V, dO, O, lse, delta, d, dQ);
-    hipLaunchKernelGGL(k_attn_bwd_dkv<128>, gk, dim3(256), 0, st, Q, K, V, dO, lse, delta, d, dK, dV);
-  } else {
-    hipLaunchKernelGGL(k_attn_bwd_dq<64>, gq, dim3(256), 0, st, Q, K, V, dO, O, lse, delta, d, dQ);
-    hipLaunchKernelGGL(k_attn_bwd_dkv<64>, gk, dim3(256), 0, st, Q, K, V, dO, lse, delta, d, dK, dV);
-  }
+  const dim3 gq(static_cast<unsigned>(n_seq * n_q * groups));
+  // The work of a group of keys falls linearly with its position and two workgroups share a compute unit: with fewer than 1024
+  // groups of 128 keys the first ones end the launch alone on their units (2 x 4096 tokens, 8 heads: 512 groups), and 64 keys
+  // a workgroup halve the longest and leave twice as many to fill in behind them.  With more, the larger group's fewer
+  // copies count (figures at the top).
+  const bool halves = n_seq * n_kv * groups < 1024;
+  const dim3 gk(static_cast<unsigned>(n_seq * n_kv * (halves ? (S + 63) / 64 : groups)));
+#define FAAR_BWD(DH)                                                                                                          \
+  do {                                                                                                                        \
+    hipLaunchKernelGGL(k_attn_bwd_dq<DH>, gq, dim3(256), 0, st, Q, K, V, dO, O, lse, delta, d, dQ);                           \
+    if (halves)                                                                                                               \
+      hipLaunchKernelGGL((k_attn_bwd_dkv<DH, 2>), gk, dim3(256), 0, st, Q, K, V, dO, lse, delta, d, dK, dV);                  \
+    else                                                                                                                      \
+      hipLaunchKernelGGL((k_attn_bwd_dkv<DH, 1>), gk, dim3(256), 0, st, Q, K, V, dO, lse, delta, d, dK, dV);                  \
+  } while (0)
+  if (dh == 128) FAAR_BWD(128);
+  else FAAR_BWD(64);
+#undef FAAR_BWD
   return hipGetLastError();
 }
 

@@ -119,8 +119,9 @@ def test_attention_forward_and_backward(n_seq, S, n_q, n_kv, dh):
 
 
 # a last key block of 32 instead of 64 and a short last group of 128 positions, at either head width; and more than 256
-# workgroups of several ranks, so that the second round of resident workgroups (taken from light to heavy) is entered
-@pytest.mark.parametrize("n_seq,S,n_q,n_kv,dh", [(1, 224, 2, 1, 128), (2, 288, 4, 4, 64), (8, 1184, 4, 4, 64)])
+# workgroups of several ranks, so that the second round of resident workgroups (taken from light to heavy) is entered; and more
+# than 1024 groups of 128 positions, where the dk / dv kernel gives a workgroup all of a group (96 positions here)
+@pytest.mark.parametrize("n_seq,S,n_q,n_kv,dh", [(1, 224, 2, 1, 128), (2, 288, 4, 4, 64), (8, 1184, 4, 4, 64), (342, 96, 3, 3, 64)])
 def test_attention_at_the_edges_of_its_blocks(n_seq, S, n_q, n_kv, dh):
     q, k, v, do = _attn_inputs(n_seq, S, n_q, n_kv, dh, 3)
     o, lse = faar.faar_attention_fwd(dev(q), dev(k), dev(v), n_seq, n_q, n_kv)
