@@ -81,7 +81,10 @@ GRAM_CASES = [
     StepCase("gram_256x128_k32", 4096, 1056, 192, 43),            # 256x128 tiles, 32-wide slices
     StepCase("gram_256x128_split_k3072", 656, 3072, 256, 44),
     StepCase("gram_256x192_split", 400, 6144, 192, 51),           # 256x192 and 256x256 tiles, contraction split
-    StepCase("gram_256x256_split", 688, 6144, 192, 52),
+    # (not seed 52: at beta = 20 one entry of its W_q - W on a x 30 outlier channel lies on a bf16 rounding boundary, and a flip of it
+    # moves its row of the gradient by up to 2^-8 |W_q - W| Gm[k][k], 3e-2 of the gradient's rms, and the loss by 2.6e-5 -- the same
+    # on 256x128 tiles as on these)
+    StepCase("gram_256x256_split", 688, 6144, 192, 53),
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}
