@@ -120,3 +120,26 @@ def test_stage2_masked_logits(V, dtype):
     Zq[0, 9] = -np.inf
     losses, _, _ = faar.faar_stage2_losses(dev(Zf), dev(Zq), 1.0, dev(Hf), dev(Hq), kl_scale=1.0 / T)
     assert losses[0].item() == np.inf
+
+
+def test_stage2_logits_masked_with_the_lowest_value():
+    """bf16's lowest finite value as a mask: in part of a row, in a row of which nothing else is left, and in z_fp alone; the float64
+    softmax of the same numbers.  V = 4096 is one chunk per lane, so chunks with and without unmasked entries occur."""
+    T, V, low = 4, 4096, torch.finfo(torch.bfloat16).min
+    gen = torch.Generator().manual_seed(7)
+    zf = torch.randn((T, V), generator=gen).to(torch.bfloat16)
+    zq = (zf.float() + 0.3 * torch.randn((T, V), generator=gen)).to(torch.bfloat16)
+    zf[1, 100:3000] = low
+    zq[1, 100:3000] = low
+    zf[2], zq[2] = low, low
+    zf[3, 5:900] = low
+    a, b = zf.double(), zq.double()
+    lp, lq = torch.log_softmax(a, -1), torch.log_softmax(b, -1)
+    p, q = lp.exp(), lq.exp()
+    kl = torch.where(p > 0, p * (lp - lq), torch.zeros_like(p)).sum()
+    h = torch.zeros((T, 8), dtype=torch.bfloat16, device="cuda")
+    losses, dZ, _ = faar.faar_stage2_losses(zf.cuda(), zq.cuda(), 1.0, h, h, kl_scale=1.0, mse_scale=1.0)
+    # the tolerances at the top of this file, and one bf16 rounding of the gradient
+    assert float(losses[0]) == pytest.approx(float(kl), rel=1e-5, abs=2e-6 * T)
+    err = (dZ.double().cpu() - (q - p)).abs()
+    assert bool((err <= 2.0 ** -8 * (q - p).abs() + 3e-6 * float(torch.maximum(p, q).max())).all())
