@@ -305,9 +305,9 @@ size_t faar_workspace_bytes(int op, int64_t O, int64_t K, int64_t T, uint32_t fl
     case FAAR_OP_LAYER_PREPARE: {
       if (T <= 0 || T > kMaxElems / (O > K ? O : K)) return 0;
       size_t need = 3 * align256((size_t)O * K * 2);  // hi/mid/lo bf16 terms of a float32 W
-      if (flags & FAAR_WS_GRADIENT_CONSTANT) {        // one bf16 term of C^T, the partial products, sums of C^2
+      if (flags & FAAR_WS_GRADIENT_CONSTANT) {        // the bf16 terms of C^T, the partial products, sums of C^2
         const int64_t Tp = padded_tokens(T);
-        const size_t h = align256((size_t)O * Tp * 2) + align256((size_t)choose_split(O, K, Tp) * O * K * 4) +
+        const size_t h = align256((size_t)O * 3 * Tp * 2) + align256((size_t)choose_split(O, K, Tp) * O * K * 4) +
                          align256((size_t)c_term_blocks(T, O) * 8);
         need = need > h ? need : h;
       }
@@ -474,20 +474,21 @@ int faar_layer_prepare(const void* W, faar_dtype wdt, int64_t O, int64_t K, cons
       if (int e = hip_status(launch_gemm_sub(xq, term[i], d, Y_fp, ydt == FAAR_BF16, i == 0, C, x_scale, st))) return e;
   }
   if (!H) return FAAR_OK;
-  // H = C^T Xq (the activations as stored, i.e. in units of x_scale): C is split into three bf16 terms, each
-  // transposed into the operand layout of the dW GEMM and multiplied with Xt on the matrix cores (exact products,
-  // float32 accumulation); the terms' partial products are summed into H.  ||C||^2 comes from the first pass over C.
+  // H = C^T Xq (the activations as stored, i.e. in units of x_scale): C is split into three bf16 terms, transposed side by side
+  // into the operand layout of the dW GEMM and multiplied with Xt on the matrix cores in one product (exact products, float32
+  // accumulation), whose partial sums add up to H.  ||C||^2 comes from the pass that makes the terms.
   Carver cv(ws);   // the float32-W terms above are no longer needed
-  bf16_t* ct = cv.take<bf16_t>((size_t)O * Tp);
+  bf16_t* ct = cv.take<bf16_t>((size_t)O * 3 * Tp);
   const int n_split = choose_split(O, K, Tp);
   float* part = cv.take<float>((size_t)n_split * O * K);
   double* sq = cv.take<double>((size_t)c_term_blocks(T, O));
-  const GemmDims d2{O, K, Tp, Tp, Tp};
-  for (int term = 0; term < 3; ++term) {
-    if (int e = hip_status(launch_c_term_transposed(C, T, O, term, ct, Tp, term == 0 ? sq : nullptr, st))) return e;
-    if (int e = hip_status(launch_gemm_f32(ct, static_cast<const bf16_t*>(Xt), d2, part, n_split, st))) return e;
-    if (int e = hip_status(launch_accumulate_partials(H, part, n_split, (int64_t)O * K, O * K, term == 0, st))) return e;
-  }
+  if (int e = hip_status(launch_c_terms_transposed(C, T, O, ct, sq, st))) return e;
+  // with one split the product is H itself
+  float* out = n_split == 1 ? H : part;
+  if (int e = hip_status(launch_gemm_f32_terms(ct, static_cast<const bf16_t*>(Xt), GemmDims{O, K, Tp, 3 * Tp, Tp}, out, n_split, st)))
+    return e;
+  if (n_split > 1)
+    if (int e = hip_status(launch_accumulate_partials(H, part, n_split, (int64_t)O * K, O * K, st))) return e;
   return hip_status(launch_sum_doubles(sq, c_term_blocks(T, O), c_norm2, st));
 }
 

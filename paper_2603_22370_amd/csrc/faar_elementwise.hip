@@ -739,14 +739,15 @@ k_transpose_bf16(const bf16_t* __restrict__ in, int64_t rows, int64_t cols, bf16
 }
 
 // ---- the constant part of the gradient, H = C^T X_q (once per layer) -----------------------------------------------
-// C (float32, tokens interleaved in groups of four: [ceil(T/4)][O][4]) -> one of its three bf16 terms hi / mid / lo
-// (each the rounding of the running remainder: together all 24 significand bits), transposed to [O, ld_out] with
-// zero padding, i.e. in the operand layout of the dW GEMM.  64 outputs x 64 tokens per workgroup through LDS; both
-// sides move whole 128-byte (or longer) runs.  With sq_partials != null the workgroup also writes its sum of C^2.
+// C (float32, tokens interleaved in groups of four: [ceil(T/4)][O][4]) -> its three bf16 terms hi / mid / lo (each the rounding of
+// the running remainder: together all 24 significand bits), transposed to [O, 3, Tp] with zero padding, i.e. side by side in
+// the operand layout of the dW GEMM.  64 outputs x 64 tokens per workgroup through LDS; both sides move whole 128-byte (or
+// longer) runs.  HBM-bound; C is read once for all three (8192 x 2048: three passes of 21 us -> one of 31).  The workgroup also
+// writes its sum of C^2.
 __global__ void __launch_bounds__(256)
-k_c_term_transposed(const float* __restrict__ C, int64_t T, int64_t O, int term, bf16_t* __restrict__ out, int64_t ld_out,
-                    unsigned tiles_o, double* __restrict__ sq_partials) {
-  __shared__ uint32_t tile[64][33];            // [output][token pair], pitch 33 words
+k_c_terms_transposed(const float* __restrict__ C, int64_t T, int64_t O, bf16_t* __restrict__ out, int64_t Tp, unsigned tiles_o,
+                     double* __restrict__ sq_partials) {
+  __shared__ uint32_t tile[3][64][33];         // [term][output][token pair], pitch 33 words
   const int64_t o0 = (blockIdx.x % tiles_o) * 64LL, t0 = (blockIdx.x / tiles_o) * 64LL;
   const int og = threadIdx.x & 63, gq = threadIdx.x >> 6;
   const int64_t groups = (T + 3) / 4;
@@ -758,18 +759,20 @@ k_c_term_transposed(const float* __restrict__ C, int64_t T, int64_t O, int term,
     float4 c = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (gg < groups && o < O) c = *reinterpret_cast<const float4*>(C + (gg * O + o) * 4);
     const float x[4] = {c.x, c.y, c.z, c.w};
-    uint32_t b[4];
+    uint32_t b[3][4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       sq += x[q] * x[q];
-      const uint32_t h = f32_to_bf16(x[q]);
-      const float r1 = x[q] - bf16_to_f32(h);
-      const uint32_t m = f32_to_bf16(r1);
-      const float r2 = r1 - bf16_to_f32(m);
-      b[q] = term == 0 ? h : (term == 1 ? m : f32_to_bf16(r2));
+      b[0][q] = f32_to_bf16(x[q]);
+      const float r1 = x[q] - bf16_to_f32(b[0][q]);
+      b[1][q] = f32_to_bf16(r1);
+      b[2][q] = f32_to_bf16(r1 - bf16_to_f32(b[1][q]));
     }
-    tile[og][2 * g] = b[0] | (b[1] << 16);
-    tile[og][2 * g + 1] = b[2] | (b[3] << 16);
+#pragma unroll
+    for (int term = 0; term < 3; ++term) {
+      tile[term][og][2 * g] = b[term][0] | (b[term][1] << 16);
+      tile[term][og][2 * g + 1] = b[term][2] | (b[term][3] << 16);
+    }
   }
   __syncthreads();
   const int sub = threadIdx.x >> 3, ch = threadIdx.x & 7;
@@ -777,24 +780,24 @@ k_c_term_transposed(const float* __restrict__ C, int64_t T, int64_t O, int term,
   for (int p = 0; p < 2; ++p) {
     const int row = p * 32 + sub;
     const int64_t o = o0 + row, t = t0 + ch * 8;
-    if (o < O && t < ld_out)                   // ld_out is a multiple of 64: a chunk is inside or outside as a whole
-      *reinterpret_cast<uint4*>(out + o * ld_out + t) =
-          make_uint4(tile[row][ch * 4], tile[row][ch * 4 + 1], tile[row][ch * 4 + 2], tile[row][ch * 4 + 3]);
+    if (o < O && t < Tp) {                     // Tp is a multiple of 64: a chunk is inside or outside as a whole
+#pragma unroll
+      for (int term = 0; term < 3; ++term) {
+        const uint32_t* r = tile[term][row] + ch * 4;
+        *reinterpret_cast<uint4*>(out + (o * 3 + term) * Tp + t) = make_uint4(r[0], r[1], r[2], r[3]);
+      }
+    }
   }
-  if (sq_partials) {
-    __syncthreads();
-    const double bs = block_sum(static_cast<double>(sq));
-    if (threadIdx.x == 0) sq_partials[blockIdx.x] = bs;
-  }
+  const double bs = block_sum(static_cast<double>(sq));
+  if (threadIdx.x == 0) sq_partials[blockIdx.x] = bs;
 }
 
-// H = (first ? 0 : H) + sum over the splits of the partial products
+// H = sum over the splits of the partial products
 __global__ void __launch_bounds__(kEltThreads)
-k_accumulate_partials(float* __restrict__ H, const float* __restrict__ partials, int n_split, int64_t stride, int64_t n4,
-                      bool first) {
+k_accumulate_partials(float* __restrict__ H, const float* __restrict__ partials, int n_split, int64_t stride, int64_t n4) {
   const int64_t i = blockIdx.x * (int64_t)kEltThreads + threadIdx.x;
   if (i >= n4) return;
-  float4 a = first ? make_float4(0.0f, 0.0f, 0.0f, 0.0f) : reinterpret_cast<const float4*>(H)[i];
+  float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   for (int s = 0; s < n_split; ++s) {
     const float4 p = *reinterpret_cast<const float4*>(partials + s * stride + i * 4);
     a.x += p.x; a.y += p.y; a.z += p.z; a.w += p.w;
@@ -1067,21 +1070,18 @@ hipError_t launch_check_forward_tag(const ForwardGuard& guard, hipStream_t st) {
 
 int64_t c_term_blocks(int64_t T, int64_t O) { return ((O + 63) / 64) * (padded_tokens(T) / 64); }
 
-hipError_t launch_c_term_transposed(const float* C, int64_t T, int64_t O, int term, bf16_t* out, int64_t ld_out,
-                                    double* sq_partials, hipStream_t st) {
-  if (ld_out != padded_tokens(T)) return hipErrorInvalidValue;
+hipError_t launch_c_terms_transposed(const float* C, int64_t T, int64_t O, bf16_t* out, double* sq_partials, hipStream_t st) {
   const int64_t tiles_o = (O + 63) / 64, blocks = c_term_blocks(T, O);
   if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_c_term_transposed, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, C, T, O, term, out, ld_out,
-                     static_cast<unsigned>(tiles_o), sq_partials);
+  hipLaunchKernelGGL(k_c_terms_transposed, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, C, T, O, out,
+                     padded_tokens(T), static_cast<unsigned>(tiles_o), sq_partials);
   return hipGetLastError();
 }
 
-hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, bool first,
-                                      hipStream_t st) {
+hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, hipStream_t st) {
   const int64_t n4 = n / 4;   // n = O * K is a multiple of 16
   hipLaunchKernelGGL(k_accumulate_partials, dim3(static_cast<unsigned>((n4 + kEltThreads - 1) / kEltThreads)), dim3(kEltThreads),
-                     0, st, H, partials, n_split, stride, n4, first);
+                     0, st, H, partials, n_split, stride, n4);
   return hipGetLastError();
 }
 

@@ -233,12 +233,25 @@ struct EpiF32 {
   __device__ __forceinline__ void finish(int) {}
 };
 
+// As EpiF32, for an A operand that is the sum of kTerms bf16 matrices side by side ([M, kTerms * Kd]): every work item walks its
+// slices once per term, the last term first, so that the small ones are added up before the sums are large.
+// 2048 x 2048 outputs, 8192 tokens, 4 splits: three products of 59 us, 13 of them writing partials, and three passes over the
+// partials of 14 -> 160 and one of 13; the error against 64 bits is that of the separate products or less (2.7e-7 of the norm).
+struct EpiF32Terms : EpiF32 {
+  static constexpr int kTerms = 3;
+};
+template <class E, class = void> struct TermsOf { static constexpr int value = 1; };
+template <class E> struct TermsOf<E, std::void_t<decltype(E::kTerms)>> { static constexpr int value = E::kTerms; };
+
 // C_out(m, n) = (first ? Y[m][n] : C_out(m, n)) - x_scale * acc, with C_out in the row-group-interleaved layout
 // [ceil(M/4)][N][4]: element (m, n) at ((m / 4) * N + n) * 4 + m % 4, so that the four consecutive rows a lane
 // holds of one column are one 16-byte access and the 16 or 32 lanes of a row group touch contiguous memory.
 // Rows M..4*ceil(M/4)-1 are written as zero.
+// A bf16 Y whose rows are whole 16-byte chunks passes through LDS (stage_y): a lane's four rows of one column are four loads of two
+// bytes otherwise, in segments of 32 bytes (8192 x 2048 outputs, contraction 2048: 104 -> 69 us).
 template <bool kYbf16>
 struct EpiSub {
+  static constexpr bool kStagedInput = kYbf16;
   static constexpr bool kRowStaged = false;
   static constexpr bool kWarm = false;
   static constexpr bool kTransposedOut = false;
@@ -253,10 +266,9 @@ struct EpiSub {
   __device__ __forceinline__ void begin() { xs = x_scale ? *x_scale : 1.0f; }
   __device__ __forceinline__ void rows4(const float (&acc)[4], int64_t m, int64_t n, int, const GemmDims& d) {
     if (n >= d.N || m >= d.M) return;  // m is a multiple of 4
-    float4* p = reinterpret_cast<float4*>(C_out + ((m >> 2) * d.N + n) * 4);
     float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (!first) {
-      const float4 c = *p;
+      const float4 c = *reinterpret_cast<const float4*>(C_out + ((m >> 2) * d.N + n) * 4);
       y[0] = c.x; y[1] = c.y; y[2] = c.z; y[3] = c.w;
     } else {
 #pragma unroll
@@ -266,10 +278,20 @@ struct EpiSub {
           y[q] = kYbf16 ? bf16_to_f32(static_cast<const bf16_t*>(Y)[idx]) : static_cast<const float*>(Y)[idx];
         }
     }
+    store4(acc, y, m, n, d);
+  }
+  __device__ __forceinline__ void store4(const float (&acc)[4], const float (&y)[4], int64_t m, int64_t n, const GemmDims& d) {
+    if (n >= d.N || m >= d.M) return;
     float o[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) o[q] = (m + q < d.M) ? y[q] - xs * acc[q] : 0.0f;
-    *p = make_float4(o[0], o[1], o[2], o[3]);
+    *reinterpret_cast<float4*>(C_out + ((m >> 2) * d.N + n) * 4) = make_float4(o[0], o[1], o[2], o[3]);
+  }
+  __device__ __forceinline__ bool staged_input(const GemmDims& d) const { return first && d.N % 8 == 0; }
+  // columns n..n+7 of row m of Y (n and N multiples of 8), zero outside
+  __device__ __forceinline__ uint4 input8(int64_t m, int64_t n, const GemmDims& d) const {
+    if (m >= d.M || n >= d.N) return make_uint4(0u, 0u, 0u, 0u);
+    return *reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(Y) + m * d.N + n);
   }
   __device__ __forceinline__ void finish(int) {}
 };
@@ -515,11 +537,58 @@ __device__ __forceinline__ int token_key(int t) {
 }
 
 // Hands a wavefront's TMW x TN accumulator tiles (rows wm .., columns wn .. of the output tile at m0, n0) to the epilogue
+template <class E, class = void> struct StagedInput { static constexpr bool value = false; };
+template <class E> struct StagedInput<E, std::void_t<decltype(E::kStagedInput)>> { static constexpr bool value = E::kStagedInput; };
+
 template <class C, int TMW, class Epi>
 __device__ __forceinline__ void epilogue(Epi& epi, f32x4 (&acc)[TMW][C::TN], bf16_t* lds, int64_t m0, int64_t n0, int wm, int wn,
                                          int split, const GemmDims& d, int tid, int lane, int wave, int wc) {
   constexpr int TN = C::TN;
   const int col = lane & 15, rq = lane >> 4;
+  if constexpr (StagedInput<Epi>::value) {
+    if (epi.staged_input(d)) {
+      // every wavefront brings 16 x WN of the bf16 input at a time through its own piece of LDS, a whole row group ahead
+      constexpr int PITCH = C::WN + 4, RUNS = C::WN / 32;   // 4 * PITCH = 32 bytes mod 256: the four row groups miss each other
+      static_assert(C::NW * 16 * PITCH <= C::NS * C::STAGE && C::WN % 32 == 0, "staging fits in the ring");
+      bf16_t* stg = lds + wave * 16 * PITCH;
+      uint4 next[RUNS];
+      auto fetch = [&](int i) {
+#pragma unroll
+        for (int t = 0; t < RUNS; ++t) {
+          const int idx = lane + 64 * t;
+          next[t] = epi.input8(m0 + wm + i * 16 + idx / (C::WN / 8), n0 + wn + (idx % (C::WN / 8)) * 8, d);
+        }
+      };
+      fetch(0);
+      __syncthreads();                               // nobody reads the ring any more
+#pragma unroll
+      for (int i = 0; i < TMW; ++i) {
+#pragma unroll
+        for (int t = 0; t < RUNS; ++t) {
+          const int idx = lane + 64 * t;
+          uint2* p = reinterpret_cast<uint2*>(stg + (idx / (C::WN / 8)) * PITCH + (idx % (C::WN / 8)) * 8);
+          p[0] = make_uint2(next[t].x, next[t].y);
+          p[1] = make_uint2(next[t].z, next[t].w);
+        }
+        if (i + 1 < TMW) fetch(i + 1);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          float y[4];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) y[v] = bf16_to_f32(stg[(4 * rq + v) * PITCH + j * 16 + col]);
+          const float r[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+          epi.store4(r, y, m0 + wm + i * 16 + 4 * rq, n0 + wn + j * 16 + col, d);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+      return;
+    }
+  }
   if constexpr (Epi::kTransposedOut) {
     // Output is wanted transposed ([n][m], m contiguous) while a lane holds 4 consecutive m of one n: stage a 32-column slab
     // (two 16-column tiles) per wavefront column through LDS and write whole rows with 16 B per lane
@@ -615,7 +684,8 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
   const int ksteps = static_cast<int>((d.Kd + DBK64 - 1) / DBK64);
   const int kbeg = split * ksteps_per_split;
   const int kend = kbeg + ksteps_per_split < ksteps ? kbeg + ksteps_per_split : ksteps;
-  const int nk = kend - kbeg;
+  constexpr int kTerms = TermsOf<Epi>::value;
+  const int nk = kTerms * (kend - kbeg);
   constexpr int P = C::P, KK = C::KK, NF = C::NF, NM = C::NM, TM = C::TM, TN = C::TN;
   // vector-memory instructions a wavefront issues per slice: the copies, and one side read with kWarm.  Loads complete
   // in order, so the wait counts below are in units of this
@@ -699,12 +769,22 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
       }
       return g;
     };
+    // with kTerms: slice `rel` of the work item is slice rel % per of its tokens, in the operand's last term first; the offsets (of A
+    // and B) from the first slice's sources, the same for every copy
+    static_assert(kTerms == 1 || (!C::kTokenA && !C::kTokenB && !kTail), "terms lie side by side in the rows of A");
+    auto term_offsets = [&](int rel, int64_t& of_a, int64_t& of_b) {
+      const int per = kend - kbeg, pass = (rel >= per) + (rel >= 2 * per);
+      of_b = (int64_t)(kbeg + rel - pass * per) * DBK64;
+      of_a = of_b + (kTerms - 1 - pass) * d.Kd;
+    };
 #pragma unroll
     for (int s = 0; s < C::NS; ++s) {
       const int t = kbeg + (s < nk ? s : nk - 1);
+      int64_t of_a = 0, of_b = 0;
+      if constexpr (kTerms > 1) term_offsets(t - kbeg, of_a, of_b);
 #pragma unroll
       for (int q = 0; q < P; ++q)
-        dma16(source(q, t),
+        dma16(kTerms > 1 ? gsrc[q] + (wave * P + q < C::BM / 8 ? of_a : of_b) : source(q, t),
               __builtin_amdgcn_readfirstlane(lds_addr_of(lds + s * C::STAGE + (wave * P + q) * C::RPI * DBK64)));
       FAAR_SIDE_READ(s)
     }
@@ -764,6 +844,8 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
       const bf16_t* sn = lds + ((it + 1) % C::NS) * C::STAGE;
       const bool more = it + C::NS < nk;
       const int64_t gslice = kbeg + it + C::NS;
+      int64_t of_a = 0, of_b = 0;
+      if constexpr (kTerms > 1) term_offsets(more ? it + C::NS : 0, of_a, of_b);
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
         constexpr int kFirst = decltype(kOdd)::value;
@@ -818,7 +900,9 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
           if (Epi::kMode != 1 && kk == KK - 1 && m % C::DSTEP == 0 && m / C::DSTEP < P) {
             // slice it+NS into the stage just released; past the end every lane re-reads one valid address
             const int q = m / C::DSTEP;
-            const bf16_t* g = more ? source(q, gslice) : A;
+            const bf16_t* g;
+            if constexpr (kTerms > 1) g = gsrc[q] + (wave * P + q < C::BM / 8 ? of_a : of_b);
+            else g = more ? source(q, gslice) : A;
             dma16(g, __builtin_amdgcn_readfirstlane(lds_addr_of(st + (wave * P + q) * C::RPI * DBK64)));
           }
           if (Epi::kMode != 1 && kk == KK - 1 && m == (P - 1) * C::DSTEP + 1) {   // right after the slice's last copy
@@ -1038,6 +1122,12 @@ hipError_t launch_gemm_f32(const bf16_t* A, const bf16_t* B, GemmDims d, float* 
   Plan p = plan_gemm(d, true, kEpiF32);
   if (p.n_split != n_split) return hipErrorInvalidValue;  // the caller sized its workspace with choose_split
   return run(A, B, d, p, e, st);
+}
+
+hipError_t launch_gemm_f32_terms(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split, hipStream_t st) {
+  const Plan p = plan_gemm(GemmDims{d.M, d.N, d.Kd, d.Kd, d.Kd}, true, kEpiF32);
+  if (p.n_split != n_split || d.Kd % DBK64 != 0 || d.lda < 3 * d.Kd || d.lda % 8 != 0) return hipErrorInvalidValue;
+  return run(A, B, d, p, EpiF32Terms{{out}}, st);
 }
 
 int choose_split_gram(int64_t O, int64_t K) { return plan_gemm(GemmDims{O, K, K, K, K}, true, kEpiGram).n_split; }

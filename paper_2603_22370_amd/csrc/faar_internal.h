@@ -105,14 +105,12 @@ hipError_t launch_finalize_losses(const double* mse_partials, int64_t n_mse, flo
 hipError_t launch_transpose_bf16(const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out,
                                  int64_t ld_out, hipStream_t st);
 hipError_t launch_check_forward_tag(const ForwardGuard& guard, hipStream_t st);
-// Term `term` (0 hi, 1 mid, 2 lo) of the float32 C [ceil(T/4)][O][4] as bf16, transposed to [O, ld_out] (ld_out =
-// padded_tokens(T), zero padded); sq_partials (nullable): c_term_blocks(T, O) per-workgroup sums of C^2
+// The three bf16 terms (hi, mid, lo) of the float32 C [ceil(T/4)][O][4], transposed to [O, 3, padded_tokens(T)], zero padded;
+// sq_partials: c_term_blocks(T, O) per-workgroup sums of C^2
 int64_t c_term_blocks(int64_t T, int64_t O);
-hipError_t launch_c_term_transposed(const float* C, int64_t T, int64_t O, int term, bf16_t* out, int64_t ld_out,
-                                    double* sq_partials, hipStream_t st);
-// H[0..n) = (first ? 0 : H) + sum_s partials[s * stride + i]
-hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, bool first,
-                                      hipStream_t st);
+hipError_t launch_c_terms_transposed(const float* C, int64_t T, int64_t O, bf16_t* out, double* sq_partials, hipStream_t st);
+// H[0..n) = sum_s partials[s * stride + i]
+hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, hipStream_t st);
 hipError_t launch_sum_doubles(const double* p, int64_t n, double* out, hipStream_t st);
 // gram[i] = bf16(sum_s partials[s * K * K + i]) for the K x K matrix; diag_lo[k] = that sum at (k, k) minus its bf16 rounding
 hipError_t launch_gram_finish(const float* partials, int n_split, int64_t K, bf16_t* gram, float* diag_lo, hipStream_t st);
@@ -193,6 +191,8 @@ int64_t gemm_residual_partials(int64_t M, int64_t N, int64_t Kd);
 hipError_t launch_gemm_f32(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split,
                            hipStream_t st);
 int choose_split(int64_t M, int64_t N, int64_t Kd);
+// The same with A the sum of three matrices side by side ([M, 3 * Kd], lda >= 3 * Kd; Kd a multiple of 64)
+hipError_t launch_gemm_f32_terms(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split, hipStream_t st);
 // The same product from token-major operands: out[s][m][n] = sum_t A[t][m] * B[t][n], A [T, lda], B [T, ldb] (the contraction
 // index is the row index; d.Kd = T).  Only where gemm_tn_usable says so (T a multiple of 64, M and N multiples of 8, a shape
 // the planner gives 256 x 256 tiles); n_split = choose_split(M, N, T) as for launch_gemm_f32.

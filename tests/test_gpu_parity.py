@@ -915,3 +915,25 @@ def test_full_size_codec_bit_exact(name):
     assert np.array_equal(host(codes2), hp["codes"]) and np.array_equal(host(dec), hp["decisions"])
     assert np.array_equal(host(Wf).view(np.uint32), hp["W_final"].view(np.uint32))
     assert int(flips.item()) == hp["flip_count"]
+
+
+@pytest.mark.parametrize("O,K,T", [(100, 48, 67), (104, 64, 67), (264, 128, 200), (520, 272, 1025)])
+def test_layer_prepare_constants_against_float64(O, K, T):
+    """C = Y - X W^T and H = C^T X, ||C||^2 (of the C that was returned): rows of Y that are whole 16-byte chunks and rows that are not,
+    partial tiles and token groups, one split of the contraction and several."""
+    gen = torch.Generator(device="cuda").manual_seed(O + T)
+    W = (0.02 * torch.randn((O, K), generator=gen, device="cuda")).to(torch.bfloat16)
+    X = torch.randn((T, K), generator=gen, device="cuda").to(torch.bfloat16)
+    Y = torch.randn((T, O), generator=gen, device="cuda").to(torch.bfloat16)
+    sg, scales, _, _ = faar.faar_quant_rtn(W)
+    _, C, _, H, c2 = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
+    Xd, Wd, Yd = X.double().cpu(), W.double().cpu(), Y.double().cpu()
+    c = C.flatten()[:(T + 3) // 4 * 4 * O].view(-1, O, 4).permute(0, 2, 1).reshape(-1, O).double().cpu()
+    assert not c[T:].any()
+    c = c[:T]
+    # products of bf16 values are exact in float32; n additions round at most n + 1 times by 2^-24 of the terms' absolute sum
+    assert bool(((c - (Yd - Xd @ Wd.T)).abs() <= (K + 2) * 2.0 ** -24 * (Yd.abs() + Xd.abs() @ Wd.abs().T)).all())
+    # C as three bf16 terms is exact to 2^-24; three additions per token
+    h = H.view(O, K).double().cpu()
+    assert bool(((h - c.T @ Xd).abs() <= (3 * T + 4) * 2.0 ** -24 * (c.abs().T @ Xd.abs())).all())
+    assert float(c2) == pytest.approx(float((c * c).sum()), rel=1e-6)
