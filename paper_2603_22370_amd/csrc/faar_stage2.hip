@@ -112,10 +112,23 @@ k_stage2_kl(const ZT* __restrict__ Zf, const ZT* __restrict__ Zq, int64_t v8, fl
   const ZT* zq = Zq + row * v8 * 8;
   const float ninf = -INFINITY;
   RowStats st{ninf, 0.0f, 0.0f, ninf, 0.0f};
+  // the next chunk is on its way while this one is added up (1408 rows of 72488 float32 logits: 406 -> 399 us)
+  float na[8], nb[8];
+  if (threadIdx.x < v8) {
+    W8<ZT>::load(zf + threadIdx.x * 8, na);
+    W8<ZT>::load(zq + threadIdx.x * 8, nb);
+  }
   for (int64_t c = threadIdx.x; c < v8; c += kRowThreads) {
     float a[8], b[8];
-    W8<ZT>::load(zf + c * 8, a);
-    W8<ZT>::load(zq + c * 8, b);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      a[j] = na[j];
+      b[j] = nb[j];
+    }
+    if (c + kRowThreads < v8) {
+      W8<ZT>::load(zf + (c + kRowThreads) * 8, na);
+      W8<ZT>::load(zq + (c + kRowThreads) * 8, nb);
+    }
     accumulate8(st, a, b, k);
   }
   // fixed-order reduction: butterfly inside each wavefront, then the wavefronts in index order
