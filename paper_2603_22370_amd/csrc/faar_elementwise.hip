@@ -81,6 +81,27 @@ __global__ void __launch_bounds__(kEltThreads) k_amax_final(const float* __restr
 // Shared by the single-tensor kernels and the batched ones below.  Inputs that a kernel reads exactly once are
 // loaded with the nontemporal hint.
 
+// The eight round-to-nearest nibbles of a chunk, by the hardware's float -> E2M1 conversion.  It rounds ties to even, the codec rounds
+// them up: setting the lowest bit of the quotient's pattern lifts an exact midpoint (whose significand ends in zeros) above itself and
+// moves no other value across one -- the float just below a midpoint has that bit set already.  The quotient is held at the largest
+// node (also where it is not a number, as code 7 always was), and the sign, a zero's too, is the weight's.
+// The quantise kernels are bound by the vector unit: about 120 instead of 190 instructions for 8 weights; 28 tensors of 201 M weights in
+// all, tensor scale included: 275 -> 249 us.
+__device__ __forceinline__ uint32_t encode_e2m1x8(const float (&w)[8], const BlockDivider& div) {
+  float q[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float wt = fminf(div.quotient<true>(fabsf(w[j])), 6.0f);
+    q[j] = __uint_as_float((__float_as_uint(w[j]) & 0x80000000u) | __float_as_uint(wt) | 1u);
+  }
+  uint32_t packed = 0;
+  packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, q[0], q[1], 1.0f, 0);
+  packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, q[2], q[3], 1.0f, 1);
+  packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, q[4], q[5], 1.0f, 2);
+  packed = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(packed, q[6], q[7], 1.0f, 3);
+  return packed;
+}
+
 // Round-to-nearest quantisation (Sec. 3.1; Table 2 steps 2-3).  Both lanes of an even/odd pair must be active.
 template <typename WT, bool kDequant>
 __device__ __forceinline__ void quant_chunk(const WT* __restrict__ W, int64_t i, float sg, uint8_t* __restrict__ scales,
@@ -97,17 +118,25 @@ __device__ __forceinline__ void quant_chunk(const WT* __restrict__ W, int64_t i,
   uint32_t packed = 0;
   float dq[8];
   const BlockDivider div(s, a);
-  auto encode = [&](auto fast) {
+  auto encode = [&] {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const float wt = div.quotient<decltype(fast)::value>(fabsf(w[j]));
+      const float wt = div.quotient<false>(fabsf(w[j]));
       // a zero weight has wt == 0 and therefore magnitude code 0; its nibble keeps the sign bit of w
       const uint32_t nib = ((__float_as_uint(w[j]) >> 31) << 3) | nearest_magnitude_code(wt);
       packed |= nib << (4 * j);
       if (kDequant) dq[j] = dequant(nib, sgv, dq_in_units ? 1.0f : sg);  // in units of s_global: an exact product
     }
   };
-  if (div.fast) encode(std::true_type{}); else encode(std::false_type{});
+  if (div.fast) {
+    packed = encode_e2m1x8(w, div);
+    if (kDequant) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) dq[j] = dequant((packed >> (4 * j)) & 15u, sgv, dq_in_units ? 1.0f : sg);
+    }
+  } else {
+    encode();
+  }
   codes[i] = packed;
   if ((i & 1) == 0) scales[i >> 1] = static_cast<uint8_t>(byte);
   if (kDequant) W8<WT>::store(W_dq + i * 8, dq);

@@ -937,3 +937,35 @@ def test_layer_prepare_constants_against_float64(O, K, T):
     h = H.view(O, K).double().cpu()
     assert bool(((h - c.T @ Xd).abs() <= (3 * T + 4) * 2.0 ** -24 * (c.abs().T @ Xd.abs())).all())
     assert float(c2) == pytest.approx(float((c * c).sum()), rel=1e-6)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("scale", [1.0, 0.0625, 24.0])
+def test_round_to_nearest_codes_at_and_next_to_every_midpoint(bf16, scale):
+    """Blocks whose scale is exactly `scale` (largest magnitude 6 scale, tensor scale given as 1): midpoints go up, the floats next to
+    them to their own side, zeros keep their sign -- through the single-tensor, the dequantising and the batched kernel."""
+    mids = np.array([0.25, 0.75, 1.25, 1.75, 2.5, 3.5, 5.0], dtype=np.float32)
+    near = [mids, np.array([0.0, 0.5, 1.0, 6.0, 2.0 ** -40, 5.999], dtype=np.float32)]
+    if not bf16:
+        near += [np.nextafter(mids, np.float32(0)), np.nextafter(mids, np.float32(9)),
+                 np.nextafter(np.nextafter(mids, np.float32(0)), np.float32(0))]
+    mag = np.concatenate(near)
+    vals = np.concatenate([mag, -mag])
+    blocks = np.zeros(((len(vals) + 14) // 15, 16), dtype=np.float32)
+    blocks[:, :15].flat[:len(vals)] = vals
+    blocks[:, 15] = 6.0
+    W = torch.from_numpy(np.repeat(blocks * np.float32(scale), 2, axis=0)).cuda()
+    if bf16:
+        W = W.to(torch.bfloat16)
+    w = W.float().cpu().numpy() / np.float32(scale)   # the codec decides on the float32 quotient
+    want = (np.abs(w)[..., None] >= mids).sum(-1) | (np.signbit(w).astype(np.int64) << 3)
+    want = (want[:, 0::2] | (want[:, 1::2] << 4)).astype(np.uint8).ravel()
+    one = torch.ones(1, dtype=torch.float32, device="cuda")
+    for dq in (False, True):
+        _, _, codes, _ = faar.faar_quant_rtn(W, s_global=one, want_dq=dq)
+        assert np.array_equal(codes.cpu().numpy().ravel(), want)
+    batch_codes = torch.empty(W.numel() // 2, dtype=torch.uint8, device="cuda")
+    batch_scales = torch.empty(W.numel() // 16, dtype=torch.uint8, device="cuda")
+    items, dt = faar.binding.tensor_batch([W], [one], [batch_scales], codes=[batch_codes])
+    faar.faar_quant_rtn_batch(items, dt, None, s_global_given=True)
+    assert np.array_equal(batch_codes.cpu().numpy(), want)
