@@ -119,9 +119,7 @@ enum {
   FAAR_GEMM_L64 = 0, /* 256x256 tile */
   FAAR_GEMM_M64 = 1, /* 256x128 tile */
   FAAR_GEMM_S64 = 2, /* 128x128 tile */
-  FAAR_GEMM_N64 = 3, /* 128x64 tile */
-  FAAR_GEMM_A64 = 4, /* 192x256 tile */
-  FAAR_GEMM_B64 = 5  /* 256x192 tile */
+  FAAR_GEMM_N64 = 3  /* 128x64 tile */
 };
 
 /* Library version, MAJOR*10000 + MINOR*100 + PATCH.  Pure host function. */

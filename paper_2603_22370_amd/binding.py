@@ -221,7 +221,7 @@ def faar_dw_split(O: int, K: int, T: int) -> int:
 
 
 K_GEMM_C, K_GEMM_FWD, K_ATTENTION_FWD, K_ATTENTION_BWD, K_GEMM_GRAM = 10, 11, 12, 13, 14
-GEMM_KINDS = ("L64", "M64", "S64", "N64", "A64", "B64")
+GEMM_KINDS = ("L64", "M64", "S64", "N64")
 
 
 def faar_gemm_plan(which: int, O: int, K: int, T: int):

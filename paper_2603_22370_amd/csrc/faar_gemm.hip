@@ -957,13 +957,7 @@ typedef Dma64Cfg<256, 256, 2, 4, 2> CfgL64;  // 2 x 64 KB
 typedef Dma64Cfg<256, 128, 4, 2, 3> CfgM64;  // 3 x 48 KB: copies stay in flight for two slices
 typedef Dma64Cfg<128, 128, 2, 2, 4, kNT, 2> CfgS64;  // 4 x 32 KB, two contraction groups
 typedef Dma64Cfg<128, 64, 2, 2, 6, kNT, 2> CfgN64;   // 6 x 24 KB, two contraction groups
-// 2 x 56 KB: a 2048 x 6144 product is 192 tiles of 256x256 -- a quarter of the chip idle -- but 256 of these (as the Gram-form
-// product of such a layer: 175 -> 165 us)
-typedef Dma64Cfg<192, 256, 2, 4, 2> CfgA64;
-typedef Dma64Cfg<256, 192, 4, 2, 2> CfgB64;
-typedef Dma64Cfg<192, 256, 2, 4, 2, kNN> CfgA64N;
-typedef Dma64Cfg<256, 192, 4, 2, 2, kNN> CfgB64N;
-typedef Dma64Cfg<256, 256, 2, 4, 2, kNN> CfgL64N;   // the same on a token-major B
+typedef Dma64Cfg<256, 256, 2, 4, 2, kNN> CfgL64N;   // the same four on a token-major B
 typedef Dma64Cfg<256, 128, 4, 2, 3, kNN> CfgM64N;
 typedef Dma64Cfg<128, 128, 2, 2, 4, kNN, 2> CfgS64N;
 typedef Dma64Cfg<128, 64, 2, 2, 6, kNN, 2> CfgN64N;
@@ -975,8 +969,8 @@ typedef Dma64Cfg<256, 192, 4, 2, 2, kTN> CfgT64B;
 
 inline int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
-enum { KIND_L64 = 0, KIND_M64 = 1, KIND_S64 = 2, KIND_N64 = 3, KIND_A64 = 4, KIND_B64 = 5, KINDS = 6 };   // FAAR_GEMM_*
-constexpr int kTileRows[KINDS] = {256, 256, 128, 128, 192, 256}, kTileCols[KINDS] = {256, 128, 128, 64, 256, 192};
+enum { KIND_L64 = 0, KIND_M64 = 1, KIND_S64 = 2, KIND_N64 = 3, KINDS = 4 };   // FAAR_GEMM_*
+constexpr int kTileRows[KINDS] = {256, 256, 128, 128}, kTileCols[KINDS] = {256, 128, 128, 64};
 
 struct Plan {
   int kind, tiles_m, tiles_n, n_split;
@@ -991,16 +985,19 @@ struct Plan {
 // Large tiles cut LDS and L2 traffic per flop but quantise badly on small outputs; splitting the contraction
 // (allowed only where partial sums may be written separately) buys back occupancy at the price of one more
 // float32 partial per split, which the consumer has to read.
+// (Tiles with one side of 192 would fill units that these leave idle: alone, the Gram-form product of a 2048x6144 layer takes 165
+// instead of 175 us on them, single-stream steps of layers 768 to 2304 wide 3-5 % less.  They move more bytes a flop, which costs
+// where other streams use those units: seven linears on three streams 1.3-4.1 % more, three Gram-form jobs of 2304x2304 12 %, of
+// 2048x6144 7 %.  So only the token-major dW GEMM of a step that is said to be alone takes them, gemm_tn_tiles.)
 struct EpiCost { float read_bytes, write_bytes; };  // per output element
 
 Plan plan_gemm(const GemmDims& d, bool may_split, EpiCost epi) {
-  constexpr double slice_us[KINDS] = {1.666, 1.104, 0.66, 0.42, 1.33, 1.33};
+  constexpr double slice_us[KINDS] = {1.666, 1.104, 0.66, 0.42};
   const double cu_bytes_per_us = 17600.0;   // ~4.5 TB/s over 256 compute units
   const int64_t ksteps = (d.Kd + DBK64 - 1) / DBK64;
   Plan best{-1, 0, 0, 0};
   double best_cost = 0.0;
-  // (the 192-wide shapes are not offered to the dW GEMM: it has a token-major form of its own, gemm_tn_tiles)
-  for (int kind = 0; kind < (may_split && epi.read_bytes == 0.0f ? KIND_A64 : KINDS); ++kind) {
+  for (int kind = 0; kind < KINDS; ++kind) {
     for (int sp = 1; sp <= (may_split ? 8 : 1); ++sp) {
       if (sp > 1 && d.Kd / sp < 512) break;
       const int64_t per = (ksteps + sp - 1) / sp;
@@ -1041,20 +1038,14 @@ hipError_t run(const bf16_t* A, const bf16_t* B, GemmDims d, Plan p, Epi epi, hi
   } while (0)
   if constexpr (kB) {
     if (p.kind == KIND_L64) FAAR_LAUNCH(CfgL64N);
-    else if (p.kind == KIND_A64) FAAR_LAUNCH(CfgA64N);
-    else if (p.kind == KIND_B64) FAAR_LAUNCH(CfgB64N);
     else if (p.kind == KIND_M64) FAAR_LAUNCH(CfgM64N);
     else if (p.kind == KIND_S64) FAAR_LAUNCH(CfgS64N);
     else FAAR_LAUNCH(CfgN64N);
   } else {
-    if constexpr (!Epi::kPaddedContraction) {   // not offered to the dW GEMM
-      if (p.kind == KIND_A64) FAAR_LAUNCH(CfgA64);
-      else if (p.kind == KIND_B64) FAAR_LAUNCH(CfgB64);
-    }
     if (p.kind == KIND_L64) FAAR_LAUNCH(CfgL64);
     else if (p.kind == KIND_M64) FAAR_LAUNCH(CfgM64);
     else if (p.kind == KIND_S64) FAAR_LAUNCH(CfgS64);
-    else if (p.kind == KIND_N64) FAAR_LAUNCH(CfgN64);
+    else FAAR_LAUNCH(CfgN64);
   }
 #undef FAAR_LAUNCH
   return hipGetLastError();

@@ -51,10 +51,10 @@ STEP_CASES = [
     StepCase("dw_token_major_256x192_split", 6576, 528, 2048, 37, whole_device=True),
     StepCase("dw_token_major_256x192_split_long", 6576, 528, 4096, 38, whole_device=True),
     StepCase("dw_split_256x128", 6576, 272, 2048, 39),           # dW GEMM: 256x128 tiles, contraction split
-    StepCase("dx_256x192", 16, 3072, 4096, 48, chained=True),    # dX GEMM: 256x192 tiles
-    # token-major dY out of the residual GEMM (with H) on 192x256 and 256x192 tiles
-    StepCase("rows_192x256", 14336, 160, 6144, 49),
-    StepCase("rows_256x192", 4416, 544, 8192, 50),
+    StepCase("dx_o16", 16, 3072, 4096, 48, chained=True),        # dX GEMM: contraction 16
+    # token-major dY out of the residual GEMM (with H): contractions that end 32 into a slice, last tiles of 256 x 64 outputs
+    StepCase("rows_k160_t6144", 14336, 160, 6144, 49),
+    StepCase("rows_k544", 4416, 544, 8192, 50),
     # residual contractions that end inside a slice: 16 and 48 of 64 on 128x64 tiles, 16 on 128x128 (config-sized ones above: 32)
     StepCase("tail_16", 272, 80, 192, 45, chained=True),
     StepCase("tail_48", 136, 624, 520, 46, chained=True),
@@ -80,11 +80,10 @@ GRAM_CASES = [
     StepCase("gram_256x128_k64", 4096, 1088, 192, 42),            # 256x128 tiles, 64-wide slices, whole
     StepCase("gram_256x128_k32", 4096, 1056, 192, 43),            # 256x128 tiles, 32-wide slices
     StepCase("gram_256x128_split_k3072", 656, 3072, 256, 44),
-    StepCase("gram_256x192_split", 400, 6144, 192, 51),           # 256x192 and 256x256 tiles, contraction split
+    StepCase("gram_o400_k6144", 400, 6144, 192, 51),              # contraction split, last tiles of 16 and of 176 rows
     # (not seed 52: at beta = 20 one entry of its W_q - W on a x 30 outlier channel lies on a bf16 rounding boundary, and a flip of it
-    # moves its row of the gradient by up to 2^-8 |W_q - W| Gm[k][k], 3e-2 of the gradient's rms, and the loss by 2.6e-5 -- the same
-    # on 256x128 tiles as on these)
-    StepCase("gram_256x256_split", 688, 6144, 192, 53),
+    # moves its row of the gradient by up to 2^-8 |W_q - W| Gm[k][k], 3e-2 of the gradient's rms, and the loss by 2.6e-5)
+    StepCase("gram_o688_k6144", 688, 6144, 192, 53),
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}

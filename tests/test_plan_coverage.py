@@ -44,6 +44,17 @@ def test_parity_cases_reach_every_gemm_variant():
     assert {k[1] for k in reachable} == set(fb.GEMM_KINDS)
 
 
+def test_tiles_192_wide_are_only_for_a_step_that_has_the_device_to_itself():
+    """They fill compute units that 256-wide tiles leave idle, which are not idle where other streams share the device: only
+    the token-major dW GEMM takes them, and only where the caller says it is alone (FAAR_STEP_WHOLE_DEVICE)."""
+    dims = DIMS + [1152, 2304, 5120]
+    for O, K, T in itertools.product(dims, dims, [64, 512, 2048, 4096, 8192, 16384]):
+        if O * K * T <= 2 ** 40:
+            for which in (*GEMMS.values(), fb.K_GEMM_FWD, fb.K_GEMM_GRAM):
+                assert 192 not in fb.faar_gemm_plan(which, O, K, T)[1:3], (which, O, K, T)
+            assert fb.faar_dw_token_major(O, K, T) in (0, 1)
+
+
 def test_benchmark_shapes_are_parity_cases_at_full_size():
     """Every (variant, split) the Llama3-1B- and Qwen3-1.7B-shaped linears take at the benchmark's token counts is
     also taken by a full-size parity case (several contraction slices, ring wrap-around, all tiles)."""
