@@ -114,12 +114,17 @@ enum {
   FAAR_K_GEMM_GRAM = 14      /* (W_q - W) (X_q^T X_q), loss, gradient   (faar_layer_step_gram) */
 };
 
-/* GEMM kernel variants (output tiles), as reported by faar_gemm_plan */
+/* GEMM kernel variants (output tiles), as reported by faar_gemm_plan.  0 to 3 named variants that no product takes any more; a
+ * value keeps its meaning, so that a program built against an older header reads these as they are. */
 enum {
-  FAAR_GEMM_L64 = 0, /* 256x256 tile */
-  FAAR_GEMM_M64 = 1, /* 256x128 tile */
-  FAAR_GEMM_S64 = 2, /* 128x128 tile */
-  FAAR_GEMM_N64 = 3  /* 128x64 tile */
+  FAAR_GEMM_GENERIC = 0, /* not reported (register-staged 128x128 tile) */
+  FAAR_GEMM_L = 1,       /* not reported (256x256 tile, slices of 32 of the contraction) */
+  FAAR_GEMM_M = 2,       /* not reported (256x128 tile, slices of 32) */
+  FAAR_GEMM_S = 3,       /* not reported (128x128 tile, slices of 32) */
+  FAAR_GEMM_L64 = 4,     /* 256x256 tile */
+  FAAR_GEMM_M64 = 5,     /* 256x128 tile */
+  FAAR_GEMM_S64 = 6,     /* 128x128 tile */
+  FAAR_GEMM_N64 = 7      /* 128x64 tile */
 };
 
 /* Library version, MAJOR*10000 + MINOR*100 + PATCH.  Pure host function. */

@@ -221,14 +221,15 @@ def faar_dw_split(O: int, K: int, T: int) -> int:
 
 
 K_GEMM_C, K_GEMM_FWD, K_ATTENTION_FWD, K_ATTENTION_BWD, K_GEMM_GRAM = 10, 11, 12, 13, 14
-GEMM_KINDS = ("L64", "M64", "S64", "N64")
+GEMM_L64 = 4                                  # FAAR_GEMM_L64, the first value reported
+GEMM_KINDS = ("L64", "M64", "S64", "N64")     # from it on
 
 
 def faar_gemm_plan(which: int, O: int, K: int, T: int):
     """-> (variant name, tile rows, tile columns, contraction splits) of one GEMM of a layer of these sizes."""
     out = (c_int32 * 4)()
     _check(lib().faar_gemm_plan(which, O, K, T, out), "faar_gemm_plan")
-    return GEMM_KINDS[out[0]], int(out[1]), int(out[2]), int(out[3])
+    return GEMM_KINDS[out[0] - GEMM_L64], int(out[1]), int(out[2]), int(out[3])
 
 
 PROBE_FULL, PROBE_MFMA_ONLY, PROBE_DMA_ONLY = 0, 1, 2
@@ -250,7 +251,7 @@ def faar_gemm_probe(mode: int, A, B):
     info = (c_int32 * 2)()
     _check(lib().faar_gemm_probe(mode, M, N, Kd, _ptr(A), _ptr(B), _ptr(clocks), cap, _ptr(sink), info, _stream()),
            "faar_gemm_probe")
-    return clocks[:info[0]], GEMM_KINDS[info[1]]
+    return clocks[:info[0]], GEMM_KINDS[info[1] - GEMM_L64]
 
 
 def faar_dw_token_major(O: int, K: int, T: int, whole_device: bool = False) -> int:

@@ -248,11 +248,14 @@ int faar_gemm_probe(int mode, int64_t M, int64_t N, int64_t Kd, const void* A, c
                                          GemmDims{M, N, Kd, Kd, Kd}, clocks, capacity, sink, &kind, &items,
                                          static_cast<hipStream_t>(stream));
   info[0] = static_cast<int32_t>(items);
-  info[1] = kind;
+  info[1] = FAAR_GEMM_L64 + kind;
   if (e == hipErrorNotSupported) return FAAR_E_UNSUPPORTED;
   if (e == hipErrorInvalidValue) return FAAR_E_WORKSPACE;
   return hip_status(e);
 }
+
+static_assert(FAAR_GEMM_M64 == FAAR_GEMM_L64 + 1 && FAAR_GEMM_S64 == FAAR_GEMM_L64 + 2 && FAAR_GEMM_N64 == FAAR_GEMM_L64 + 3,
+              "the planner's order");
 
 int faar_gemm_plan(int which, int64_t O, int64_t K, int64_t T, int32_t* out) {
   if (!out) return FAAR_E_NULL;
@@ -268,7 +271,7 @@ int faar_gemm_plan(int which, int64_t O, int64_t K, int64_t T, int32_t* out) {
     case FAAR_K_GEMM_GRAM: p = gemm_plan_info(kGemmEpiGram, O, K, K); break;
     default: return FAAR_E_ARG;
   }
-  out[0] = p.kind; out[1] = p.bm; out[2] = p.bn; out[3] = p.n_split;
+  out[0] = FAAR_GEMM_L64 + p.kind; out[1] = p.bm; out[2] = p.bn; out[3] = p.n_split;
   return FAAR_OK;
 }
 

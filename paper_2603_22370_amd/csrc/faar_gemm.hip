@@ -969,7 +969,7 @@ typedef Dma64Cfg<256, 192, 4, 2, 2, kTN> CfgT64B;
 
 inline int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
-enum { KIND_L64 = 0, KIND_M64 = 1, KIND_S64 = 2, KIND_N64 = 3, KINDS = 4 };   // FAAR_GEMM_*
+enum { KIND_L64 = 0, KIND_M64 = 1, KIND_S64 = 2, KIND_N64 = 3, KINDS = 4 };   // + FAAR_GEMM_L64: FAAR_GEMM_*
 constexpr int kTileRows[KINDS] = {256, 256, 128, 128}, kTileCols[KINDS] = {256, 128, 128, 64};
 
 struct Plan {

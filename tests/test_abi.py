@@ -105,6 +105,21 @@ def test_error_codes_without_a_gpu():
     assert L.faar_last_hip_error() == 0
 
 
+def test_gemm_variant_values_keep_their_meaning():
+    """faar_gemm_plan's numbers are part of the ABI: a program built against an older header decodes them with its own copy."""
+    src = open(os.path.join(ROOT, "include", "faar.h")).read()
+    value = {k: int(v) for k, v in re.findall(r"FAAR_GEMM_([A-Z0-9]+)\s*=\s*(\d+)", src)}
+    assert {k: value[k] for k in ("GENERIC", "L", "M", "S", "L64", "M64")} == dict(GENERIC=0, L=1, M=2, S=3, L64=4, M64=5)
+    assert len(set(value.values())) == len(value)
+    tiles = {value["L64"]: (256, 256), value["M64"]: (256, 128), value["S64"]: (128, 128), value["N64"]: (128, 64)}
+    seen, out = set(), (ctypes.c_int32 * 4)()
+    for O, K, T in [(6144, 2048, 8192), (512, 2048, 8192), (1024, 2048, 2048), (256, 256, 64)]:
+        assert fb.lib().faar_gemm_plan(fb.K_GEMM_RESIDUAL, O, K, T, out) == 0
+        assert tiles[out[0]] == (out[1], out[2])
+        seen.add(out[0])
+    assert seen == set(tiles)
+
+
 def test_missing_library_is_a_loud_error(monkeypatch):
     monkeypatch.setattr(fb, "_lib", None)
     monkeypatch.setattr(fb, "LIB_PATH", "/nonexistent/libfaar.so")
