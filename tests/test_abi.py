@@ -113,7 +113,7 @@ def test_gemm_variant_values_keep_their_meaning():
     assert len(set(value.values())) == len(value)
     tiles = {value["L64"]: (256, 256), value["M64"]: (256, 128), value["S64"]: (128, 128), value["N64"]: (128, 64)}
     seen, out = set(), (ctypes.c_int32 * 4)()
-    for O, K, T in [(6144, 2048, 8192), (512, 2048, 8192), (1024, 2048, 2048), (256, 256, 64)]:
+    for O, K, T in [(6144, 2048, 8192), (3072, 96, 2048), (512, 2048, 8192), (256, 256, 64)]:
         assert fb.lib().faar_gemm_plan(fb.K_GEMM_RESIDUAL, O, K, T, out) == 0
         assert tiles[out[0]] == (out[1], out[2])
         seen.add(out[0])
