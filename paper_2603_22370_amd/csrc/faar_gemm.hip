@@ -991,13 +991,13 @@ struct Plan {
 // 2048x6144 7 %.  So only the token-major dW GEMM of a step that is said to be alone takes them, gemm_tn_tiles.)
 struct EpiCost { float read_bytes, write_bytes; };  // per output element
 
-Plan plan_gemm(const GemmDims& d, bool may_split, EpiCost epi) {
-  constexpr double slice_us[KINDS] = {1.666, 1.104, 0.66, 0.42};
+constexpr double kSliceUs[KINDS] = {1.666, 1.104, 0.66, 0.42};
+Plan plan_gemm(const GemmDims& d, bool may_split, EpiCost epi, int kinds = KINDS, const double* slice_us = kSliceUs) {
   const double cu_bytes_per_us = 17600.0;   // ~4.5 TB/s over 256 compute units
   const int64_t ksteps = (d.Kd + DBK64 - 1) / DBK64;
   Plan best{-1, 0, 0, 0};
   double best_cost = 0.0;
-  for (int kind = 0; kind < KINDS; ++kind) {
+  for (int kind = 0; kind < kinds; ++kind) {
     for (int sp = 1; sp <= (may_split ? 8 : 1); ++sp) {
       if (sp > 1 && d.Kd / sp < 512) break;
       const int64_t per = (ksteps + sp - 1) / sp;
@@ -1179,6 +1179,14 @@ hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, floa
   return run_tn<CfgT64>(A, B, d, n_split, EpiF32{out}, st);
 }
 
+// What the probe runs a product on: the two large tiles, which have its variants.  Whether it takes a product at all is a matter of
+// its own, not of the tiles that the library's products have come to take since: it refuses those that 128x128 tiles at 0.72 us a
+// slice would finish first.
+static Plan plan_probe(const GemmDims& d, bool may_split) {
+  static constexpr double slice_us[KIND_S64 + 1] = {kSliceUs[KIND_L64], kSliceUs[KIND_M64], 0.72};
+  return plan_gemm(d, may_split, kEpiF32, KIND_S64 + 1, slice_us);
+}
+
 template <class Epi>
 static hipError_t run_probe(const bf16_t* A, const bf16_t* B, const GemmDims& d, const Plan& p, Epi epi, hipStream_t st) {
   const dim3 grid(static_cast<unsigned>((p.items() + 7) / 8 * 8));
@@ -1192,13 +1200,13 @@ static hipError_t run_probe(const bf16_t* A, const bf16_t* B, const GemmDims& d,
 
 hipError_t launch_gemm_probe(int mode, const bf16_t* A, const bf16_t* B, GemmDims d, unsigned long long* clocks,
                              int64_t capacity, float* sink, int* kind, int64_t* items, hipStream_t st) {
-  const Plan p = plan_gemm(d, false, kEpiF32);
+  const Plan p = plan_probe(d, false);
   *kind = p.kind;
   *items = p.items();
-  if (p.kind != KIND_L64 && p.kind != KIND_M64) return hipErrorNotSupported;   // the variants exist for the two large tiles
+  if (p.kind != KIND_L64 && p.kind != KIND_M64) return hipErrorNotSupported;
   if (p.items() > capacity) return hipErrorInvalidValue;
   if (mode & 4) {   // the same loops on token-major operands: the buffers are read as A [Kd, M], B [Kd, N]
-    if (!gemm_tn_usable(d.M, d.N, d.Kd)) return hipErrorNotSupported;
+    if (d.M % 8 != 0 || d.N % 8 != 0 || plan_probe(d, true).kind != KIND_L64) return hipErrorNotSupported;
     const GemmDims t{d.M, d.N, d.Kd, d.M, d.N};
     if (mode & 8) {   // ... on 192-wide tiles (whole loop only), whichever of the two shapes divides the product better
       if ((mode & 3) != 0) return hipErrorNotSupported;

@@ -120,6 +120,22 @@ def test_gemm_variant_values_keep_their_meaning():
     assert seen == set(tiles)
 
 
+def test_gemm_probe_takes_the_products_its_two_tiles_are_for():
+    """With room for no clocks at all the call ends on the host: FAAR_E_WORKSPACE for a product it takes, FAAR_E_UNSUPPORTED for one it
+    refuses.  What it takes does not move with the tiles the library's own products are given."""
+    p = ctypes.c_void_p(0x1000)
+    info = (ctypes.c_int32 * 2)()
+    def probe(mode, M, N, Kd):
+        return fb.lib().faar_gemm_probe(mode, M, N, Kd, p, p, p, 0, p, info, None)
+    for M, N, Kd in [(6144, 2048, 8192), (2048, 6144, 8192), (8192, 2048, 4096), (1152, 8192, 1024), (12288, 320, 512)]:
+        for mode in (0, 1, 2, 4, 5, 6, 12):
+            assert probe(mode, M, N, Kd) == -4, (mode, M, N, Kd)
+        assert info[0] > 0 and info[1] in (4, 5)                 # L64 or M64
+    assert probe(0, 6144, 2048, 8192) == -4 and tuple(info) == (192, 4)
+    for M, N, Kd in [(256, 256, 4096), (512, 2048, 1024), (1024, 1024, 64)]:
+        assert probe(0, M, N, Kd) == -7, (M, N, Kd)
+
+
 def test_missing_library_is_a_loud_error(monkeypatch):
     monkeypatch.setattr(fb, "_lib", None)
     monkeypatch.setattr(fb, "LIB_PATH", "/nonexistent/libfaar.so")

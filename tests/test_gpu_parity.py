@@ -969,3 +969,16 @@ def test_round_to_nearest_codes_at_and_next_to_every_midpoint(bf16, scale):
     items, dt = faar.binding.tensor_batch([W], [one], [batch_scales], codes=[batch_codes])
     faar.faar_quant_rtn_batch(items, dt, None, s_global_given=True)
     assert np.array_equal(batch_codes.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("M,N,Kd", [(6144, 2048, 512), (1160, 8192, 1024)])
+def test_gemm_probe_runs_every_mode(M, N, Kd):
+    """Every work item of every measurement loop reports its clocks, also on the products whose 192-wide token-major tiles it is for."""
+    fb = faar.binding
+    A = torch.randn((M, Kd), device="cuda").to(torch.bfloat16)
+    B = torch.randn((N, Kd), device="cuda").to(torch.bfloat16)
+    tm = fb.PROBE_TOKEN_MAJOR
+    for mode in (0, 1, 2, tm, tm + 1, tm + 2, fb.PROBE_TOKEN_MAJOR_192):
+        clocks, variant = fb.faar_gemm_probe(mode, A, B)
+        assert variant in ("L64", "M64") and len(clocks) > 0 and bool((clocks > 0).all())
+        clocks.zero_()
