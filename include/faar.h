@@ -307,7 +307,9 @@ int faar_softquant_fwd_bwd_static(const void* W, faar_dtype wdt, int64_t O, int6
  *   Y_fp in [T*O] of dtype ydt -- the frozen full-precision layer output X W^T.  Y_fp and C may both be NULL (a layer
  *        that is only stepped jointly, FAAR_STEP_JOINT): then only Xt and icodes are produced
  *   ws   FAAR_OP_LAYER_PREPARE workspace (queried with FAAR_WS_GRADIENT_CONSTANT when H is wanted; needed for a
- *        float32 W or with H)
+ *        float32 W or with H).  With H, a buffer that holds one of the three terms of C instead of all -- 4 * O *
+ *        faar_padded_tokens(T) bytes less, where the terms and not W decide the size -- is enough: the terms are then taken one
+ *        after the other (slower, H summed in another order)
  */
 int faar_layer_prepare(const void* W, faar_dtype wdt, int64_t O, int64_t K,
                        const float* s_global, const uint8_t* scales,

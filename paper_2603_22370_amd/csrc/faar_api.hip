@@ -275,6 +275,17 @@ int faar_gemm_plan(int which, int64_t O, int64_t K, int64_t T, int32_t* out) {
   return FAAR_OK;
 }
 
+// Workspace of faar_layer_prepare: hi/mid/lo bf16 terms of a float32 W; then, in the same place, n_terms of the bf16 terms of C^T,
+// the partial products and sums of C^2 (n_terms 0: none of these)
+static size_t prepare_bytes(int64_t O, int64_t K, int64_t T, int n_terms) {
+  const size_t w = 3 * align256((size_t)O * K * 2);
+  if (n_terms == 0) return w;
+  const int64_t Tp = padded_tokens(T);
+  const size_t h = align256((size_t)O * n_terms * Tp * 2) + align256((size_t)choose_split(O, K, Tp) * O * K * 4) +
+                   align256((size_t)c_term_blocks(T, O) * 8);
+  return w > h ? w : h;
+}
+
 size_t faar_workspace_bytes(int op, int64_t O, int64_t K, int64_t T, uint32_t flags) {
   if (op == FAAR_OP_STAGE2_LOSSES) {  // O = vocabulary size, K = hidden size, T = tokens
     if (T <= 0 || O <= 0 || K <= 0 || T > kMaxElems / K) return 0;
@@ -307,14 +318,7 @@ size_t faar_workspace_bytes(int op, int64_t O, int64_t K, int64_t T, uint32_t fl
       return align256((size_t)softquant_bwd_blocks(O * K) * sizeof(double));
     case FAAR_OP_LAYER_PREPARE: {
       if (T <= 0 || T > kMaxElems / (O > K ? O : K)) return 0;
-      size_t need = 3 * align256((size_t)O * K * 2);  // hi/mid/lo bf16 terms of a float32 W
-      if (flags & FAAR_WS_GRADIENT_CONSTANT) {        // the bf16 terms of C^T, the partial products, sums of C^2
-        const int64_t Tp = padded_tokens(T);
-        const size_t h = align256((size_t)O * 3 * Tp * 2) + align256((size_t)choose_split(O, K, Tp) * O * K * 4) +
-                         align256((size_t)c_term_blocks(T, O) * 8);
-        need = need > h ? need : h;
-      }
-      return need;
+      return prepare_bytes(O, K, T, (flags & FAAR_WS_GRADIENT_CONSTANT) ? 3 : 0);
     }
     case FAAR_OP_LAYER_STEP:
       if (T <= 0 || T > kMaxElems / (O > K ? O : K)) return 0;
@@ -456,7 +460,7 @@ int faar_layer_prepare(const void* W, faar_dtype wdt, int64_t O, int64_t K, cons
     return FAAR_E_ARG;
   const bool bf = wdt == FAAR_BF16;
   if (((!bf && Y_fp) || H) &&
-      (!ws || !aligned16(ws) || ws_bytes < faar_workspace_bytes(FAAR_OP_LAYER_PREPARE, O, K, T, H ? FAAR_WS_GRADIENT_CONSTANT : 0)))
+      (!ws || !aligned16(ws) || ws_bytes < prepare_bytes(O, K, T, H ? 1 : 0)))
     return FAAR_E_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bf16_t* xq = static_cast<const bf16_t*>(Xq);
@@ -479,19 +483,25 @@ int faar_layer_prepare(const void* W, faar_dtype wdt, int64_t O, int64_t K, cons
   if (!H) return FAAR_OK;
   // H = C^T Xq (the activations as stored, i.e. in units of x_scale): C is split into three bf16 terms, transposed side by side
   // into the operand layout of the dW GEMM and multiplied with Xt on the matrix cores in one product (exact products, float32
-  // accumulation), whose partial sums add up to H.  ||C||^2 comes from the pass that makes the terms.
+  // accumulation), whose partial sums add up to H.  ||C||^2 comes from the pass that makes the terms.  A workspace with room for
+  // one term takes them one after the other, in three products.
   Carver cv(ws);   // the float32-W terms above are no longer needed
-  bf16_t* ct = cv.take<bf16_t>((size_t)O * 3 * Tp);
+  const int terms = ws_bytes >= prepare_bytes(O, K, T, 3) ? 3 : 1;
+  bf16_t* ct = cv.take<bf16_t>((size_t)O * terms * Tp);
   const int n_split = choose_split(O, K, Tp);
   float* part = cv.take<float>((size_t)n_split * O * K);
   double* sq = cv.take<double>((size_t)c_term_blocks(T, O));
-  if (int e = hip_status(launch_c_terms_transposed(C, T, O, ct, sq, st))) return e;
-  // with one split the product is H itself
-  float* out = n_split == 1 ? H : part;
-  if (int e = hip_status(launch_gemm_f32_terms(ct, static_cast<const bf16_t*>(Xt), GemmDims{O, K, Tp, 3 * Tp, Tp}, out, n_split, st)))
-    return e;
-  if (n_split > 1)
-    if (int e = hip_status(launch_accumulate_partials(H, part, n_split, (int64_t)O * K, O * K, st))) return e;
+  // all terms at once and one split: the product is H itself
+  float* out = terms == 3 && n_split == 1 ? H : part;
+  const GemmDims d2{O, K, Tp, terms * Tp, Tp};
+  const bf16_t* xt = static_cast<const bf16_t*>(Xt);
+  for (int term = 0; term < 3; term += terms) {
+    if (int e = hip_status(launch_c_terms_transposed(C, T, O, term, terms, ct, term == 0 ? sq : nullptr, st))) return e;
+    if (int e = hip_status(terms == 3 ? launch_gemm_f32_terms(ct, xt, d2, out, n_split, st) : launch_gemm_f32(ct, xt, d2, out, n_split, st)))
+      return e;
+    if (out != H)
+      if (int e = hip_status(launch_accumulate_partials(H, part, n_split, (int64_t)O * K, O * K, term == 0, st))) return e;
+  }
   return hip_status(launch_sum_doubles(sq, c_term_blocks(T, O), c_norm2, st));
 }
 

@@ -771,12 +771,13 @@ k_transpose_bf16(const bf16_t* __restrict__ in, int64_t rows, int64_t cols, bf16
 // C (float32, tokens interleaved in groups of four: [ceil(T/4)][O][4]) -> its three bf16 terms hi / mid / lo (each the rounding of
 // the running remainder: together all 24 significand bits), transposed to [O, 3, Tp] with zero padding, i.e. side by side in
 // the operand layout of the dW GEMM.  64 outputs x 64 tokens per workgroup through LDS; both sides move whole 128-byte (or
-// longer) runs.  HBM-bound; C is read once for all three (8192 x 2048: three passes of 21 us -> one of 31).  The workgroup also
-// writes its sum of C^2.
+// longer) runs.  HBM-bound; C is read once for all three (8192 x 2048: three passes of 21 us -> one of 31).  With kTerms = 1 only
+// term `first` is made, into [O, Tp].  The workgroup also writes its sum of C^2 where it is wanted.
+template <int kTerms>
 __global__ void __launch_bounds__(256)
-k_c_terms_transposed(const float* __restrict__ C, int64_t T, int64_t O, bf16_t* __restrict__ out, int64_t Tp, unsigned tiles_o,
-                     double* __restrict__ sq_partials) {
-  __shared__ uint32_t tile[3][64][33];         // [term][output][token pair], pitch 33 words
+k_c_terms_transposed(const float* __restrict__ C, int64_t T, int64_t O, int first, bf16_t* __restrict__ out, int64_t Tp,
+                     unsigned tiles_o, double* __restrict__ sq_partials) {
+  __shared__ uint32_t tile[kTerms][64][33];    // [term][output][token pair], pitch 33 words
   const int64_t o0 = (blockIdx.x % tiles_o) * 64LL, t0 = (blockIdx.x / tiles_o) * 64LL;
   const int og = threadIdx.x & 63, gq = threadIdx.x >> 6;
   const int64_t groups = (T + 3) / 4;
@@ -797,8 +798,12 @@ k_c_terms_transposed(const float* __restrict__ C, int64_t T, int64_t O, bf16_t* 
       b[1][q] = f32_to_bf16(r1);
       b[2][q] = f32_to_bf16(r1 - bf16_to_f32(b[1][q]));
     }
+    if (kTerms == 1 && first > 0) {
 #pragma unroll
-    for (int term = 0; term < 3; ++term) {
+      for (int q = 0; q < 4; ++q) b[0][q] = first == 1 ? b[1][q] : b[2][q];
+    }
+#pragma unroll
+    for (int term = 0; term < kTerms; ++term) {
       tile[term][og][2 * g] = b[term][0] | (b[term][1] << 16);
       tile[term][og][2 * g + 1] = b[term][2] | (b[term][3] << 16);
     }
@@ -811,22 +816,25 @@ k_c_terms_transposed(const float* __restrict__ C, int64_t T, int64_t O, bf16_t* 
     const int64_t o = o0 + row, t = t0 + ch * 8;
     if (o < O && t < Tp) {                     // Tp is a multiple of 64: a chunk is inside or outside as a whole
 #pragma unroll
-      for (int term = 0; term < 3; ++term) {
+      for (int term = 0; term < kTerms; ++term) {
         const uint32_t* r = tile[term][row] + ch * 4;
-        *reinterpret_cast<uint4*>(out + (o * 3 + term) * Tp + t) = make_uint4(r[0], r[1], r[2], r[3]);
+        *reinterpret_cast<uint4*>(out + (o * kTerms + term) * Tp + t) = make_uint4(r[0], r[1], r[2], r[3]);
       }
     }
   }
-  const double bs = block_sum(static_cast<double>(sq));
-  if (threadIdx.x == 0) sq_partials[blockIdx.x] = bs;
+  if (sq_partials) {
+    const double bs = block_sum(static_cast<double>(sq));
+    if (threadIdx.x == 0) sq_partials[blockIdx.x] = bs;
+  }
 }
 
-// H = sum over the splits of the partial products
+// H = (first ? 0 : H) + sum over the splits of the partial products
 __global__ void __launch_bounds__(kEltThreads)
-k_accumulate_partials(float* __restrict__ H, const float* __restrict__ partials, int n_split, int64_t stride, int64_t n4) {
+k_accumulate_partials(float* __restrict__ H, const float* __restrict__ partials, int n_split, int64_t stride, int64_t n4,
+                      bool first) {
   const int64_t i = blockIdx.x * (int64_t)kEltThreads + threadIdx.x;
   if (i >= n4) return;
-  float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  float4 a = first ? make_float4(0.0f, 0.0f, 0.0f, 0.0f) : reinterpret_cast<const float4*>(H)[i];
   for (int s = 0; s < n_split; ++s) {
     const float4 p = *reinterpret_cast<const float4*>(partials + s * stride + i * 4);
     a.x += p.x; a.y += p.y; a.z += p.z; a.w += p.w;
@@ -1099,18 +1107,25 @@ hipError_t launch_check_forward_tag(const ForwardGuard& guard, hipStream_t st) {
 
 int64_t c_term_blocks(int64_t T, int64_t O) { return ((O + 63) / 64) * (padded_tokens(T) / 64); }
 
-hipError_t launch_c_terms_transposed(const float* C, int64_t T, int64_t O, bf16_t* out, double* sq_partials, hipStream_t st) {
+hipError_t launch_c_terms_transposed(const float* C, int64_t T, int64_t O, int first, int n_terms, bf16_t* out, double* sq_partials,
+                                     hipStream_t st) {
   const int64_t tiles_o = (O + 63) / 64, blocks = c_term_blocks(T, O);
   if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_c_terms_transposed, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, C, T, O, out,
-                     padded_tokens(T), static_cast<unsigned>(tiles_o), sq_partials);
+  const dim3 grid(static_cast<unsigned>(blocks));
+  if (n_terms == 3)
+    hipLaunchKernelGGL(k_c_terms_transposed<3>, grid, dim3(256), 0, st, C, T, O, 0, out, padded_tokens(T),
+                       static_cast<unsigned>(tiles_o), sq_partials);
+  else
+    hipLaunchKernelGGL(k_c_terms_transposed<1>, grid, dim3(256), 0, st, C, T, O, first, out, padded_tokens(T),
+                       static_cast<unsigned>(tiles_o), sq_partials);
   return hipGetLastError();
 }
 
-hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, hipStream_t st) {
+hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, bool first,
+                                      hipStream_t st) {
   const int64_t n4 = n / 4;   // n = O * K is a multiple of 16
   hipLaunchKernelGGL(k_accumulate_partials, dim3(static_cast<unsigned>((n4 + kEltThreads - 1) / kEltThreads)), dim3(kEltThreads),
-                     0, st, H, partials, n_split, stride, n4);
+                     0, st, H, partials, n_split, stride, n4, first);
   return hipGetLastError();
 }
 

@@ -105,12 +105,15 @@ hipError_t launch_finalize_losses(const double* mse_partials, int64_t n_mse, flo
 hipError_t launch_transpose_bf16(const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out,
                                  int64_t ld_out, hipStream_t st);
 hipError_t launch_check_forward_tag(const ForwardGuard& guard, hipStream_t st);
-// The three bf16 terms (hi, mid, lo) of the float32 C [ceil(T/4)][O][4], transposed to [O, 3, padded_tokens(T)], zero padded;
-// sq_partials: c_term_blocks(T, O) per-workgroup sums of C^2
+// The bf16 terms (hi, mid, lo) of the float32 C [ceil(T/4)][O][4]: all three transposed to [O, 3, padded_tokens(T)], zero padded
+// (n_terms 3, first 0), or term `first` alone to [O, padded_tokens(T)] (n_terms 1); sq_partials (nullable): c_term_blocks(T, O)
+// per-workgroup sums of C^2
 int64_t c_term_blocks(int64_t T, int64_t O);
-hipError_t launch_c_terms_transposed(const float* C, int64_t T, int64_t O, bf16_t* out, double* sq_partials, hipStream_t st);
-// H[0..n) = sum_s partials[s * stride + i]
-hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, hipStream_t st);
+hipError_t launch_c_terms_transposed(const float* C, int64_t T, int64_t O, int first, int n_terms, bf16_t* out, double* sq_partials,
+                                     hipStream_t st);
+// H[0..n) = (first ? 0 : H) + sum_s partials[s * stride + i]
+hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, bool first,
+                                      hipStream_t st);
 hipError_t launch_sum_doubles(const double* p, int64_t n, double* out, hipStream_t st);
 // gram[i] = bf16(sum_s partials[s * K * K + i]) for the K x K matrix; diag_lo[k] = that sum at (k, k) minus its bf16 rounding
 hipError_t launch_gram_finish(const float* partials, int n_split, int64_t K, bf16_t* gram, float* diag_lo, hipStream_t st);

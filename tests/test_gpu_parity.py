@@ -939,6 +939,33 @@ def test_layer_prepare_constants_against_float64(O, K, T):
     assert float(c2) == pytest.approx(float((c * c).sum()), rel=1e-6)
 
 
+@pytest.mark.parametrize("O,K,T", [(104, 64, 67), (264, 512, 200), (520, 272, 1025), (1024, 256, 4096)])
+def test_layer_prepare_with_room_for_one_term_of_the_constant(O, K, T):
+    """A workspace that holds one of the three bf16 terms of C^T instead of all of them (or just the three terms of a float32 W, where
+    those take more) is accepted, one byte less is not; everything but the order of H's sums is the same."""
+    gen = torch.Generator(device="cuda").manual_seed(O + T)
+    X = torch.randn((T, K), generator=gen, device="cuda").to(torch.bfloat16)
+    Y = torch.randn((T, O), generator=gen, device="cuda").to(torch.bfloat16)
+    Tp, up = faar.faar_padded_tokens(T), lambda n: (n + 255) // 256 * 256
+    small = max(3 * up(2 * O * K), up(2 * O * Tp) + up(4 * faar.binding.faar_dw_split(O, K, T) * O * K) + up(8 * ((O + 63) // 64) * (Tp // 64)))
+    assert small <= faar.faar_workspace_bytes(faar.binding.OP_LAYER_PREPARE, O, K, T, faar.binding.FAAR_WS_GRADIENT_CONSTANT)
+    for dtype in (torch.bfloat16, torch.float32):
+        W = (0.02 * torch.randn((O, K), generator=gen, device="cuda")).to(dtype)
+        sg, scales, _, _ = faar.faar_quant_rtn(W)
+        full = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
+        ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+        tight = faar.faar_layer_prepare(W, sg, scales, X, Y, ws=ws, gradient_constant=True)
+        for i in (0, 1, 2, 4):                       # Xt, C, the interval codes, ||C||^2
+            assert torch.equal(full[i], tight[i])
+        c = tight[1].flatten()[:(T + 3) // 4 * 4 * O].view(-1, O, 4).permute(0, 2, 1).reshape(-1, O).double().cpu()[:T]
+        Xd = X.double().cpu()
+        h = tight[3].view(O, K).double().cpu()
+        # the bound of the test above and one more addition for each of the three products' partial sums
+        assert bool(((h - c.T @ Xd).abs() <= (3 * T + 34) * 2.0 ** -24 * (c.abs().T @ Xd.abs())).all())
+        with pytest.raises(faar.FaarError):
+            faar.faar_layer_prepare(W, sg, scales, X, Y, ws=ws[:-1], gradient_constant=True)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("scale", [1.0, 0.0625, 24.0])
 def test_round_to_nearest_codes_at_and_next_to_every_midpoint(bf16, scale):
