@@ -24,6 +24,7 @@ class StepCase:
     chained: bool = False           # dY_ext given and dX requested
     full_size: bool = False         # a benchmark shape at its real size: one beta, no repeated variants
     fp32_small: bool = False        # the 256x256 float32 parity configuration (own generator)
+    on_boundary: bool = False       # an entry of W_q - W lies on a bf16 rounding boundary where a flip counts (Gram form)
     whole_device: bool = False      # stepped with FAAR_STEP_WHOLE_DEVICE: the token-major dW GEMM may take 192-wide tiles
 
 
@@ -81,9 +82,8 @@ GRAM_CASES = [
     StepCase("gram_256x128_k32", 4096, 1056, 192, 43),            # 256x128 tiles, 32-wide slices
     StepCase("gram_256x128_split_k3072", 656, 3072, 256, 44),
     StepCase("gram_o400_k6144", 400, 6144, 192, 51),              # contraction split, last tiles of 16 and of 176 rows
-    # (not seed 52: at beta = 20 one entry of its W_q - W on a x 30 outlier channel lies on a bf16 rounding boundary, and a flip of it
-    # moves its row of the gradient by up to 2^-8 |W_q - W| Gm[k][k], 3e-2 of the gradient's rms, and the loss by 2.6e-5)
     StepCase("gram_o688_k6144", 688, 6144, 192, 53),
+    StepCase("gram_o688_k6144_boundary", 688, 6144, 192, 52, on_boundary=True),   # see tests/boundary_flips.py
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}

@@ -8,6 +8,7 @@ from oracle import faar_oracle as fo
 from workloads import synth
 
 from parity_cases import BY_NAME, GRAM_CASES, STEP_CASES
+import boundary_flips
 import test_gpu_parity as tp
 
 pytestmark = pytest.mark.gpu
@@ -86,9 +87,15 @@ def _assert_gram_case(name, beta):
     errs = {"loss_exact": abs(losses[0] - ex["L_mse"]) / ex["L_mse"], "loss_declared": abs(losses[0] - de["L_mse"]) / de["L_mse"],
             "round": abs(losses[1] - ex["L_round"]) / ex["L_round"], "total": abs(losses[2] - ex["L"]) / ex["L"]}
     g = m.astype(np.float64) / (1 - HYP["beta1"])
+    more = 0.0
+    if BY_NAME[name].on_boundary:
+        # the loss and, element by element, the gradient may be away by what the flips of the entries on a boundary change
+        more, dv = boundary_flips.allowance(c, q, V0, beta, 1.0 / (c.T * c.O))
+        off = g - de["dV"]
+        g = de["dV"] + np.sign(off) * np.maximum(np.abs(off) - dv, 0.0)
     errs["grad"] = tp.grad_errors(g, ref)
     assert errs["loss_exact"] <= tp.loss_tol(name), errs
-    assert errs["loss_declared"] <= TOL_LOSS_DECLARED, errs
+    assert errs["loss_declared"] <= TOL_LOSS_DECLARED + more / de["L_mse"], errs
     assert errs["round"] <= 1e-5, errs
     assert errs["total"] <= tp.loss_tol(name), errs
     tp._check_grad(g, ref, tp.GRAD_ELEM_MAX_BY_CASE.get(name, tp.GRAD_ELEM_MAX), BY_NAME[name].full_size)

@@ -325,3 +325,27 @@ def test_adam_matches_a_library_optimiser_over_several_steps():
         with torch.no_grad():
             p.clamp_(0.0, 1.0)
         assert np.allclose(np.asarray(V, dtype=np.float64), p.detach().numpy(), rtol=1e-6, atol=1e-7), t
+
+
+def test_parity_cases_on_a_rounding_boundary_are_what_they_say():
+    """The Gram-form parity cases that are allowed flips of entries of W_q - W (tests/boundary_flips.py): at one of the two sharpnesses
+    they run at, an entry lies within float32 noise of a bf16 rounding boundary, and one flip of it moves the loss by more than the
+    tolerance for the others or an element of its row of the gradient by more than theirs."""
+    import boundary_flips
+    from parity_cases import GRAM_CASES
+
+    cases = [p for p in GRAM_CASES if p.on_boundary]
+    assert cases
+    for p in cases:
+        c = synth.llm_linear(p.name, p.O, p.K, p.T, p.seed)
+        q = fo.quant_rtn(c.W, c.w_is_bf16)
+        V0 = fo.init_v(c.W, q["s_global"], q["scales"])["V"]
+        alpha, found = 1.0 / (c.T * c.O), False
+        for beta in (4.0, 20.0):
+            ref = fo.stage1_loss_and_grads(c.W, q["s_global"], q["scales"], V0, c.Xq, c.Y_fp, beta, 0.0, alpha, declared_rounding="gram")
+            dist, loss, Gm, ulp, coef = boundary_flips.flips(c, q, V0, beta, alpha)
+            rms = np.sqrt(np.mean(ref["dV"] ** 2))
+            for i, j in np.argwhere((dist <= 0.5) & (np.abs(c.Xq).max(axis=0) > 30.0)[None, :]):
+                moved = 2.0 * alpha * ulp[i, j] * np.abs(Gm[j] * coef[i])
+                found = found or loss[i, j] > 1.8e-5 * ref["L_mse"] or (moved - 2.0 ** -7 * np.abs(ref["dV"][i])).max() > 2e-2 * rms
+        assert found, p.name
