@@ -777,9 +777,13 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
       of_b = (int64_t)(kbeg + rel - pass * per) * DBK64;
       of_a = of_b + (kTerms - 1 - pass) * d.Kd;
     };
+    // A product of fewer slices than the ring has stages copies no more than it has: every copy is then waited for before the first
+    // slice, and the counted waits of the loop hold of themselves
+    const bool short_loop = nk < C::NS;
 #pragma unroll
     for (int s = 0; s < C::NS; ++s) {
-      const int t = kbeg + (s < nk ? s : nk - 1);
+      if (short_loop && s >= nk) break;
+      const int t = kbeg + s;
       int64_t of_a = 0, of_b = 0;
       if constexpr (kTerms > 1) term_offsets(t - kbeg, of_a, of_b);
 #pragma unroll
@@ -825,7 +829,8 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
     };
     bf16x8 fa[2][TM], fb[2][TN];
 
-    FAAR_WAIT_VMCNT(PW * (C::NS - 1));  // slice 0 has landed (mine); barrier: everybody's
+    if (short_loop) FAAR_WAIT_VMCNT(0);
+    else FAAR_WAIT_VMCNT(PW * (C::NS - 1));  // slice 0 has landed (mine); barrier: everybody's
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -913,7 +918,17 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
       }
     };
     if constexpr (KK == 2) {
-      for (int it = 0; it < nk; ++it) slice(it, std::integral_constant<int, 0>{});
+      // where the contraction ends in the first half of its last slice, the second half is zeros: one phase of matrix instructions on
+      // the fragments at hand
+      const bool half = kTail && kend == ksteps && tail <= DBK64 / 2;
+      for (int it = 0; it < nk - half; ++it) slice(it, std::integral_constant<int, 0>{});
+      if constexpr (kTail) {
+        if (half) {
+#pragma unroll
+          for (int m = 0; m < NM; ++m)
+            acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[0][m / TN], fb[0][m % TN], acc[m / TN][m % TN], 0, 0, 0);
+        }
+      }
     } else {
       for (int it = 0; it < nk; it += 2) {
         slice(it, std::integral_constant<int, 0>{});

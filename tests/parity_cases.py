@@ -84,6 +84,15 @@ GRAM_CASES = [
     StepCase("gram_o400_k6144", 400, 6144, 192, 51),              # contraction split, last tiles of 16 and of 176 rows
     StepCase("gram_o688_k6144", 688, 6144, 192, 53),
     StepCase("gram_o688_k6144_boundary", 688, 6144, 192, 52, on_boundary=True),   # see tests/boundary_flips.py
+    # contraction split, the last split ending 16 and 48 into a slice: on 256x256, 256x128, 128x128 and 128x64 tiles
+    StepCase("gram_256x256_split_k16", 272, 5584, 192, 60),
+    StepCase("gram_256x256_split_k48", 272, 5616, 192, 61),
+    StepCase("gram_256x128_split_k16", 160, 5392, 192, 62),
+    StepCase("gram_256x128_split_k48", 160, 5424, 192, 63),
+    StepCase("gram_128x128_split_k16", 16, 4112, 192, 64),
+    StepCase("gram_128x128_split_k48", 16, 4144, 192, 65),
+    StepCase("gram_128x64_split_k16", 16, 1040, 192, 66),
+    StepCase("gram_128x64_split_k48", 16, 1072, 192, 67, on_boundary=True),
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}
