@@ -14,7 +14,9 @@ namespace {
 constexpr int kRowThreads = 1024;
 
 // Running statistics of one row's logits a (z_fp) and b (z_q), k = log2(e) / tau:
-//   ma = max a, sa = sum 2^(k (a - ma)), w = sum 2^(k (a - ma)) (a - b);  mb = max b, sb = sum 2^(k (b - mb))
+//   ma = max a, sa = sum 2^(k (a - ma)), w = ws sum 2^(k (a - ma)) (a - b);  mb = max b, sb = sum 2^(k (b - mb))
+// with ws = min(1, 1 / tau): entries of z_q at the type's lowest value make terms of that size, and their sum over tau has to stay
+// finite where it is
 // The vector unit bounds these kernels as much as memory does (four exponentials of four issue slots an entry), so what
 // surrounds the exponentials counts: the maxima are those of the logits as they are (the subtraction comes first, so logits of any
 // size and masks of the type's lowest value keep their meaning), one product makes the exponent, and nothing is compared with -inf.
@@ -48,7 +50,7 @@ __device__ __forceinline__ RowStats shuffle_xor(const RowStats& x, int o) {
 // Eight vocabulary entries added to the running sums.  A logit of -inf (a masked entry) has probability 0: it adds nothing to
 // either sum, and by the convention 0 log 0 = 0 nothing to the KL term either -- also where only z_fp is -inf.  Where P_fp > 0
 // and z_q = -inf the term, and the row's KL, is +inf.  A row whose logits are all -inf has no softmax; its results are NaN.
-__device__ __forceinline__ void accumulate8(RowStats& st, const float (&a)[8], const float (&b)[8], float k) {
+__device__ __forceinline__ void accumulate8(RowStats& st, const float (&a)[8], const float (&b)[8], float k, float ws) {
   float ca = a[0], cb = b[0];
 #pragma unroll
   for (int j = 1; j < 8; ++j) {
@@ -66,28 +68,31 @@ __device__ __forceinline__ void accumulate8(RowStats& st, const float (&a)[8], c
     st.mb = cb;
   }
   const float ra = finite_ref(st.ma), rb = finite_ref(st.mb);
-  float e[8], w = 0.0f;
+  float w = 0.0f;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    e[j] = exp2_hw((a[j] - ra) * k);
-    st.sa += e[j];
+    const float e = exp2_hw((a[j] - ra) * k);
+    st.sa += e;
     st.sb += exp2_hw((b[j] - rb) * k);
-    w = __builtin_fmaf(e[j], a[j] - b[j], w);
+    w = __builtin_fmaf(e, a[j] - b[j], w);
   }
-  if (w != w) {      // 0 * inf: a masked entry among them, left out (or a NaN, which stays)
+  w *= ws;
+  if (!(fabsf(w) <= 3.402823466e+38f)) {   // 0 * inf: a masked entry among them, left out (or a NaN, which stays); or too large unscaled
     w = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (e[j] != 0.0f) w += e[j] * (a[j] - b[j]);
+    for (int j = 0; j < 8; ++j) {
+      const float e = exp2_hw((a[j] - ra) * k);   // again: eight registers less over the common path
+      if (e != 0.0f) w += e * (a[j] * ws - b[j] * ws);
+    }
   }
   st.w += w;
 }
 
-// KL(P_fp || P_q) of a row: sum_j P_fp (log P_fp - log P_q) = w / (tau sa) - (ma - mb) / tau - log(sa / sb); combined in double, with
+// KL(P_fp || P_q) of a row: sum_j P_fp (log P_fp - log P_q) = w / (ws tau sa) - (ma - mb) / tau - log(sa / sb); combined in double, with
 // the two log-sum-exp terms taken as one difference so that nearly equal distributions do not cancel at size log(vocab)
-__device__ __forceinline__ double row_kl(const RowStats& t, float inv_tau) {
-  return (static_cast<double>(t.w) / static_cast<double>(t.sa) - (static_cast<double>(t.ma) - static_cast<double>(t.mb))) *
-             static_cast<double>(inv_tau) -
+__device__ __forceinline__ double row_kl(const RowStats& t, float inv_tau, float ws) {
+  return (static_cast<double>(t.w) / (static_cast<double>(ws) * static_cast<double>(t.sa)) -
+          (static_cast<double>(t.ma) - static_cast<double>(t.mb))) * static_cast<double>(inv_tau) -
          log(static_cast<double>(t.sa) / static_cast<double>(t.sb));
 }
 
@@ -105,7 +110,7 @@ struct GradCoef {
 
 template <typename ZT>
 __global__ void __launch_bounds__(kRowThreads)
-k_stage2_kl(const ZT* __restrict__ Zf, const ZT* __restrict__ Zq, int64_t v8, float inv_tau, float k, float grad_coef,
+k_stage2_kl(const ZT* __restrict__ Zf, const ZT* __restrict__ Zq, int64_t v8, float inv_tau, float ws, float k, float grad_coef,
             ZT* __restrict__ dZq, double* __restrict__ kl_rows) {
   const int64_t row = blockIdx.x;
   const ZT* zf = Zf + row * v8 * 8;
@@ -129,7 +134,7 @@ k_stage2_kl(const ZT* __restrict__ Zf, const ZT* __restrict__ Zq, int64_t v8, fl
       W8<ZT>::load(zf + (c + kRowThreads) * 8, na);
       W8<ZT>::load(zq + (c + kRowThreads) * 8, nb);
     }
-    accumulate8(st, a, b, k);
+    accumulate8(st, a, b, k, ws);
   }
   // fixed-order reduction: butterfly inside each wavefront, then the wavefronts in index order
 #pragma unroll
@@ -142,7 +147,7 @@ k_stage2_kl(const ZT* __restrict__ Zf, const ZT* __restrict__ Zq, int64_t v8, fl
     RowStats t = per_wave[0];
     for (int i = 1; i < kRowThreads / 64; ++i) t = merge(t, per_wave[i], k);
     row_stats = t;
-    kl_rows[row] = row_kl(t, inv_tau);
+    kl_rows[row] = row_kl(t, inv_tau, ws);
   }
   if (!dZq) return;
   __syncthreads();
@@ -173,7 +178,7 @@ __device__ __forceinline__ void unpack8(const uint4& q, float (&x)[8]) {
 
 template <int NC>
 __global__ void __launch_bounds__(kRowThreads)
-k_stage2_kl_resident(const bf16_t* __restrict__ Zf, const bf16_t* __restrict__ Zq, int64_t v8, float inv_tau, float k,
+k_stage2_kl_resident(const bf16_t* __restrict__ Zf, const bf16_t* __restrict__ Zq, int64_t v8, float inv_tau, float ws, float k,
                      float grad_coef, bf16_t* __restrict__ dZq, double* __restrict__ kl_rows) {
   static_assert(NC >= kLdsChunks, "the LDS part is a prefix of the per-lane chunks");
   __shared__ uint4 q_lds[kLdsChunks][kRowThreads];
@@ -194,7 +199,7 @@ k_stage2_kl_resident(const bf16_t* __restrict__ Zf, const bf16_t* __restrict__ Z
       float a[8], b[8];
       unpack8(rf[q], a);
       unpack8(rq, b);
-      accumulate8(st, a, b, k);
+      accumulate8(st, a, b, k, ws);
     }
   }
 #pragma unroll
@@ -207,7 +212,7 @@ k_stage2_kl_resident(const bf16_t* __restrict__ Zf, const bf16_t* __restrict__ Z
     RowStats t = per_wave[0];
     for (int i = 1; i < kRowThreads / 64; ++i) t = merge(t, per_wave[i], k);
     row_stats = t;
-    kl_rows[row] = row_kl(t, inv_tau);
+    kl_rows[row] = row_kl(t, inv_tau, ws);
   }
   if (!dZq) return;
   __syncthreads();
@@ -305,24 +310,25 @@ int64_t stage2_mse_blocks(int64_t n) {
 
 hipError_t launch_stage2(const Stage2Args& a, hipStream_t st) {
   const float inv_tau = 1.0f / a.tau;
+  const float ws = std::fmin(1.0f, inv_tau);
   const float grad_coef = a.lambda_kl * a.kl_scale * inv_tau;
   const float k = static_cast<float>(1.4426950408889634 / static_cast<double>(a.tau));   // logits -> exponents of two
   const int64_t v8 = a.vocab / 8;
   if (a.z_bf16 && v8 <= 16 * kRowThreads)
     hipLaunchKernelGGL(k_stage2_kl_resident<16>, dim3(static_cast<unsigned>(a.T)), dim3(kRowThreads), 0, st,
-                       static_cast<const bf16_t*>(a.Z_fp), static_cast<const bf16_t*>(a.Z_q), v8, inv_tau, k, grad_coef,
+                       static_cast<const bf16_t*>(a.Z_fp), static_cast<const bf16_t*>(a.Z_q), v8, inv_tau, ws, k, grad_coef,
                        static_cast<bf16_t*>(a.dZ_q), a.kl_rows);
   else if (a.z_bf16 && v8 <= 19 * kRowThreads)
     hipLaunchKernelGGL(k_stage2_kl_resident<19>, dim3(static_cast<unsigned>(a.T)), dim3(kRowThreads), 0, st,
-                       static_cast<const bf16_t*>(a.Z_fp), static_cast<const bf16_t*>(a.Z_q), v8, inv_tau, k, grad_coef,
+                       static_cast<const bf16_t*>(a.Z_fp), static_cast<const bf16_t*>(a.Z_q), v8, inv_tau, ws, k, grad_coef,
                        static_cast<bf16_t*>(a.dZ_q), a.kl_rows);
   else if (a.z_bf16)
     hipLaunchKernelGGL(k_stage2_kl<bf16_t>, dim3(static_cast<unsigned>(a.T)), dim3(kRowThreads), 0, st,
-                       static_cast<const bf16_t*>(a.Z_fp), static_cast<const bf16_t*>(a.Z_q), a.vocab / 8, inv_tau, k, grad_coef,
+                       static_cast<const bf16_t*>(a.Z_fp), static_cast<const bf16_t*>(a.Z_q), a.vocab / 8, inv_tau, ws, k, grad_coef,
                        static_cast<bf16_t*>(a.dZ_q), a.kl_rows);
   else
     hipLaunchKernelGGL(k_stage2_kl<float>, dim3(static_cast<unsigned>(a.T)), dim3(kRowThreads), 0, st,
-                       static_cast<const float*>(a.Z_fp), static_cast<const float*>(a.Z_q), a.vocab / 8, inv_tau, k, grad_coef,
+                       static_cast<const float*>(a.Z_fp), static_cast<const float*>(a.Z_q), a.vocab / 8, inv_tau, ws, k, grad_coef,
                        static_cast<float*>(a.dZ_q), a.kl_rows);
   if (hipError_t e = hipGetLastError()) return e;
   const int64_t nh = a.T * a.D;

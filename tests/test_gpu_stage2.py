@@ -143,3 +143,24 @@ def test_stage2_logits_masked_with_the_lowest_value():
     assert float(losses[0]) == pytest.approx(float(kl), rel=1e-5, abs=2e-6 * T)
     err = (dZ.double().cpu() - (q - p)).abs()
     assert bool((err <= 2.0 ** -8 * (q - p).abs() + 3e-6 * float(torch.maximum(p, q).max())).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("tau", [4.0, 2.0, 0.5])
+def test_stage2_lowest_value_in_the_quantised_logits_alone(dtype, tau):
+    """A few entries at the type's lowest value in z_q where P_fp is not small, at the row's end and within one lane's eight: the KL term
+    is of the order of that value over tau, and finite wherever the sum of P_fp (z_fp - z_q) / max(tau, 1) before the division by the
+    softmax's denominator is."""
+    T, V = 3, 4096
+    zf = torch.zeros((T, V), dtype=dtype)
+    zq = torch.zeros((T, V), dtype=dtype)
+    low, n = torch.finfo(dtype).min, {4.0: 3, 2.0: 1, 0.5: 1}[tau]
+    zq[1, 8:8 + n] = low
+    zq[2, V - n:] = low * 0.9375
+    a, b = zf.double() / tau, zq.double() / tau
+    lp, lq = torch.log_softmax(a, -1), torch.log_softmax(b, -1)
+    kl = (lp.exp() * (lp - lq)).sum(-1)
+    h = torch.zeros((T, 8), dtype=dtype, device="cuda")
+    for row in range(T):
+        losses, _, _ = faar.faar_stage2_losses(zf[row:row + 1].cuda(), zq[row:row + 1].cuda(), tau, h[:1], h[:1], kl_scale=1.0)
+        assert float(losses[0]) == pytest.approx(float(kl[row]), rel=1e-5, abs=1e-6)
