@@ -185,19 +185,21 @@ k_stage2_kl_resident(const bf16_t* __restrict__ Zf, const bf16_t* __restrict__ Z
   const int64_t row = blockIdx.x;
   const uint4* zf = reinterpret_cast<const uint4*>(Zf + row * v8 * 8);
   const uint4* zq = reinterpret_cast<const uint4*>(Zq + row * v8 * 8);
+  const unsigned n8 = static_cast<unsigned>(v8);   // at most NC * 1024
   const float ninf = -INFINITY;
   RowStats st{ninf, 0.0f, 0.0f, ninf, 0.0f};
-  uint4 rf[NC];
+  constexpr int kHeld = NC < 18 ? NC : 18;         // a 19th chunk's four registers are not there: it is read again
+  uint4 rf[kHeld];
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    const int64_t c = threadIdx.x + (int64_t)q * kRowThreads;
-    rf[q] = make_uint4(0u, 0u, 0u, 0u);
-    if (c < v8) {
-      rf[q] = zf[c];
-      const uint4 rq = zq[c];
+    const unsigned c = threadIdx.x + q * kRowThreads;
+    if (q < kHeld) rf[q % kHeld] = make_uint4(0u, 0u, 0u, 0u);
+    if (c < n8) {
+      const uint4 ra = zf[c], rq = zq[c];
+      if (q < kHeld) rf[q % kHeld] = ra;
       if (q < kLdsChunks) q_lds[q][threadIdx.x] = rq;
       float a[8], b[8];
-      unpack8(rf[q], a);
+      unpack8(ra, a);
       unpack8(rq, b);
       accumulate8(st, a, b, k, ws);
     }
@@ -212,25 +214,30 @@ k_stage2_kl_resident(const bf16_t* __restrict__ Zf, const bf16_t* __restrict__ Z
     RowStats t = per_wave[0];
     for (int i = 1; i < kRowThreads / 64; ++i) t = merge(t, per_wave[i], k);
     row_stats = t;
-    kl_rows[row] = row_kl(t, inv_tau, ws);
   }
-  if (!dZq) return;
+  // the row's KL, whose logarithm takes more registers than are left beside the row, when the row is no longer needed
+  auto finish = [&] {
+    if (threadIdx.x == 0) kl_rows[row] = row_kl(row_stats, inv_tau, ws);
+  };
+  if (!dZq) return finish();
   __syncthreads();
   const GradCoef grad(row_stats, grad_coef);
   uint4* g = reinterpret_cast<uint4*>(dZq + row * v8 * 8);
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    const int64_t c = threadIdx.x + (int64_t)q * kRowThreads;
-    if (c < v8) {
+    const unsigned c = threadIdx.x + q * kRowThreads;
+    if (c < n8) {
+      const uint4 ra = q < kHeld ? rf[q % kHeld] : zf[c];
       const uint4 rq = q < kLdsChunks ? q_lds[q][threadIdx.x] : zq[c];   // each lane reads back its own LDS slots
       float a[8], b[8];
-      unpack8(rf[q], a);
+      unpack8(ra, a);
       unpack8(rq, b);
       float o[8];
       grad(a, b, k, o);
       g[c] = make_uint4(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]), pack_bf16x2(o[6], o[7]));
     }
   }
+  finish();
 }
 
 template <typename HT>
