@@ -109,9 +109,13 @@ enum {
   FAAR_K_STAGE2_KL = 9,      /* the three launches of faar_stage2_losses, bracketed together */
   FAAR_K_GEMM_C = 10,        /* Y_fp - X_q W^T of faar_layer_prepare (faar_gemm_plan only: it has no time bracket) */
   FAAR_K_GEMM_FWD = 11,      /* X_q W_q^T of faar_linear_forward */
-  FAAR_K_ATTENTION_FWD = 12, /* the attention kernel of faar_attention_fwd (not the transpose before it) */
-  FAAR_K_ATTENTION_BWD = 13, /* the three kernels of faar_attention_bwd (not the transposes before them) */
-  FAAR_K_GEMM_GRAM = 14      /* (W_q - W) (X_q^T X_q), loss, gradient   (faar_layer_step_gram) */
+  FAAR_K_ATTENTION_FWD = 12, /* the kernel of faar_attention_fwd */
+  FAAR_K_ATTENTION_BWD = 13, /* the two kernels of faar_attention_bwd */
+  FAAR_K_GEMM_GRAM = 14,     /* (W_q - W) (X_q^T X_q), loss, gradient   (faar_layer_step_gram) */
+  /* faar_gemm_plan only (FAAR_K_GEMM_RESIDUAL brackets them): the residual GEMM of a step */
+  FAAR_K_GEMM_LOSS = 15,     /* ... that is given an upstream gradient: the loss alone, against C */
+  FAAR_K_GEMM_LOSS_H = 16,   /* ... the same with the gradient constant H */
+  FAAR_K_GEMM_RESIDUAL_H = 17 /* ... with H and the step's own gradient */
 };
 
 /* GEMM kernel variants (output tiles), as reported by faar_gemm_plan.  0 to 3 named variants that no product takes any more; a
@@ -157,9 +161,10 @@ size_t faar_workspace_bytes(int op, int64_t O, int64_t K, int64_t T, uint32_t fl
 int faar_dw_split(int64_t O, int64_t K, int64_t T);
 
 /* Which kernel variant, output tile and contraction split the library uses for one of the GEMMs of a layer of
- * these sizes: which = FAAR_K_GEMM_RESIDUAL (T x O x K), FAAR_K_GEMM_DW (O x K x padded T; the only one that may
- * split its contraction), FAAR_K_GEMM_DX (T x K x O), FAAR_K_GEMM_C (T x O x K, in faar_layer_prepare) or FAAR_K_GEMM_FWD (T x O x K, in
- * faar_linear_forward).
+ * these sizes: which = FAAR_K_GEMM_RESIDUAL (T x O x K), FAAR_K_GEMM_DW (O x K x padded T; it may
+ * split its contraction), FAAR_K_GEMM_DX (T x K x O), FAAR_K_GEMM_C (T x O x K, in faar_layer_prepare), FAAR_K_GEMM_FWD (T x O x K, in
+ * faar_linear_forward), FAAR_K_GEMM_GRAM (O x K x K, may split as well) or one of the other forms of the residual GEMM
+ * (FAAR_K_GEMM_LOSS, FAAR_K_GEMM_LOSS_H, FAAR_K_GEMM_RESIDUAL_H).
  * out[0..3] = variant (FAAR_GEMM_*), tile rows, tile columns, contraction splits.  Pure host function; lets tests
  * prove that their cases reach every variant. */
 int faar_gemm_plan(int which, int64_t O, int64_t K, int64_t T, int32_t* out);

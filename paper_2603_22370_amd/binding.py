@@ -221,6 +221,7 @@ def faar_dw_split(O: int, K: int, T: int) -> int:
 
 
 K_GEMM_C, K_GEMM_FWD, K_ATTENTION_FWD, K_ATTENTION_BWD, K_GEMM_GRAM = 10, 11, 12, 13, 14
+K_GEMM_LOSS, K_GEMM_LOSS_H, K_GEMM_RESIDUAL_H = 15, 16, 17      # faar_gemm_plan only
 GEMM_L64 = 4                                  # FAAR_GEMM_L64, the first value reported
 GEMM_KINDS = ("L64", "M64", "S64", "N64")     # from it on
 

@@ -269,6 +269,9 @@ int faar_gemm_plan(int which, int64_t O, int64_t K, int64_t T, int32_t* out) {
     case FAAR_K_GEMM_C: p = gemm_plan_info(kGemmEpiSub, T, O, K); break;
     case FAAR_K_GEMM_FWD: p = gemm_plan_info(kGemmEpiBf16, T, O, K); break;
     case FAAR_K_GEMM_GRAM: p = gemm_plan_info(kGemmEpiGram, O, K, K); break;
+    case FAAR_K_GEMM_LOSS: p = gemm_plan_info(kGemmEpiLoss, T, O, K); break;
+    case FAAR_K_GEMM_LOSS_H: p = gemm_plan_info(kGemmEpiNone, T, O, K); break;
+    case FAAR_K_GEMM_RESIDUAL_H: p = gemm_plan_info(kGemmEpiBf16, T, O, K); break;
     default: return FAAR_E_ARG;
   }
   out[0] = FAAR_GEMM_L64 + p.kind; out[1] = p.bm; out[2] = p.bn; out[3] = p.n_split;

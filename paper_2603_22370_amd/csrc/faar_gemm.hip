@@ -1117,6 +1117,7 @@ GemmPlanInfo gemm_plan_info(int epilogue, int64_t M, int64_t N, int64_t Kd) {
                : epilogue == kGemmEpiF32    ? plan_gemm(d, true, kEpiF32)
                : epilogue == kGemmEpiSub    ? plan_gemm(d, false, kEpiSub)
                : epilogue == kGemmEpiNone   ? plan_gemm(d, false, kEpiNone)
+               : epilogue == kGemmEpiLoss   ? plan_gemm(d, false, kEpiLoss)
                : epilogue == kGemmEpiGram   ? plan_gemm(d, true, kEpiGram)
                                             : plan_gemm(d, false, kEpiBf16);
   return GemmPlanInfo{p.kind, kTileRows[p.kind], kTileCols[p.kind], p.n_split};

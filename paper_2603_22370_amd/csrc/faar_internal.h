@@ -206,7 +206,7 @@ hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, floa
                               hipStream_t st);
 // The kernel variant, tile shape and contraction split the launchers above pick for an M x N x Kd product
 // (kind: 0 / 1 / 2 / 3 for 256x256 / 256x128 / 128x128 / 128x64 tiles).  Pure host function.
-enum { kGemmEpiResidual = 0, kGemmEpiF32 = 1, kGemmEpiSub = 2, kGemmEpiBf16 = 3, kGemmEpiNone = 4, kGemmEpiGram = 5 };
+enum { kGemmEpiResidual = 0, kGemmEpiF32 = 1, kGemmEpiSub = 2, kGemmEpiBf16 = 3, kGemmEpiNone = 4, kGemmEpiGram = 5, kGemmEpiLoss = 6 };
 struct GemmPlanInfo { int kind, bm, bn, n_split; };
 GemmPlanInfo gemm_plan_info(int epilogue, int64_t M, int64_t N, int64_t Kd);
 // C_out(m, n) = (first ? Y[m][n] : C_out(m, n)) - x_scale * acc   (Y bf16 or float32 row-major; C_out interleaved)

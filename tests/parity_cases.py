@@ -33,10 +33,10 @@ STEP_CASES = [
     StepCase("ragged", 96, 80, 100, 21, quantised_acts=True, chained=True),   # nothing a multiple of a tile
     StepCase("kproj_slice", 512, 2048, 640, 22),
     StepCase("three_tiles", 320, 256, 300, 23, quantised_acts=True, chained=True),
-    StepCase("wide_two_slices", 12288, 64, 2048, 24),
+    StepCase("wide_two_slices", 12288, 64, 2048, 24),             # one slice of 64
     StepCase("mid_k96", 3072, 96, 2048, 25, quantised_acts=True),
     # small shapes that exist to reach one kernel variant each
-    StepCase("tall_k32", 14336, 32, 640, 26),                    # residual / C GEMMs on 256x256 tiles, 32-wide slices
+    StepCase("tall_k32", 14336, 32, 640, 26),                    # residual / C GEMMs on 256x256 tiles, half a slice
     StepCase("dx_o32_t640", 32, 12288, 640, 27, chained=True),   # dX GEMM: contraction 32, 256x256 tiles
     StepCase("dx_o32_t300", 32, 12288, 300, 28, chained=True),   # dX GEMM: contraction 32, 256x128 tiles
     StepCase("dx_o80", 80, 96, 100, 29, chained=True),           # dX GEMM: ragged contraction
@@ -60,7 +60,7 @@ STEP_CASES = [
     StepCase("tail_16", 272, 80, 192, 45, chained=True),
     StepCase("tail_48", 136, 624, 520, 46, chained=True),
     StepCase("tail_128x128", 1000, 208, 3001, 47),
-    # token-major dY out of the residual GEMM (with H) on 256x256 tiles with 32-wide slices: K a multiple of 32 only
+    # token-major dY out of the residual GEMM (with H) on 256x256 tiles, contraction ending 32 into a slice
     StepCase("rows_k160", 12288, 160, 4096, 33),
     # the shapes the benchmark times, at full size
     StepCase("llama_q_proj", 2048, 2048, 4096, 0, full_size=True),
@@ -77,9 +77,9 @@ STEP_CASES = [
 # Cases only the Gram-matrix form of the step runs (tests/test_gpu_gram.py, next to all of STEP_CASES): shapes whose
 # O x K x K product takes a kernel variant none of the above reaches with that epilogue
 GRAM_CASES = [
-    StepCase("gram_256x128_split", 1024, 2112, 256, 41),          # 256x128 tiles, 64-wide slices, contraction split
-    StepCase("gram_256x128_k64", 4096, 1088, 192, 42),            # 256x128 tiles, 64-wide slices, whole
-    StepCase("gram_256x128_k32", 4096, 1056, 192, 43),            # 256x128 tiles, 32-wide slices
+    StepCase("gram_256x128_split", 1024, 2112, 256, 41),          # 256x128 tiles, contraction split
+    StepCase("gram_256x128_k64", 4096, 1088, 192, 42),            # 256x128 tiles, whole
+    StepCase("gram_256x128_k32", 4096, 1056, 192, 43),            # 256x128 tiles, contraction ending 32 into a slice
     StepCase("gram_256x128_split_k3072", 656, 3072, 256, 44),
     StepCase("gram_o400_k6144", 400, 6144, 192, 51),              # contraction split, last tiles of 16 and of 176 rows
     StepCase("gram_o688_k6144", 688, 6144, 192, 53),
@@ -93,6 +93,18 @@ GRAM_CASES = [
     StepCase("gram_128x128_split_k48", 16, 4144, 192, 65),
     StepCase("gram_128x64_split_k16", 16, 1040, 192, 66),
     StepCase("gram_128x64_split_k48", 16, 1072, 192, 67, on_boundary=True),
+]
+
+# (O, K, T) of layers that between them run every GEMM instantiation -- epilogue, tile, contraction whole or split, ending with a slice,
+# in its first half or in its second, and with fewer slices than the ring of stages or more -- which the cases above do not
+# (tests/test_gpu_variants.py runs all of a layer's products on them, tests/test_plan_coverage.py counts)
+VARIANT_SHAPES = [
+    (6144, 16, 300), (6144, 64, 300), (6144, 320, 300), (320, 272, 8192), (16, 1040, 2048), (64, 1040, 2048),        # 128-row tiles
+    (12288, 16, 300), (12288, 48, 300), (12288, 64, 300), (12288, 240, 300), (14336, 272, 300), (14336, 304, 64),   # 256x128
+    (48, 1040, 4096), (64, 1040, 4096), (272, 320, 16384), (432, 1040, 4096),
+    (1040, 16, 8192), (1040, 48, 8192), (1040, 64, 8192), (1040, 144, 8192), (1040, 176, 8192), (12288, 192, 64),   # 256x256
+    (12288, 192, 640), (14336, 560, 64), (48, 2064, 4096), (64, 2064, 4096), (160, 2064, 4096), (432, 2064, 4096),
+    (14336, 640, 192), (14336, 528, 512), (14336, 560, 512), (14336, 560, 640),                                     # dY token-major
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}

@@ -1,6 +1,6 @@
 """CPU-only: the layer-step parity cases together reach every GEMM kernel variant the library can pick.
 
-faar_gemm_plan is a pure host function that reports the variant (tile shape, slice width, contraction split)
+faar_gemm_plan is a pure host function that reports the variant (tile shape, contraction split)
 the library uses for each GEMM of a layer.  The set of (GEMM, variant, split or not) combinations that ANY layer
 shape can produce is found by scanning a wide grid of shapes; the parity cases must cover all of it, so that no
 kernel instantiation runs in the benchmark without having been compared with the oracle."""
@@ -8,7 +8,7 @@ import itertools
 
 from paper_2603_22370_amd import binding as fb
 
-from parity_cases import GRAM_CASES, STEP_CASES
+from parity_cases import GRAM_CASES, STEP_CASES, VARIANT_SHAPES
 
 GEMMS = {"residual": fb.K_GEMM_RESIDUAL, "dw": fb.K_GEMM_DW, "dx": fb.K_GEMM_DX, "c": fb.K_GEMM_C}
 DIMS = [16, 32, 48, 64, 80, 96, 128, 160, 192, 224, 256, 288, 320, 384, 448, 512, 640, 768, 1024, 1280, 1536, 2048,
@@ -154,3 +154,54 @@ def test_token_major_dw_gemm_tiles_are_all_reached_by_parity_cases():
     assert combo(6144, 2048, 8192, True) in full and combo(2048, 6144, 8192, True) in full
     # ... and beside other streams 256 x 256 ones, split or not, which full-size cases run as well
     assert {(1, "whole"), (1, "split")} <= full
+
+
+STAGES = {"L64": 2, "M64": 3, "S64": 4, "N64": 6}      # slices the ring of a tile shape holds
+
+
+def _instantiation(epilogue, which, contraction, O, K, T):
+    """(epilogue, tile, split, where the contraction ends in its last slice, whether a work item walks more slices than the ring
+    holds).  Only the tiles of 256 rows treat the two halves of a slice differently."""
+    kind, _, _, split = fb.faar_gemm_plan(which, O, K, T)
+    slices, tail = (contraction + 63) // 64, contraction % 64
+    ends = "whole" if tail == 0 else "tail" if kind in ("S64", "N64") else "half" if tail <= 32 else "more"
+    return (epilogue, kind, "split" if split > 1 else "one", ends, "wraps" if -(-slices // split) > STAGES[kind] else "short")
+
+
+def _instantiations(O, K, T, chained=True, forward=True):
+    """Everything a layer's set-up, steps (both forms; chained: also with an upstream gradient and dX), Gram-form step and forward run."""
+    yield _instantiation("residual", fb.K_GEMM_RESIDUAL, K, O, K, T)
+    yield _instantiation("rows" if fb.faar_dw_token_major(O, K, T) else "perturbation", fb.K_GEMM_RESIDUAL_H, K, O, K, T)
+    yield _instantiation("dw", fb.K_GEMM_DW, (T + 63) // 64 * 64, O, K, T)
+    yield _instantiation("c", fb.K_GEMM_C, K, O, K, T)
+    yield _instantiation("gram", fb.K_GEMM_GRAM, K, O, K, 1)
+    if chained:
+        yield _instantiation("loss", fb.K_GEMM_LOSS, K, O, K, T)
+        yield _instantiation("loss_h", fb.K_GEMM_LOSS_H, K, O, K, T)
+        yield _instantiation("dx", fb.K_GEMM_DX, O, O, K, T)
+    if forward:
+        yield _instantiation("forward", fb.K_GEMM_FWD, K, O, K, T)
+
+
+def test_every_gemm_instantiation_is_compared_with_an_oracle():
+    """Over layer shapes that end in every place of a slice, the epilogues that only some steps use among them: each instantiation that
+    a shape reaches is run by a parity case or by tests/test_gpu_variants.py."""
+    outs = [16, 48, 64, 96, 160, 256, 272, 320, 432, 640, 1000, 1040, 1280, 2048, 3072, 4096, 6144, 8192, 12288, 14336]
+    ins = [16, 32, 48, 64, 80, 112, 144, 176, 192, 240, 256, 272, 304, 320, 432, 528, 560, 640, 1024, 1040, 1072, 2048, 2064, 2096,
+           3072, 4112, 4144, 5584, 5616, 6144]
+    tokens = [1, 33, 64, 65, 128, 192, 300, 512, 640, 1024, 2048, 4096, 8192, 16384]
+    reachable = {}
+    for O, K, T in itertools.product(outs, ins, tokens):
+        if O * K * T <= 2 ** 38:
+            for x in _instantiations(O, K, T):
+                reachable.setdefault(x, (O, K, T))
+    covered = {_instantiation("gram", fb.K_GEMM_GRAM, c.K, c.O, c.K, 1) for c in GRAM_CASES}
+    for c in STEP_CASES:
+        covered.update(_instantiations(c.O, c.K, c.T, c.chained, False))
+    for O, K, T in FORWARD_CASES:
+        covered.add(_instantiation("forward", fb.K_GEMM_FWD, K, O, K, T))
+    for shape in VARIANT_SHAPES:
+        covered.update(_instantiations(*shape))
+    missing = {k: v for k, v in reachable.items() if k not in covered}
+    assert not missing, f"instantiations that no test compares (with an example shape): {missing}"
+    assert {k[0] for k in reachable} == {"residual", "rows", "perturbation", "dw", "c", "gram", "loss", "loss_h", "dx", "forward"}
