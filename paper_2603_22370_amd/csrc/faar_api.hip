@@ -508,6 +508,14 @@ int faar_layer_prepare(const void* W, faar_dtype wdt, int64_t O, int64_t K, cons
   return hip_status(launch_sum_doubles(sq, c_term_blocks(T, O), c_norm2, st));
 }
 
+// The product on W_q as it lies takes its fragments of W_q with twice as many LDS reads and is 4-12 % slower than on a transposed
+// copy; the copy costs a pass over W_q.  Wide layers of many tokens are where the former is more: a step with dY_ext and dX on the
+// copy / as it lies, in us: 2048x6144 at 16384 tokens 1095 / 1118, 1024x4096 at 32768 708 / 732, 512x4096 at 16384 248 / 255; but
+// 2048x6144 at 8192 596 / 592, 1024x4096 230 / 226, 1024x2048 at 16384 208 / 204, 4096x14336 at 16384 4874 / 4855.
+static bool transposed_dx(int64_t O, int64_t K, int64_t T) {
+  return O >= 512 && K >= 4096 && T >= 16384 && T >= 2 * K;   // K * round_up(O, 64) <= T * O: the copy fits
+}
+
 int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const float* s_global,
                     const uint8_t* scales, float* V, float* adam_m, float* adam_v, const void* Xq, const float* x_scale,
                     const void* Xt, const float* C, const uint8_t* icodes, const float* H, const double* c_norm2,
@@ -629,11 +637,17 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
       if (int e = hip_status(launch_gemm_f32(dYt, static_cast<const bf16_t*>(Xt), d2, G, L.n_split, st))) return e;
     }
   }
-  // s4: dX = dY W_q
+  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of the step's own dY,
+  // which the upstream gradient stands in for
   if (dX) {
-    const GemmDims d3{T, K, O, O, K};
+    const int64_t Op = round_up(O, 64);
+    const bool transposed = dY_ext && transposed_dx(O, K, T);
+    if (transposed)
+      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dY, Op, st))) return e;
     Bracket b(FAAR_K_GEMM_DX, st);
-    if (int e = hip_status(launch_gemm_bf16_nn(dY_used, wq_full, d3, static_cast<bf16_t*>(dX), st))) return e;
+    if (int e = hip_status(transposed ? launch_gemm_bf16(dY_used, dY, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
+                                      : launch_gemm_bf16_nn(dY_used, wq_full, GemmDims{T, K, O, O, K}, static_cast<bf16_t*>(dX), st)))
+      return e;
   }
   // s5 + s6: dV, Adam, clip; the same launch sums the losses (both kinds of partials are complete by now:
   // they come from earlier kernels) and, when asked, runs s1 of the next step on the updated V

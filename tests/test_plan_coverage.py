@@ -178,7 +178,9 @@ def _instantiations(O, K, T, chained=True, forward=True):
     if chained:
         yield _instantiation("loss", fb.K_GEMM_LOSS, K, O, K, T)
         yield _instantiation("loss_h", fb.K_GEMM_LOSS_H, K, O, K, T)
-        yield _instantiation("dx", fb.K_GEMM_DX, O, O, K, T)
+        # wide layers of many tokens: on a transposed copy of W_q, with the kernels of the forward
+        on_copy = O >= 512 and K >= 4096 and T >= 16384 and T >= 2 * K
+        yield _instantiation("forward" if on_copy else "dx", fb.K_GEMM_DX, O, O, K, T)
     if forward:
         yield _instantiation("forward", fb.K_GEMM_FWD, K, O, K, T)
 
