@@ -510,14 +510,7 @@ k_step_fwd(const WT* __restrict__ W, int64_t n8, const float* __restrict__ s_glo
 
 // The forward-tag check of a step that consumes a prepared forward, for steps whose first kernel is not the residual
 // GEMM (which otherwise does it): compare, clear, write the verdict.
-__global__ void k_check_forward_tag(ForwardGuard guard) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    bool ok = true;
-    for (int i = 0; i < kTagWords; ++i) ok = ok && guard.slot[i] == guard.expect.w[i];
-    for (int i = 0; i < kTagWords; ++i) guard.slot[i] = 0u;
-    guard.slot[kTagWords] = ok ? 1u : 0u;
-  }
-}
+__global__ void k_check_forward_tag(ForwardGuard guard) { consume_forward_tag(guard); }
 
 // ---- loss finalisation: fixed-order sums of the per-block partials (one block) ---------------
 struct LossSums {

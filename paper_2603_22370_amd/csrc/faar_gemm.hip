@@ -63,16 +63,8 @@ struct EpiResidualT {
   const float* x_scale;  // device scalar multiplying the A operand (activations stored in units of it); null = 1
   float xs;
   __device__ __forceinline__ void begin() { xs = x_scale ? *x_scale : 1.0f; }
-  // first thing workgroup 0 does: is the forward in the workspace the one this step's caller says it is?
   ForwardGuard guard;
-  __device__ __forceinline__ void once() {
-    if (guard.slot && blockIdx.x == 0 && threadIdx.x == 0) {
-      bool ok = true;
-      for (int i = 0; i < kTagWords; ++i) ok = ok && guard.slot[i] == guard.expect.w[i];
-      for (int i = 0; i < kTagWords; ++i) guard.slot[i] = 0u;   // consumed: a replay of this step must not match
-      guard.slot[kTagWords] = ok ? 1u : 0u;
-    }
-  }
+  __device__ __forceinline__ void once() { consume_forward_tag(guard); }
   float two_alpha;
   bf16_t* dYt;
   int64_t ldt;
@@ -133,14 +125,7 @@ struct EpiPerturbationRows {
   bf16_t* dY;
   double* partials;
   float sum;
-  __device__ __forceinline__ void once() {
-    if (guard.slot && blockIdx.x == 0 && threadIdx.x == 0) {
-      bool ok = true;
-      for (int i = 0; i < kTagWords; ++i) ok = ok && guard.slot[i] == guard.expect.w[i];
-      for (int i = 0; i < kTagWords; ++i) guard.slot[i] = 0u;
-      guard.slot[kTagWords] = ok ? 1u : 0u;
-    }
-  }
+  __device__ __forceinline__ void once() { consume_forward_tag(guard); }
   __device__ __forceinline__ void begin() { xs = x_scale ? *x_scale : 1.0f; }
   __device__ __forceinline__ void rows4(const float (&acc)[4], int64_t m, int64_t n, int, const GemmDims& d) {
     if (n >= d.N) return;
@@ -182,14 +167,7 @@ struct EpiSumSq {
   ForwardGuard guard;
   double* partials;
   float sum;
-  __device__ __forceinline__ void once() {
-    if (guard.slot && blockIdx.x == 0 && threadIdx.x == 0) {
-      bool ok = true;
-      for (int i = 0; i < kTagWords; ++i) ok = ok && guard.slot[i] == guard.expect.w[i];
-      for (int i = 0; i < kTagWords; ++i) guard.slot[i] = 0u;
-      guard.slot[kTagWords] = ok ? 1u : 0u;
-    }
-  }
+  __device__ __forceinline__ void once() { consume_forward_tag(guard); }
   __device__ __forceinline__ void begin() { xs = x_scale ? *x_scale : 1.0f; }
   __device__ __forceinline__ void rows4(const float (&acc)[4], int64_t m, int64_t n, int, const GemmDims& d) {
     if (n >= d.N || m >= d.M) return;   // m is a multiple of 4
@@ -349,14 +327,7 @@ struct EpiGram {
   float* out;
   double* partials;
   float sum;
-  __device__ __forceinline__ void once() {
-    if (guard.slot && blockIdx.x == 0 && threadIdx.x == 0) {
-      bool ok = true;
-      for (int i = 0; i < kTagWords; ++i) ok = ok && guard.slot[i] == guard.expect.w[i];
-      for (int i = 0; i < kTagWords; ++i) guard.slot[i] = 0u;
-      guard.slot[kTagWords] = ok ? 1u : 0u;
-    }
-  }
+  __device__ __forceinline__ void once() { consume_forward_tag(guard); }
   __device__ __forceinline__ void begin() { xs = x_scale ? *x_scale : 1.0f; }
   __device__ __forceinline__ void rows4(const float (&acc)[4], int64_t m, int64_t n, int split, const GemmDims& d) {
     if (n >= d.N) return;

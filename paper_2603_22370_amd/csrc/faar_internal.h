@@ -24,6 +24,16 @@ inline int64_t padded_tokens(int64_t T) { return round_up(T, 64); }
 constexpr int kTagWords = 12;
 struct ForwardTag { uint32_t w[kTagWords]; };
 struct ForwardGuard { uint32_t* slot; ForwardTag expect; };  // slot == nullptr: nothing to check
+// Done by one thread of a launch (workgroup 0 of a step's product, before anything else): is the forward in the workspace the one
+// this step's caller says it is?
+__device__ __forceinline__ void consume_forward_tag(const ForwardGuard& guard) {
+  if (guard.slot && blockIdx.x == 0 && threadIdx.x == 0) {
+    bool ok = true;
+    for (int i = 0; i < kTagWords; ++i) ok = ok && guard.slot[i] == guard.expect.w[i];
+    for (int i = 0; i < kTagWords; ++i) guard.slot[i] = 0u;   // consumed: a replay of this step must not match
+    guard.slot[kTagWords] = ok ? 1u : 0u;
+  }
+}
 
 // ---- elementwise kernels (faar_elementwise.hip) -------------------------------------------
 hipError_t launch_amax(const void* W, bool w_bf16, int64_t n, float* partials, float* s_global,
