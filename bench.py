@@ -898,7 +898,7 @@ def run_block_joint(args) -> dict:
     for kname, kid, fl, what in [("gemm_fwd", fb.K_GEMM_FWD, flops_mlp, "down_proj forward"), ("gemm_dw", fb.K_GEMM_DW, 2.0 * T * n_kv * dh * D, "v_proj dW"),
                                  ("gemm_dx", fb.K_GEMM_DX, 2.0 * T * n_kv * dh * D, "v_proj dX"), ("bwd_adam", fb.K_BWD_ADAM, 0.0, "v_proj"),
                                  ("attention_fwd", fb.K_ATTENTION_FWD, 2.0 * n_seq * n_q * S * S * dh, "causal: half the S x S scores count"),
-                                 ("attention_bwd", fb.K_ATTENTION_BWD, 5.0 * n_seq * n_q * S * S * dh, "three kernels; causal half of five S x S x dh products")]:
+                                 ("attention_bwd", fb.K_ATTENTION_BWD, 5.0 * n_seq * n_q * S * S * dh, "two kernels; causal half of five S x S x dh products")]:
         ms = timer.time(kid, lambda i: block_step(), 4, position=-1)     # the last launch of that kernel in a block step
         row = {"ms": round(ms, 5), "launch": what}
         if fl:

@@ -546,7 +546,7 @@ int faar_rope(const void* x, int64_t T, int64_t H, int64_t dh, const float* cos_
  *   q in bf16 [T * n_q * dh], k, v in bf16 [T * n_kv * dh], T = n_seq * S tokens, sequence b = rows b*S .. (b+1)*S - 1;
  *   o out bf16 [T * n_q * dh]; lse out float [n_q * T]: log of the softmax denominator per head and query (for the backward).
  *   S % 32 == 0, dh 64 or 128, n_q % n_kv == 0, scale > 0.  float32 arithmetic, probabilities rounded to bf16 as matrix-core
- *   operands.  ws: FAAR_OP_ATTENTION_FWD (required; its contents are not used). */
+ *   operands.  ws: FAAR_OP_ATTENTION_FWD (required, of the size queried; its contents are not used). */
 int faar_attention_fwd(const void* q, const void* k, const void* v, int64_t n_seq, int64_t S, int64_t n_q, int64_t n_kv,
                        int64_t dh, float scale, void* o, float* lse, void* ws, size_t ws_bytes, void* stream);
 

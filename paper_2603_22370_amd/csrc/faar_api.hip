@@ -300,8 +300,8 @@ size_t faar_workspace_bytes(int op, int64_t O, int64_t K, int64_t T, uint32_t fl
       return align256(kAmaxPartials * sizeof(float));
     case FAAR_OP_LINEAR_FORWARD:
       return align256((size_t)O * K * 2);   // W_q in bf16
-    // The attention sizes allow for transposed copies of the operands, which the kernels no longer make: a caller's buffer of
-    // the size it has always queried stays good
+    // The attention sizes are those of the transposed copies of the operands that the kernels no longer make: what this call returns,
+    // and what the attention calls accept and refuse by it, stays what it was
     case FAAR_OP_ATTENTION_FWD:             // O = n_q * dh, K = n_kv * dh; nothing is stored there
       if (T <= 0) return 0;
       return align256((size_t)K * (padded_tokens(T) + 64) * 2);

@@ -3,7 +3,7 @@
 // every layer's rounding variables).  The operations are those of the Llama3 / Qwen3 blocks the paper evaluates: rotary
 // position embedding ("rotate-half" form) and causal softmax attention with grouped key / value heads, forward and
 // backward.  Activations and gradients are bf16 between kernels, arithmetic is float32, products run on the matrix
-// cores (v_mfma_f32_16x16x32_bf16) with the probabilities and their gradients rounded to bf16 as operands.
+// cores (v_mfma_f32_32x32x16_bf16) with the probabilities and their gradients rounded to bf16 as operands.
 //
 // Layouts.  q, o, dO, dq: [T, n_q * dh]; k, v, dk, dv: [T, n_kv * dh]; T = n_seq * S tokens, sequence b = rows b*S ..
 // (b+1)*S-1, S a multiple of 32; query head j reads key / value head j / (n_q / n_kv).
@@ -19,13 +19,13 @@
 //     values it must supply for 16-token step t, with the contraction index permuted, which the transposing reads follow.
 // What bounds these kernels: the vector unit as much as the matrix cores (an exponential costs four issue slots, the rest of
 // the softmax as many again: about one VALU cycle per matrix cycle), so the aim is to keep both busy: two independent
-// workgroups per compute unit (256 registers a lane, 64 KB of LDS each), one barrier per 64 tokens, the softmax reductions
+// workgroups per compute unit (256 registers a lane, 64 KB of LDS each; with heads of 64 three or four), one barrier per 64 tokens, the softmax reductions
 // inside a lane but for one exchange between the two halves of the wavefront.
 //
-// Measured, forward / dq / dk + dv in us, against 16x16x32 products on transposed copies with 32-token blocks (whose dk / dv
-// kernel held one workgroup per compute unit): 2 sequences of 4096 tokens, 16 / 8 heads of 128: 338 / 370 / 1008, and 37 of
-// transposes and 12 for delta -> 158 / 210 / 363; forward and backward of 32 sequences of 512: 112 and 507 (+ 98) -> 77 and 260.
-// dk + dv on 64 instead of 128 keys a workgroup: 2 x 4096 tokens (512 groups of 128) 380 -> 334, 32 x 512 (1024 groups) 118 -> 122.
+// Measured, forward and backward in us (calls back to back, the former kernels' transposes included), against 16x16x32 products on
+// transposed copies with 32-token blocks, whose dk / dv kernel held one workgroup per compute unit: 2 sequences of 4096 tokens,
+// 16 / 8 heads of 128: 341 and 1424 -> 146 and 476; of 64: 194 and 642 -> 84 and 269; 32 sequences of 512, heads of 128: 120 and
+// 551 -> 68 and 228.  By kernel, forward / dq / dk + dv: 2 x 4096, heads of 128: 168 / 217 / 319.
 #include <algorithm>
 
 #include "faar_internal.h"
@@ -181,6 +181,9 @@ struct Tile {
 // ones fill the tail; those of the second round of 256 -- the second resident workgroup of every compute unit -- run from
 // light to heavy, so that a unit's two residents add up to about the same work everywhere.  The head / sequence index varies
 // fastest and by key / value head first, so that (where their number is a multiple of 8) an XCD sees the same few of them.
+// Without the turn of the second round the forward takes 146 -> 150 us (2 x 4096 tokens, 16 / 8 heads of 128) and 172 -> 179
+// (1 x 8192, 8 / 1 heads).  Heads of 64 leave room for three or four residents, and the same rule serves them: 83 -> 86 (2 x 4096)
+// and 157 -> 165 (1 x 8192, 16 / 8 heads) without it, while turning every other round of four is within 2 % either way.
 __device__ __forceinline__ void work_item(int id, int pairs, int ranks, int& rank, int& pair) {
   rank = id / pairs;
   pair = id - rank * pairs;
@@ -649,7 +652,9 @@ hipError_t launch_attention_bwd(const bf16_t* dO, const bf16_t* Q, const bf16_t*
   // The work of a group of keys falls linearly with its position and two workgroups share a compute unit: with fewer than 1024
   // groups of 128 keys the first ones end the launch alone on their units (2 x 4096 tokens, 8 heads: 512 groups), and 64 keys
   // a workgroup halve the longest and leave twice as many to fill in behind them.  With more, the larger group's fewer
-  // copies count (figures at the top).
+  // copies count.  dq + dk + dv in us on 128 / 64 keys, heads of 128: 64 groups (1 x 8192, one key / value head) 2430 / 1468,
+  // 512 groups (2 x 4096) 508 / 462, 1024 (8 x 2048) 1003 / 1027; heads of 64, of which three share a unit: 64 groups 1624 / 978,
+  // 512 (2 x 4096) 306 / 261, 1024 (4 x 4096) 478 / 491, 2048 (16 x 2048) 517 / 554.
   const bool halves = n_seq * n_kv * groups < 1024;
   const dim3 gk(static_cast<unsigned>(n_seq * n_kv * (halves ? (S + 63) / 64 : groups)));
 #define FAAR_BWD(DH)                                                                                                          \
