@@ -868,6 +868,25 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
                 fb[cur ^ 1][j] = __builtin_bit_cast(bf16x8, t);
               }
             }
+          } else if constexpr (C::kTokenB && !C::kTokenA && C::WGK == 1 && 2 * (TM + 2 * TN) <= NM) {
+            // B alone token-major, where there are MFMAs to spare: the same, one read each -- two for a fragment of B, one for a
+            // fragment of A (dX on 256x256 tiles 1-4 % faster, T = 8192, 2048 x 6144: 176.5 -> 173.9 us; 256x128 tiles, with 12
+            // reads to 16 MFMAs, lost as much and stay as they were)
+            constexpr int R = TM + 2 * TN;
+            const int r = kk == KK - 1 ? (m * R + NM - 1) / NM : m;
+            if (r < R && (kk < KK - 1 || r * NM / R == m)) {
+              if (r == 0 || r > 2 * TN) {
+                const int i = r == 0 ? 0 : r - 2 * TN;
+                fa[cur ^ 1][i] = frag_a(src, nkk, i);
+              } else {
+                const int j = (r - 1) / 2, h = (r - 1) % 2;
+                typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+                const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(src + b_tr[j] + 32 * nkk * C::BN + h * 4 * C::BN));
+                s16x8 t = __builtin_bit_cast(s16x8, fb[cur ^ 1][j]);
+                if (h == 0) t.lo = v; else t.hi = v;
+                fb[cur ^ 1][j] = __builtin_bit_cast(bf16x8, t);
+              }
+            }
           } else
           if (Epi::kMode != 2 && m % C::FSTEP == 0 && m / C::FSTEP < NF) {  // next phase's fragments: A0, B0..B(TN-1), A1..A(TM-1)
             const int f = m / C::FSTEP;
