@@ -512,8 +512,14 @@ int faar_layer_prepare(const void* W, faar_dtype wdt, int64_t O, int64_t K, cons
 // copy; the copy costs a pass over W_q.  Wide layers of many tokens are where the former is more: a step with dY_ext and dX on the
 // copy / as it lies, in us: 2048x6144 at 16384 tokens 1095 / 1118, 1024x4096 at 32768 708 / 732, 512x4096 at 16384 248 / 255; but
 // 2048x6144 at 8192 596 / 592, 1024x4096 230 / 226, 1024x2048 at 16384 208 / 204, 4096x14336 at 16384 4874 / 4855.
+// So are deep products of fewer than 192 tiles of 256x256: on a chip that is not full, and runs faster for it, the LDS reads alone
+// decide (7360x1216 at 7104 tokens: the product 127 / 164, the step 459 / 476; 8192x2560 at 4096 628 / 644; from 192 tiles on the
+// difference is gone: 8192x1536 at 8192 629 / 629).
 static bool transposed_dx(int64_t O, int64_t K, int64_t T) {
-  return O >= 512 && K >= 4096 && T >= 16384 && T >= 2 * K;   // K * round_up(O, 64) <= T * O: the copy fits
+  if (T * O < K * round_up(O, 64)) return false;             // no room for the copy
+  if (O >= 512 && K >= 4096 && T >= 16384 && T >= 2 * K) return true;
+  const GemmPlanInfo p = gemm_plan_info(kGemmEpiBf16, T, K, O);
+  return O >= 4096 && p.bm == 256 && p.bn == 256 && ((T + 255) / 256) * ((K + 255) / 256) < 192;
 }
 
 int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const float* s_global,
@@ -637,15 +643,15 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
       if (int e = hip_status(launch_gemm_f32(dYt, static_cast<const bf16_t*>(Xt), d2, G, L.n_split, st))) return e;
     }
   }
-  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of the step's own dY,
-  // which the upstream gradient stands in for
+  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of dY^T, which nothing
+  // reads after the dW GEMM
   if (dX) {
     const int64_t Op = round_up(O, 64);
-    const bool transposed = dY_ext && transposed_dx(O, K, T);
+    const bool transposed = transposed_dx(O, K, T);
     if (transposed)
-      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dY, Op, st))) return e;
+      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dYt, Op, st))) return e;
     Bracket b(FAAR_K_GEMM_DX, st);
-    if (int e = hip_status(transposed ? launch_gemm_bf16(dY_used, dY, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
+    if (int e = hip_status(transposed ? launch_gemm_bf16(dY_used, dYt, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
                                       : launch_gemm_bf16_nn(dY_used, wq_full, GemmDims{T, K, O, O, K}, static_cast<bf16_t*>(dX), st)))
       return e;
   }

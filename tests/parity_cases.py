@@ -105,7 +105,7 @@ VARIANT_SHAPES = [
     (1040, 16, 8192), (1040, 48, 8192), (1040, 64, 8192), (1040, 144, 8192), (1040, 176, 8192), (12288, 192, 64),   # 256x256
     (12288, 192, 640), (14336, 560, 64), (48, 2064, 4096), (64, 2064, 4096), (160, 2064, 4096), (432, 2064, 4096),
     (14336, 640, 192), (14336, 528, 512), (14336, 560, 512), (14336, 560, 640),                                     # dY token-major
-    (520, 4096, 16384),                                                                                             # dX on W_q^T
+    (520, 4096, 16384), (4104, 1280, 8192),                                                                         # dX on W_q^T
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}

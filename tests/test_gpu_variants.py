@@ -66,22 +66,23 @@ def test_all_products_of_a_layer(O, K, T):
     R = A - c
     loss = alpha * float((R * R).sum())
     dY_ext = (1e-3 * torch.randn((T, O), generator=gen, device="cuda")).to(torch.bfloat16)
-    for chained in (False, True):
+    for chained, own in ((False, False), (True, False), (True, True)):     # own: dX of the step's own dY
         for with_h in (False, True):
             V, m, u = V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)
             losses = torch.zeros(3, dtype=torch.float32, device="cuda")
             dX = torch.empty((T, K), dtype=torch.bfloat16, device="cuda") if chained else None
             faar.faar_layer_step(W, sg, scales, V, m, u, X, Xt, C, icodes, BETA, LAMBDA, alpha, *ADAM, 1, losses,
-                                 faar.layer_step_workspace(O, K, T, chained=chained), dY_ext=dY_ext if chained else None, dX=dX,
+                                 faar.layer_step_workspace(O, K, T, chained=chained), dY_ext=None if own or not chained else dY_ext, dX=dX,
                                  H=H if with_h else None, c_norm2=c_norm2 if with_h else None)
             assert float(losses[0]) == pytest.approx(loss, rel=2e-5)
             if chained:
-                G = _mm(dY_ext.double().T, Xd)
-                want = _mm(dY_ext.double(), Wq)
+                dY = _bf16(2.0 * alpha * R) if own else dY_ext.double()
+                G = _mm(dY.T, Xd)
+                want = _mm(dY, Wq)
                 # the output's rounding; the step forms W_q in a pass of its own, which may round a value on a bf16 boundary the other
-                # way: two such terms of the largest size; and one float32 rounding per term
-                d = dY_ext.double().abs()
-                flips = 2.0 * U8 * d.amax(dim=1, keepdim=True) * Wq.abs().amax(dim=0, keepdim=True)
+                # way: two such terms of the largest size (two more of its own dY); and one float32 rounding per term
+                d = dY.abs()
+                flips = (4.0 if own else 2.0) * U8 * d.amax(dim=1, keepdim=True) * Wq.abs().amax(dim=0, keepdim=True)
                 assert bool(((dX.double() - want).abs() <= U8 * want.abs() + flips + (O + 2) * EPS * _mm(d, Wq.abs())).all())
                 assert float((dX.double() - want).norm()) <= 2.5e-3 * float(want.norm())
             elif with_h:

@@ -178,8 +178,10 @@ def _instantiations(O, K, T, chained=True, forward=True):
     if chained:
         yield _instantiation("loss", fb.K_GEMM_LOSS, K, O, K, T)
         yield _instantiation("loss_h", fb.K_GEMM_LOSS_H, K, O, K, T)
-        # wide layers of many tokens: on a transposed copy of W_q, with the kernels of the forward
-        on_copy = O >= 512 and K >= 4096 and T >= 16384 and T >= 2 * K
+        # wide layers of many tokens, and products that fill less than three quarters of the chip with 256x256 tiles: on a transposed
+        # copy of W_q, with the kernels of the forward
+        few = fb.faar_gemm_plan(fb.K_GEMM_DX, O, K, T)[0] == "L64" and -(-T // 256) * -(-K // 256) < 192
+        on_copy = T * O >= K * ((O + 63) // 64 * 64) and (O >= 512 and K >= 4096 and T >= 16384 and T >= 2 * K or O >= 4096 and few)
         yield _instantiation("forward" if on_copy else "dx", fb.K_GEMM_DX, O, O, K, T)
     if forward:
         yield _instantiation("forward", fb.K_GEMM_FWD, K, O, K, T)
