@@ -67,8 +67,7 @@ def test_benchmark_shapes_are_parity_cases_at_full_size():
     for shapes, T, chained in ((llama, 4096, False), (qwen, 8192, False), (qwen, 16384, True)):
         for O, K in shapes:
             for combo in _combos(O, K, T, chained):
-                if combo[1] in ("L64", "M64"):          # the two fast kernels; the 128x128 one is covered by small cases
-                    assert combo in full, (O, K, T, combo)
+                assert combo in full, (O, K, T, combo)
 
 
 def test_forward_gemm_of_the_joint_step_runs_kernels_that_parity_cases_cover():
