@@ -313,7 +313,7 @@ size_t faar_workspace_bytes(int op, int64_t O, int64_t K, int64_t T, uint32_t fl
       if (T <= 0 || O % 8 != 0) return 0;
       return align256((size_t)block_loss_blocks(T * O) * sizeof(double));
     case FAAR_OP_QUANT_RTN_BATCH:   // whatever the number and sizes of the tensors: launches reuse it in stream order
-      return align256((size_t)kBatchMax * kBatchAmaxBlocks * sizeof(float));
+      return align256((size_t)kBatchPartials * sizeof(float));
     case FAAR_OP_INIT_V:
     case FAAR_OP_HARDEN_PACK:
       return 256;  // none needed; a non-zero size keeps callers' allocation code uniform
@@ -399,12 +399,10 @@ static int codec_batch(int op, const faar_tensor* items, int64_t n_items, faar_d
       const int64_t tb = (t.n / 8 + kEltThreads - 1) / kEltThreads;
       if (j > 0 && blocks + tb > 0x7FFFFFFFll) break;
       if (tb > 0x7FFFFFFFll) return FAAR_E_SHAPE;   // unreachable below kMaxElems; kept next to the limit it protects
-      B.first_block[j] = static_cast<uint32_t>(blocks);
       B.it[j] = CodecItem{t.W, t.s_global, t.scales, t.V, reinterpret_cast<uint32_t*>(t.codes), t.n / 8};
       blocks += tb;
     }
     B.n = j;
-    B.first_block[j] = static_cast<uint32_t>(blocks);
     if (int e = hip_status(launch_codec_batch(op, B, wdt == FAAR_BF16, given, static_cast<float*>(ws), st))) return e;
   }
   return FAAR_OK;

@@ -49,20 +49,22 @@ hipError_t launch_harden_pack(const void* W, bool w_bf16, int64_t n, const float
                               hipStream_t st);
 // Batched codec operations: up to kBatchMax tensors per launch, descriptors passed in the kernel arguments.
 constexpr int kBatchMax = 72;          // 72 descriptors of 48 bytes + the index table stay below the 4 KB argument limit
-constexpr int kBatchAmaxBlocks = 64;   // workgroups (and partial maxima) per tensor in the batched amax pass
+constexpr int kBatchChunks = 4;        // chunks of 8 weights a thread of the batched amax and quantise kernels takes at a time
+constexpr int kBatchPartials = 64 * kBatchMax;   // partial maxima of a launch
 struct CodecItem {
   const void* W; float* s_global; uint8_t* scales; float* V; uint32_t* codes;
   int64_t n8;                          // chunks of 8 weights
 };
 struct CodecBatch {
   int n;                               // tensors in this launch
-  uint32_t first_block[kBatchMax + 1]; // first workgroup of each tensor; [n] = grid size
+  uint32_t first_block[kBatchMax + 1]; // first workgroup of each tensor; [n] = grid size (set by the launcher, kernel by kernel)
+  int64_t per_wg;                      // groups of chunks a workgroup of the amax pass walks
   CodecItem it[kBatchMax];
 };
-static_assert(sizeof(CodecBatch) <= 4096, "kernel arguments are limited to 4 KB");
+static_assert(sizeof(CodecBatch) <= 4096 - 16, "kernel arguments are limited to 4 KB");
 enum { kBatchQuant = 0, kBatchInitV = 1, kBatchHardenPack = 2 };
-// partials: kBatchAmaxBlocks floats per tensor (quantise without given tensor scales only)
-hipError_t launch_codec_batch(int op, const CodecBatch& B, bool w_bf16, bool sglobal_given, float* partials, hipStream_t st);
+// partials: kBatchPartials floats (quantise without given tensor scales only)
+hipError_t launch_codec_batch(int op, CodecBatch& B, bool w_bf16, bool sglobal_given, float* partials, hipStream_t st);
 
 // Wt = bf16(W_q) or bf16(W_q - W); Wq_full (nullable) additionally receives bf16(W_q).
 hipError_t launch_softquant_fwd(const void* W, bool w_bf16, int64_t n, const float* s_global,
