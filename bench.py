@@ -107,6 +107,13 @@ class HipEvents:
         return float(ms.value)
 
 
+def product_updates_v(form, O, K, T) -> bool:
+    """Whether a step's dW (Gram-form) product ends in the pass over V, m, u: the library's rule for products that are not split."""
+    from paper_2603_22370_amd import binding as fb
+    _, bm, bn, split = fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T) if form == "token" else fb.faar_gemm_plan(fb.K_GEMM_GRAM, O, K, 1)
+    return split == 1 and (-(-O // bm) * -(-K // bn) >= 96 if form == "token" else O * K >= 1 << 22)
+
+
 class KernelTimer:
     """Average duration of one kernel of the path in steady state: the library brackets each of its launches with a pair
     of HIP events out of a ring, on the stream it is launched on; the calls are issued back to back without host
@@ -294,7 +301,9 @@ class LinearJob:
         probe["softquant_fwd"] = timer.time(fb.K_SOFTQUANT_FWD, first_step_call, n_probe)
         gemms = ([("gemm_residual", fb.K_GEMM_RESIDUAL), ("gemm_dw", fb.K_GEMM_DW)] if self.form == "token"
                  else [("gemm_gram", fb.K_GEMM_GRAM)])
-        for name, kid in gemms + [("bwd_adam", fb.K_BWD_ADAM)]:
+        if not product_updates_v(self.form, self.O, self.K, self.T):
+            gemms = gemms + [("bwd_adam", fb.K_BWD_ADAM)]
+        for name, kid in gemms:
             probe[name] = timer.time(kid, step_call, n_probe)
         if codec:
             probe["quant_rtn"] = timer.time(fb.K_QUANT_RTN, lambda i: faar.faar_quant_rtn(self.W, ws=self.ws_q), n_probe)
@@ -321,11 +330,16 @@ class LinearJob:
                              "frac": round(ach / HBM_PEAK_GBS, 4)}
                 if step_bytes < 256e6:     # the step's working set fits the 256 MB Infinity Cache: not an HBM rate
                     out[name]["note"] = "effective rate: working set resident in the Infinity Cache"
+            if name in ("gemm_dw", "gemm_gram") and "bwd_adam" not in probe:
+                # one kernel: the product and, in its epilogue, the pass over V, m, u without the gradient's 8 bytes a weight
+                b = bpw["bwd_adam"] - 4 * (self.dw_split if self.form == "token" else self.gram_split)
+                out[name]["ends_in"] = "bwd_adam"
+                out[name]["update_bytes"] = int(b * N)
             # the dW GEMM has its own counter rows for the 192-wide tiles a step takes when it has the device to itself
             from paper_2603_22370_amd import binding as fb
             wide = (name == "gemm_dw" and self.form == "token" and self.whole_device
                     and fb.faar_dw_token_major(self.O, self.K, self.T, True) in (2, 3))
-            out[name]["traffic"] = traffic_for(name + ("_whole_device" if wide else ""), self.O, self.K, self.T)
+            out[name]["traffic"] = None if "ends_in" in out[name] else traffic_for(name + ("_whole_device" if wide else ""), self.O, self.K, self.T)
         return out
 
 
@@ -430,7 +444,7 @@ def run_layer(args) -> dict:
                               "flipped_decisions": int(j.state["flips"].item()), "hardened_loss": {"rtn": rtn, "faar": opt},
                               "kernels": table}
     # the kernel that takes the largest share of a step of the whole layer
-    dom_l, dom_k = max(((l, k) for l in per_linear for k in (("gemm_gram", "bwd_adam") if gram else ("gemm_residual", "gemm_dw", "bwd_adam"))),
+    dom_l, dom_k = max(((l, k) for l in per_linear for k in (("gemm_gram", "bwd_adam") if gram else ("gemm_residual", "gemm_dw", "bwd_adam")) if k in per_linear[l]),
                        key=lambda lk: per_linear[lk[0]]["kernels"][lk[1]]["ms"])
     dom = per_linear[dom_l]["kernels"][dom_k]
     ms_per_step = elapsed / args.steps * 1e3
@@ -535,7 +549,7 @@ def run_linear(args) -> dict:
     probe["softquant_fwd_bwd_call"] = te0.elapsed_time(te1) / n_probe
     del dWt
     kernels = j.kernel_table(probe)
-    dom = max(("gemm_gram", "bwd_adam") if gram else ("gemm_residual", "gemm_dw", "bwd_adam"), key=lambda k: probe[k])
+    dom = max((k for k in (("gemm_gram", "bwd_adam") if gram else ("gemm_residual", "gemm_dw", "bwd_adam")) if k in probe), key=lambda k: probe[k])
     roofline = {"kernel": dom, "bound": kernels[dom]["bound"], "achieved": kernels[dom]["achieved"],
                 "peak": BF16_PEAK_TFLOPS if kernels[dom]["bound"] == "mfma" else HBM_PEAK_GBS,
                 "unit": kernels[dom]["unit"], "frac": kernels[dom]["frac"], "traffic": kernels[dom]["traffic"],
@@ -625,8 +639,10 @@ def run_block_chained(args) -> dict:
         flops = 2.0 * T * O * K
         total_flops += 3 * flops
         row = {}
-        for kname, kid in [("gemm_residual", fb.K_GEMM_RESIDUAL), ("gemm_dw", fb.K_GEMM_DW), ("gemm_dx", fb.K_GEMM_DX),
-                           ("bwd_adam", fb.K_BWD_ADAM)]:
+        kinds = [("gemm_residual", fb.K_GEMM_RESIDUAL), ("gemm_dw", fb.K_GEMM_DW), ("gemm_dx", fb.K_GEMM_DX)]
+        if not product_updates_v("token", O, K, T):
+            kinds.append(("bwd_adam", fb.K_BWD_ADAM))
+        for kname, kid in kinds:
             ms = timer.time(kid, lambda i: step_linear(L), 6)
             if kname.startswith("gemm"):
                 row[kname] = {"ms": round(ms, 5), "tflops": round(flops / (ms * 1e-3) / 1e12, 1),
@@ -636,6 +652,8 @@ def run_block_chained(args) -> dict:
                 row[kname] = {"ms": round(ms, 5), "gbs": round(b * O * K / (ms * 1e-3) / 1e9, 1),
                               "frac": round(b * O * K / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
         row["dw_split"] = j.dw_split
+        if "bwd_adam" not in row:
+            row["gemm_dw"]["ends_in"] = "bwd_adam"
         row["losses"] = j.losses.cpu().numpy().tolist()
         per_linear[j.name] = row
     dom_l, dom_k = max(((l, k) for l in per_linear for k in ("gemm_residual", "gemm_dw", "gemm_dx")),

@@ -81,7 +81,7 @@ StepLayout step_layout(int64_t O, int64_t K, int64_t T, bool chained) {
   L.n_split = choose_split(O, K, L.Tp);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t r = off; off += align256(bytes); return r; };
-  L.guard = take((size_t)(kTagWords + 1) * 4);  // first, so that every user of a step workspace finds it
+  L.guard = take((size_t)(kArrivals + 1) * 4);  // first, so that every user of a step workspace finds it
   L.delta = take((size_t)O * K * 2);
   L.dYt = take((size_t)O * L.Tp * 2);
   L.G = take((size_t)L.n_split * O * K * 4);
@@ -107,7 +107,7 @@ GramLayout gram_layout(int64_t O, int64_t K) {
   L.n_split = choose_split_gram(O, K);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t r = off; off += align256(bytes); return r; };
-  L.guard = take((size_t)(kTagWords + 1) * 4);
+  L.guard = take((size_t)(kArrivals + 1) * 4);
   L.delta = take((size_t)O * K * 2);
   L.G = take((size_t)L.n_split * O * K * 4);
   L.mse_partials = take((size_t)gemm_gram_partials(O, K) * 8);
@@ -629,32 +629,8 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
     if (!token_major)
       if (int e = hip_status(launch_transpose_bf16(dY_used, T, O, dYt, L.Tp, st))) return e;
   }
-  // s3: G = dY^T X_q, contraction over tokens, split for occupancy
-  {
-    Bracket b(FAAR_K_GEMM_DW, st);
-    if (token_major || rows_form) {
-      if (int e = hip_status(launch_gemm_f32_tn(rows_form ? dYt : dY_used, xq, GemmDims{O, K, T, O, K}, G, L.n_split,
-                                                (flags & FAAR_STEP_WHOLE_DEVICE) != 0, st)))
-        return e;
-    } else {
-      const GemmDims d2{O, K, L.Tp, L.Tp, L.Tp};
-      if (int e = hip_status(launch_gemm_f32(dYt, static_cast<const bf16_t*>(Xt), d2, G, L.n_split, st))) return e;
-    }
-  }
-  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of dY^T, which nothing
-  // reads after the dW GEMM
-  if (dX) {
-    const int64_t Op = round_up(O, 64);
-    const bool transposed = transposed_dx(O, K, T);
-    if (transposed)
-      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dYt, Op, st))) return e;
-    Bracket b(FAAR_K_GEMM_DX, st);
-    if (int e = hip_status(transposed ? launch_gemm_bf16(dY_used, dYt, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
-                                      : launch_gemm_bf16_nn(dY_used, wq_full, GemmDims{T, K, O, O, K}, static_cast<bf16_t*>(dX), st)))
-      return e;
-  }
-  // s5 + s6: dV, Adam, clip; the same launch sums the losses (both kinds of partials are complete by now:
-  // they come from earlier kernels) and, when asked, runs s1 of the next step on the updated V
+  // s5 + s6: dV, Adam, clip; the same kernel sums the losses (both kinds of partials are complete by then: they come from earlier
+  // kernels) and, when asked, runs s1 of the next step on the updated V
   StepBwdArgs a{};
   a.W = W; a.w_bf16 = bf; a.n = n;
   a.s_global = s_global; a.scales = scales; a.icodes = icodes;
@@ -670,6 +646,43 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
   a.next_tag = forward_tag(opt->t + 1, beta_next, V, W, scales, n, wq_full != nullptr, Hs);
   a.H = Hs; a.two_alpha_h = (Hs && !dY_ext) ? 2.0f * mse_scale : 0.0f;
   a.cross_partials = cross_p; a.c_norm2 = c_norm2; a.cross_next = cross_next;
+
+  const bool tn = token_major || rows_form;
+  const bool transposed = dX && transposed_dx(O, K, T);
+  // A dW product that is not split ends in the pass over V.  It then overwrites W_q when the next step's is wanted too, so dX comes
+  // first there -- unless dX wants the transposed copy of W_q, which lies in the place of dY^T, and dW that dY^T
+  const bool dx_first = dX && beta_next > 0.0f;
+  const bool in_dw = gemm_dw_updates(O, K, L.Tp) && !(dx_first && transposed && !tn);
+  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of dY^T, which no dW GEMM
+  // after it reads
+  auto input_gradient = [&]() -> int {
+    const int64_t Op = round_up(O, 64);
+    if (transposed)
+      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dYt, Op, st))) return e;
+    Bracket b(FAAR_K_GEMM_DX, st);
+    return hip_status(transposed ? launch_gemm_bf16(dY_used, dYt, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
+                                 : launch_gemm_bf16_nn(dY_used, wq_full, GemmDims{T, K, O, O, K}, static_cast<bf16_t*>(dX), st));
+  };
+  if (in_dw && dx_first)
+    if (int e = input_gradient()) return e;
+  // s3: G = dY^T X_q, contraction over tokens, split for occupancy
+  const bf16_t* dw_a = tn ? (rows_form ? dYt : dY_used) : dYt;
+  const bf16_t* dw_b = tn ? xq : static_cast<const bf16_t*>(Xt);
+  const GemmDims d2 = tn ? GemmDims{O, K, T, O, K} : GemmDims{O, K, L.Tp, L.Tp, L.Tp};
+  const bool whole = (flags & FAAR_STEP_WHOLE_DEVICE) != 0;
+  if (in_dw) {
+    Bracket b(FAAR_K_GEMM_DW, st);
+    Bracket b2(FAAR_K_BWD_ADAM, st);
+    if (int e = hip_status(launch_gemm_dw_update(dw_a, dw_b, d2, tn, whole, a, st))) return e;
+  } else {
+    Bracket b(FAAR_K_GEMM_DW, st);
+    if (int e = hip_status(tn ? launch_gemm_f32_tn(dw_a, dw_b, d2, G, L.n_split, whole, st)
+                              : launch_gemm_f32(dw_a, dw_b, d2, G, L.n_split, st)))
+      return e;
+  }
+  if (dX && !(in_dw && dx_first))
+    if (int e = input_gradient()) return e;
+  if (in_dw) return FAAR_OK;
   Bracket b(FAAR_K_BWD_ADAM, st);
   return hip_status(launch_step_bwd_adam(a, st));
 }
@@ -727,6 +740,16 @@ int faar_layer_step_gram(const void* W, faar_dtype wdt, int64_t O, int64_t K, co
   double* cross_p = reinterpret_cast<double*>(base + L.cross_partials) + (opt->t & 1) * kStepBwdMaxBlocks;
   double* cross_next = reinterpret_cast<double*>(base + L.cross_partials) + ((opt->t + 1) & 1) * kStepBwdMaxBlocks;
   uint32_t* guard_slot = reinterpret_cast<uint32_t*>(base + L.guard);
+  // A product that is not split ends in the pass over V.  Its workgroups still read W_q - W while others write the next step's, so the
+  // two take turns between the place of W_q - W and that of the gradient, which does not exist then; the tag says which form left it
+  const bool in_product = gemm_gram_updates(O, K);
+  bf16_t* delta_next = delta;
+  if (in_product) (opt->t & 1 ? delta : delta_next) = reinterpret_cast<bf16_t*>(G);
+  auto tag = [&](int32_t t, float b) {
+    ForwardTag g = forward_tag(t, b, V, W, scales, n, false, H);
+    if (in_product) g.w[11] |= 4u;
+    return g;
+  };
   ForwardGuard guard{nullptr, {}};
   // s1: W_q - W (bf16), Round-Loss partials and <W_q - W, H> partials -- unless the previous step left them
   if (!(flags & FAAR_WS_FORWARD_READY)) {
@@ -736,15 +759,7 @@ int faar_layer_step_gram(const void* W, faar_dtype wdt, int64_t O, int64_t K, co
       return e;
   } else {
     guard.slot = guard_slot;
-    guard.expect = forward_tag(opt->t, beta, V, W, scales, n, false, H);
-  }
-  // s2 + s3 in one product: (W_q - W) Gm, with the quadratic term of the loss summed in the epilogue
-  int64_t n_mse = 0;
-  {
-    Bracket b(FAAR_K_GEMM_GRAM, st);
-    if (int e = hip_status(launch_gemm_gram(delta, static_cast<const bf16_t*>(gram), O, K, gram_lo, x_scale, 2.0f * mse_scale, G,
-                                            L.n_split, mse_p, &n_mse, guard, st)))
-      return e;
+    guard.expect = tag(opt->t, beta);
   }
   // s5 + s6 as in faar_layer_step
   StepBwdArgs a{};
@@ -756,12 +771,25 @@ int faar_layer_step_gram(const void* W, faar_dtype wdt, int64_t O, int64_t K, co
   a.opt.lr = opt->lr; a.opt.beta1 = opt->beta1; a.opt.beta2 = opt->beta2; a.opt.eps = opt->eps;
   a.opt.inv_bc1 = static_cast<float>(1.0 / (1.0 - std::pow((double)opt->beta1, (double)opt->t)));
   a.opt.inv_bc2 = static_cast<float>(1.0 / (1.0 - std::pow((double)opt->beta2, (double)opt->t)));
-  a.mse_partials = mse_p; a.n_mse = n_mse; a.mse_scale = mse_scale; a.round_partials = round_p; a.losses = losses;
-  a.beta_next = beta_next; a.delta_next = delta; a.wq_full_next = nullptr; a.round_next = round_next;
+  a.mse_partials = mse_p; a.mse_scale = mse_scale; a.round_partials = round_p; a.losses = losses;
+  a.beta_next = beta_next; a.delta_next = delta_next; a.wq_full_next = nullptr; a.round_next = round_next;
   a.guard_slot = guard_slot;
-  a.next_tag = forward_tag(opt->t + 1, beta_next, V, W, scales, n, false, H);
+  a.next_tag = tag(opt->t + 1, beta_next);
   a.H = H; a.two_alpha_h = 2.0f * mse_scale;
   a.cross_partials = cross_p; a.c_norm2 = c_norm2; a.cross_next = cross_next;
+  if (in_product) {
+    double* sums = reinterpret_cast<double*>(reinterpret_cast<char*>(G) + align256((size_t)n * 2));   // behind W_q - W
+    Bracket b(FAAR_K_GEMM_GRAM, st);
+    Bracket b2(FAAR_K_BWD_ADAM, st);
+    return hip_status(launch_gemm_gram_update(delta, static_cast<const bf16_t*>(gram), O, K, gram_lo, sums, guard, a, st));
+  }
+  // s2 + s3 in one product: (W_q - W) Gm, with the quadratic term of the loss summed in the epilogue
+  {
+    Bracket b(FAAR_K_GEMM_GRAM, st);
+    if (int e = hip_status(launch_gemm_gram(delta, static_cast<const bf16_t*>(gram), O, K, gram_lo, x_scale, 2.0f * mse_scale, G,
+                                            L.n_split, mse_p, &a.n_mse, guard, st)))
+      return e;
+  }
   Bracket b(FAAR_K_BWD_ADAM, st);
   return hip_status(launch_step_bwd_adam(a, st));
 }

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "faar_internal.h"
+#include "faar_step.h"
 
 namespace faar {
 namespace {
@@ -16,12 +17,6 @@ __device__ __forceinline__ float pair_max(float a) {
 __device__ __forceinline__ float wave_max(float a) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) a = fmaxf(a, __shfl_xor(a, o));
-  return a;
-}
-
-__device__ __forceinline__ double wave_sum(double a) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
   return a;
 }
 
@@ -446,60 +441,13 @@ k_interval_codes(const WT* __restrict__ W, int64_t n8, const float* __restrict__
   icodes[i] = packed;
 }
 
-// lower node and interval width of magnitude code k in 0..6
-__device__ __forceinline__ float node_lo(uint32_t k) {
-  return k < 2u ? 0.5f * static_cast<float>(k) : __uint_as_float(((126u + (k >> 1)) << 23) | ((k & 1u) << 22));
-}
-__device__ __forceinline__ float node_width(uint32_t k) { return k < 4u ? 0.5f : (k < 6u ? 1.0f : 2.0f); }
-// sigmoid through the hardware exp2 / reciprocal units (about 1 ulp each; not decision arithmetic)
-__device__ __forceinline__ float h_beta_fast(float v, float beta) {
-  return __builtin_amdgcn_rcpf(1.0f + __expf(-beta * (v - 0.5f)));
-}
-// signed scale  sign(w) * s  of a coded weight (0 for a zero weight)
-__device__ __forceinline__ float signed_scale(uint32_t nib, float s) {
-  return (nib & 7u) == 7u ? 0.0f : ((nib & 8u) ? -s : s);
-}
-
-// soft-quantised weight of one coded element
-__device__ __forceinline__ float soft_weight(uint32_t nib, float s, float v, float beta) {
-  const uint32_t k = nib & 7u;
-  return signed_scale(nib, s) * (node_lo(k) + h_beta_fast(v, beta) * node_width(k));
-}
-
-__device__ __forceinline__ void store_bf16x8(bf16_t* p, const float (&x)[8]) {
-  *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]),
-                                            pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
-}
-
-// delta = bf16(W_q - W) (and bf16(W_q)) for eight weights, plus their Round-Loss terms sum(1 - (2v - 1)^2) and, when
-// the layer carries the constant H = C^T X_q (use_h; hh its eight values), the cross term sum(delta * H) of the loss, taken on the
-// ROUNDED delta -- the operand the residual GEMM actually multiplies
 template <typename WT, bool kFull>
 __device__ __forceinline__ float forward8(const WT* __restrict__ W, int64_t i, uint32_t codes, float s,
                                           const float (&v)[8], float beta, bf16_t* __restrict__ delta,
                                           bf16_t* __restrict__ Wq_full, bool use_h, const float (&hh)[8], float& cross) {
-  float w[8], out[8], full[8];
+  float w[8];
   W8<WT>::load(W + i * 8, w);
-  float rsum = 0.0f;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float wq = soft_weight((codes >> (4 * j)) & 15u, s, v[j], beta);
-    out[j] = wq - w[j];
-    if (kFull) full[j] = wq;
-    const float t = 2.0f * v[j] - 1.0f;
-    rsum += 1.0f - t * t;
-  }
-  const uint4 packed = make_uint4(pack_bf16x2(out[0], out[1]), pack_bf16x2(out[2], out[3]),
-                                  pack_bf16x2(out[4], out[5]), pack_bf16x2(out[6], out[7]));
-  *reinterpret_cast<uint4*>(delta + i * 8) = packed;
-  if (use_h) {   // hh stays in registers: indexed by constants only
-    const uint32_t r[4] = {packed.x, packed.y, packed.z, packed.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      cross += __uint_as_float(r[j] << 16) * hh[2 * j] + __uint_as_float(r[j] & 0xFFFF0000u) * hh[2 * j + 1];
-  }
-  if (kFull) store_bf16x8(Wq_full + i * 8, full);
-  return rsum;
+  return soft_forward8(w, codes, s, v, beta, delta + i * 8, kFull ? Wq_full + i * 8 : nullptr, use_h, hh, cross);
 }
 
 template <typename WT, bool kFull>
@@ -511,6 +459,7 @@ k_step_fwd(const WT* __restrict__ W, int64_t n8, const float* __restrict__ s_glo
   if (blockIdx.x == 0 && threadIdx.x == 0) {  // a fresh forward: whatever tag the workspace held is void, verdict 1
     for (int i = 0; i < kTagWords; ++i) guard_slot[i] = 0u;
     guard_slot[kTagWords] = 1u;
+    guard_slot[kArrivals] = 0u;
   }
   float rsum = 0.0f, cross = 0.0f;
   const float sg = *s_global_p;
@@ -534,73 +483,7 @@ k_step_fwd(const WT* __restrict__ W, int64_t n8, const float* __restrict__ s_glo
 // GEMM (which otherwise does it): compare, clear, write the verdict.
 __global__ void k_check_forward_tag(ForwardGuard guard) { consume_forward_tag(guard); }
 
-// ---- loss finalisation: fixed-order sums of the per-block partials (one block) ---------------
-struct LossSums {
-  const double* mse_partials;
-  int64_t n_mse;
-  float mse_scale;
-  // with the constant part of the residual carried separately (R = A - C, A = x_scale * acc):
-  // ||R||^2 = sum A^2 - 2 x_scale <delta, H> + ||C||^2; cross_partials sum to <delta, H>.  Null: mse_partials are ||R||^2.
-  const double* cross_partials;
-  int64_t n_cross;
-  const double* c_norm2;
-  const float* x_scale;
-  const double* round_partials;
-  int64_t n_round;
-  double inv_n;
-  float lambda_round;
-  float *loss_mse, *loss_round, *loss_total;
-};
-
-__device__ __forceinline__ void finalize_block(const LossSums& f, bool valid = true) {
-  if (!valid) {  // the step ran on a forward pass that is not the one its caller described: no result
-    if (threadIdx.x == 0) {
-      const float nan = __uint_as_float(0x7FC00000u);
-      if (f.loss_mse) *f.loss_mse = nan;
-      if (f.loss_round) *f.loss_round = nan;
-      if (f.loss_total) *f.loss_total = nan;
-    }
-    return;
-  }
-  double a = 0.0, b = 0.0, c = 0.0;
-  // per-thread partial sums in a fixed order; loads of one batch are independent
-#pragma unroll 4
-  for (int64_t i = threadIdx.x; i < f.n_mse; i += kEltThreads) a += f.mse_partials[i];
-#pragma unroll 4
-  for (int64_t i = threadIdx.x; i < f.n_round; i += kEltThreads) b += f.round_partials[i];
-  if (f.cross_partials) {
-#pragma unroll 4
-    for (int64_t i = threadIdx.x; i < f.n_cross; i += kEltThreads) c += f.cross_partials[i];
-  }
-  __shared__ double sa[kEltThreads / 64], sb[kEltThreads / 64], sc[kEltThreads / 64];
-  a = wave_sum(a);
-  b = wave_sum(b);
-  c = wave_sum(c);
-  if ((threadIdx.x & 63) == 0) {
-    sa[threadIdx.x >> 6] = a;
-    sb[threadIdx.x >> 6] = b;
-    sc[threadIdx.x >> 6] = c;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    a = 0.0;
-    b = 0.0;
-    c = 0.0;
-    for (int i = 0; i < kEltThreads / 64; ++i) {
-      a += sa[i];
-      b += sb[i];
-      c += sc[i];
-    }
-    if (f.cross_partials) a += *f.c_norm2 - 2.0 * static_cast<double>(f.x_scale ? *f.x_scale : 1.0f) * c;
-    const double mse = a * static_cast<double>(f.mse_scale);
-    const double rl = b * f.inv_n;
-    if (f.loss_mse) *f.loss_mse = static_cast<float>(mse);
-    if (f.loss_round) *f.loss_round = static_cast<float>(rl);
-    if (f.loss_total) *f.loss_total = static_cast<float>(mse + static_cast<double>(f.lambda_round) * rl);
-  }
-}
-
-__global__ void __launch_bounds__(kEltThreads) k_finalize_losses(LossSums f) { finalize_block(f); }
+__global__ void __launch_bounds__(kEltThreads) k_finalize_losses(LossSums f) { finalize_block<kEltThreads>(f); }
 
 // Backward + Adam + clip over grid-stride blocks 0..gridDim.x-2.  With kEmit the same pass writes the next
 // step's delta (and W_q) from the updated V at beta_next, with that V's Round-Loss partials.  The last block
@@ -617,7 +500,7 @@ k_step_bwd_adam(int64_t n8, const float* __restrict__ s_global_p, const uint8_t*
   const int workers = static_cast<int>(gridDim.x) - 1;
   const bool valid = guard_slot[kTagWords] != 0u;  // written by an earlier kernel of this step
   if (static_cast<int>(blockIdx.x) == workers) {
-    finalize_block(fin, valid);
+    finalize_block<kEltThreads>(fin, valid);
     if (kEmit && valid && threadIdx.x == 0) {      // nobody in this launch reads the tag words
       for (int i = 0; i < kTagWords; ++i) guard_slot[i] = next_tag.w[i];
     }
@@ -646,17 +529,7 @@ k_step_bwd_adam(int64_t n8, const float* __restrict__ s_global_p, const uint8_t*
 #pragma unroll
       for (int j = 0; j < 8; ++j) g[j] -= two_alpha_h * hh[j];
     }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t nib = (codes >> (4 * j)) & 15u;
-      const float h = h_beta_fast(v[j], beta);
-      const float d = (xs * g[j]) * (signed_scale(nib, s) * node_width(nib & 7u) * beta * (h * (1.0f - h))) +
-                      lam_over_n * (4.0f - 8.0f * v[j]);
-      m[j] = o.beta1 * m[j] + (1.0f - o.beta1) * d;
-      u[j] = o.beta2 * u[j] + (1.0f - o.beta2) * (d * d);
-      const float step = o.lr * (m[j] * o.inv_bc1) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(u[j] * o.inv_bc2) + o.eps);
-      v[j] = fminf(fmaxf(v[j] - step, 0.0f), 1.0f);  // V clipped to [0, 1] after every update
-    }
+    adam8(g, codes, s, xs, beta, lam_over_n, o, v, m, u);
     store8(V + i * 8, v);
     store8(M + i * 8, m);
     store8(U + i * 8, u);
@@ -1073,14 +946,28 @@ hipError_t launch_step_fwd(const void* W, bool w_bf16, int64_t n, const float* s
   return hipGetLastError();
 }
 
+static LossSums loss_sums(const StepBwdArgs& a) {
+  const int64_t workers = step_bwd_blocks(a.n);
+  return LossSums{a.mse_partials, a.n_mse, a.mse_scale, a.H ? a.cross_partials : nullptr, workers, a.c_norm2, a.x_scale,
+                  a.round_partials, workers, 1.0 / static_cast<double>(a.n),
+                  a.lambda_round, a.losses, a.losses + 1, a.losses + 2};
+}
+static float lambda_over_n(const StepBwdArgs& a) {
+  return static_cast<float>(static_cast<double>(a.lambda_round) / static_cast<double>(a.n));
+}
+
+StepUpdate step_update(const StepBwdArgs& a) {
+  return StepUpdate{a.s_global, a.scales, reinterpret_cast<const uint32_t*>(a.icodes), a.V, a.m, a.u, a.x_scale, a.H, a.two_alpha_h,
+                    a.beta, lambda_over_n(a), a.opt, loss_sums(a), a.W, a.beta_next, a.delta_next, a.wq_full_next, a.round_next,
+                    a.cross_next, static_cast<int>(step_bwd_blocks(a.n)), a.guard_slot, a.next_tag};
+}
+
 hipError_t launch_step_bwd_adam(const StepBwdArgs& a, hipStream_t st) {
   const int64_t n8 = a.n / 8;
   const int64_t workers = step_bwd_blocks(a.n);
   const dim3 g(static_cast<unsigned>(workers + 1)), b(kEltThreads);  // the extra block finishes the losses
-  const float lam_over_n = static_cast<float>(static_cast<double>(a.lambda_round) / static_cast<double>(a.n));
-  const LossSums fin{a.mse_partials, a.n_mse, a.mse_scale, a.H ? a.cross_partials : nullptr, workers, a.c_norm2, a.x_scale,
-                     a.round_partials, workers, 1.0 / static_cast<double>(a.n),
-                     a.lambda_round, a.losses, a.losses + 1, a.losses + 2};
+  const float lam_over_n = lambda_over_n(a);
+  const LossSums fin = loss_sums(a);
   const uint32_t* c32 = reinterpret_cast<const uint32_t*>(a.icodes);
 #define FAAR_SB(WT, E, F) \
   hipLaunchKernelGGL((k_step_bwd_adam<WT, E, F>), g, b, 0, st, n8, a.s_global, a.scales, c32, a.V, a.m, a.u, a.beta, a.G, \

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "faar_internal.h"
+#include "faar_step.h"
 
 namespace faar {
 namespace {
@@ -31,19 +32,22 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // ---- epilogues -----------------------------------------------------------------------------
 
 // fixed-order sum of one float per lane over the workgroup's wavefronts (4 or 8), as a double, to partials[item]
-__device__ __forceinline__ void finish_sum(float sum, double* partials, int item) {
+// (the sum itself comes back in thread 0)
+__device__ __forceinline__ double workgroup_sum(double a) {
   __shared__ double s[8];
-  double a = static_cast<double>(sum);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+  a = wave_sum(a);
   if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = a;
   __syncthreads();
+  double t = 0.0;
   if (threadIdx.x == 0) {
-    double t = 0.0;
     const int nw = blockDim.x >> 6;
     for (int i = 0; i < nw; ++i) t += s[i];
-    partials[item] = t;
   }
+  return t;
+}
+__device__ __forceinline__ void finish_sum(double sum, double* partials, int item) {
+  const double t = workgroup_sum(sum);
+  if (threadIdx.x == 0) partials[item] = t;
 }
 
 // kWithC:  R = x_scale * acc - C;  sum R^2;  dYt[n][m] = bf16(two_alpha R) (zero-padded to ldt); optional dY[m][n].
@@ -210,6 +214,162 @@ struct EpiF32 {
     o[1] = make_float4(r[4], r[5], r[6], r[7]);
   }
   __device__ __forceinline__ void finish(int) {}
+};
+
+struct GramOperands {
+  const bf16_t* delta;     // the A operand, [M, N] row-major: not the buffer that the next step's forward goes to
+  const float* diag_lo;    // [N]
+  double* partials;        // one per work item
+  bool check; ForwardTag expect;
+};
+// The weight gradient, used where it is made: dL/dV, Adam, clip and the next step's forward of the tile's weights straight from the
+// accumulators (a product that is not split).  Bound by HBM: V, m, u, W, H, codes in and V, m, u, the next W_q - W out; the gradient
+// itself, 8 of 42.5 bytes a weight, is neither written nor read, and a launch is saved.  The loads of the next 8 weights a lane takes
+// are on their way while it works on its 8.  The losses of the step, whose partial sums are complete, are added up by workgroup 0.
+// Whole steps, us: 6144x2048 at 8192 tokens, alone 422.8 -> 396.5; 8192x2048 at 4096 346.5 -> 312; 2048x8192 at 4096 in a chain
+// 472 -> 446; 1024x2048 at 512 38.1 -> 34.5; seven linears on three streams 6.92 -> 6.78 ms.
+// kGram: the same for delta * gram (EpiGram), on the buffer of W_q - W that the next step's does not go to.  2048x6144: 241 -> 221 on
+// 256x192 tiles, 6144x2048 144 -> 132, 4096x4096 236 -> 212, 8192x2048 187 -> 164.
+template <typename WT, bool kGram = false>
+struct EpiStep {
+  static constexpr bool kWarm = false;
+  static constexpr bool kRowStaged = false;
+  static constexpr bool kTransposedOut = false;
+  static constexpr int kMode = 0;
+  static constexpr bool kPaddedContraction = !kGram;
+  static constexpr bool kLateFetch = kGram;  // the first fetch after the first strips have left their registers
+  static constexpr bool kChunked = true;     // the main loop hands it runs of 8 columns with what fetch() brought for them
+  StepUpdate p;
+  GramOperands gr;           // kGram: see EpiGramStep
+  float sg, xs;
+  double rsum, cross;   // 96 to 128 weights a lane: their runs of 8 meet in double
+  bool valid;
+  double mse;
+  struct Chunk { float4 v0, v1, m0, m1, u0, u1, h0, h1; uint4 w, a; uint32_t codes, scale; };
+  static constexpr bool kFetchW = sizeof(WT) == 2 && !kGram;   // ahead of their use; there are no registers for the others
+  __device__ __forceinline__ void once() {
+    if (!kGram && blockIdx.x == 0) finish_losses();
+  }
+  __device__ __forceinline__ void begin() {
+    sg = *p.s_global;
+    xs = p.x_scale ? *p.x_scale : 1.0f;
+    if constexpr (kGram) {
+      valid = true;                            // a forward made by this step's own first kernel, or a prepared one under this tag
+      if (gr.check)
+        for (int i = 0; i < kTagWords; ++i) valid = valid && p.guard_slot[i] == gr.expect.w[i];
+    } else {
+      valid = p.guard_slot[kTagWords] != 0u;   // written by an earlier kernel of this step
+    }
+  }
+  __device__ __forceinline__ void finish_losses() {
+    const bool ok = p.guard_slot[kTagWords] != 0u;
+    finalize_block<512>(p.fin, ok);
+    if (p.beta_next > 0.0f && ok && threadIdx.x == 0) {   // nobody in this launch reads the tag words
+      for (int i = 0; i < kTagWords; ++i) p.guard_slot[i] = p.next_tag.w[i];
+    }
+  }
+  __device__ __forceinline__ bool skip() const { return !valid; }
+  // Addresses: one 32-bit offset within the tile for all arrays, on bases that are uniform.  e0: first element of the tile (a multiple
+  // of 16); o: offset of the run's first one (a multiple of 8).  (A pointer each would take the registers of a run.)
+  template <typename P> static __device__ __forceinline__ const P* at(const P* base, int64_t e0, uint32_t bytes) {
+    return reinterpret_cast<const P*>(reinterpret_cast<const char*>(base + e0) + bytes);
+  }
+  __device__ __forceinline__ void fetch(Chunk& c, int64_t e0, uint32_t o) const {
+    c.scale = p.scales[(e0 >> 4) + (o >> 4)];
+    c.codes = p.icodes[(e0 >> 3) + (o >> 3)];
+    const float4* v = reinterpret_cast<const float4*>(at(p.V, e0, 4 * o));
+    const float4* mm = reinterpret_cast<const float4*>(at(p.M, e0, 4 * o));
+    const float4* uu = reinterpret_cast<const float4*>(at(p.U, e0, 4 * o));
+    c.v0 = v[0]; c.v1 = v[1]; c.m0 = mm[0]; c.m1 = mm[1]; c.u0 = uu[0]; c.u1 = uu[1];
+    if (p.H) {
+      const float4* h = reinterpret_cast<const float4*>(at(p.H, e0, 4 * o));
+      c.h0 = h[0]; c.h1 = h[1];
+    }
+    if (kGram) c.a = *reinterpret_cast<const uint4*>(at(gr.delta, e0, 2 * o));
+    if (kFetchW && p.beta_next > 0.0f) c.w = *reinterpret_cast<const uint4*>(at(static_cast<const WT*>(p.W), e0, 2 * o));
+  }
+  __device__ __forceinline__ void run8(const float (&r)[8], const Chunk& c, int64_t e0, uint32_t o, int64_t n) {
+    float g[8], hh[8] = {c.h0.x, c.h0.y, c.h0.z, c.h0.w, c.h1.x, c.h1.y, c.h1.z, c.h1.w};
+    float v[8] = {c.v0.x, c.v0.y, c.v0.z, c.v0.w, c.v1.x, c.v1.y, c.v1.z, c.v1.w};
+    float mm[8] = {c.m0.x, c.m0.y, c.m0.z, c.m0.w, c.m1.x, c.m1.y, c.m1.z, c.m1.w};
+    float uu[8] = {c.u0.x, c.u0.y, c.u0.z, c.u0.w, c.u1.x, c.u1.y, c.u1.z, c.u1.w};
+    if constexpr (kGram) {
+      const float4 l0 = *reinterpret_cast<const float4*>(gr.diag_lo + n), l1 = *reinterpret_cast<const float4*>(gr.diag_lo + n + 4);
+      const float lo[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
+      const uint32_t dw[4] = {c.a.x, c.a.y, c.a.z, c.a.w};
+      const float k_out = p.two_alpha_h * xs, k_sum = xs * xs;
+      float sum = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float a = __uint_as_float((j & 1) ? (dw[j >> 1] & 0xFFFF0000u) : (dw[j >> 1] << 16));
+        const float t = r[j] + a * lo[j];
+        sum += k_sum * (t * a);
+        g[j] = k_out * t - p.two_alpha_h * hh[j];
+      }
+      mse += sum;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) g[j] = p.H ? r[j] - p.two_alpha_h * hh[j] : r[j];
+    }
+    const float s = effective_scale(c.scale, sg);
+    adam8(g, c.codes, s, xs, p.beta, p.lam_over_n, p.o, v, mm, uu);
+    store8(const_cast<float*>(at(p.V, e0, 4 * o)), v);
+    store8(const_cast<float*>(at(p.M, e0, 4 * o)), mm);
+    store8(const_cast<float*>(at(p.U, e0, 4 * o)), uu);
+    if (p.beta_next > 0.0f) {
+      float w[8];
+      if constexpr (kFetchW) {
+        const uint32_t q[4] = {c.w.x, c.w.y, c.w.z, c.w.w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = __uint_as_float((j & 1) ? (q[j >> 1] & 0xFFFF0000u) : (q[j >> 1] << 16));
+      } else {
+        W8<WT>::load(at(static_cast<const WT*>(p.W), e0, sizeof(WT) * o), w);
+      }
+      float x = 0.0f;
+      rsum += soft_forward8(w, c.codes, s, v, p.beta_next, const_cast<bf16_t*>(at(p.delta, e0, 2 * o)),
+                            p.wq_full ? const_cast<bf16_t*>(at(p.wq_full, e0, 2 * o)) : nullptr, p.H != nullptr, hh, x);
+      cross += x;
+    }
+  }
+  // the partial sums of the next step's forward, one per work item, and zeros in the slots that no work item has
+  __device__ __forceinline__ void finish(int item, int items) {
+    if (p.beta_next > 0.0f && valid) next_sums(item, items);
+    if constexpr (kGram) finish_gram(item, items);
+  }
+  // The loss needs this launch's own sums: the workgroup that arrives last adds them up.  What it reads of the others are the partial
+  // sums alone, stored past the L2 of the writer's die and read past the reader's (no write-back of a whole L2, which is what a
+  // release at device scope costs); the tag, which every workgroup has read by then, is cleared or replaced by it as well.
+  __device__ __forceinline__ void finish_gram(int item, int items) {
+    __shared__ uint32_t last;
+    if (!valid && item == 0) finalize_block<512>(p.fin, false);      // also where the counter is not a count
+    __syncthreads();
+    const double t = workgroup_sum(mse);
+    if (threadIdx.x == 0) {
+      uint32_t* counter = p.guard_slot + kArrivals;
+      __hip_atomic_store(gr.partials + item, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // the sum is where the others see it before the count says so
+      last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == static_cast<uint32_t>(items) - 1u;
+    }
+    __syncthreads();
+    if (!last) return;
+    if (valid) finalize_block<512, true>(p.fin);
+    if (threadIdx.x == 0) {
+      for (int i = 0; i < kTagWords; ++i) p.guard_slot[i] = p.beta_next > 0.0f && valid ? p.next_tag.w[i] : 0u;
+      p.guard_slot[kArrivals] = 0u;
+    }
+  }
+  __device__ __forceinline__ void next_sums(int item, int items) {
+    finish_sum(rsum, p.round_next, item);
+    __syncthreads();
+    if (p.H) {
+      finish_sum(cross, p.cross_next, item);
+      __syncthreads();
+    }
+    for (int k = item + items * (1 + static_cast<int>(threadIdx.x)); k < p.n_next; k += items * static_cast<int>(blockDim.x)) {
+      p.round_next[k] = 0.0;
+      if (p.H) p.cross_next[k] = 0.0;
+    }
+  }
 };
 
 // As EpiF32, for an A operand that is the sum of kTerms bf16 matrices side by side ([M, kTerms * Kd]): every work item walks its
@@ -512,6 +672,9 @@ __device__ __forceinline__ int token_key(int t) {
 template <class E, class = void> struct StagedInput { static constexpr bool value = false; };
 template <class E> struct StagedInput<E, std::void_t<decltype(E::kStagedInput)>> { static constexpr bool value = E::kStagedInput; };
 
+template <class E, class = void> struct Chunked { static constexpr bool value = false; };
+template <class E> struct Chunked<E, std::void_t<decltype(E::kChunked)>> { static constexpr bool value = E::kChunked; };
+
 template <class C, int TMW, class Epi>
 __device__ __forceinline__ void epilogue(Epi& epi, f32x4 (&acc)[TMW][C::TN], bf16_t* lds, int64_t m0, int64_t n0, int wm, int wn,
                                          int split, const GemmDims& d, int tid, int lane, int wave, int wc) {
@@ -594,6 +757,67 @@ __device__ __forceinline__ void epilogue(Epi& epi, f32x4 (&acc)[TMW][C::TN], bf1
         const uint2 lo = src[0], hi = src[1];
         epi.store_chunk(make_uint4(lo.x, lo.y, hi.x, hi.y), m0 + ch * 8, n0 + (row / 32) * C::WN + jj * 32 + (row % 32), d);
       }
+    }
+  } else if constexpr (Chunked<Epi>::value) {
+    // strips of 16 rows of the wavefront's accumulator tiles, two or, where the ring has room, four at a time, through its own piece of
+    // LDS, as above, and out again in runs of 8 columns of a row; the epilogue's own operands of a run are fetched while the run before
+    // it is worked on (which takes the registers of the accumulators that have left).  Four strips of 64 columns fill the ring without
+    // padding: their 16-column groups are XOR-permuted by the row group instead.
+    constexpr bool kFour = Epi::kLateFetch && C::WN == 64 && TMW % 4 == 0 && C::NW * 64 * 64 * 4 <= C::NS * C::STAGE * 2;
+    constexpr int STRIPS = kFour ? 4 : 2, PITCH = kFour ? 64 : C::WN + 4, CPR = C::WN / 8, RUNS = 16 * STRIPS * CPR / 64;
+    constexpr int STAGES = TMW / STRIPS;
+    static_assert(TMW % STRIPS == 0 && RUNS % 2 == 0 && C::NW * 16 * STRIPS * PITCH * 4 <= C::NS * C::STAGE * 2, "staging fits in the ring");
+    if (epi.skip()) return;
+    float* stg = reinterpret_cast<float*>(lds) + wave * 16 * STRIPS * PITCH;
+    typename Epi::Chunk ck[2];
+    const int64_t e0 = m0 * d.N + n0;
+    const int mrows = static_cast<int>(d.M - m0 < C::BM ? d.M - m0 : C::BM), ncols = static_cast<int>(d.N - n0 < C::BN ? d.N - n0 : C::BN);
+    auto place = [&](int g, int& m, int& n) {
+      int idx = lane + 64 * g;
+      asm volatile("" : "+v"(idx));                  // nothing of the addresses is kept from run to run
+      m = wm + idx / CPR;
+      n = wn + (idx % CPR) * 8;
+      return m < mrows && n < ncols;
+    };
+    auto fetch = [&](typename Epi::Chunk& c, int g) {
+      int m, n;
+      if (place(g, m, n)) epi.fetch(c, e0, static_cast<uint32_t>(m) * static_cast<uint32_t>(d.N) + n);
+    };
+    auto work = [&](const typename Epi::Chunk& c, int st, int t) {
+      const int idx = lane + 64 * t, row = idx / CPR, cg = idx % CPR;
+      const float* src = stg + row * PITCH + (kFour ? (cg * 8) ^ (((row >> 2) & 3) * 16) : cg * 8);
+      const float4 a = *reinterpret_cast<const float4*>(src);
+      const float4 b = *reinterpret_cast<const float4*>(src + 4);
+      const float r[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+      int m, n;
+      if (place(st * RUNS + t, m, n)) epi.run8(r, c, e0, static_cast<uint32_t>(m) * static_cast<uint32_t>(d.N) + n, n0 + n);
+    };
+    if (!Epi::kLateFetch) fetch(ck[0], 0);
+    __syncthreads();                                 // nobody reads the ring any more
+#pragma unroll
+    for (int st = 0; st < STAGES; ++st) {
+#pragma unroll
+      for (int h = 0; h < STRIPS; ++h)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            stg[(16 * h + 4 * rq + v) * PITCH + (kFour ? (j * 16) ^ (rq * 16) : j * 16) + col] = acc[STRIPS * st + h][j][v];
+      if (Epi::kLateFetch && st == 0) fetch(ck[0], 0);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 1
+      for (int t = 0; t < RUNS; t += 2) {
+        const int g = st * RUNS + t;
+        fetch(ck[1], g + 1);
+        work(ck[0], st, t);
+        if (g + 2 < STAGES * RUNS) fetch(ck[0], g + 2);
+        work(ck[1], st, t + 1);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
   } else if constexpr (Epi::kRowStaged) {
     // every wavefront stages one 16 x WN row of its accumulator tiles at a time through its own piece of LDS and hands the
@@ -957,7 +1181,8 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
   } else {
     epilogue<C, TM>(epi, acc, lds, m0, n0, wm, wn, split, d, tid, lane, wave, wxy % C::WGN);
   }
-  epi.finish(item);
+  if constexpr (Chunked<Epi>::value) epi.finish(item, tiles_m * tiles_n * n_split);
+  else epi.finish(item);
 }
 
 typedef Dma64Cfg<256, 256, 2, 4, 2> CfgL64;  // 2 x 64 KB
@@ -973,6 +1198,8 @@ typedef Dma64Cfg<256, 256, 2, 4, 2, kTN> CfgT64;  // CfgL64 on token-major opera
 // idle -- but 32 x 8 = 256 tiles of 192 x 256
 typedef Dma64Cfg<192, 256, 2, 4, 2, kTN> CfgT64A;
 typedef Dma64Cfg<256, 192, 4, 2, 2, kTN> CfgT64B;
+typedef Dma64Cfg<192, 256, 2, 4, 2> CfgL64A;   // the same on NT operands, for the Gram-form product that ends in the pass over V
+typedef Dma64Cfg<256, 192, 4, 2, 2> CfgL64B;
 
 inline int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 
@@ -1129,6 +1356,96 @@ hipError_t launch_gemm_f32_terms(const bf16_t* A, const bf16_t* B, GemmDims d, f
   return run(A, B, d, p, EpiF32Terms{{out}}, st);
 }
 
+template <class C, class Epi>
+static hipError_t run_tn(const bf16_t* A, const bf16_t* B, const GemmDims& d, int n_split, Epi epi, hipStream_t st) {
+  const int tiles_m = ceil_div(d.M, C::BM), tiles_n = ceil_div(d.N, C::BN);
+  const int ksteps = static_cast<int>(d.Kd / DBK64);
+  const int per_split = (ksteps + n_split - 1) / n_split;
+  const int64_t items = (int64_t)tiles_m * tiles_n * n_split;
+  const dim3 grid(static_cast<unsigned>((items + 7) / 8 * 8));
+  hipLaunchKernelGGL((k_gemm_dma64<C, false, Epi>), grid, dim3(C::THREADS), 0, st, A, B, d, tiles_m, tiles_n, n_split, per_split, epi);
+  return hipGetLastError();
+}
+
+// 1 256 x 256, 2 192 x 256, 3 256 x 192: whichever needs the fewest rounds of the 256 compute units, weighted by the tile's area
+static int fewest_rounds(int64_t M, int64_t N, int n_split) {
+  const int64_t cus = 256;
+  auto rounds_area = [&](int64_t bm, int64_t bn) {
+    const int64_t items = (int64_t)ceil_div(M, bm) * ceil_div(N, bn) * n_split;
+    return (items + cus - 1) / cus * bm * bn;
+  };
+  const int64_t c1 = rounds_area(256, 256), c2 = rounds_area(192, 256), c3 = rounds_area(256, 192);
+  if (c2 < c1 && c2 <= c3) return 2;
+  if (c3 < c1) return 3;
+  return 1;
+}
+
+// The dW product updates V in its epilogue, token-major (tn) or on transposed operands, where it is not split -- and not by a few
+// workgroups, whose 8192 weights each then take longer than a kernel over all of them (512x512 at 512 tokens, 32 work items: 21.5 us a
+// step, 23.2 this way; 400x1024 at 300, 64: 23.1 / 23.7; 1280x1280 at 320, 200: 32.6 / 29.8; 1024x1024 at 64, 128: 24.8 / 23.2).
+constexpr int64_t kUpdateMinItems = 96;
+// The Gram form's loss waits for the last of its workgroups, about 4 us, which smaller layers do not get back (768x768 17.1 -> 20.5
+// us, 1000x1488 27.7 -> 30.7, 1024x2048 32.7 -> 33.0; 2048x2048 49.1 -> 48.2).
+constexpr int64_t kGramUpdateMin = (int64_t)1 << 22;
+constexpr int64_t kUpdateMaxColumns = 1 << 21;   // 256 rows of them, 4 bytes each, are 32-bit offsets
+bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp) {
+  const Plan p = plan_gemm(GemmDims{O, K, Tp, Tp, Tp}, true, kEpiF32);
+  return p.n_split == 1 && p.items() >= kUpdateMinItems && p.items() <= step_bwd_blocks(O * K) && K <= kUpdateMaxColumns;
+}
+
+template <typename WT>
+static hipError_t run_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bool tn, bool fill_device, const StepBwdArgs& a, hipStream_t st) {
+  const EpiStep<WT> e{step_update(a), GramOperands{}, 0.0f, 1.0f, 0.0, 0.0, true, 0.0};
+  if (!tn) return run(A, B, d, plan_gemm(d, true, kEpiF32), e, st);
+  const int tiles = gemm_tn_tiles(d.M, d.N, d.Kd, fill_device);
+  if (tiles == 2) return run_tn<CfgT64A>(A, B, d, 1, e, st);
+  if (tiles == 3) return run_tn<CfgT64B>(A, B, d, 1, e, st);
+  if (tiles == 1) return run_tn<CfgT64>(A, B, d, 1, e, st);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bool tn, bool fill_device, const StepBwdArgs& a,
+                                 hipStream_t st) {
+  if (!gemm_dw_updates(d.M, d.N, d.Kd) || d.lda % 8 != 0 || d.ldb % 8 != 0) return hipErrorInvalidValue;
+  return a.w_bf16 ? run_dw_update<bf16_t>(A, B, d, tn, fill_device, a, st) : run_dw_update<float>(A, B, d, tn, fill_device, a, st);
+}
+
+bool gemm_gram_updates(int64_t O, int64_t K) {
+  const Plan p = plan_gemm(GemmDims{O, K, K, K, K}, true, kEpiGram);
+  return p.n_split == 1 && O * K >= kGramUpdateMin && K <= kUpdateMaxColumns && 2 * p.items() <= step_bwd_blocks(O * K);
+}
+
+template <typename WT>
+static hipError_t run_gram_update(const bf16_t* delta, const bf16_t* gram, const GemmDims& d, const GramOperands& g, StepBwdArgs a,
+                                  hipStream_t st) {
+  const Plan p = plan_gemm(d, true, kEpiGram);
+  // 192-wide tiles where these need fewer rounds of the compute units, weighted by the tile's area, as in gemm_tn_tiles.  Alone they
+  // are worth 20 of 241 us on 2048x6144; beside other streams 256x256 tiles would be faster (seven Gram-form jobs on three streams:
+  // 12.0 k steps/s on those, 11.0 k this way, 11.0 k with the pass over V on its own)
+  const int tiles = p.kind != KIND_L64 ? 1 : fewest_rounds(d.M, d.N, 1);
+  const int tm = tiles == 2 ? ceil_div(d.M, 192) : p.tiles_m, tn = tiles == 3 ? ceil_div(d.N, 192) : p.tiles_n;
+  a.n_mse = (int64_t)tm * tn;
+  const EpiStep<WT, true> e{step_update(a), g, 0.0f, 1.0f, 0.0, 0.0, true, 0.0};
+  if (tiles == 1) return run(delta, gram, d, p, e, st);
+  const int ksteps = static_cast<int>((d.Kd + DBK64 - 1) / DBK64);
+  const dim3 grid(static_cast<unsigned>((a.n_mse + 7) / 8 * 8));
+#define FAAR_LAUNCH(CFG, TAIL) \
+  hipLaunchKernelGGL((k_gemm_dma64<CFG, TAIL, EpiStep<WT, true>>), grid, dim3(CFG::THREADS), 0, st, delta, gram, d, tm, tn, 1, ksteps, e)
+  if (d.Kd % DBK64 == 0) { if (tiles == 2) FAAR_LAUNCH(CfgL64A, false); else FAAR_LAUNCH(CfgL64B, false); }
+  else                   { if (tiles == 2) FAAR_LAUNCH(CfgL64A, true);  else FAAR_LAUNCH(CfgL64B, true); }
+#undef FAAR_LAUNCH
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_gram_update(const bf16_t* delta, const bf16_t* gram, int64_t O, int64_t K, const float* diag_lo, double* partials,
+                                   const ForwardGuard& guard, StepBwdArgs a, hipStream_t st) {
+  if (!gemm_gram_updates(O, K)) return hipErrorInvalidValue;
+  const GemmDims d{O, K, K, K, K};
+  a.mse_partials = partials;
+  const GramOperands g{delta, diag_lo, partials, guard.slot != nullptr, guard.expect};
+  return a.w_bf16 ? run_gram_update<bf16_t>(delta, gram, d, g, a, st) : run_gram_update<float>(delta, gram, d, g, a, st);
+}
+
 int choose_split_gram(int64_t O, int64_t K) { return plan_gemm(GemmDims{O, K, K, K, K}, true, kEpiGram).n_split; }
 int64_t gemm_gram_partials(int64_t O, int64_t K) { return plan_gemm(GemmDims{O, K, K, K, K}, true, kEpiGram).items(); }
 
@@ -1153,28 +1470,9 @@ int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device) {
   const Plan p = plan_gemm(GemmDims{M, N, T, T, T}, true, kEpiF32);
   if (p.kind != KIND_L64) return 0;
   if (!fill_device) return 1;
-  const int64_t cus = 256;
-  auto rounds_area = [&](int64_t bm, int64_t bn) {
-    const int64_t items = (int64_t)ceil_div(M, bm) * ceil_div(N, bn) * p.n_split;
-    return (items + cus - 1) / cus * bm * bn;
-  };
-  const int64_t c1 = rounds_area(256, 256), c2 = rounds_area(192, 256), c3 = rounds_area(256, 192);
-  if (c2 < c1 && c2 <= c3) return 2;
-  if (c3 < c1) return 3;
-  return 1;
+  return fewest_rounds(M, N, p.n_split);
 }
 bool gemm_tn_usable(int64_t M, int64_t N, int64_t T) { return gemm_tn_tiles(M, N, T, false) != 0; }
-
-template <class C, class Epi>
-static hipError_t run_tn(const bf16_t* A, const bf16_t* B, const GemmDims& d, int n_split, Epi epi, hipStream_t st) {
-  const int tiles_m = ceil_div(d.M, C::BM), tiles_n = ceil_div(d.N, C::BN);
-  const int ksteps = static_cast<int>(d.Kd / DBK64);
-  const int per_split = (ksteps + n_split - 1) / n_split;
-  const int64_t items = (int64_t)tiles_m * tiles_n * n_split;
-  const dim3 grid(static_cast<unsigned>((items + 7) / 8 * 8));
-  hipLaunchKernelGGL((k_gemm_dma64<C, false, Epi>), grid, dim3(C::THREADS), 0, st, A, B, d, tiles_m, tiles_n, n_split, per_split, epi);
-  return hipGetLastError();
-}
 
 hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split, bool fill_device,
                               hipStream_t st) {

@@ -22,6 +22,7 @@ inline int64_t padded_tokens(int64_t T) { return round_up(T, 64); }
 // implies (verdict = equal), and in both cases clears the tag; the kernel that updates V reads the verdict, and
 // writes the tag of the next step's forward when it produces one.
 constexpr int kTagWords = 12;
+constexpr int kArrivals = kTagWords + 1;   // word of the slot in which a launch counts the workgroups that are done; 0 between launches
 struct ForwardTag { uint32_t w[kTagWords]; };
 struct ForwardGuard { uint32_t* slot; ForwardTag expect; };  // slot == nullptr: nothing to check
 // Done by one thread of a launch (workgroup 0 of a step's product, before anything else): is the forward in the workspace the one
@@ -216,6 +217,15 @@ bool gemm_tn_usable(int64_t M, int64_t N, int64_t T);
 int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device);
 hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split, bool fill_device,
                               hipStream_t st);
+// The dW product of a step that ends in the pass over V (StepBwdArgs; its G, n_split and split_stride are not used): where the plan
+// does not split it.  A, B as for launch_gemm_f32_tn (tn) or launch_gemm_f32
+bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp);
+hipError_t launch_gemm_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bool tn, bool fill_device, const StepBwdArgs& a,
+                                 hipStream_t st);
+// The same for the Gram form's product (a.delta_next must not be delta); partials: one double per work item
+bool gemm_gram_updates(int64_t O, int64_t K);
+hipError_t launch_gemm_gram_update(const bf16_t* delta, const bf16_t* gram, int64_t O, int64_t K, const float* diag_lo, double* partials,
+                                   const ForwardGuard& guard, StepBwdArgs a, hipStream_t st);
 // The kernel variant, tile shape and contraction split the launchers above pick for an M x N x Kd product
 // (kind: 0 / 1 / 2 / 3 for 256x256 / 256x128 / 128x128 / 128x64 tiles).  Pure host function.
 enum { kGemmEpiResidual = 0, kGemmEpiF32 = 1, kGemmEpiSub = 2, kGemmEpiBf16 = 3, kGemmEpiNone = 4, kGemmEpiGram = 5, kGemmEpiLoss = 6 };

@@ -1,0 +1,117 @@
+"""Products that end in the pass over V (dW where the plan does not split it, the Gram form's on large layers): every tile shape with both
+weight types against float64 products on the device, and steps chained through the forward that they leave against steps that make
+their own."""
+import pytest
+import torch
+
+import paper_2603_22370_amd as faar
+from paper_2603_22370_amd import binding as fb
+from test_gpu_variants import ADAM, BETA, LAMBDA, _bf16, _check_gradient, _mm
+
+pytestmark = pytest.mark.gpu
+
+# (O, K, T, alone on the device): N64, S64, M64, L64 on transposed operands, the three token-major tiles; ragged edges in both directions
+DW = [(1056, 656, 64, False), (648, 2816, 64, False), (648, 5408, 64, False), (7176, 1088, 65, False), (7176, 1088, 64, False),
+      (7176, 1088, 64, True), (6224, 1808, 64, True)]
+# M64, S64, then L64: 256x256, 192x256, 256x192; contractions that end inside a slice and that do not
+GRAM = [(6496, 656), (3912, 1088), (6496, 1232), (6496, 1808), (7176, 1664), (7176, 1088), (6632, 1232), (7040, 1664), (8128, 1376)]
+
+
+def _layer(O, K, T, dtype):
+    gen = torch.Generator(device="cuda").manual_seed(O * 31 + K * 7 + T)
+    W = (0.02 * torch.randn((O, K), generator=gen, device="cuda")).to(dtype)
+    X = torch.randn((T, K), generator=gen, device="cuda").to(torch.bfloat16)
+    Y = (X.float() @ W.float().T + 0.05 * torch.randn((T, O), generator=gen, device="cuda")).to(torch.bfloat16)
+    sg, scales, _, _ = faar.faar_quant_rtn(W)
+    V = 0.05 + 0.9 * torch.rand((O, K), generator=gen, device="cuda")
+    return W, X, Y, sg, scales, V, gen
+
+
+def _steps(step, V0, prepared, betas=(BETA, 13.0, 14.5)):
+    """Three steps, each on a forward of its own or on the one the step before left; t from 2, so that both turns of the Gram form's
+    buffers come first."""
+    V, m, u = V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)
+    out = []
+    for i, beta in enumerate(betas):
+        losses = torch.zeros(3, dtype=torch.float32, device="cuda")
+        nxt = betas[i + 1] if prepared and i + 1 < len(betas) else 0.0
+        extra = step(V, m, u, beta, 2 + i, losses, nxt, prepared and i > 0)
+        out += [losses, *(x.clone() for x in extra)]
+    return [V, m, u, *out]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("O,K,T,alone", DW)
+def test_weight_gradient_that_updates_v(O, K, T, alone, dtype):
+    assert fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)[3] == 1
+    W, X, Y, sg, scales, V0, gen = _layer(O, K, T, dtype)
+    Xt, C, icodes, H, c_norm2 = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
+    alpha = 1.0 / (T * O)
+    dY = (1e-3 * torch.randn((T, O), generator=gen, device="cuda")).to(torch.bfloat16)
+
+    def step(chained, ws, V, m, u, beta, t, losses, nxt, ready):
+        dX = torch.empty((T, K), dtype=torch.bfloat16, device="cuda") if chained else None
+        faar.faar_layer_step(W, sg, scales, V, m, u, X, Xt, C, icodes, beta, LAMBDA, alpha, *ADAM, t, losses, ws,
+                             dY_ext=dY if chained else None, dX=dX, beta_next=nxt, forward_ready=ready, H=H, c_norm2=c_norm2,
+                             whole_device=alone)
+        return [dX] if chained else []
+
+    for chained in (False, True):
+        ws = faar.layer_step_workspace(O, K, T, chained=chained)
+        V, m, u = V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)
+        step(chained, ws, V, m, u, BETA, 1, torch.zeros(3, device="cuda"), 0.0, False)
+        if chained:
+            G = _mm(dY.double().T, X.double())
+        else:
+            delta = faar.faar_softquant_fwd_bwd(W, sg, scales, V0, BETA, emit_delta=True)[0].double()
+            G = _mm(_bf16(2.0 * alpha * _mm(X.double(), delta.T)).T, X.double()) - 2.0 * alpha * H.view(O, K).double()
+        _check_gradient(m, G, W, sg, scales, V0)
+        runs = [_steps(lambda *a: step(chained, ws, *a), V0, prepared) for prepared in (False, True)]
+        for k, (a, b) in enumerate(zip(*runs)):
+            if a.dtype == torch.float32 and a.numel() == 3:      # the same terms, added up in other groups
+                assert torch.allclose(a, b, rtol=2e-7, atol=0.0), (k, a, b)
+            else:
+                assert torch.equal(a, b), k
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("O,K", GRAM)
+def test_gram_product_that_updates_v(O, K, dtype):
+    T = 192
+    assert O * K >= 1 << 22 and fb.faar_gemm_plan(fb.K_GEMM_GRAM, O, K, 1)[3] == 1
+    W, X, Y, sg, scales, V0, _ = _layer(O, K, T, dtype)
+    Xt, C, icodes, H, c_norm2 = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
+    gram, gram_lo = fb.faar_gram_prepare(Xt, T)
+    alpha = 1.0 / (T * O)
+    ws = fb.layer_step_gram_workspace(O, K)
+    ws.fill_(0xA5)
+
+    def step(V, m, u, beta, t, losses, nxt, ready):
+        fb.faar_layer_step_gram(W, sg, scales, V, m, u, icodes, H, c_norm2, gram, gram_lo, beta, LAMBDA, alpha, *ADAM, t, losses, ws,
+                                beta_next=nxt, forward_ready=ready)
+        return []
+
+    V, m, u = V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)
+    losses = torch.zeros(3, dtype=torch.float32, device="cuda")
+    step(V, m, u, BETA, 1, losses, 0.0, False)
+    delta = faar.faar_softquant_fwd_bwd(W, sg, scales, V0, BETA, emit_delta=True)[0].double()
+    h = H.view(O, K).double()
+    dG = _mm(delta, gram.view(K, K).double() + torch.diag(gram_lo.double()))
+    want = alpha * float((dG * delta).sum() - 2.0 * (delta * h).sum() + c_norm2.double())
+    assert float(losses[0]) == pytest.approx(want, rel=2e-5)
+    _check_gradient(m, 2.0 * alpha * (dG - h), W, sg, scales, V0)
+    runs = [_steps(step, V0, prepared) for prepared in (False, True)]
+    for k, (a, b) in enumerate(zip(*runs)):
+        if a.numel() == 3:
+            assert torch.allclose(a, b, rtol=2e-7, atol=0.0), (k, a, b)
+        else:
+            assert torch.equal(a, b), k
+    # a step told of a forward that is another step's: NaN losses, nothing touched, and no forward is left for anyone
+    state = [V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)]
+    first = torch.zeros(3, dtype=torch.float32, device="cuda")
+    step(*state, BETA, 5, first, 13.0, False)
+    snap = [x.clone() for x in state]
+    for t in (7, 6):
+        bad = torch.zeros(3, dtype=torch.float32, device="cuda")
+        step(*state, 13.0, t, bad, 0.0, True)
+        assert bool(torch.isnan(bad).all()) and all(torch.equal(x, y) for x, y in zip(state, snap))
