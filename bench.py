@@ -444,7 +444,7 @@ def run_layer(args) -> dict:
                               "flipped_decisions": int(j.state["flips"].item()), "hardened_loss": {"rtn": rtn, "faar": opt},
                               "kernels": table}
     # the kernel that takes the largest share of a step of the whole layer
-    dom_l, dom_k = max(((l, k) for l in per_linear for k in (("gemm_gram", "bwd_adam") if gram else ("gemm_residual", "gemm_dw", "bwd_adam")) if k in per_linear[l]),
+    dom_l, dom_k = max(((l, k) for l in per_linear for k in (("gemm_gram", "bwd_adam") if gram else ("gemm_residual", "gemm_dw", "bwd_adam")) if k in per_linear[l]["kernels"]),
                        key=lambda lk: per_linear[lk[0]]["kernels"][lk[1]]["ms"])
     dom = per_linear[dom_l]["kernels"][dom_k]
     ms_per_step = elapsed / args.steps * 1e3

@@ -233,7 +233,8 @@ int64_t faar_padded_tokens(int64_t T) { return T > 0 ? padded_tokens(T) : 0; }
 
 int faar_dw_token_major(int64_t O, int64_t K, int64_t T, uint32_t flags) {
   if (check_shape(O, K) != FAAR_OK || T <= 0) return 0;
-  return gemm_tn_tiles(O, K, T, (flags & FAAR_STEP_WHOLE_DEVICE) != 0);
+  const int n_split = gemm_dw_updates(O, K, padded_tokens(T), false) ? 1 : choose_split(O, K, padded_tokens(T));
+  return gemm_tn_tiles(O, K, T, (flags & FAAR_STEP_WHOLE_DEVICE) != 0, n_split);
 }
 
 int faar_gemm_probe(int mode, int64_t M, int64_t N, int64_t Kd, const void* A, const void* B,
@@ -569,7 +570,17 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
   // The constant part of the gradient is carried separately when the caller provides it -- unless dX has to come
   // from the locally derived dY, which then must contain the constant
   const float* Hs = (H && !(dX && !dY_ext)) ? H : nullptr;
+  // A dW product that is not split ends in the pass over V, and so comes before dX where the next step's W_q may not overwrite this
+  // one's: the two take turns between W_q's place and that of the gradient, which does not exist then
+  const bool in_dw = gemm_dw_updates(O, K, L.Tp, dX && !joint);
   bf16_t* wq_full = chained && dX ? reinterpret_cast<bf16_t*>(base + L.wq_full) : nullptr;
+  bf16_t* wq_next = wq_full;
+  if (in_dw && wq_full) (opt->t & 1 ? wq_full : wq_next) = reinterpret_cast<bf16_t*>(G);
+  auto tag = [&](int32_t t, float b) {
+    ForwardTag g = forward_tag(t, b, V, W, scales, n, wq_full != nullptr, Hs);
+    if (in_dw && wq_full) g.w[11] |= 4u;
+    return g;
+  };
   bf16_t* dY = chained ? reinterpret_cast<bf16_t*>(base + L.dY) : nullptr;
   const bf16_t* xq = static_cast<const bf16_t*>(Xq);
 
@@ -584,7 +595,7 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
       return e;
   } else {
     guard.slot = guard_slot;
-    guard.expect = forward_tag(opt->t, beta, V, W, scales, n, wq_full != nullptr, Hs);
+    guard.expect = tag(opt->t, beta);
   }
   // s2: residual GEMM + loss + dY -- not in a joint step, whose loss is computed downstream of the layer; there the
   // activations change from step to step, so their transpose for the dW GEMM is refreshed here
@@ -641,47 +652,38 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
   a.opt.inv_bc1 = static_cast<float>(1.0 / (1.0 - std::pow((double)opt->beta1, (double)opt->t)));
   a.opt.inv_bc2 = static_cast<float>(1.0 / (1.0 - std::pow((double)opt->beta2, (double)opt->t)));
   a.mse_partials = mse_p; a.n_mse = n_mse; a.mse_scale = mse_scale; a.round_partials = round_p; a.losses = losses;
-  a.beta_next = beta_next; a.delta_next = delta; a.wq_full_next = wq_full; a.round_next = round_next;
+  a.beta_next = beta_next; a.delta_next = delta; a.wq_full_next = wq_next; a.round_next = round_next;
   a.guard_slot = guard_slot;
-  a.next_tag = forward_tag(opt->t + 1, beta_next, V, W, scales, n, wq_full != nullptr, Hs);
+  a.next_tag = tag(opt->t + 1, beta_next);
   a.H = Hs; a.two_alpha_h = (Hs && !dY_ext) ? 2.0f * mse_scale : 0.0f;
   a.cross_partials = cross_p; a.c_norm2 = c_norm2; a.cross_next = cross_next;
 
-  const bool tn = token_major || rows_form;
-  const bool transposed = dX && transposed_dx(O, K, T);
-  // A dW product that is not split ends in the pass over V.  It then overwrites W_q when the next step's is wanted too, so dX comes
-  // first there -- unless dX wants the transposed copy of W_q, which lies in the place of dY^T, and dW that dY^T
-  const bool dx_first = dX && beta_next > 0.0f;
-  const bool in_dw = gemm_dw_updates(O, K, L.Tp) && !(dx_first && transposed && !tn);
-  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of dY^T, which no dW GEMM
-  // after it reads
-  auto input_gradient = [&]() -> int {
-    const int64_t Op = round_up(O, 64);
-    if (transposed)
-      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dYt, Op, st))) return e;
-    Bracket b(FAAR_K_GEMM_DX, st);
-    return hip_status(transposed ? launch_gemm_bf16(dY_used, dYt, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
-                                 : launch_gemm_bf16_nn(dY_used, wq_full, GemmDims{T, K, O, O, K}, static_cast<bf16_t*>(dX), st));
-  };
-  if (in_dw && dx_first)
-    if (int e = input_gradient()) return e;
   // s3: G = dY^T X_q, contraction over tokens, split for occupancy
-  const bf16_t* dw_a = tn ? (rows_form ? dYt : dY_used) : dYt;
+  const bool tn = token_major || rows_form;
+  const bf16_t* dw_a = tn && !rows_form ? dY_used : dYt;
   const bf16_t* dw_b = tn ? xq : static_cast<const bf16_t*>(Xt);
   const GemmDims d2 = tn ? GemmDims{O, K, T, O, K} : GemmDims{O, K, L.Tp, L.Tp, L.Tp};
   const bool whole = (flags & FAAR_STEP_WHOLE_DEVICE) != 0;
-  if (in_dw) {
+  {
     Bracket b(FAAR_K_GEMM_DW, st);
-    Bracket b2(FAAR_K_BWD_ADAM, st);
-    if (int e = hip_status(launch_gemm_dw_update(dw_a, dw_b, d2, tn, whole, a, st))) return e;
-  } else {
-    Bracket b(FAAR_K_GEMM_DW, st);
-    if (int e = hip_status(tn ? launch_gemm_f32_tn(dw_a, dw_b, d2, G, L.n_split, whole, st)
-                              : launch_gemm_f32(dw_a, dw_b, d2, G, L.n_split, st)))
+    Bracket b2(in_dw ? FAAR_K_BWD_ADAM : -1, st);
+    if (int e = hip_status(in_dw ? launch_gemm_dw_update(dw_a, dw_b, d2, tn, whole, a, st)
+                           : tn  ? launch_gemm_f32_tn(dw_a, dw_b, d2, G, L.n_split, whole, st)
+                                 : launch_gemm_f32(dw_a, dw_b, d2, G, L.n_split, st)))
       return e;
   }
-  if (dX && !(in_dw && dx_first))
-    if (int e = input_gradient()) return e;
+  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of dY^T, which nothing
+  // reads after the dW GEMM
+  if (dX) {
+    const int64_t Op = round_up(O, 64);
+    const bool transposed = transposed_dx(O, K, T);
+    if (transposed)
+      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dYt, Op, st))) return e;
+    Bracket b(FAAR_K_GEMM_DX, st);
+    if (int e = hip_status(transposed ? launch_gemm_bf16(dY_used, dYt, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
+                                      : launch_gemm_bf16_nn(dY_used, wq_full, GemmDims{T, K, O, O, K}, static_cast<bf16_t*>(dX), st)))
+      return e;
+  }
   if (in_dw) return FAAR_OK;
   Bracket b(FAAR_K_BWD_ADAM, st);
   return hip_status(launch_step_bwd_adam(a, st));
@@ -1058,7 +1060,8 @@ int faar_block_joint_step(const faar_block* blk, const void* x, const void* y_fp
     const faar_block_linear& l = blk->lin[slot];
     const bool xt_ready = xt_shared && xt_valid;
     xt_valid = (xt_shared && xt_valid) || !gemm_tn_usable(O, K, T);
-    const uint32_t flags = FAAR_WS_CHAINED | FAAR_STEP_JOINT | (xt_ready ? FAAR_STEP_XT_READY : 0u);
+    // one call after the other on one stream: a step has the device to itself
+    const uint32_t flags = FAAR_WS_CHAINED | FAAR_STEP_JOINT | FAAR_STEP_WHOLE_DEVICE | (xt_ready ? FAAR_STEP_XT_READY : 0u);
     return faar_layer_step(l.W, blk->wdt, O, K, l.s_global, l.scales, l.V, l.adam_m, l.adam_u, X, nullptr, at(L.xt), nullptr,
                            l.icodes, nullptr, nullptr, T, dY, dX, beta, 0.0f, lambda_round, 0.0f, opt, l.losses, flags,
                            at(L.step_ws), L.step_bytes, stream);
