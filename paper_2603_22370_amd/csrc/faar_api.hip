@@ -597,6 +597,30 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
     guard.slot = guard_slot;
     guard.expect = tag(opt->t, beta);
   }
+  // s5 + s6: dV, Adam, clip; the same kernel sums the losses (both kinds of partials are complete by then: they come from earlier
+  // kernels) and, when asked, runs s1 of the next step on the updated V
+  StepBwdArgs a{};
+  a.W = W; a.w_bf16 = bf; a.n = n;
+  a.s_global = s_global; a.scales = scales; a.icodes = icodes;
+  a.V = V; a.m = adam_m; a.u = adam_v;
+  a.beta = beta; a.G = G; a.n_split = L.n_split; a.split_stride = (int64_t)O * K; a.x_scale = x_scale;
+  a.lambda_round = lambda_round;
+  a.opt.lr = opt->lr; a.opt.beta1 = opt->beta1; a.opt.beta2 = opt->beta2; a.opt.eps = opt->eps;
+  a.opt.inv_bc1 = static_cast<float>(1.0 / (1.0 - std::pow((double)opt->beta1, (double)opt->t)));
+  a.opt.inv_bc2 = static_cast<float>(1.0 / (1.0 - std::pow((double)opt->beta2, (double)opt->t)));
+  a.mse_partials = mse_p; a.mse_scale = mse_scale; a.round_partials = round_p; a.losses = losses;
+  a.beta_next = beta_next; a.delta_next = delta; a.wq_full_next = wq_next; a.round_next = round_next;
+  a.guard_slot = guard_slot;
+  a.next_tag = tag(opt->t + 1, beta_next);
+  a.H = Hs; a.two_alpha_h = (Hs && !dY_ext) ? 2.0f * mse_scale : 0.0f;
+  a.cross_partials = cross_p; a.c_norm2 = c_norm2; a.cross_next = cross_next;
+  if (!joint && !dY_ext && !dX && small_step(O, K, T)) {
+    Bracket b(FAAR_K_GEMM_RESIDUAL, st);
+    Bracket b2(FAAR_K_GEMM_DW, st);
+    Bracket b3(FAAR_K_BWD_ADAM, st);
+    return hip_status(launch_small_step(xq, static_cast<const bf16_t*>(Xt), Hs ? nullptr : C, O, K, T, 2.0f * mse_scale,
+                                        reinterpret_cast<double*>(G), guard, a, st));
+  }
   // s2: residual GEMM + loss + dY -- not in a joint step, whose loss is computed downstream of the layer; there the
   // activations change from step to step, so their transpose for the dW GEMM is refreshed here
   int64_t n_mse = 0;
@@ -640,30 +664,13 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
     if (!token_major)
       if (int e = hip_status(launch_transpose_bf16(dY_used, T, O, dYt, L.Tp, st))) return e;
   }
-  // s5 + s6: dV, Adam, clip; the same kernel sums the losses (both kinds of partials are complete by then: they come from earlier
-  // kernels) and, when asked, runs s1 of the next step on the updated V
-  StepBwdArgs a{};
-  a.W = W; a.w_bf16 = bf; a.n = n;
-  a.s_global = s_global; a.scales = scales; a.icodes = icodes;
-  a.V = V; a.m = adam_m; a.u = adam_v;
-  a.beta = beta; a.G = G; a.n_split = L.n_split; a.split_stride = (int64_t)O * K; a.x_scale = x_scale;
-  a.lambda_round = lambda_round;
-  a.opt.lr = opt->lr; a.opt.beta1 = opt->beta1; a.opt.beta2 = opt->beta2; a.opt.eps = opt->eps;
-  a.opt.inv_bc1 = static_cast<float>(1.0 / (1.0 - std::pow((double)opt->beta1, (double)opt->t)));
-  a.opt.inv_bc2 = static_cast<float>(1.0 / (1.0 - std::pow((double)opt->beta2, (double)opt->t)));
-  a.mse_partials = mse_p; a.n_mse = n_mse; a.mse_scale = mse_scale; a.round_partials = round_p; a.losses = losses;
-  a.beta_next = beta_next; a.delta_next = delta; a.wq_full_next = wq_next; a.round_next = round_next;
-  a.guard_slot = guard_slot;
-  a.next_tag = tag(opt->t + 1, beta_next);
-  a.H = Hs; a.two_alpha_h = (Hs && !dY_ext) ? 2.0f * mse_scale : 0.0f;
-  a.cross_partials = cross_p; a.c_norm2 = c_norm2; a.cross_next = cross_next;
-
   // s3: G = dY^T X_q, contraction over tokens, split for occupancy
   const bool tn = token_major || rows_form;
   const bf16_t* dw_a = tn && !rows_form ? dY_used : dYt;
   const bf16_t* dw_b = tn ? xq : static_cast<const bf16_t*>(Xt);
   const GemmDims d2 = tn ? GemmDims{O, K, T, O, K} : GemmDims{O, K, L.Tp, L.Tp, L.Tp};
   const bool whole = (flags & FAAR_STEP_WHOLE_DEVICE) != 0;
+  a.n_mse = n_mse;
   {
     Bracket b(FAAR_K_GEMM_DW, st);
     Bracket b2(in_dw ? FAAR_K_BWD_ADAM : -1, st);

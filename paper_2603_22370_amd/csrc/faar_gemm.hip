@@ -256,7 +256,7 @@ struct EpiStep {
     if constexpr (kGram) {
       valid = true;                            // a forward made by this step's own first kernel, or a prepared one under this tag
       if (gr.check)
-        for (int i = 0; i < kTagWords; ++i) valid = valid && p.guard_slot[i] == gr.expect.w[i];
+        for (int i = 0; i < kTagWords; ++i) valid &= p.guard_slot[i] == gr.expect.w[i];   // all loads at once
     } else {
       valid = p.guard_slot[kTagWords] != 0u;   // written by an earlier kernel of this step
     }

@@ -30,7 +30,7 @@ struct ForwardGuard { uint32_t* slot; ForwardTag expect; };  // slot == nullptr:
 __device__ __forceinline__ void consume_forward_tag(const ForwardGuard& guard) {
   if (guard.slot && blockIdx.x == 0 && threadIdx.x == 0) {
     bool ok = true;
-    for (int i = 0; i < kTagWords; ++i) ok = ok && guard.slot[i] == guard.expect.w[i];
+    for (int i = 0; i < kTagWords; ++i) ok &= guard.slot[i] == guard.expect.w[i];   // all loads at once, not one after the other
     for (int i = 0; i < kTagWords; ++i) guard.slot[i] = 0u;   // consumed: a replay of this step must not match
     guard.slot[kTagWords] = ok ? 1u : 0u;
   }
@@ -177,6 +177,13 @@ hipError_t launch_attention_fwd(const bf16_t* Q, const bf16_t* K, const bf16_t* 
 hipError_t launch_attention_bwd(const bf16_t* dO, const bf16_t* Q, const bf16_t* K, const bf16_t* V, const bf16_t* O,
                                 const float* lse, float* delta, int64_t n_seq, int64_t S, int64_t n_q, int64_t n_kv, int64_t dh,
                                 float scale, bf16_t* dQ, bf16_t* dK, bf16_t* dV, hipStream_t st);
+
+// ---- a whole step of a small layer in one launch (faar_small.hip): the step's own loss and dY, no dX; a.delta_next is the W_q - W that
+// the step reads.  C null: the constant is carried as a.H.  partials: one double per 16 rows
+constexpr int64_t kSmallMax = 1 << 14;
+bool small_step(int64_t O, int64_t K, int64_t T);
+hipError_t launch_small_step(const bf16_t* X, const bf16_t* Xt, const float* C, int64_t O, int64_t K, int64_t T, float two_alpha,
+                             double* partials, const ForwardGuard& guard, StepBwdArgs a, hipStream_t st);
 
 // ---- bf16 MFMA GEMMs (faar_gemm.hip) ------------------------------------------------------
 // All GEMMs are "NT": acc[m][n] = sum_k A[m][k] * B[n][k], A [M, lda], B [N, ldb] bf16 row-major

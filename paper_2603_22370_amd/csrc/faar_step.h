@@ -99,6 +99,16 @@ struct LossSums {
   float *loss_mse, *loss_round, *loss_total;
 };
 
+// the step's losses from the sums of its partials
+__device__ __forceinline__ void write_losses(const LossSums& f, double a, double b, double c) {
+  if (f.cross_partials) a += *f.c_norm2 - 2.0 * static_cast<double>(f.x_scale ? *f.x_scale : 1.0f) * c;
+  const double mse = a * static_cast<double>(f.mse_scale);
+  const double rl = b * f.inv_n;
+  if (f.loss_mse) *f.loss_mse = static_cast<float>(mse);
+  if (f.loss_round) *f.loss_round = static_cast<float>(rl);
+  if (f.loss_total) *f.loss_total = static_cast<float>(mse + static_cast<double>(f.lambda_round) * rl);
+}
+
 // kSameLaunch: mse_partials were stored past the writers' L2 in this launch, and are read past this one's
 template <int kThreads, bool kSameLaunch = false>
 __device__ __forceinline__ void finalize_block(const LossSums& f, bool valid = true) {
@@ -143,12 +153,7 @@ __device__ __forceinline__ void finalize_block(const LossSums& f, bool valid = t
       b += sb[i];
       c += sc[i];
     }
-    if (f.cross_partials) a += *f.c_norm2 - 2.0 * static_cast<double>(f.x_scale ? *f.x_scale : 1.0f) * c;
-    const double mse = a * static_cast<double>(f.mse_scale);
-    const double rl = b * f.inv_n;
-    if (f.loss_mse) *f.loss_mse = static_cast<float>(mse);
-    if (f.loss_round) *f.loss_round = static_cast<float>(rl);
-    if (f.loss_total) *f.loss_total = static_cast<float>(mse + static_cast<double>(f.lambda_round) * rl);
+    write_losses(f, a, b, c);
   }
 }
 
