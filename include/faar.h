@@ -102,7 +102,7 @@ enum {
   FAAR_K_GEMM_RESIDUAL = 2,  /* X_q (W_q - W)^T - C, loss, dY           (faar_layer_step) */
   FAAR_K_GEMM_DW = 3,        /* dY^T X_q                                (faar_layer_step) */
   FAAR_K_GEMM_DX = 4,        /* dY W_q                                  (faar_layer_step) */
-  FAAR_K_BWD_ADAM = 5,       /* dV, Round Loss, Adam, clip              (faar_layer_step) */
+  FAAR_K_BWD_ADAM = 5,       /* dV, Round Loss, Adam, clip              (faar_layer_step); a product that ends in it counts as both */
   FAAR_K_QUANT_RTN = 6,      /* the quantise kernel of faar_quant_rtn (not its amax pass) */
   FAAR_K_INIT_V = 7,
   FAAR_K_HARDEN_PACK = 8,

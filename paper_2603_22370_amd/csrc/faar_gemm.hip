@@ -130,6 +130,7 @@ struct EpiPerturbationRows {
   bf16_t* dY;
   double* partials;
   float sum;
+  double total;   // of several tiles (run4)
   __device__ __forceinline__ void once() { consume_forward_tag(guard); }
   __device__ __forceinline__ void begin() { xs = x_scale ? *x_scale : 1.0f; }
   __device__ __forceinline__ void rows4(const float (&acc)[4], int64_t m, int64_t n, int, const GemmDims& d) {
@@ -154,7 +155,22 @@ struct EpiPerturbationRows {
     }
     *reinterpret_cast<uint4*>(dY + m * d.N + n) = make_uint4(w[0], w[1], w[2], w[3]);
   }
-  __device__ __forceinline__ void finish(int item) { finish_sum(sum, partials, item); }
+  // columns n .. n + 3 of row m of the tile at m0, n0
+  __device__ __forceinline__ void run4(const float (&acc)[4], int64_t m0, int64_t n0, int m, int n, const GemmDims& d) {
+    if (m0 + m >= d.M || n0 + n >= d.N) return;
+    uint32_t b[4];
+    float s4 = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float r = xs * acc[j];
+      s4 += r * r;
+      b[j] = f32_to_bf16(two_alpha * r);
+    }
+    total += s4;
+    *reinterpret_cast<uint2*>(reinterpret_cast<char*>(dY + m0 * d.N + n0) + (static_cast<uint32_t>(m) * static_cast<uint32_t>(d.N) + n) * 2u) =
+        make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
+  }
+  __device__ __forceinline__ void finish(int item) { finish_sum(total + sum, partials, item); }
 };
 
 // The loss of a step whose dY comes from upstream, and nothing else: per work item the sum of (x_scale * acc - C)^2, or without C
@@ -465,6 +481,12 @@ struct EpiBf16 {
     } else {
       for (int j = 0; j < 8 && n + j < d.N; ++j) o[j] = static_cast<bf16_t>(f32_to_bf16(sc * r[j]));
     }
+  }
+  // columns n .. n + 3 of row m of the tile at m0, n0; N a multiple of 4
+  __device__ __forceinline__ void run4(const float (&r)[4], int64_t m0, int64_t n0, int m, int n, const GemmDims& d) {
+    if (m0 + m >= d.M || n0 + n >= d.N) return;
+    *reinterpret_cast<uint2*>(reinterpret_cast<char*>(out + m0 * d.N + n0) + (static_cast<uint32_t>(m) * static_cast<uint32_t>(d.N) + n) * 2u) =
+        make_uint2(f32_to_bf16(sc * r[0]) | (f32_to_bf16(sc * r[1]) << 16), f32_to_bf16(sc * r[2]) | (f32_to_bf16(sc * r[3]) << 16));
   }
   __device__ __forceinline__ void finish(int) {}
 };
@@ -1185,6 +1207,144 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
   else epi.finish(item);
 }
 
+// ---- several tiles a workgroup ----------------------------------------------------------------------------------------
+// The same main loop for NT products of two and more rounds of the compute units: 256 resident workgroups walk their tiles, and the
+// copies past the end of a tile are those of the next one's first slices, so that neither a tile's stores nor the latency of its first
+// copies stand by themselves.  The ring therefore stays in use during the epilogue, which goes without LDS: the copies place the rows of
+// B so that a lane's TN accumulator tiles are TN consecutive columns, and 16 lanes store a whole line.  The copies' addresses are buffer
+// descriptors with one offset a lane (rows beyond M or N read as zeros), which also leaves 20 registers more than pointers do.
+// A wavefront's stores count in the same in-order counter as its copies: those of the first two slices are older than the stores, and
+// the wait in the first slice's last phase covers both.
+// 16384x6144x2048, bf16 out: 321 -> 292 us between other kernels, 350 -> 332 with nothing but itself running (bound by power).  Whole
+// steps: 6144x2048 at 8192 tokens 407 -> 399, at 16384 781 -> 764, 8192x2048 at 4096 (two rounds) 304.5 -> 299.5, a block 5.52 -> 5.44 ms.
+typedef uint32_t u32x4r __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void dma16_buffer(u32x4r rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+__device__ __forceinline__ u32x4r buffer_of(const void* p, int64_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  u32x4r r;
+  r.x = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a));
+  r.y = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32) & 0xFFFFu);
+  r.z = __builtin_amdgcn_readfirstlane(bytes > 0xFFFFFFFFll ? 0xFFFFFFFFu : static_cast<uint32_t>(bytes));
+  r.w = 0x00020000u;
+  return r;
+}
+
+template <class C, class Epi>
+__global__ void __launch_bounds__(C::THREADS)
+k_gemm_dma64_rounds(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d, int tiles_m, int tiles_n, Epi epi) {
+  __shared__ __attribute__((aligned(1024))) bf16_t lds[C::NS * C::STAGE];
+  static_assert(!C::kTokenA && !C::kTokenB && C::WGK == 1 && C::KK == 2 && C::NS == 2 && C::TN == 4, "NT, two phases, two stages");
+  constexpr int P = C::P, NF = C::NF, NM = C::NM, TM = C::TM, TN = C::TN;
+  static_assert((C::BM / 8) % P == 0, "a wavefront copies rows of one operand");
+  epi.once();
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave / C::WGN) * C::WM, wn = (wave % C::WGN) * C::WN;
+  int pid = blockIdx.x, tm, tn, split, item;
+  if (!item_coords(pid, tiles_m, tiles_n, 1, tm, tn, split, item)) return;
+  const int nk = static_cast<int>(d.Kd / DBK64);
+  epi.begin();
+
+  // Copy u fills LDS rows 8 u .. 8 u + 7 of the stacked [A rows; B rows]: lane / 8 -> row, lane % 8 -> slot, chunk = slot ^ (row / 2) % 8
+  // as above, of which only bit 2 depends on u (its parity).  LDS row p of B's WN-row groups holds row TN * (p % 16) + p / 16 % TN.
+  const bool of_a = wave * P < C::BM / 8;
+  const uint32_t ld2 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>((of_a ? d.lda : d.ldb) * 2));
+  const uint32_t v0 = (lane / 8) * (of_a ? 1 : TN) * ld2 + ((lane % 8) ^ (lane / 16)) * 16, v1 = v0 ^ 64u;
+  static_assert(P % 2 == 0, "the parity of a copy is that of its number in the wavefront");
+  u32x4r rs;
+  auto set_tile = [&](int tm_, int tn_) {
+    const int64_t m0 = (int64_t)tm_ * C::BM, n0 = (int64_t)tn_ * C::BN;
+    rs = of_a ? buffer_of(A + m0 * d.lda, (d.M - m0) * d.lda * 2) : buffer_of(B + n0 * d.ldb, (d.N - n0) * d.ldb * 2);
+  };
+  auto copy = [&](int q, int slice, int stage) {
+    const int u = wave * P + q, ub = u - C::BM / 8;
+    const uint32_t row = of_a ? u * 8 : 8 * TN * (ub & 1) + (ub % (C::WN / 8)) / 2 + C::WN * (ub / (C::WN / 8));
+    dma16_buffer(rs, (q & 1) ? v1 : v0, __builtin_amdgcn_readfirstlane(row * ld2 + slice * (DBK64 * 2)),
+                 __builtin_amdgcn_readfirstlane(lds_addr_of(lds + stage * C::STAGE + u * C::RPI * DBK64)));
+  };
+  set_tile(tm, tn);
+#pragma unroll
+  for (int s = 0; s < C::NS; ++s)
+#pragma unroll
+    for (int q = 0; q < P; ++q) copy(q, s, s);
+
+  f32x4 acc[TM][TN];
+  const int fr = lane & 15, kc = lane >> 4, sw = (fr / C::RB) % C::CPR;
+  int a_off[2], b_off[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    const int slot = ((4 * kk + kc) ^ sw) * 8;
+    a_off[kk] = (wm + fr) * DBK64 + slot;
+    b_off[kk] = C::BM * DBK64 + (wn + fr) * DBK64 + slot;
+  }
+  auto frag_a = [&](const bf16_t* src, int kk, int i) -> bf16x8 { return *reinterpret_cast<const bf16x8*>(src + a_off[kk] + i * 16 * DBK64); };
+  auto frag_b = [&](const bf16_t* src, int kk, int j) -> bf16x8 { return *reinterpret_cast<const bf16x8*>(src + b_off[kk] + j * 16 * DBK64); };
+  bf16x8 fa[2][TM], fb[2][TN];
+  FAAR_WAIT_VMCNT(P * (C::NS - 1));
+  __builtin_amdgcn_s_barrier();
+  int stage = 0;
+  for (;;) {
+    const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
+    pid += gridDim.x;
+    const bool more = item_coords(pid, tiles_m, tiles_n, 1, tm, tn, split, item);
+    const bf16_t* st0 = lds + stage * C::STAGE;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      fa[0][i] = frag_a(st0, 0, i);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fb[0][j] = frag_b(st0, 0, j);
+    int rel = C::NS;                 // the slice that this iteration's copies bring, of the tile they stand at
+    for (int it = 0; it < nk; ++it) {
+      bf16_t* st = lds + stage * C::STAGE;
+      const bf16_t* sn = lds + (stage ^ 1) * C::STAGE;
+      if (rel == nk) {               // from here on the next tile's (without one, this tile's again: never read)
+        rel = 0;
+        if (more) set_tile(tm, tn);
+      }
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        if (kk == 1) {               // as in k_gemm_dma64: the next slice has landed, this one's last fragments are in registers
+          __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+          __builtin_amdgcn_s_barrier();
+        }
+        const bf16_t* src = kk == 0 ? st : sn;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+          const int mi = m / TN, mj = (mi & 1) ? TN - 1 - m % TN : m % TN;
+          acc[mi][mj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[kk][mi], fb[kk][mj], acc[mi][mj], 0, 0, 0);
+          if (m % C::FSTEP == 0 && m / C::FSTEP < NF) {
+            const int f = m / C::FSTEP;
+            if (f == 0) fa[kk ^ 1][0] = frag_a(src, kk ^ 1, 0);
+            else if (f <= TN) fb[kk ^ 1][f - 1] = frag_b(src, kk ^ 1, f - 1);
+            else fa[kk ^ 1][f - TN] = frag_a(src, kk ^ 1, f - TN);
+          }
+          if (kk == 1 && m % C::DSTEP == 0 && m / C::DSTEP < P) copy(m / C::DSTEP, rel, stage);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      ++rel;
+      stage ^= 1;
+    }
+    // lane -> columns wn + 4 (lane % 16) + 0..3, rows wm + 16 i + 4 (lane / 16) + 0..3
+    int mrow = wm + 4 * kc, ncol = wn + fr * TN;
+    asm volatile("" : "+v"(mrow), "+v"(ncol));   // no address is kept across the main loop
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float r[4] = {acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]};
+        epi.run4(r, m0, n0, mrow + i * 16 + v, ncol, d);
+      }
+    if (!more) break;
+  }
+  FAAR_WAIT_VMCNT(0);   // no copy may still be in flight into this workgroup's LDS when it retires
+  epi.finish(blockIdx.x);
+}
+
 typedef Dma64Cfg<256, 256, 2, 4, 2> CfgL64;  // 2 x 64 KB
 typedef Dma64Cfg<256, 128, 4, 2, 3> CfgM64;  // 3 x 48 KB: copies stay in flight for two slices
 typedef Dma64Cfg<128, 128, 2, 2, 4, kNT, 2> CfgS64;  // 4 x 32 KB, two contraction groups
@@ -1285,6 +1445,21 @@ hipError_t run(const bf16_t* A, const bf16_t* B, GemmDims d, Plan p, Epi epi, hi
   return hipGetLastError();
 }
 
+// Whether a product walks several tiles a workgroup: 256x256 tiles, two rounds of them, whole slices, more of them than the ring holds,
+// offsets within a tile's rows below 2^32.  Long contractions have fewer ends of tiles to hide, and their rows, a multiple of 4 KB apart,
+// meet in the same channels when all workgroups walk in step (16384x2048, contraction 6144: 309 us, 320 this way)
+constexpr int kRoundsGrid = 256;
+bool walks_rounds(const GemmDims& d, const Plan& p) {
+  return p.kind == KIND_L64 && p.items() >= 2 * kRoundsGrid && d.Kd <= 4096 && p.n_split == 1 && d.Kd % DBK64 == 0 && d.Kd > 2 * DBK64 && d.N % 4 == 0 &&
+         std::max(std::max(d.lda, d.ldb), d.N) <= (1 << 22);
+}
+
+template <class Epi>
+hipError_t run_rounds(const bf16_t* A, const bf16_t* B, const GemmDims& d, const Plan& p, Epi epi, hipStream_t st) {
+  hipLaunchKernelGGL((k_gemm_dma64_rounds<CfgL64, Epi>), dim3(kRoundsGrid), dim3(CfgL64::THREADS), 0, st, A, B, d, p.tiles_m, p.tiles_n, epi);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 int64_t gemm_residual_partials(int64_t M, int64_t N, int64_t Kd) {  // the most any of the epilogues writes
@@ -1298,8 +1473,12 @@ hipError_t launch_gemm_residual_rows(const bf16_t* A, const bf16_t* B, GemmDims 
                                      bf16_t* dY, double* mse_partials, int64_t* n_partials, const ForwardGuard& guard,
                                      hipStream_t st) {
   if (d.N % 8 != 0) return hipErrorInvalidValue;
-  EpiPerturbationRows e{x_scale, 1.0f, guard, two_alpha, dY, mse_partials, 0.0f};
+  EpiPerturbationRows e{x_scale, 1.0f, guard, two_alpha, dY, mse_partials, 0.0f, 0.0};
   const Plan p = plan_gemm(d, false, kEpiBf16);
+  if (walks_rounds(d, p)) {
+    *n_partials = kRoundsGrid;
+    return run_rounds(A, B, d, p, e, st);
+  }
   *n_partials = p.items();
   return run(A, B, d, p, e, st);
 }
@@ -1562,7 +1741,8 @@ hipError_t launch_gemm_bf16_nn(const bf16_t* A, const bf16_t* B, GemmDims d, bf1
 
 hipError_t launch_gemm_bf16(const bf16_t* A, const bf16_t* B, GemmDims d, bf16_t* out, const float* scale, hipStream_t st) {
   EpiBf16 e{out, scale, 1.0f};
-  return run(A, B, d, plan_gemm(d, false, kEpiBf16), e, st);
+  const Plan p = plan_gemm(d, false, kEpiBf16);
+  return walks_rounds(d, p) ? run_rounds(A, B, d, p, e, st) : run(A, B, d, p, e, st);
 }
 
 }  // namespace faar
