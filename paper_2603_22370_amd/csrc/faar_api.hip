@@ -467,8 +467,8 @@ int faar_layer_prepare(const void* W, faar_dtype wdt, int64_t O, int64_t K, cons
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bf16_t* xq = static_cast<const bf16_t*>(Xq);
   const int64_t Tp = padded_tokens(T);
-  if (int e = hip_status(launch_interval_codes(W, bf, O * K, s_global, scales, icodes, st))) return e;
-  if (int e = hip_status(launch_transpose_bf16(xq, T, K, static_cast<bf16_t*>(Xt), Tp, st))) return e;
+  if (int e = hip_status(launch_codes_and_transpose(W, bf, O * K, s_global, scales, icodes, xq, T, K, static_cast<bf16_t*>(Xt), Tp, st)))
+    return e;
   if (!Y_fp) return FAAR_OK;
   const GemmDims d{T, O, K, K, K};
   if (bf) {
@@ -502,9 +502,11 @@ int faar_layer_prepare(const void* W, faar_dtype wdt, int64_t O, int64_t K, cons
     if (int e = hip_status(terms == 3 ? launch_gemm_f32_terms(ct, xt, d2, out, n_split, st) : launch_gemm_f32(ct, xt, d2, out, n_split, st)))
       return e;
     if (out != H)
-      if (int e = hip_status(launch_accumulate_partials(H, part, n_split, (int64_t)O * K, O * K, term == 0, st))) return e;
+      if (int e = hip_status(launch_accumulate_partials(H, part, n_split, (int64_t)O * K, O * K, term == 0, term == 0 ? sq : nullptr,
+                                                        c_term_blocks(T, O), c_norm2, st)))
+        return e;
   }
-  return hip_status(launch_sum_doubles(sq, c_term_blocks(T, O), c_norm2, st));
+  return out != H ? FAAR_OK : hip_status(launch_sum_doubles(sq, c_term_blocks(T, O), c_norm2, st));
 }
 
 // The product on W_q as it lies takes its fragments of W_q with twice as many LDS reads and is 4-12 % slower than on a transposed

@@ -416,11 +416,8 @@ k_softquant_bwd(const WT* __restrict__ W, int64_t n8, const float* __restrict__ 
 // (sign(0) = 0 in Eq. 2: no contribution to W_q and no data gradient).
 
 template <typename WT>
-__global__ void __launch_bounds__(kEltThreads)
-k_interval_codes(const WT* __restrict__ W, int64_t n8, const float* __restrict__ s_global_p,
-                 const uint8_t* __restrict__ scales, uint32_t* __restrict__ icodes) {
-  const int64_t i = blockIdx.x * (int64_t)kEltThreads + threadIdx.x;
-  if (i >= n8) return;
+__device__ __forceinline__ void interval_codes_chunk(const WT* __restrict__ W, int64_t i, const float* __restrict__ s_global_p,
+                                                     const uint8_t* __restrict__ scales, uint32_t* __restrict__ icodes) {
   const float s = effective_scale(scales[i >> 1], *s_global_p);
   float w[8];
   W8<WT>::load(W + i * 8, w);
@@ -618,11 +615,10 @@ k_hardened_delta(const WT* __restrict__ W, int64_t n8, const float* __restrict__
 // ---- bf16 transpose with zero padding (X_q^T for the dW GEMM) -------------------------------
 // 64 x 64 tiles through LDS; 16-byte global accesses on both sides (rows of the tile are 128 contiguous bytes).
 // The LDS row pitch of 33 words makes the transposed 2-byte reads of a wavefront hit 32 distinct banks.
-__global__ void __launch_bounds__(256)
-k_transpose_bf16(const bf16_t* __restrict__ in, int64_t rows, int64_t cols, bf16_t* __restrict__ out,
-                 int64_t ld_out, unsigned tiles_c) {
+__device__ __forceinline__ void transpose_tile(const bf16_t* __restrict__ in, int64_t rows, int64_t cols, bf16_t* __restrict__ out,
+                                               int64_t ld_out, unsigned tiles_c, unsigned block) {
   __shared__ uint32_t tile[64][33];
-  const int64_t r0 = (blockIdx.x / tiles_c) * 64LL, c0 = (blockIdx.x % tiles_c) * 64LL;
+  const int64_t r0 = (block / tiles_c) * 64LL, c0 = (block % tiles_c) * 64LL;
   const int sub = threadIdx.x >> 3, ch = threadIdx.x & 7;
   const bool vec_in = (cols % 8) == 0;
 #pragma unroll
@@ -658,6 +654,24 @@ k_transpose_bf16(const bf16_t* __restrict__ in, int64_t rows, int64_t cols, bf16
           make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
     }
   }
+}
+
+__global__ void __launch_bounds__(256)
+k_transpose_bf16(const bf16_t* __restrict__ in, int64_t rows, int64_t cols, bf16_t* __restrict__ out,
+                 int64_t ld_out, unsigned tiles_c) {
+  transpose_tile(in, rows, cols, out, ld_out, tiles_c, blockIdx.x);
+}
+
+// A layer's interval codes and the transpose of its activations, which have nothing to do with each other, in one launch: the codes'
+// workgroups come first (set-up of 2048x2048 at 8192 tokens, ||C||^2 in the accumulating launch as well: 307.5 -> 302.9 us)
+template <typename WT>
+__global__ void __launch_bounds__(256)
+k_codes_and_transpose(const WT* __restrict__ W, int64_t n8, const float* __restrict__ s_global_p, const uint8_t* __restrict__ scales,
+                      uint32_t* __restrict__ icodes, unsigned code_blocks, const bf16_t* __restrict__ in, int64_t rows, int64_t cols,
+                      bf16_t* __restrict__ out, int64_t ld_out, unsigned tiles_c) {
+  if (blockIdx.x >= code_blocks) return transpose_tile(in, rows, cols, out, ld_out, tiles_c, blockIdx.x - code_blocks);
+  const int64_t i = blockIdx.x * (int64_t)kEltThreads + threadIdx.x;
+  if (i < n8) interval_codes_chunk<WT>(W, i, s_global_p, scales, icodes);
 }
 
 // ---- the constant part of the gradient, H = C^T X_q (once per layer) -----------------------------------------------
@@ -721,11 +735,24 @@ k_c_terms_transposed(const float* __restrict__ C, int64_t T, int64_t O, int firs
   }
 }
 
-// H = (first ? 0 : H) + sum over the splits of the partial products
+// out[0] = sum of n doubles, in a fixed order (one workgroup)
+__device__ __forceinline__ void sum_doubles(const double* __restrict__ p, int64_t n, double* __restrict__ out) {
+  double a = 0.0;
+  for (int64_t i = threadIdx.x; i < n; i += kEltThreads) a += p[i];
+  const double t = block_sum(a);
+  if (threadIdx.x == 0) *out = t;
+}
+__global__ void __launch_bounds__(kEltThreads) k_sum_doubles(const double* __restrict__ p, int64_t n, double* __restrict__ out) {
+  sum_doubles(p, n, out);
+}
+
+// H = (first ? 0 : H) + sum over the splits of the partial products.  Where sq is given, workgroup 0 has no part in that and adds up
+// ||C||^2 instead (on its own a launch of 6 us).
 __global__ void __launch_bounds__(kEltThreads)
 k_accumulate_partials(float* __restrict__ H, const float* __restrict__ partials, int n_split, int64_t stride, int64_t n4,
-                      bool first) {
-  const int64_t i = blockIdx.x * (int64_t)kEltThreads + threadIdx.x;
+                      bool first, const double* __restrict__ sq, int64_t n_sq, double* __restrict__ c_norm2) {
+  if (sq && blockIdx.x == 0) return sum_doubles(sq, n_sq, c_norm2);
+  const int64_t i = (blockIdx.x - (sq ? 1 : 0)) * (int64_t)kEltThreads + threadIdx.x;
   if (i >= n4) return;
   float4 a = first ? make_float4(0.0f, 0.0f, 0.0f, 0.0f) : reinterpret_cast<const float4*>(H)[i];
   for (int s = 0; s < n_split; ++s) {
@@ -757,14 +784,6 @@ k_gram_finish(const float* __restrict__ partials, int n_split, int64_t K, bf16_t
     if (col + j == row) diag_lo[row] = v[j] - __uint_as_float(b[j] << 16);
   }
   *reinterpret_cast<uint2*>(gram + i * 4) = make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
-}
-
-// out[0] = sum of n doubles, in a fixed order (one workgroup)
-__global__ void __launch_bounds__(kEltThreads) k_sum_doubles(const double* __restrict__ p, int64_t n, double* __restrict__ out) {
-  double a = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += kEltThreads) a += p[i];
-  const double t = block_sum(a);
-  if (threadIdx.x == 0) *out = t;
 }
 
 // float32 -> hi + mid + lo bf16 terms (24 significand bits covered by 3 x 8).
@@ -919,15 +938,21 @@ hipError_t launch_softquant_bwd(const void* W, bool w_bf16, int64_t n, const flo
   return hipGetLastError();
 }
 
-hipError_t launch_interval_codes(const void* W, bool w_bf16, int64_t n, const float* s_global,
-                                 const uint8_t* scales, uint8_t* icodes, hipStream_t st) {
-  const int64_t n8 = n / 8;
-  const dim3 g(blocks_for(n8)), b(kEltThreads);
+hipError_t launch_codes_and_transpose(const void* W, bool w_bf16, int64_t n, const float* s_global, const uint8_t* scales, uint8_t* icodes,
+                                      const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out, int64_t ld_out, hipStream_t st) {
+  static_assert(kEltThreads == 256, "one workgroup size for both");
+  if (ld_out % 64 != 0) return hipErrorInvalidValue;  // whole 8-element chunks are stored
+  const int64_t n8 = n / 8, code_blocks = blocks_for(n8), tiles_c = (cols + 63) / 64, tiles = tiles_c * ((ld_out + 63) / 64);
+  if (code_blocks + tiles > 0x7FFFFFFFLL) {
+    if (hipError_t e = launch_transpose_bf16(in, rows, cols, out, ld_out, st)) return e;
+  }
+  const dim3 g(static_cast<unsigned>(code_blocks + (code_blocks + tiles > 0x7FFFFFFFLL ? 0 : tiles))), b(kEltThreads);
   uint32_t* c32 = reinterpret_cast<uint32_t*>(icodes);
-  if (w_bf16)
-    hipLaunchKernelGGL(k_interval_codes<bf16_t>, g, b, 0, st, static_cast<const bf16_t*>(W), n8, s_global, scales, c32);
-  else
-    hipLaunchKernelGGL(k_interval_codes<float>, g, b, 0, st, static_cast<const float*>(W), n8, s_global, scales, c32);
+#define FAAR_CT(WT)                                                                                                               \
+  hipLaunchKernelGGL(k_codes_and_transpose<WT>, g, b, 0, st, static_cast<const WT*>(W), n8, s_global, scales, c32,                  \
+                     static_cast<unsigned>(code_blocks), in, rows, cols, out, ld_out, static_cast<unsigned>(tiles_c))
+  if (w_bf16) FAAR_CT(bf16_t); else FAAR_CT(float);
+#undef FAAR_CT
   return hipGetLastError();
 }
 
@@ -1048,10 +1073,10 @@ hipError_t launch_c_terms_transposed(const float* C, int64_t T, int64_t O, int f
 }
 
 hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, bool first,
-                                      hipStream_t st) {
+                                      const double* sq, int64_t n_sq, double* c_norm2, hipStream_t st) {
   const int64_t n4 = n / 4;   // n = O * K is a multiple of 16
-  hipLaunchKernelGGL(k_accumulate_partials, dim3(static_cast<unsigned>((n4 + kEltThreads - 1) / kEltThreads)), dim3(kEltThreads),
-                     0, st, H, partials, n_split, stride, n4, first);
+  hipLaunchKernelGGL(k_accumulate_partials, dim3(static_cast<unsigned>((n4 + kEltThreads - 1) / kEltThreads + (sq ? 1 : 0))),
+                     dim3(kEltThreads), 0, st, H, partials, n_split, stride, n4, first, sq, n_sq, c_norm2);
   return hipGetLastError();
 }
 

@@ -25,14 +25,17 @@ constexpr int kTagWords = 12;
 constexpr int kArrivals = kTagWords + 1;   // word of the slot in which a launch counts the workgroups that are done; 0 between launches
 struct ForwardTag { uint32_t w[kTagWords]; };
 struct ForwardGuard { uint32_t* slot; ForwardTag expect; };  // slot == nullptr: nothing to check
-// Done by one thread of a launch (workgroup 0 of a step's product, before anything else): is the forward in the workspace the one
-// this step's caller says it is?
+// Done by one wavefront of a launch (workgroup 0 of a step's product, before anything else): is the forward in the workspace the one
+// this step's caller says it is?  A word a lane: the step waits for one load (by one thread, all words at once, the residual GEMM of a small layer took 0.5 us longer)
 __device__ __forceinline__ void consume_forward_tag(const ForwardGuard& guard) {
-  if (guard.slot && blockIdx.x == 0 && threadIdx.x == 0) {
-    bool ok = true;
-    for (int i = 0; i < kTagWords; ++i) ok &= guard.slot[i] == guard.expect.w[i];   // all loads at once, not one after the other
-    for (int i = 0; i < kTagWords; ++i) guard.slot[i] = 0u;   // consumed: a replay of this step must not match
-    guard.slot[kTagWords] = ok ? 1u : 0u;
+  if (guard.slot && blockIdx.x == 0 && threadIdx.x < 64) {
+    const int lane = static_cast<int>(threadIdx.x);
+    uint32_t want = 0u;
+#pragma unroll
+    for (int i = 0; i < kTagWords; ++i) want = lane == i ? guard.expect.w[i] : want;
+    const bool ok = __all(lane >= kTagWords || guard.slot[lane < kTagWords ? lane : 0] == want);
+    if (lane < kTagWords) guard.slot[lane] = 0u;              // consumed: a replay of this step must not match
+    if (lane == 0) guard.slot[kTagWords] = ok ? 1u : 0u;
   }
 }
 
@@ -80,8 +83,9 @@ int64_t softquant_bwd_blocks(int64_t n);
 int64_t step_bwd_blocks(int64_t n);
 struct AdamScalars { float lr, beta1, beta2, eps, inv_bc1, inv_bc2; };
 // Interval codes signbit(w) << 3 | (w == 0 ? 7 : k_lo), two per byte, for the per-step kernels below.
-hipError_t launch_interval_codes(const void* W, bool w_bf16, int64_t n, const float* s_global,
-                                 const uint8_t* scales, uint8_t* icodes, hipStream_t st);
+// (launched together with the transpose of the activations, see launch_transpose_bf16)
+hipError_t launch_codes_and_transpose(const void* W, bool w_bf16, int64_t n, const float* s_global, const uint8_t* scales, uint8_t* icodes,
+                                      const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out, int64_t ld_out, hipStream_t st);
 // Step forward on cached codes: delta = bf16(W_q - W) (+ bf16(W_q) when Wq_full), and the Round-Loss
 // partial sums of V, one per block (step_bwd_blocks(n) of them).
 hipError_t launch_step_fwd(const void* W, bool w_bf16, int64_t n, const float* s_global, const uint8_t* scales,
@@ -125,8 +129,9 @@ int64_t c_term_blocks(int64_t T, int64_t O);
 hipError_t launch_c_terms_transposed(const float* C, int64_t T, int64_t O, int first, int n_terms, bf16_t* out, double* sq_partials,
                                      hipStream_t st);
 // H[0..n) = (first ? 0 : H) + sum_s partials[s * stride + i]
+// and, where sq is given, c_norm2[0] = sum of its n_sq doubles
 hipError_t launch_accumulate_partials(float* H, const float* partials, int n_split, int64_t stride, int64_t n, bool first,
-                                      hipStream_t st);
+                                      const double* sq, int64_t n_sq, double* c_norm2, hipStream_t st);
 hipError_t launch_sum_doubles(const double* p, int64_t n, double* out, hipStream_t st);
 // gram[i] = bf16(sum_s partials[s * K * K + i]) for the K x K matrix; diag_lo[k] = that sum at (k, k) minus its bf16 rounding
 hipError_t launch_gram_finish(const float* partials, int n_split, int64_t K, bf16_t* gram, float* diag_lo, hipStream_t st);
