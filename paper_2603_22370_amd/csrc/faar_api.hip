@@ -233,8 +233,7 @@ int64_t faar_padded_tokens(int64_t T) { return T > 0 ? padded_tokens(T) : 0; }
 
 int faar_dw_token_major(int64_t O, int64_t K, int64_t T, uint32_t flags) {
   if (check_shape(O, K) != FAAR_OK || T <= 0) return 0;
-  const int n_split = gemm_dw_updates(O, K, padded_tokens(T), false) ? 1 : choose_split(O, K, padded_tokens(T));
-  return gemm_tn_tiles(O, K, T, (flags & FAAR_STEP_WHOLE_DEVICE) != 0, n_split);
+  return gemm_tn_tiles(O, K, T, (flags & FAAR_STEP_WHOLE_DEVICE) != 0);
 }
 
 int faar_gemm_probe(int mode, int64_t M, int64_t N, int64_t Kd, const void* A, const void* B,
@@ -574,7 +573,7 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
   const float* Hs = (H && !(dX && !dY_ext)) ? H : nullptr;
   // A dW product that is not split ends in the pass over V, and so comes before dX where the next step's W_q may not overwrite this
   // one's: the two take turns between W_q's place and that of the gradient, which does not exist then
-  const bool in_dw = gemm_dw_updates(O, K, L.Tp, dX && !joint);
+  const bool in_dw = gemm_dw_updates(O, K, L.Tp);
   bf16_t* wq_full = chained && dX ? reinterpret_cast<bf16_t*>(base + L.wq_full) : nullptr;
   bf16_t* wq_next = wq_full;
   if (in_dw && wq_full) (opt->t & 1 ? wq_full : wq_next) = reinterpret_cast<bf16_t*>(G);

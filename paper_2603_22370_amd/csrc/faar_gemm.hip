@@ -1567,27 +1567,19 @@ constexpr int64_t kUpdateMinItems = 96;
 // us, 1000x1488 27.7 -> 30.7, 1024x2048 32.7 -> 33.0; 2048x2048 49.1 -> 48.2).
 constexpr int64_t kGramUpdateMin = (int64_t)1 << 22;
 constexpr int64_t kUpdateMaxColumns = 1 << 21;   // 256 rows of them, 4 bytes each, are 32-bit offsets
-// Products of 192 to 256 tiles of 256x256 are not split for it either, whatever the planner says: it counts a slice as if every unit
-// were busy, and the partial sums of a split cost more than the units that stay idle (6144x2048 at 16384 tokens, 4 splits of 192 tiles
-// and a pass over V that reads four gradients 433 us; one split that ends in it 403, on 256 tiles of 192x256 380).
-// Not of wide layers inside a chain, whose dX then finds less in the caches (2048x6144 at 16384 tokens 1112 / 1122 us).
-static Plan dw_update_plan(int64_t O, int64_t K, int64_t Tp, bool in_chain) {
-  Plan p = plan_gemm(GemmDims{O, K, Tp, Tp, Tp}, true, kEpiF32);
-  const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-  if (p.kind == KIND_L64 && tiles >= 192 && tiles <= 256 && !(in_chain && K > 2 * O)) p.n_split = 1;
-  return p;
-}
-
-bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp, bool in_chain) {
-  const Plan p = dw_update_plan(O, K, Tp, in_chain);
+// What the plan splits stays split, although a single sum with the update behind it can be faster (6144x2048 at 16384 tokens, 4 splits of
+// 192 tiles and a pass over V that reads four gradients 433 us; one sum that ends in it 403): rounding errors grow with the root of a
+// sum's length, and the gradient there was 7.9e-7 of its norm from 64 bits that way, 4.4e-7 as four partial sums.
+bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp) {
+  const Plan p = plan_gemm(GemmDims{O, K, Tp, Tp, Tp}, true, kEpiF32);
   return p.n_split == 1 && p.items() >= kUpdateMinItems && p.items() <= step_bwd_blocks(O * K) && K <= kUpdateMaxColumns;
 }
 
 template <typename WT>
 static hipError_t run_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bool tn, bool fill_device, const StepBwdArgs& a, hipStream_t st) {
   const EpiStep<WT> e{step_update(a), GramOperands{}, 0.0f, 1.0f, 0.0, 0.0, true, 0.0};
-  if (!tn) return run(A, B, d, dw_update_plan(d.M, d.N, d.Kd, false), e, st);
-  const int tiles = gemm_tn_tiles(d.M, d.N, d.Kd, fill_device, 1);
+  if (!tn) return run(A, B, d, plan_gemm(d, true, kEpiF32), e, st);
+  const int tiles = gemm_tn_tiles(d.M, d.N, d.Kd, fill_device);
   if (tiles == 2) return run_tn<CfgT64A>(A, B, d, 1, e, st);
   if (tiles == 3) return run_tn<CfgT64B>(A, B, d, 1, e, st);
   if (tiles == 1) return run_tn<CfgT64>(A, B, d, 1, e, st);
@@ -1596,7 +1588,7 @@ static hipError_t run_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bo
 
 hipError_t launch_gemm_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bool tn, bool fill_device, const StepBwdArgs& a,
                                  hipStream_t st) {
-  if (!gemm_dw_updates(d.M, d.N, d.Kd, false) || d.lda % 8 != 0 || d.ldb % 8 != 0) return hipErrorInvalidValue;
+  if (!gemm_dw_updates(d.M, d.N, d.Kd) || d.lda % 8 != 0 || d.ldb % 8 != 0) return hipErrorInvalidValue;
   return a.w_bf16 ? run_dw_update<bf16_t>(A, B, d, tn, fill_device, a, st) : run_dw_update<float>(A, B, d, tn, fill_device, a, st);
 }
 
@@ -1655,18 +1647,18 @@ hipError_t launch_gemm_gram(const bf16_t* delta, const bf16_t* gram, int64_t O, 
 // work items need fewer rounds of the 256 compute units, weighted by the tile's area (6144 x 2048, one split: 192 items of
 // 65536 -> one round at 65536; 256 items of 49152 -> one round at 49152).  Otherwise other kernels run on whatever units this
 // one leaves idle, and the tile with the most work per byte moved wins: 256 x 256.
-int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device, int n_split) {
+int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device) {
   if (T <= 0 || T % DBK64 != 0 || M % 8 != 0 || N % 8 != 0) return 0;
   const Plan p = plan_gemm(GemmDims{M, N, T, T, T}, true, kEpiF32);
   if (p.kind != KIND_L64) return 0;
   if (!fill_device) return 1;
-  return fewest_rounds(M, N, n_split);
+  return fewest_rounds(M, N, p.n_split);
 }
-bool gemm_tn_usable(int64_t M, int64_t N, int64_t T) { return gemm_tn_tiles(M, N, T, false, 1) != 0; }
+bool gemm_tn_usable(int64_t M, int64_t N, int64_t T) { return gemm_tn_tiles(M, N, T, false) != 0; }
 
 hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split, bool fill_device,
                               hipStream_t st) {
-  const int tiles = gemm_tn_tiles(d.M, d.N, d.Kd, fill_device, n_split);
+  const int tiles = gemm_tn_tiles(d.M, d.N, d.Kd, fill_device);
   if (tiles == 0 || d.lda % 8 != 0 || d.ldb % 8 != 0) return hipErrorInvalidValue;
   const Plan p = plan_gemm(GemmDims{d.M, d.N, d.Kd, d.Kd, d.Kd}, true, kEpiF32);
   if (p.n_split != n_split) return hipErrorInvalidValue;

@@ -226,12 +226,12 @@ hipError_t launch_gemm_f32_terms(const bf16_t* A, const bf16_t* B, GemmDims d, f
 // the planner gives 256 x 256 tiles); n_split = choose_split(M, N, T) as for launch_gemm_f32.
 bool gemm_tn_usable(int64_t M, int64_t N, int64_t T);
 // 0 not usable, 1 256 x 256 tiles, 2 192 x 256, 3 256 x 192 (the last two only with fill_device: the kernel runs alone)
-int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device, int n_split);
+int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device);
 hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, float* out, int n_split, bool fill_device,
                               hipStream_t st);
 // The dW product of a step that ends in the pass over V (StepBwdArgs; its G, n_split and split_stride are not used): where the plan
 // does not split it.  A, B as for launch_gemm_f32_tn (tn) or launch_gemm_f32
-bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp, bool in_chain);   // in_chain: dX is wanted, and the loss is the layer's own
+bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp);
 hipError_t launch_gemm_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bool tn, bool fill_device, const StepBwdArgs& a,
                                  hipStream_t st);
 // The same for the Gram form's product (a.delta_next must not be delta); partials: one double per work item

@@ -74,6 +74,31 @@ def test_weight_gradient_that_updates_v(O, K, T, alone, dtype):
                 assert torch.equal(a, b), k
 
 
+def _distance_from_64_bits(O, K, T, alone):
+    """Of the gradient in m after a first step on an upstream gradient, relative to its norm; dL/dV is affine in the gradient, its factor
+    taken from the library's own backward pass (float32: about 3e-7 of every distance)."""
+    W, X, Y, sg, scales, V, gen = _layer(O, K, T, torch.bfloat16)
+    Xt, C, icodes = faar.faar_layer_prepare(W, sg, scales, X, Y)
+    dY = torch.randn((T, O), generator=gen, device="cuda").to(torch.bfloat16)
+    G = _mm(dY.double().T, X.double())
+    _, factor, _ = faar.faar_softquant_fwd_bwd(W, sg, scales, V, BETA, dWt=torch.ones_like(V))
+    want = G * factor.double() + LAMBDA / (O * K) * (4.0 - 8.0 * V.double())
+    m, u = torch.zeros_like(V), torch.zeros_like(V)
+    faar.faar_layer_step(W, sg, scales, V, m, u, X, Xt, C, icodes, BETA, LAMBDA, 1.0 / (T * O), *ADAM, 1,
+                         torch.zeros(3, dtype=torch.float32, device="cuda"), faar.layer_step_workspace(O, K, T, chained=True), dY_ext=dY,
+                         whole_device=alone)
+    return float((m.double() / (1 - ADAM[1]) - want).norm() / want.norm())
+
+
+@pytest.mark.parametrize("alone", [False, True])
+@pytest.mark.parametrize("O,K", [(6144, 2048), (4096, 3072)])
+def test_planned_splits_stay_split(O, K, alone):
+    """Over 16384 tokens the plan has partial sums over at most 8192 of them, over 8192 a single sum: rounding errors grow with the root of
+    a sum's length, so the former are no further from 64 bits than the latter."""
+    assert fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, 16384)[3] > 1 and fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, 8192)[3] == 1
+    assert _distance_from_64_bits(O, K, 16384, alone) <= _distance_from_64_bits(O, K, 8192, alone)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("O,K", GRAM)
 def test_gram_product_that_updates_v(O, K, dtype):
