@@ -1541,17 +1541,21 @@ static hipError_t run_tn(const bf16_t* A, const bf16_t* B, const GemmDims& d, in
   const int ksteps = static_cast<int>(d.Kd / DBK64);
   const int per_split = (ksteps + n_split - 1) / n_split;
   const int64_t items = (int64_t)tiles_m * tiles_n * n_split;
+  if constexpr (Chunked<Epi>::value) {
+    if (items > epi.p.n_next) return hipErrorInvalidValue;
+  }
   const dim3 grid(static_cast<unsigned>((items + 7) / 8 * 8));
   hipLaunchKernelGGL((k_gemm_dma64<C, false, Epi>), grid, dim3(C::THREADS), 0, st, A, B, d, tiles_m, tiles_n, n_split, per_split, epi);
   return hipGetLastError();
 }
 
-// 1 256 x 256, 2 192 x 256, 3 256 x 192: whichever needs the fewest rounds of the 256 compute units, weighted by the tile's area
-static int fewest_rounds(int64_t M, int64_t N, int n_split) {
+// 1 256 x 256, 2 192 x 256, 3 256 x 192: whichever needs the fewest rounds of the 256 compute units, weighted by the tile's area; the
+// 192-wide ones, which are up to a third more, not where they are more than `most`
+static int fewest_rounds(int64_t M, int64_t N, int n_split, int64_t most = INT64_MAX) {
   const int64_t cus = 256;
   auto rounds_area = [&](int64_t bm, int64_t bn) {
     const int64_t items = (int64_t)ceil_div(M, bm) * ceil_div(N, bn) * n_split;
-    return (items + cus - 1) / cus * bm * bn;
+    return items > most && bm * bn < 256 * 256 ? INT64_MAX : (items + cus - 1) / cus * bm * bn;
   };
   const int64_t c1 = rounds_area(256, 256), c2 = rounds_area(192, 256), c3 = rounds_area(256, 192);
   if (c2 < c1 && c2 <= c3) return 2;
@@ -1570,6 +1574,7 @@ constexpr int64_t kUpdateMaxColumns = 1 << 21;   // 256 rows of them, 4 bytes ea
 // What the plan splits stays split, although a single sum with the update behind it can be faster (6144x2048 at 16384 tokens, 4 splits of
 // 192 tiles and a pass over V that reads four gradients 433 us; one sum that ends in it 403): rounding errors grow with the root of a
 // sum's length, and the gradient there was 7.9e-7 of its norm from 64 bits that way, 4.4e-7 as four partial sums.
+// A work item leaves one partial sum of the next step's losses, for which there are step_bwd_blocks(O K) slots.
 bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp) {
   const Plan p = plan_gemm(GemmDims{O, K, Tp, Tp, Tp}, true, kEpiF32);
   return p.n_split == 1 && p.items() >= kUpdateMinItems && p.items() <= step_bwd_blocks(O * K) && K <= kUpdateMaxColumns;
@@ -1652,7 +1657,7 @@ int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device) {
   const Plan p = plan_gemm(GemmDims{M, N, T, T, T}, true, kEpiF32);
   if (p.kind != KIND_L64) return 0;
   if (!fill_device) return 1;
-  return fewest_rounds(M, N, p.n_split);
+  return fewest_rounds(M, N, p.n_split, gemm_dw_updates(M, N, T) ? step_bwd_blocks(M * N) : INT64_MAX);
 }
 bool gemm_tn_usable(int64_t M, int64_t N, int64_t T) { return gemm_tn_tiles(M, N, T, false) != 0; }
 

@@ -10,9 +10,10 @@ from test_gpu_variants import ADAM, BETA, LAMBDA, _bf16, _check_gradient, _mm
 
 pytestmark = pytest.mark.gpu
 
-# (O, K, T, alone on the device): N64, S64, M64, L64 on transposed operands, the three token-major tiles; ragged edges in both directions
+# (O, K, T, alone on the device): N64, S64, M64, L64 on transposed operands, the three token-major tiles; ragged edges in both directions;
+# 1600 tiles of 256x256, for which there are slots for the next step's partial sums, and 2160 of 192x256, for which there are not
 DW = [(1056, 656, 64, False), (648, 2816, 64, False), (648, 5408, 64, False), (7176, 1088, 65, False), (7176, 1088, 64, False),
-      (7176, 1088, 64, True), (6224, 1808, 64, True)]
+      (7176, 1088, 64, True), (6224, 1808, 64, True), (5120, 20480, 64, True)]
 # M64, S64, then L64: 256x256, 192x256, 256x192; contractions that end inside a slice and that do not
 GRAM = [(6496, 656), (3912, 1088), (6496, 1232), (6496, 1808), (7176, 1664), (7176, 1088), (6632, 1232), (7040, 1664), (8128, 1376)]
 

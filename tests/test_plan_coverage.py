@@ -155,6 +155,27 @@ def test_token_major_dw_gemm_tiles_are_all_reached_by_parity_cases():
     assert {(1, "whole"), (1, "split")} <= full
 
 
+def test_products_that_update_v_have_a_slot_for_every_work_item():
+    """A work item of a dW product that ends in the pass over V leaves one partial sum of the next step's losses, and a step has one slot
+    for every 2048 weights, at most 2048: the tiles that a whole product is launched on are no more than that, whatever shape it takes."""
+    bm_bn = {1: (256, 256), 2: (192, 256), 3: (256, 192)}
+    rows = [96, 800, 2560, 5120, 6144, 6656, 8192, 10240, 14592, 16640, 17920, 18432, 20480, 24576, 65536]
+    seen = set()
+    for O, K, T in itertools.product(rows + [8 * n for n in range(600, 2600, 37)], [r // 16 * 16 for r in rows], [64, 512, 2048, 8192, 16384]):
+        if O * K > 2 ** 28 or O * K * T > 2 ** 42 or fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)[3] > 1:
+            continue
+        slots = min(2048, -(-O * K // 2048))
+        if -(-O // 256) * -(-K // 256) > slots:          # not even the planner's tiles have one each: a pass over V of its own
+            continue
+        for alone in (False, True):
+            tiles = fb.faar_dw_token_major(O, K, T, alone)
+            if tiles:
+                bm, bn = bm_bn[tiles]
+                assert -(-O // bm) * -(-K // bn) <= slots, (O, K, T, alone)
+                seen.add((alone, tiles))
+    assert seen == {(False, 1), (True, 1), (True, 2), (True, 3)}
+
+
 STAGES = {"L64": 2, "M64": 3, "S64": 4, "N64": 6}      # slices the ring of a tile shape holds
 
 
