@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "faar_copies.h"
 #include "faar_internal.h"
 #include "faar_step.h"
 
@@ -1212,11 +1213,11 @@ k_gemm_dma64(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDim
 // copies past the end of a tile are those of the next one's first slices, so that neither a tile's stores nor the latency of its first
 // copies stand by themselves.  The ring therefore stays in use during the epilogue, which goes without LDS: the copies place the rows of
 // B so that a lane's TN accumulator tiles are TN consecutive columns, and 16 lanes store a whole line.  The copies' addresses are buffer
-// descriptors with one offset a lane (rows beyond M or N read as zeros), which also leaves 20 registers more than pointers do.
+// descriptors with one 32-bit offset a lane and copy (RoundsCopy), half the registers of pointers.
 // A wavefront's stores count in the same in-order counter as its copies: those of the first two slices are older than the stores, and
 // the wait in the first slice's last phase covers both.
 // 16384x6144x2048, bf16 out: 321 -> 292 us between other kernels, 350 -> 332 with nothing but itself running (bound by power).  Whole
-// steps: 6144x2048 at 8192 tokens 407 -> 399, at 16384 781 -> 764, 8192x2048 at 4096 (two rounds) 304.5 -> 299.5, a block 5.52 -> 5.44 ms.
+// steps: 6144x2048 at 8192 tokens 407 -> 399, 8192x2048 at 4096 (two rounds) 304.5 -> 299.5; a block 1.4 %.
 typedef uint32_t u32x4r __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void dma16_buffer(u32x4r rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
@@ -1236,6 +1237,7 @@ __global__ void __launch_bounds__(C::THREADS)
 k_gemm_dma64_rounds(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d, int tiles_m, int tiles_n, Epi epi) {
   __shared__ __attribute__((aligned(1024))) bf16_t lds[C::NS * C::STAGE];
   static_assert(!C::kTokenA && !C::kTokenB && C::WGK == 1 && C::KK == 2 && C::NS == 2 && C::TN == 4, "NT, two phases, two stages");
+  static_assert(C::BM == C::BN, "one bound for the rows of either operand's tile");
   constexpr int P = C::P, NF = C::NF, NM = C::NM, TM = C::TM, TN = C::TN;
   static_assert((C::BM / 8) % P == 0, "a wavefront copies rows of one operand");
   epi.once();
@@ -1246,21 +1248,23 @@ k_gemm_dma64_rounds(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
   const int nk = static_cast<int>(d.Kd / DBK64);
   epi.begin();
 
-  // Copy u fills LDS rows 8 u .. 8 u + 7 of the stacked [A rows; B rows]: lane / 8 -> row, lane % 8 -> slot, chunk = slot ^ (row / 2) % 8
-  // as above, of which only bit 2 depends on u (its parity).  LDS row p of B's WN-row groups holds row TN * (p % 16) + p / 16 % TN.
+  // A wavefront's copies are u = wave P .. wave P + P - 1, all of one operand; their offsets are made anew for every tile
+  typedef RoundsCopy<C::BM, C::WN, TN> Copies;
+  static_assert(P % 2 == 0, "the parity of a copy is that of its number in the wavefront");
   const bool of_a = wave * P < C::BM / 8;
   const uint32_t ld2 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>((of_a ? d.lda : d.ldb) * 2));
-  const uint32_t v0 = (lane / 8) * (of_a ? 1 : TN) * ld2 + ((lane % 8) ^ (lane / 16)) * 16, v1 = v0 ^ 64u;
-  static_assert(P % 2 == 0, "the parity of a copy is that of its number in the wavefront");
   u32x4r rs;
+  uint32_t voff[P];
   auto set_tile = [&](int tm_, int tn_) {
-    const int64_t m0 = (int64_t)tm_ * C::BM, n0 = (int64_t)tn_ * C::BN;
-    rs = of_a ? buffer_of(A + m0 * d.lda, (d.M - m0) * d.lda * 2) : buffer_of(B + n0 * d.ldb, (d.N - n0) * d.ldb * 2);
+    const int64_t left = of_a ? d.M - (int64_t)tm_ * C::BM : d.N - (int64_t)tn_ * C::BN;
+    rs = of_a ? buffer_of(A + (int64_t)tm_ * C::BM * d.lda, left * ld2) : buffer_of(B + (int64_t)tn_ * C::BN * d.ldb, left * ld2);
+    const uint32_t rows = __builtin_amdgcn_readfirstlane(left < C::BM ? static_cast<uint32_t>(left) : C::BM);
+#pragma unroll
+    for (int q = 0; q < P; ++q) voff[q] = Copies::offset(wave * P + q, lane, rows, ld2);
   };
   auto copy = [&](int q, int slice, int stage) {
-    const int u = wave * P + q, ub = u - C::BM / 8;
-    const uint32_t row = of_a ? u * 8 : 8 * TN * (ub & 1) + (ub % (C::WN / 8)) / 2 + C::WN * (ub / (C::WN / 8));
-    dma16_buffer(rs, (q & 1) ? v1 : v0, __builtin_amdgcn_readfirstlane(row * ld2 + slice * (DBK64 * 2)),
+    const int u = wave * P + q;
+    dma16_buffer(rs, voff[q], __builtin_amdgcn_readfirstlane(slice * (DBK64 * 2)),
                  __builtin_amdgcn_readfirstlane(lds_addr_of(lds + stage * C::STAGE + u * C::RPI * DBK64)));
   };
   set_tile(tm, tn);
