@@ -108,10 +108,10 @@ class HipEvents:
 
 
 def product_updates_v(form, O, K, T) -> bool:
-    """Whether a step's dW (Gram-form) product ends in the pass over V, m, u: the library's rule for products that are not split."""
+    """Whether a step's dW (Gram-form) product ends in the pass over V, m, u, by the library's own answer."""
     from paper_2603_22370_amd import binding as fb
-    _, bm, bn, split = fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T) if form == "token" else fb.faar_gemm_plan(fb.K_GEMM_GRAM, O, K, 1)
-    return split == 1 and (-(-O // bm) * -(-K // bn) >= 96 if form == "token" else O * K >= 1 << 22)
+    which = (fb.K_GEMM_DW, T) if form == "token" else (fb.K_GEMM_GRAM, 1)
+    return fb.faar_gemm_form(which[0], O, K, which[1]) == fb.FORM_UPDATES_V
 
 
 class KernelTimer:
@@ -331,15 +331,19 @@ class LinearJob:
                 if step_bytes < 256e6:     # the step's working set fits the 256 MB Infinity Cache: not an HBM rate
                     out[name]["note"] = "effective rate: working set resident in the Infinity Cache"
             if name in ("gemm_dw", "gemm_gram") and "bwd_adam" not in probe:
-                # one kernel: the product and, in its epilogue, the pass over V, m, u without the gradient's 8 bytes a weight
+                # one kernel: the product and, in its epilogue, the pass over V, m, u without the gradient's 8 bytes a weight.  The rate
+                # above is the product's flops over the time of both; both_frac is the time that the two take at the peaks, one after
+                # the other, over the time they took
                 b = bpw["bwd_adam"] - 4 * (self.dw_split if self.form == "token" else self.gram_split)
                 out[name]["ends_in"] = "bwd_adam"
                 out[name]["update_bytes"] = int(b * N)
+                out[name]["both_frac"] = round((gemm_flops / (BF16_PEAK_TFLOPS * 1e12) + b * N / (HBM_PEAK_GBS * 1e9)) / (ms * 1e-3), 4)
             # the dW GEMM has its own counter rows for the 192-wide tiles a step takes when it has the device to itself
             from paper_2603_22370_amd import binding as fb
             wide = (name == "gemm_dw" and self.form == "token" and self.whole_device
                     and fb.faar_dw_token_major(self.O, self.K, self.T, True) in (2, 3))
-            out[name]["traffic"] = None if "ends_in" in out[name] else traffic_for(name + ("_whole_device" if wide else ""), self.O, self.K, self.T)
+            out[name]["traffic"] = traffic_for(name + ("_update" if "ends_in" in out[name] else "") + ("_whole_device" if wide else ""),
+                                               self.O, self.K, self.T)
         return out
 
 

@@ -169,6 +169,18 @@ int faar_dw_split(int64_t O, int64_t K, int64_t T);
  * prove that their cases reach every variant. */
 int faar_gemm_plan(int which, int64_t O, int64_t K, int64_t T, int32_t* out);
 
+/* In what form the library runs one of these GEMMs (`which` as for faar_gemm_plan): a sum of FAAR_FORM_*, 0 for a kernel of its own with
+ * one tile a workgroup, and for invalid arguments.  FAAR_K_GEMM_RESIDUAL and _RESIDUAL_H answer for steps with the layer's own gradient
+ * and no dX, FAAR_K_GEMM_DX for an operand W_q as faar_layer_step prepares it.  Pure host function. */
+enum {
+  FAAR_FORM_UPDATES_V = 1,    /* FAAR_K_GEMM_DW, FAAR_K_GEMM_GRAM: the product ends in the pass over V (FAAR_K_BWD_ADAM); the
+                               * Gram form's is then on 192-wide tiles where these need fewer rounds of the compute units */
+  FAAR_FORM_WALKS_TILES = 2,  /* 256 workgroups walk the tiles of the plan */
+  FAAR_FORM_WHOLE_STEP = 4,   /* the whole step is one launch: nothing of the plan applies */
+  FAAR_FORM_ON_COPY = 8       /* FAAR_K_GEMM_DX: on a transposed copy of W_q, with the kernels of FAAR_K_GEMM_FWD */
+};
+int faar_gemm_form(int which, int64_t O, int64_t K, int64_t T);
+
 /* Measurement hook for benchmarks: runs the main loop of the library's GEMM kernel on the product
  * acc[m][n] = sum_k A[m][k] B[n][k]  (A [M, Kd], B [N, Kd] bf16 row-major, Kd a multiple of 64) WITHOUT storing a result,
  * whole (mode 0), with only its matrix instructions (mode 1: the LDS stages are filled once and never refilled) or

@@ -81,6 +81,8 @@ def lib() -> ctypes.CDLL:
         L.faar_gemm_probe.restype = c_int
         L.faar_gemm_probe.argtypes = [c_int, c_int64, c_int64, c_int64, c_void_p, c_void_p, c_void_p, c_int64, c_void_p,
                                       ctypes.POINTER(c_int32), c_void_p]
+        L.faar_gemm_form.restype = c_int
+        L.faar_gemm_form.argtypes = [c_int, c_int64, c_int64, c_int64]
         L.faar_dw_token_major.restype = c_int
         L.faar_dw_token_major.argtypes = [c_int64, c_int64, c_int64, c_uint32]
         L.faar_padded_tokens.restype = c_int64
@@ -231,6 +233,14 @@ def faar_gemm_plan(which: int, O: int, K: int, T: int):
     out = (c_int32 * 4)()
     _check(lib().faar_gemm_plan(which, O, K, T, out), "faar_gemm_plan")
     return GEMM_KINDS[out[0] - GEMM_L64], int(out[1]), int(out[2]), int(out[3])
+
+
+FORM_UPDATES_V, FORM_WALKS_TILES, FORM_WHOLE_STEP, FORM_ON_COPY = 1, 2, 4, 8
+
+
+def faar_gemm_form(which: int, O: int, K: int, T: int) -> int:
+    """FORM_* of one GEMM of a layer of these sizes: what else its kernel does, or how it walks the plan's tiles."""
+    return int(lib().faar_gemm_form(which, O, K, T))
 
 
 PROBE_FULL, PROBE_MFMA_ONLY, PROBE_DMA_ONLY = 0, 1, 2

@@ -522,6 +522,24 @@ static bool transposed_dx(int64_t O, int64_t K, int64_t T) {
   return O >= 4096 && p.bm == 256 && p.bn == 256 && ((T + 255) / 256) * ((K + 255) / 256) < 192;
 }
 
+int faar_gemm_form(int which, int64_t O, int64_t K, int64_t T) {
+  if (check_shape(O, K) != FAAR_OK || T <= 0 || T > kMaxElems / (O > K ? O : K)) return 0;
+  const GemmDims forward{T, O, K, K, K};
+  switch (which) {
+    case FAAR_K_GEMM_RESIDUAL: return small_step(O, K, T) ? FAAR_FORM_WHOLE_STEP : 0;
+    case FAAR_K_GEMM_RESIDUAL_H:
+      if (small_step(O, K, T)) return FAAR_FORM_WHOLE_STEP;
+      return gemm_tn_usable(O, K, T) && gemm_bf16_walks(forward) ? FAAR_FORM_WALKS_TILES : 0;
+    case FAAR_K_GEMM_DW: return gemm_dw_updates(O, K, padded_tokens(T)) ? FAAR_FORM_UPDATES_V : 0;
+    case FAAR_K_GEMM_GRAM: return K <= kMaxElems / K && gemm_gram_updates(O, K) ? FAAR_FORM_UPDATES_V : 0;
+    case FAAR_K_GEMM_FWD: return gemm_bf16_walks(forward) ? FAAR_FORM_WALKS_TILES : 0;
+    case FAAR_K_GEMM_DX:
+      if (!transposed_dx(O, K, T)) return 0;
+      return FAAR_FORM_ON_COPY | (gemm_bf16_walks(GemmDims{T, K, O, O, round_up(O, 64)}) ? FAAR_FORM_WALKS_TILES : 0);
+    default: return 0;
+  }
+}
+
 int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const float* s_global,
                     const uint8_t* scales, float* V, float* adam_m, float* adam_v, const void* Xq, const float* x_scale,
                     const void* Xt, const float* C, const uint8_t* icodes, const float* H, const double* c_norm2,

@@ -1740,6 +1740,8 @@ hipError_t launch_gemm_bf16_nn(const bf16_t* A, const bf16_t* B, GemmDims d, bf1
   return run<true>(A, B, d, plan_gemm(d, false, kEpiBf16), e, st);
 }
 
+bool gemm_bf16_walks(const GemmDims& d) { return walks_rounds(d, plan_gemm(d, false, kEpiBf16)); }
+
 hipError_t launch_gemm_bf16(const bf16_t* A, const bf16_t* B, GemmDims d, bf16_t* out, const float* scale, hipStream_t st) {
   EpiBf16 e{out, scale, 1.0f};
   const Plan p = plan_gemm(d, false, kEpiBf16);

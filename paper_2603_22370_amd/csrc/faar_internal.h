@@ -258,7 +258,8 @@ int64_t gemm_gram_partials(int64_t O, int64_t K);
 hipError_t launch_gemm_gram(const bf16_t* delta, const bf16_t* gram, int64_t O, int64_t K, const float* diag_lo,
                             const float* x_scale, float two_alpha, float* out, int n_split, double* partials,
                             int64_t* n_partials, const ForwardGuard& guard, hipStream_t st);
-// out[m][n] = bf16(scale * acc), scale a device scalar (null = 1)
+// out[m][n] = bf16(scale * acc), scale a device scalar (null = 1); whether it walks its tiles (launch_gemm_residual_rows alike)
+bool gemm_bf16_walks(const GemmDims& d);
 hipError_t launch_gemm_bf16(const bf16_t* A, const bf16_t* B, GemmDims d, bf16_t* out, const float* scale,
                             hipStream_t st);
 // out[m][n] = bf16(sum_k A[m][k] B[k][n]), B [Kd, ldb] row-major; N, Kd multiples of 8

@@ -18,10 +18,14 @@ def _tiles(O, K, T):
 
 # three slices and more, odd and even numbers of them; 528 to 585 tiles; the last two on the kernel of one tile a workgroup (a width that
 # is not a multiple of 4, a contraction beyond 4096)
-@pytest.mark.parametrize("O,K,T", [(4092, 192, 8429), (4092, 256, 8429), (4100, 576, 8430), (2052, 320, 16389), (2051, 320, 16389),
-                                   (2056, 4160, 16389)])
+FORWARD = [(4092, 192, 8429), (4092, 256, 8429), (4100, 576, 8430), (2052, 320, 16389), (2051, 320, 16389), (2056, 4160, 16389)]
+STEP = [(4104, 1088, 8384), (6152, 1024, 6208)]
+
+
+@pytest.mark.parametrize("O,K,T", FORWARD)
 def test_forward(O, K, T):
     assert _tiles(O, K, T)[0] == "L64" and _tiles(O, K, T)[1] >= 512
+    assert (fb.faar_gemm_form(fb.K_GEMM_FWD, O, K, T) == fb.FORM_WALKS_TILES) == (O % 4 == 0 and K <= 4096)
     W, X, _, sg, scales, V, _ = _layer(O, K, T, torch.bfloat16)
     Wq = faar.faar_softquant_fwd_bwd(W, sg, scales, V, BETA)[0].double()
     got = faar.faar_linear_forward(W, sg, scales, V, BETA, X)
@@ -31,9 +35,10 @@ def test_forward(O, K, T):
         assert bool(((got[rows].double() - want).abs() <= U8 * want.abs() + (K + 2) * EPS * _mm(x.abs(), Wq.abs().T)).all())
 
 
-@pytest.mark.parametrize("O,K,T", [(4104, 1088, 8384), (6152, 1024, 6208)])
+@pytest.mark.parametrize("O,K,T", STEP)
 def test_residual_of_a_step(O, K, T):
     assert _tiles(O, K, T)[0] == "L64" and _tiles(O, K, T)[1] >= 512 and fb.faar_dw_token_major(O, K, T)
+    assert fb.faar_gemm_form(fb.K_GEMM_RESIDUAL_H, O, K, T) == fb.FORM_WALKS_TILES
     W, X, Y, sg, scales, V, _ = _layer(O, K, T, torch.bfloat16)
     Xt, C, icodes, H, c_norm2 = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
     c = C.flatten()[:(T + 3) // 4 * 4 * O].view(-1, O, 4).permute(0, 2, 1).reshape(-1, O).double()[:T]

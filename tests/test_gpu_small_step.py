@@ -4,19 +4,22 @@ import pytest
 import torch
 
 import paper_2603_22370_amd as faar
+from paper_2603_22370_amd import binding as fb
 from test_gpu_update_in_product import _layer, _steps
 from test_gpu_variants import ADAM, BETA, LAMBDA, _bf16, _check_gradient, _mm
 
 pytestmark = pytest.mark.gpu
 
-# the last two are beyond it
-SHAPES = [(1, 16, 1), (16, 32, 16), (17, 48, 63), (250, 256, 64), (256, 256, 64), (33, 240, 65), (1024, 256, 64), (1000, 144, 113),
-          (64, 1024, 16), (128, 16, 1024), (512, 80, 200), (256, 272, 64), (256, 128, 129)]
+SHAPES = [(1, 16, 1), (16, 32, 16), (250, 256, 64), (256, 256, 64), (33, 240, 65), (1024, 256, 64), (1000, 144, 113),
+          (64, 1024, 16), (16, 32, 400), (9, 16, 1024)]
+# more activations than it takes, or more workgroups than there are slots for the next step's sums
+BEYOND = [(256, 272, 64), (256, 128, 129), (17, 48, 63), (128, 16, 1024), (512, 80, 200)]
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("O,K,T", SHAPES)
+@pytest.mark.parametrize("O,K,T", SHAPES + BEYOND)
 def test_small_step(O, K, T, dtype):
+    assert fb.faar_gemm_form(fb.K_GEMM_RESIDUAL, O, K, T) == (fb.FORM_WHOLE_STEP if (O, K, T) in SHAPES else 0)
     W, X, Y, sg, scales, V0, _ = _layer(O, K, T, dtype)
     Xt, C, icodes, H, c_norm2 = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
     alpha = 1.0 / (T * O)

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 DW = [(1056, 656, 64, False), (648, 2816, 64, False), (648, 5408, 64, False), (7176, 1088, 65, False), (7176, 1088, 64, False),
       (7176, 1088, 64, True), (6224, 1808, 64, True), (5120, 20480, 64, True)]
 # M64, S64, then L64: 256x256, 192x256, 256x192; contractions that end inside a slice and that do not
-GRAM = [(6496, 656), (3912, 1088), (6496, 1232), (6496, 1808), (7176, 1664), (7176, 1088), (6632, 1232), (7040, 1664), (8128, 1376)]
+GRAM = [(6496, 656), (3912, 1088), (6496, 1232), (6496, 1808), (7176, 1664), (7176, 1088), (6632, 1232), (7040, 1664), (8128, 1376),
+        (8280, 1392)]
 
 
 def _layer(O, K, T, dtype):
@@ -44,7 +45,7 @@ def _steps(step, V0, prepared, betas=(BETA, 13.0, 14.5)):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("O,K,T,alone", DW)
 def test_weight_gradient_that_updates_v(O, K, T, alone, dtype):
-    assert fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)[3] == 1
+    assert fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)[3] == 1 and fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T) == fb.FORM_UPDATES_V
     W, X, Y, sg, scales, V0, gen = _layer(O, K, T, dtype)
     Xt, C, icodes, H, c_norm2 = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
     alpha = 1.0 / (T * O)
@@ -105,6 +106,7 @@ def test_planned_splits_stay_split(O, K, alone):
 def test_gram_product_that_updates_v(O, K, dtype):
     T = 192
     assert O * K >= 1 << 22 and fb.faar_gemm_plan(fb.K_GEMM_GRAM, O, K, 1)[3] == 1
+    assert fb.faar_gemm_form(fb.K_GEMM_GRAM, O, K, 1) == fb.FORM_UPDATES_V
     W, X, Y, sg, scales, V0, _ = _layer(O, K, T, dtype)
     Xt, C, icodes, H, c_norm2 = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
     gram, gram_lo = fb.faar_gram_prepare(Xt, T)

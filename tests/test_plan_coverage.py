@@ -9,6 +9,9 @@ import itertools
 from paper_2603_22370_amd import binding as fb
 
 from parity_cases import GRAM_CASES, STEP_CASES, VARIANT_SHAPES
+from test_gpu_rounds import FORWARD as WALKED_FORWARD, STEP as WALKED_STEP
+from test_gpu_small_step import SHAPES as SMALL_SHAPES
+from test_gpu_update_in_product import DW as UPDATE_DW, GRAM as UPDATE_GRAM
 
 GEMMS = {"residual": fb.K_GEMM_RESIDUAL, "dw": fb.K_GEMM_DW, "dx": fb.K_GEMM_DX, "c": fb.K_GEMM_C}
 DIMS = [16, 32, 48, 64, 80, 96, 128, 160, 192, 224, 256, 288, 320, 384, 448, 512, 640, 768, 1024, 1280, 1536, 2048,
@@ -162,11 +165,11 @@ def test_products_that_update_v_have_a_slot_for_every_work_item():
     rows = [96, 800, 2560, 5120, 6144, 6656, 8192, 10240, 14592, 16640, 17920, 18432, 20480, 24576, 65536]
     seen = set()
     for O, K, T in itertools.product(rows + [8 * n for n in range(600, 2600, 37)], [r // 16 * 16 for r in rows], [64, 512, 2048, 8192, 16384]):
-        if O * K > 2 ** 28 or O * K * T > 2 ** 42 or fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)[3] > 1:
+        if O * K > 2 ** 28 or O * K * T > 2 ** 42 or fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T) != fb.FORM_UPDATES_V:
             continue
         slots = min(2048, -(-O * K // 2048))
-        if -(-O // 256) * -(-K // 256) > slots:          # not even the planner's tiles have one each: a pass over V of its own
-            continue
+        _, bm, bn, split = fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)
+        assert split == 1 and -(-O // bm) * -(-K // bn) <= slots, (O, K, T)
         for alone in (False, True):
             tiles = fb.faar_dw_token_major(O, K, T, alone)
             if tiles:
@@ -188,28 +191,71 @@ def _instantiation(epilogue, which, contraction, O, K, T):
     return (epilogue, kind, "split" if split > 1 else "one", ends, "wraps" if -(-slices // split) > STAGES[kind] else "short")
 
 
-def _instantiations(O, K, T, chained=True, forward=True):
-    """Everything a layer's set-up, steps (both forms; chained: also with an upstream gradient and dX), Gram-form step and forward run."""
-    yield _instantiation("residual", fb.K_GEMM_RESIDUAL, K, O, K, T)
-    yield _instantiation("rows" if fb.faar_dw_token_major(O, K, T) else "perturbation", fb.K_GEMM_RESIDUAL_H, K, O, K, T)
-    yield _instantiation("dw", fb.K_GEMM_DW, (T + 63) // 64 * 64, O, K, T)
+def _widths(O, K):
+    """The tile of a Gram-form product that ends in the pass over V, where the plan says 256x256: rounds of 256 units, by area."""
+    cost = {(bm, bn): -(-(-(-O // bm) * -(-K // bn)) // 256) * bm * bn for bm, bn in ((256, 256), (192, 256), (256, 192))}
+    return min(cost, key=lambda t: (cost[t], t != (256, 256), t != (192, 256)))
+
+
+def _gram_instantiation(O, K):
+    x = _instantiation("gram", fb.K_GEMM_GRAM, K, O, K, 1)
+    if fb.faar_gemm_form(fb.K_GEMM_GRAM, O, K, 1) & fb.FORM_UPDATES_V:
+        assert x[2] == "one"
+        return ("gram, update", _widths(O, K) if x[1] == "L64" else x[1], x[3])
+    return x
+
+
+def _dw_instantiations(O, K, T, alone, nt=True):
+    """The dW product on transposed operands (nt: where a step of the caller's takes them) and on the token-major ones."""
+    x = _instantiation("dw", fb.K_GEMM_DW, (T + 63) // 64 * 64, O, K, T)
+    tiles = fb.faar_dw_token_major(O, K, T, alone)
+    if fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T) & fb.FORM_UPDATES_V:
+        assert x[2] == "one"
+        if nt or not tiles:
+            yield ("update", x[1])
+        if tiles:
+            yield ("update", f"token-major {tiles}")
+    elif nt or not tiles:
+        yield x
+
+
+def _walk(epilogue, which, contraction, O, K, T):
+    if fb.faar_gemm_form(which, O, K, T) & fb.FORM_WALKS_TILES:
+        assert fb.faar_gemm_plan(which, O, K, T)[0] == "L64" and contraction % 64 == 0
+        return (epilogue + ", walked", "odd" if contraction // 64 % 2 else "even")
+    return _instantiation(epilogue, which, contraction, O, K, T)
+
+
+def _instantiations(O, K, T, chained=True, forward=True, alone=(False,), own_dx=True):
+    """Everything a layer's set-up, steps (both forms; chained: also with an upstream gradient and dX; own_dx: with dX of their own
+    gradient), Gram-form step and forward run."""
+    small = fb.faar_gemm_form(fb.K_GEMM_RESIDUAL, O, K, T) & fb.FORM_WHOLE_STEP
+    if small:
+        yield ("small", "one group of columns" if K <= 256 else "more", "one group of tokens" if T <= 256 else "more")
+    else:
+        yield _walk("rows" if fb.faar_dw_token_major(O, K, T) else "perturbation", fb.K_GEMM_RESIDUAL_H, K, O, K, T)
+    if not small or chained and own_dx:
+        yield _instantiation("residual", fb.K_GEMM_RESIDUAL, K, O, K, T)
+    if not small or chained:
+        for a in alone:
+            yield from _dw_instantiations(O, K, T, a)
     yield _instantiation("c", fb.K_GEMM_C, K, O, K, T)
-    yield _instantiation("gram", fb.K_GEMM_GRAM, K, O, K, 1)
+    yield _gram_instantiation(O, K)
     if chained:
         yield _instantiation("loss", fb.K_GEMM_LOSS, K, O, K, T)
         yield _instantiation("loss_h", fb.K_GEMM_LOSS_H, K, O, K, T)
         # wide layers of many tokens, and products that fill less than three quarters of the chip with 256x256 tiles: on a transposed
         # copy of W_q, with the kernels of the forward
-        few = fb.faar_gemm_plan(fb.K_GEMM_DX, O, K, T)[0] == "L64" and -(-T // 256) * -(-K // 256) < 192
-        on_copy = T * O >= K * ((O + 63) // 64 * 64) and (O >= 512 and K >= 4096 and T >= 16384 and T >= 2 * K or O >= 4096 and few)
-        yield _instantiation("forward" if on_copy else "dx", fb.K_GEMM_DX, O, O, K, T)
+        on_copy = fb.faar_gemm_form(fb.K_GEMM_DX, O, K, T) & fb.FORM_ON_COPY
+        yield _walk("forward" if on_copy else "dx", fb.K_GEMM_DX, O, O, K, T)
     if forward:
-        yield _instantiation("forward", fb.K_GEMM_FWD, K, O, K, T)
+        yield _walk("forward", fb.K_GEMM_FWD, K, O, K, T)
 
 
 def test_every_gemm_instantiation_is_compared_with_an_oracle():
     """Over layer shapes that end in every place of a slice, the epilogues that only some steps use among them: each instantiation that
-    a shape reaches is run by a parity case or by tests/test_gpu_variants.py."""
+    a shape reaches is run by a parity case, by tests/test_gpu_variants.py or by the tests of the products that update V, walk their
+    tiles or are a whole step."""
     outs = [16, 48, 64, 96, 160, 256, 272, 320, 432, 640, 1000, 1040, 1280, 2048, 3072, 4096, 6144, 8192, 12288, 14336]
     ins = [16, 32, 48, 64, 80, 112, 144, 176, 192, 240, 256, 272, 304, 320, 432, 528, 560, 640, 1024, 1040, 1072, 2048, 2064, 2096,
            3072, 4112, 4144, 5584, 5616, 6144]
@@ -217,15 +263,22 @@ def test_every_gemm_instantiation_is_compared_with_an_oracle():
     reachable = {}
     for O, K, T in itertools.product(outs, ins, tokens):
         if O * K * T <= 2 ** 38:
-            for x in _instantiations(O, K, T):
+            for x in _instantiations(O, K, T, alone=(False, True)):
                 reachable.setdefault(x, (O, K, T))
-    covered = {_instantiation("gram", fb.K_GEMM_GRAM, c.K, c.O, c.K, 1) for c in GRAM_CASES}
+    covered = {_gram_instantiation(c.O, c.K) for c in GRAM_CASES}
     for c in STEP_CASES:
-        covered.update(_instantiations(c.O, c.K, c.T, c.chained, False))
+        covered.update(_instantiations(c.O, c.K, c.T, c.chained, False, (c.whole_device,), own_dx=False))
     for O, K, T in FORWARD_CASES:
-        covered.add(_instantiation("forward", fb.K_GEMM_FWD, K, O, K, T))
+        covered.add(_walk("forward", fb.K_GEMM_FWD, K, O, K, T))
     for shape in VARIANT_SHAPES:
         covered.update(_instantiations(*shape))
+    for O, K, T, alone in UPDATE_DW:
+        covered.update(_dw_instantiations(O, K, T, alone, nt=False))
+    covered.update(_gram_instantiation(O, K) for O, K in UPDATE_GRAM)
+    covered.update(x for O, K, T in SMALL_SHAPES for x in _instantiations(O, K, T, False, False) if x[0] == "small")
+    covered.update(_walk("forward", fb.K_GEMM_FWD, K, O, K, T) for O, K, T in WALKED_FORWARD)
+    covered.update(_walk("rows", fb.K_GEMM_RESIDUAL_H, K, O, K, T) for O, K, T in WALKED_STEP)
     missing = {k: v for k, v in reachable.items() if k not in covered}
     assert not missing, f"instantiations that no test compares (with an example shape): {missing}"
-    assert {k[0] for k in reachable} == {"residual", "rows", "perturbation", "dw", "c", "gram", "loss", "loss_h", "dx", "forward"}
+    assert {k[0] for k in reachable} == {"residual", "rows", "rows, walked", "perturbation", "dw", "update", "c", "gram", "gram, update",
+                                         "loss", "loss_h", "dx", "forward", "forward, walked", "small"}
