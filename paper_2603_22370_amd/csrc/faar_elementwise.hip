@@ -98,14 +98,14 @@ __device__ __forceinline__ uint32_t encode_e2m1x8(const float (&w)[8], const Blo
 }
 
 // Round-to-nearest quantisation (Sec. 3.1; Table 2 steps 2-3).  Both lanes of an even/odd pair must be active.
-template <typename WT, bool kDequant>
+template <typename WT, bool kDequant, bool kFast>
 __device__ __forceinline__ void quant_chunk(const float (&w)[8], int64_t i, float sg, uint8_t* __restrict__ scales,
                                             uint32_t* __restrict__ codes, WT* __restrict__ W_dq, bool dq_in_units) {
   float a = 0.0f;
 #pragma unroll
   for (int j = 0; j < 8; ++j) a = fmaxf(a, fabsf(w[j]));
   a = pair_max(a);
-  const uint32_t byte = block_scale_byte_fast(a, sg);
+  const uint32_t byte = kFast ? block_scale_byte_fast(a, sg) : block_scale_byte(a, sg);
   const float sgv = e4m3_value(byte);
   const float s = sgv * sg;
   uint32_t packed = 0;
@@ -212,7 +212,7 @@ k_quant_rtn(const WT* __restrict__ W, int64_t n8, const float* __restrict__ s_gl
   if (i >= n8) return;  // n8 is even: both lanes of a pair leave together
   float w[8];
   W8<WT>::load_stream(W + i * 8, w);
-  quant_chunk<WT, kDequant>(w, i, *s_global_p, scales, codes, W_dq, dq_in_units);
+  quant_chunk<WT, kDequant, true>(w, i, *s_global_p, scales, codes, W_dq, dq_in_units);
 }
 
 template <typename WT>
@@ -254,7 +254,8 @@ __device__ __forceinline__ int batch_item(const CodecBatch& B, uint32_t block) {
 // before the first is looked at, and leaves one partial maximum; k_batch_amax_final (one workgroup per tensor) finishes them.  The
 // pass is bound by the bytes in flight: with 64 workgroups a tensor, whatever its size, and a chunk at a time, the large tensors had a
 // dozen loads a compute unit on their way (28 tensors of 201 M bf16 weights: 122 us, 3.3 TB/s; now 70 us, 5.8 TB/s).
-template <typename WT>
+// kKeep: the quantise pass finds the weights in the last-level cache.
+template <typename WT, bool kKeep>
 __global__ void __launch_bounds__(kEltThreads) k_batch_amax_partial(CodecBatch B, float* __restrict__ partials) {
   const int item = batch_item(B, blockIdx.x);
   const WT* W = static_cast<const WT*>(B.it[item].W);
@@ -268,7 +269,8 @@ __global__ void __launch_bounds__(kEltThreads) k_batch_amax_partial(CodecBatch B
 #pragma unroll
     for (int c = 0; c < kBatchChunks; ++c) {
       const int64_t i = i0 + c * kEltThreads;
-      W8<WT>::load_stream(W + (i < end ? i : i0) * 8, w[c]);
+      if (kKeep) W8<WT>::load(W + (i < end ? i : i0) * 8, w[c]);
+      else W8<WT>::load_stream(W + (i < end ? i : i0) * 8, w[c]);
     }
 #pragma unroll
     for (int c = 0; c < kBatchChunks; ++c)
@@ -301,23 +303,28 @@ __global__ void __launch_bounds__(kEltThreads) k_batch_amax_final(CodecBatch B, 
   }
 }
 
-// Four chunks a thread, their loads first: with one, 48 workgroups follow each other on every slot of the chip, each a chain of loads
-// (its tensor, the tensor's scale, the weights) of 2.3 us.  The far end of the tensors, where the amax pass ended, comes first.
+// Four chunks a thread (kChunks 1: see kBatchKeepBytes), their loads first: with one, 48 workgroups follow each other on every slot of
+// the chip, each a chain of loads (its tensor, the tensor's scale, the weights) of 2.3 us.  The far end of the tensors, where the amax pass ended, comes first.
 // 201 M bf16 weights: 112.6 -> 108.8 us, and 118 in the other order.
-template <typename WT>
+template <typename WT, int kChunks>
 __global__ void __launch_bounds__(kEltThreads) k_batch_quant_rtn(CodecBatch B) {
-  const uint32_t block = gridDim.x - 1 - blockIdx.x;
+  const uint32_t block = kChunks > 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
   const int item = batch_item(B, block);
   const CodecItem& t = B.it[item];
-  const int64_t first = (block - B.first_block[item]) * (int64_t)(kBatchChunks * kEltThreads) + threadIdx.x;
-  float w[kBatchChunks][8];
+  const int64_t first = (block - B.first_block[item]) * (int64_t)(kChunks * kEltThreads) + threadIdx.x;
+  float w[kChunks][8];
+  if constexpr (kChunks == 1) {
+    if (first >= t.n8) return;
+    W8<WT>::load_stream(static_cast<const WT*>(t.W) + first * 8, w[0]);
+    return quant_chunk<WT, false, false>(w[0], first, *t.s_global, t.scales, t.codes, nullptr, false);
+  }
 #pragma unroll
-  for (int c = 0; c < kBatchChunks; ++c)
+  for (int c = 0; c < kChunks; ++c)
     if (first + c * kEltThreads < t.n8) W8<WT>::load(static_cast<const WT*>(t.W) + (first + c * kEltThreads) * 8, w[c]);
   const float sg = *t.s_global;
 #pragma unroll
-  for (int c = 0; c < kBatchChunks; ++c)
-    if (first + c * kEltThreads < t.n8) quant_chunk<WT, false>(w[c], first + c * kEltThreads, sg, t.scales, t.codes, nullptr, false);
+  for (int c = 0; c < kChunks; ++c)
+    if (first + c * kEltThreads < t.n8) quant_chunk<WT, false, true>(w[c], first + c * kEltThreads, sg, t.scales, t.codes, nullptr, false);
 }
 
 template <typename WT>
@@ -833,6 +840,10 @@ hipError_t launch_quant_rtn(const void* W, bool w_bf16, int64_t n, const float* 
   return hipGetLastError();
 }
 
+// Tensors of up to 64 MB together: the amax pass leaves them in the last-level cache and the quantise kernel takes a chunk a thread, on
+// four times as many workgroups (the two passes, us, this way / streamed: 0.6 M bf16 weights 9.0 / 11.4, 6.7 M in two launches 23.5 /
+// 27.1, 14.7 M 20.8 / 23.6, 29.5 M 37.4 / 37.9; 60 M 67.2 / 62.3, 117 M 131 / 111, 201 M 210 / 176)
+constexpr int64_t kBatchKeepBytes = (int64_t)1 << 26;
 // the workgroups of a launch in which each takes `chunks` chunks of one tensor
 static dim3 batch_grid(CodecBatch& B, int64_t chunks) {
   uint32_t blocks = 0;
@@ -848,19 +859,32 @@ hipError_t launch_codec_batch(int op, CodecBatch& B, bool w_bf16, bool sglobal_g
   const dim3 b(kEltThreads);
   constexpr int64_t kGroup = (int64_t)kBatchChunks * kEltThreads;
   if (op == kBatchQuant) {
+    int64_t bytes = 0;
+    for (int k = 0; k < B.n; ++k) bytes += B.it[k].n8 * (w_bf16 ? 16 : 32);
+    const bool keep = bytes <= kBatchKeepBytes;
     if (!sglobal_given) {
       // as many groups a workgroup as leave room for every tensor's last one among the partial maxima
       int64_t groups = 0;
       for (int k = 0; k < B.n; ++k) groups += (B.it[k].n8 + kGroup - 1) / kGroup;
       B.per_wg = (groups + kBatchPartials - kBatchMax - 1) / (kBatchPartials - kBatchMax);
       const dim3 ga = batch_grid(B, B.per_wg * kGroup);
-      if (w_bf16) hipLaunchKernelGGL(k_batch_amax_partial<bf16_t>, ga, b, 0, st, B, partials);
-      else hipLaunchKernelGGL(k_batch_amax_partial<float>, ga, b, 0, st, B, partials);
+#define FAAR_AMAX(WT)                                                                                 \
+  do {                                                                                                \
+    if (keep) hipLaunchKernelGGL((k_batch_amax_partial<WT, true>), ga, b, 0, st, B, partials);        \
+    else hipLaunchKernelGGL((k_batch_amax_partial<WT, false>), ga, b, 0, st, B, partials);            \
+  } while (0)
+      if (w_bf16) FAAR_AMAX(bf16_t); else FAAR_AMAX(float);
+#undef FAAR_AMAX
       hipLaunchKernelGGL(k_batch_amax_final, dim3(static_cast<unsigned>(B.n)), b, 0, st, B, partials);
     }
-    const dim3 g = batch_grid(B, kGroup);
-    if (w_bf16) hipLaunchKernelGGL(k_batch_quant_rtn<bf16_t>, g, b, 0, st, B);
-    else hipLaunchKernelGGL(k_batch_quant_rtn<float>, g, b, 0, st, B);
+    const dim3 g = batch_grid(B, keep ? kEltThreads : kGroup);
+#define FAAR_QUANT(WT)                                                                                \
+  do {                                                                                                \
+    if (keep) hipLaunchKernelGGL((k_batch_quant_rtn<WT, 1>), g, b, 0, st, B);                         \
+    else hipLaunchKernelGGL((k_batch_quant_rtn<WT, kBatchChunks>), g, b, 0, st, B);                   \
+  } while (0)
+    if (w_bf16) FAAR_QUANT(bf16_t); else FAAR_QUANT(float);
+#undef FAAR_QUANT
     return hipGetLastError();
   }
   const dim3 g = batch_grid(B, kEltThreads);

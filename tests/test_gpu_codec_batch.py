@@ -20,11 +20,11 @@ def _quantise(Ws, given=None):
     return [[t.cpu().numpy() for t in ts] for ts in zip(sgs, scs, cds)]
 
 
-@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-def test_largest_weight_at_the_ends_of_the_groups(dtype):
+@pytest.mark.parametrize("dtype,large", [(torch.bfloat16, 700), (torch.float32, 700), (torch.bfloat16, 3), (torch.float32, 3)])
+def test_largest_weight_at_the_ends_of_the_groups(dtype, large):
     """One tensor per case, the largest weight its last one, its group's first, or the last of a full group; 72 in one launch, so that
-    large tensors beside small ones make a workgroup walk several groups."""
-    sizes = [16, GROUP - 16, GROUP, GROUP + 16, 2 * GROUP + 16, 700 * GROUP + 48] * 12
+    large tensors beside small ones make a workgroup walk several groups; streamed (700) and within 64 MB (3)."""
+    sizes = [16, GROUP - 16, GROUP, GROUP + 16, 2 * GROUP + 16, large * GROUP + 48] * 12
     gen = torch.Generator(device="cuda").manual_seed(5)
     Ws = []
     for k, n in enumerate(sizes):
@@ -38,17 +38,19 @@ def test_largest_weight_at_the_ends_of_the_groups(dtype):
             assert np.array_equal(cd, q["codes"].ravel()) and np.array_equal(sc, q["scales"].ravel()), k
 
 
+@pytest.mark.parametrize("streamed", [False, True])
 @pytest.mark.parametrize("scale", [1e-30, 1e-19, 1.0, 1e19, 1e30])
 @pytest.mark.parametrize("sg", [1e-25, 3e-4, 1.0, 1e25])
-def test_block_scale_bytes_at_any_size(scale, sg):
-    """The block scale is E4M3((amax / 6) / s_global) by IEEE divisions: amax over 24 binades, zero blocks and exact ties among them."""
+def test_block_scale_bytes_at_any_size(scale, sg, streamed):
+    """The block scale is E4M3((amax / 6) / s_global) by IEEE divisions: amax over 24 binades, zero blocks and exact ties among them.
+    streamed: in a launch over more than 64 MB, whose kernel makes the quotients through reciprocals."""
     gen = torch.Generator(device="cuda").manual_seed(9)
     a = torch.randn((64, 16), generator=gen, device="cuda") * torch.exp2(torch.arange(64, device="cuda") * 24.0 / 64 - 12.0)[:, None]
     a[3] = 0.0
     W = a * scale
     W[4, :] = 6.0 * 1.0625 * float(np.float32(sg))     # a tie between two E4M3 values where nothing rounds
     W = W.reshape(1, -1).contiguous()
-    _, sc, _ = _quantise([W], given=sg)[0]
+    _, sc, _ = _quantise([W] + [torch.zeros((1, 1 << 24), device="cuda")] * streamed, given=sg)[0]
     with np.errstate(over="ignore", under="ignore"):
         want = fo.block_scale_bytes(W.cpu().numpy(), np.float32(sg))
     assert np.array_equal(sc, np.asarray(want, dtype=np.uint8).ravel())
