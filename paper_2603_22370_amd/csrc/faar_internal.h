@@ -185,7 +185,7 @@ hipError_t launch_attention_bwd(const bf16_t* dO, const bf16_t* Q, const bf16_t*
 
 // ---- a whole step of a small layer in one launch (faar_small.hip): the step's own loss and dY, no dX; a.delta_next is the W_q - W that
 // the step reads.  C null: the constant is carried as a.H.  partials: one double per 16 rows
-constexpr int64_t kSmallMax = 1 << 14;
+constexpr int64_t kSmallMax = 1 << 15;   // activations
 bool small_step(int64_t O, int64_t K, int64_t T);
 hipError_t launch_small_step(const bf16_t* X, const bf16_t* Xt, const float* C, int64_t O, int64_t K, int64_t T, float two_alpha,
                              double* partials, const ForwardGuard& guard, StepBwdArgs a, hipStream_t st);

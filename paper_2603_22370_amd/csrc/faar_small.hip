@@ -3,8 +3,10 @@
 // Rows of a layer are independent: a row's residuals, its gradient and its update need that row's weights and all activations.  A
 // workgroup takes 16 rows from the residual through the update, so nothing waits for another launch: what bounds such a step is the
 // chain of loads, barriers and launches, not bytes or operations.  The gradient dY stays in LDS, G in the accumulators.  The losses
-// are added up by the workgroup that is done last.
-// 256x256 float32 at 64 tokens: 17.0 us a step in three launches (19 of host time) -> 12.8 (12); 1024x256 at 64: 16.7 -> 14.2.
+// are added up by the workgroup that is done last.  A sum is two, of the even and of the odd groups of 32 terms, as in the small tiles of
+// the products: the same bits as in three launches.
+// 256x256 float32 at 64 tokens, steps of a running chain: 17.0 us in three launches (19 of host time) -> 12.8 (12); 1024x256 at 64: 16.7 ->
+// 14.2.  A layer's first step has its forward in a launch of its own before it.
 #include <type_traits>
 
 #include "faar_internal.h"
@@ -97,7 +99,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_step(SmallStep a) {
     const int tx = t0 + col < a.T ? t0 + col : a.T - 1, tg = t0 + 4 * rq;
     float4 c = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (a.C && row && tg < a.T) c = *reinterpret_cast<const float4*>(a.C + ((int64_t)(tg >> 2) * a.O + o) * 4);
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, odd = acc;
     const bf16_t* xrow = a.X + (int64_t)tx * a.K;
     for (int k0 = 8 * rq; k0 - 8 * rq < a.K; k0 += 256) {
       bf16x8 fx[8], fd[8];
@@ -108,8 +110,12 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_step(SmallStep a) {
         fd[s] = frag(drow + k, k < a.K);
       }
 #pragma unroll
-      for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[s], fd[s], acc, 0, 0, 0);
+      for (int s = 0; s < 8; s += 2) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[s], fd[s], acc, 0, 0, 0);
+        odd = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[s + 1], fd[s + 1], odd, 0, 0, 0);
+      }
     }
+    acc += odd;
     const float cc[4] = {c.x, c.y, c.z, c.w};
     uint32_t b[4];
     float sum = 0.0f;
@@ -135,19 +141,23 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_step(SmallStep a) {
       fetch_state(k0);
       fetch_x(k0, 0);
     }
-    f32x4 g0 = {0.0f, 0.0f, 0.0f, 0.0f}, g1 = g0;
+    f32x4 g0 = {0.0f, 0.0f, 0.0f, 0.0f}, g1 = g0, odd0 = g0, odd1 = g0;
     for (int t0 = 0;;) {
 #pragma unroll
-      for (int s = 0; s < 8; ++s)
-        if (t0 + 32 * s < a.Tp) {
-          const bf16x8 y = *reinterpret_cast<const bf16x8*>(yr + t0 + 32 * s);
+      for (int s = 0; s < 8; s += 2)
+        if (t0 + 32 * s < a.Tp) {                                  // Tp is a multiple of 64
+          const bf16x8 y = *reinterpret_cast<const bf16x8*>(yr + t0 + 32 * s), z = *reinterpret_cast<const bf16x8*>(yr + t0 + 32 * s + 32);
           g0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[s], y, g0, 0, 0, 0);
           g1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[s], y, g1, 0, 0, 0);
+          odd0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[s + 1], z, odd0, 0, 0, 0);
+          odd1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[s + 1], z, odd1, 0, 0, 0);
         }
       t0 += 256;
       if (t0 >= a.Tp) break;
       fetch_x(k0, t0);
     }
+    g0 += odd0;
+    g1 += odd1;
     if (in) {
       float g[8] = {g0[0], g0[1], g0[2], g0[3], g1[0], g1[1], g1[2], g1[3]};
       if (p.H) {
@@ -215,11 +225,15 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_step(SmallStep a) {
 
 }  // namespace
 
-// Every workgroup reads all activations twice, at the 20 GB/s or so that one compute unit gets from beyond its die's L2: up to 2^14 of
-// them that costs less than two launches (us in three launches / in one: 256x256 at 64 tokens 17.0 / 12.8, 1024x256 at 64 16.7 / 14.2,
-// 256x256 at 128 16.4 / 16.2, 512x256 at 128 16.6 / 16.4, 256x512 at 64 17.4 / 19.9, 256x256 at 256 17.7 / 23.3)
+// Every workgroup reads all activations twice, at the 20 GB/s or so that one compute unit gets from beyond its die's L2: up to 2^15 of
+// them that costs less than two launches, as long as a wavefront has one group of 32 columns to update (time in one launch over that
+// in three, 256 / 1024 / 4096 outputs, K inputs by T tokens: 256x64 0.77 / 0.83 / 0.84, 128x256 0.87 / 0.90 / 1.00, 256x128 0.95 / 1.00 /
+// 0.97; 128x384 1.04 / 1.04 / 1.07, 192x192 0.97 / 1.03 / 1.04, 256x192 1.10 / 1.13 / 1.04).  With two groups up to 320 inputs and 64 tokens
+// (320x64 0.93 / 0.97 / 0.92; 384x64 0.99 / 1.01 / 0.93, 320x96 1.10 / 1.12 / 1.02, 512x32 1.12 / 1.05 / -, 1024x16 - / 1.29 / -).
+// From 1024 tokens on the plan may split the sums over them, which this kernel does not.
+// And no more workgroups than there are slots for the next step's sums, one for 2048 weights: with fewer than 128 inputs up to 16 outputs.
 bool small_step(int64_t O, int64_t K, int64_t T) {
-  return O <= 1024 && K <= 1024 && T <= 1024 && T * K <= kSmallMax && (O + kSmallRows - 1) / kSmallRows <= step_bwd_blocks(O * K);
+  return O <= 4096 && K <= 320 && padded_tokens(T) < 1024 && (K <= 256 ? T * K <= kSmallMax : T <= 64) && (O + kSmallRows - 1) / kSmallRows <= step_bwd_blocks(O * K);
 }
 
 hipError_t launch_small_step(const bf16_t* X, const bf16_t* Xt, const float* C, int64_t O, int64_t K, int64_t T, float two_alpha,

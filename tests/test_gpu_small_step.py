@@ -11,9 +11,10 @@ from test_gpu_variants import ADAM, BETA, LAMBDA, _bf16, _check_gradient, _mm
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 16, 1), (16, 32, 16), (250, 256, 64), (256, 256, 64), (33, 240, 65), (1024, 256, 64), (1000, 144, 113),
-          (64, 1024, 16), (16, 32, 400), (9, 16, 1024)]
-# more activations than it takes, or more workgroups than there are slots for the next step's sums
-BEYOND = [(256, 272, 64), (256, 128, 129), (17, 48, 63), (128, 16, 1024), (512, 80, 200)]
+          (16, 32, 400), (9, 16, 960), (256, 256, 128), (256, 272, 64), (90, 320, 61), (256, 128, 129), (4090, 128, 256)]
+# more activations than it takes, more columns a wavefront than it is fast with, or more workgroups than there are slots for the next
+# step's sums
+BEYOND = [(64, 1024, 16), (256, 512, 32), (64, 336, 64), (256, 272, 65), (256, 256, 129), (17, 48, 63), (9, 16, 961), (128, 16, 1024), (512, 80, 200)]
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -52,6 +53,12 @@ def test_small_step(O, K, T, dtype):
                 assert torch.allclose(a, b, rtol=2e-7, atol=0.0), (k, a, b)
             else:
                 assert torch.equal(a, b), k
+        # the bits of the products on their own, which a step with dX of its own gradient takes
+        if not with_h and O % 8 == 0:
+            V2, m2, u2 = V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)
+            faar.faar_layer_step(W, sg, scales, V2, m2, u2, X, Xt, C, icodes, BETA, LAMBDA, alpha, *ADAM, 1, torch.zeros_like(losses),
+                                 faar.layer_step_workspace(O, K, T, chained=True), dX=torch.empty_like(X))
+            assert torch.equal(V, V2) and torch.equal(m, m2) and torch.equal(u, u2)
         # told of another step's forward: NaN losses, nothing touched, and no forward is left for anyone
         state = [V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)]
         step(*state, BETA, 5, losses, 13.0, False)
