@@ -107,11 +107,11 @@ class HipEvents:
         return float(ms.value)
 
 
-def product_updates_v(form, O, K, T) -> bool:
+def product_updates_v(form, O, K, T, with_dx=False) -> bool:
     """Whether a step's dW (Gram-form) product ends in the pass over V, m, u, by the library's own answer."""
     from paper_2603_22370_amd import binding as fb
     which = (fb.K_GEMM_DW, T) if form == "token" else (fb.K_GEMM_GRAM, 1)
-    return fb.faar_gemm_form(which[0], O, K, which[1]) == fb.FORM_UPDATES_V
+    return bool(fb.faar_gemm_form(which[0], O, K, which[1]) & (fb.FORM_UPDATES_V_WITH_DX if with_dx else fb.FORM_UPDATES_V))
 
 
 class KernelTimer:
@@ -644,7 +644,7 @@ def run_block_chained(args) -> dict:
         total_flops += 3 * flops
         row = {}
         kinds = [("gemm_residual", fb.K_GEMM_RESIDUAL), ("gemm_dw", fb.K_GEMM_DW), ("gemm_dx", fb.K_GEMM_DX)]
-        if not product_updates_v("token", O, K, T):
+        if not product_updates_v("token", O, K, T, with_dx=True):
             kinds.append(("bwd_adam", fb.K_BWD_ADAM))
         for kname, kid in kinds:
             ms = timer.time(kid, lambda i: step_linear(L), 6)

@@ -177,6 +177,7 @@ enum {
                                * Gram form's is then on 192-wide tiles where these need fewer rounds of the compute units */
   FAAR_FORM_WALKS_TILES = 2,  /* 256 workgroups walk the tiles of the plan */
   FAAR_FORM_WHOLE_STEP = 4,   /* the whole step is one launch: nothing of the plan applies */
+  FAAR_FORM_UPDATES_V_WITH_DX = 16,  /* FAAR_K_GEMM_DW: the same in a step that produces dX (FAAR_FORM_UPDATES_V: in one that does not) */
   FAAR_FORM_ON_COPY = 8       /* FAAR_K_GEMM_DX: on a transposed copy of W_q, with the kernels of FAAR_K_GEMM_FWD */
 };
 int faar_gemm_form(int which, int64_t O, int64_t K, int64_t T);

@@ -235,7 +235,7 @@ def faar_gemm_plan(which: int, O: int, K: int, T: int):
     return GEMM_KINDS[out[0] - GEMM_L64], int(out[1]), int(out[2]), int(out[3])
 
 
-FORM_UPDATES_V, FORM_WALKS_TILES, FORM_WHOLE_STEP, FORM_ON_COPY = 1, 2, 4, 8
+FORM_UPDATES_V, FORM_WALKS_TILES, FORM_WHOLE_STEP, FORM_ON_COPY, FORM_UPDATES_V_WITH_DX = 1, 2, 4, 8, 16
 
 
 def faar_gemm_form(which: int, O: int, K: int, T: int) -> int:

@@ -530,7 +530,8 @@ int faar_gemm_form(int which, int64_t O, int64_t K, int64_t T) {
     case FAAR_K_GEMM_RESIDUAL_H:
       if (small_step(O, K, T)) return FAAR_FORM_WHOLE_STEP;
       return gemm_tn_usable(O, K, T) && gemm_bf16_walks(forward) ? FAAR_FORM_WALKS_TILES : 0;
-    case FAAR_K_GEMM_DW: return gemm_dw_updates(O, K, padded_tokens(T)) ? FAAR_FORM_UPDATES_V : 0;
+    case FAAR_K_GEMM_DW:
+      return (gemm_dw_updates(O, K, T, false) ? FAAR_FORM_UPDATES_V : 0) | (gemm_dw_updates(O, K, T, true) ? FAAR_FORM_UPDATES_V_WITH_DX : 0);
     case FAAR_K_GEMM_GRAM: return K <= kMaxElems / K && gemm_gram_updates(O, K) ? FAAR_FORM_UPDATES_V : 0;
     case FAAR_K_GEMM_FWD: return gemm_bf16_walks(forward) ? FAAR_FORM_WALKS_TILES : 0;
     case FAAR_K_GEMM_DX:
@@ -589,9 +590,9 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
   // The constant part of the gradient is carried separately when the caller provides it -- unless dX has to come
   // from the locally derived dY, which then must contain the constant
   const float* Hs = (H && !(dX && !dY_ext)) ? H : nullptr;
-  // A dW product that is not split ends in the pass over V, and so comes before dX where the next step's W_q may not overwrite this
-  // one's: the two take turns between W_q's place and that of the gradient, which does not exist then
-  const bool in_dw = gemm_dw_updates(O, K, L.Tp);
+  // Where the dW product ends in the pass over V, the next step's W_q may not overwrite this one's, which dX may still need: the two
+  // take turns between W_q's place and that of the gradient, which does not exist then
+  const bool in_dw = gemm_dw_updates(O, K, T, dX != nullptr);
   bf16_t* wq_full = chained && dX ? reinterpret_cast<bf16_t*>(base + L.wq_full) : nullptr;
   bf16_t* wq_next = wq_full;
   if (in_dw && wq_full) (opt->t & 1 ? wq_full : wq_next) = reinterpret_cast<bf16_t*>(G);
@@ -683,8 +684,32 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
     if (!token_major)
       if (int e = hip_status(launch_transpose_bf16(dY_used, T, O, dYt, L.Tp, st))) return e;
   }
-  // s3: G = dY^T X_q, contraction over tokens, split for occupancy
   const bool tn = token_major || rows_form;
+  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of dY^T, which then must
+  // have been read
+  const bool transposed = dX && transposed_dx(O, K, T);
+  auto input_gradient = [&]() -> int {
+    const int64_t Op = round_up(O, 64);
+    if (transposed)
+      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dYt, Op, st))) return e;
+    Bracket b(FAAR_K_GEMM_DX, st);
+    return hip_status(transposed ? launch_gemm_bf16(dY_used, dYt, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
+                                 : launch_gemm_bf16_nn(dY_used, wq_full, GemmDims{T, K, O, O, K}, static_cast<bf16_t*>(dX), st));
+  };
+  // The update streams V, m, u through the caches: dX, which reads dY as the GEMM before it or dW has left it there, comes first (us, dW
+  // first / dX first / the update on its own: 3072x3072 at 4096 tokens 305 / 287 / 294, 2432x2832 at 3221 215 / 201 / 213, 1920x6464 at
+  // 1344 248 / 238 / 248) -- but not of wide layers over many tokens, whose dX pushes X out (2048x8192 at 4096 444 / 455 / 464,
+  // 2048x6144 at 12288 856 / 885 / 878), small tiles (576x6080 at 4164 138 / 141 / 145), nor over an operand of dW that the caller
+  // wants overwritten
+  auto apart = [&](const void* p, int64_t cols) {
+    const char *x = static_cast<const char*>(p), *y = static_cast<const char*>(dX);
+    return !p || x + T * cols * 2 <= y || y + T * K * 2 <= x;
+  };
+  const bool dx_first = in_dw && dX && gemm_dx_before_dw(O, K, T) && !(transposed && !tn) && apart(Xq, K) && apart(dY_ext, O) &&
+                        apart(Xt, (K * L.Tp + T - 1) / T);
+  if (dx_first)
+    if (int e = input_gradient()) return e;
+  // s3: G = dY^T X_q, contraction over tokens, split for occupancy
   const bf16_t* dw_a = tn && !rows_form ? dY_used : dYt;
   const bf16_t* dw_b = tn ? xq : static_cast<const bf16_t*>(Xt);
   const GemmDims d2 = tn ? GemmDims{O, K, T, O, K} : GemmDims{O, K, L.Tp, L.Tp, L.Tp};
@@ -698,18 +723,8 @@ int faar_layer_step(const void* W, faar_dtype wdt, int64_t O, int64_t K, const f
                                  : launch_gemm_f32(dw_a, dw_b, d2, G, L.n_split, st)))
       return e;
   }
-  // s4: dX = dY W_q, on W_q as it lies or, where that is faster, on a transposed copy of it -- in the place of dY^T, which nothing
-  // reads after the dW GEMM
-  if (dX) {
-    const int64_t Op = round_up(O, 64);
-    const bool transposed = transposed_dx(O, K, T);
-    if (transposed)
-      if (int e = hip_status(launch_transpose_bf16(wq_full, O, K, dYt, Op, st))) return e;
-    Bracket b(FAAR_K_GEMM_DX, st);
-    if (int e = hip_status(transposed ? launch_gemm_bf16(dY_used, dYt, GemmDims{T, K, O, O, Op}, static_cast<bf16_t*>(dX), nullptr, st)
-                                      : launch_gemm_bf16_nn(dY_used, wq_full, GemmDims{T, K, O, O, K}, static_cast<bf16_t*>(dX), st)))
-      return e;
-  }
+  if (dX && !dx_first)
+    if (int e = input_gradient()) return e;
   if (in_dw) return FAAR_OK;
   Bracket b(FAAR_K_BWD_ADAM, st);
   return hip_status(launch_step_bwd_adam(a, st));

@@ -257,7 +257,7 @@ struct EpiStep {
   static constexpr bool kLateFetch = kGram;  // the first fetch after the first strips have left their registers
   static constexpr bool kChunked = true;     // the main loop hands it runs of 8 columns with what fetch() brought for them
   StepUpdate p;
-  GramOperands gr;           // kGram: see EpiGramStep
+  GramOperands gr;           // kGram only
   float sg, xs;
   double rsum, cross;   // 96 to 128 weights a lane: their runs of 8 meet in double
   bool valid;
@@ -1386,7 +1386,8 @@ struct Plan {
 // (Tiles with one side of 192 would fill units that these leave idle: alone, the Gram-form product of a 2048x6144 layer takes 165
 // instead of 175 us on them, single-stream steps of layers 768 to 2304 wide 3-5 % less.  They move more bytes a flop, which costs
 // where other streams use those units: seven linears on three streams 1.3-4.1 % more, three Gram-form jobs of 2304x2304 12 %, of
-// 2048x6144 7 %.  So only the token-major dW GEMM of a step that is said to be alone takes them, gemm_tn_tiles.)
+// 2048x6144 7 %.  So only the token-major dW GEMM of a step that is said to be alone takes them, gemm_tn_tiles, and the Gram-form
+// product that ends in the pass over V, which saves as much as they cost there, gram_update_tiles.)
 struct EpiCost { float read_bytes, write_bytes; };  // per output element
 
 constexpr double kSliceUs[KINDS] = {1.666, 1.104, 0.66, 0.42};
@@ -1420,6 +1421,9 @@ constexpr EpiCost kEpiGram{2.0f, 4.0f}, kEpiResidual{4.0f, 2.0f}, kEpiF32{0.0f, 
 // kB: the B operand is [Kd, ldb] (kNN)
 template <bool kB = false, class Epi>
 hipError_t run(const bf16_t* A, const bf16_t* B, GemmDims d, Plan p, Epi epi, hipStream_t st) {
+  if constexpr (Chunked<Epi>::value) {
+    if (p.items() > epi.p.n_next) return hipErrorInvalidValue;
+  }
   const bool tail = d.Kd % DBK64 != 0;
   const int ksteps = static_cast<int>((d.Kd + DBK64 - 1) / DBK64);
   const int per_split = (ksteps + p.n_split - 1) / p.n_split;
@@ -1572,16 +1576,33 @@ static int fewest_rounds(int64_t M, int64_t N, int n_split, int64_t most = INT64
 // step, 23.2 this way; 400x1024 at 300, 64: 23.1 / 23.7; 1280x1280 at 320, 200: 32.6 / 29.8; 1024x1024 at 64, 128: 24.8 / 23.2).
 constexpr int64_t kUpdateMinItems = 96;
 // The Gram form's loss waits for the last of its workgroups, about 4 us, which smaller layers do not get back (768x768 17.1 -> 20.5
-// us, 1000x1488 27.7 -> 30.7, 1024x2048 32.7 -> 33.0; 2048x2048 49.1 -> 48.2).
+// us, 1000x1488 27.7 -> 30.7, 1024x2048 32.7 -> 33.0; 2048x2048 49.1 -> 48.2); nor do larger ones that leave units idle (below).
 constexpr int64_t kGramUpdateMin = (int64_t)1 << 22;
 constexpr int64_t kUpdateMaxColumns = 1 << 21;   // 256 rows of them, 4 bytes each, are 32-bit offsets
 // What the plan splits stays split, although a single sum with the update behind it can be faster (6144x2048 at 16384 tokens, 4 splits of
 // 192 tiles and a pass over V that reads four gradients 433 us; one sum that ends in it 403): rounding errors grow with the root of a
 // sum's length, and the gradient there was 7.9e-7 of its norm from 64 bits that way, 4.4e-7 as four partial sums.
 // A work item leaves one partial sum of the next step's losses, for which there are step_bwd_blocks(O K) slots.
-bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp) {
+// In several rounds of the compute units the last one's update runs on those that it has work for, and the pass of its own on all of
+// them: worth it from 13/16 of the rounds' places on, of three 256x256 rounds from 7/8 on (time over that with a pass of its own; at
+// 0.69-0.79: 4208x7760 at 1920 tokens 1.08, 5440x6576 at 3136 1.05, 4672x7104 at 4475 1.05; two rounds at 0.81-0.86: 4096x6784 at 704 0.96,
+// 5120x5184 at 1680 0.98, 5440x5040 at 2368 1.00; three: (0.84) 7040x5680 at 5056 1.03, (0.87) 5760x7344 at 704 1.02, (0.91) 6528x6848 at
+// 1408 0.95; with 256x128 tiles and no dX from 3/4 on, 4096x4672 at 970, 0.77, 0.93).  One round: with dX, which finds less in the
+// caches (with_dx), on transposed operands not of fewer than 192 large tiles over many tokens (2432x4048 at 3062 1.05, 7360x1344 at
+// 1561 1.04; 1728x5952 at 1234 0.89; 4224x3264 at 1565, 221 tiles, 0.95).
+bool gemm_dw_updates(int64_t O, int64_t K, int64_t T, bool with_dx) {
+  const int64_t Tp = padded_tokens(T);
   const Plan p = plan_gemm(GemmDims{O, K, Tp, Tp, Tp}, true, kEpiF32);
-  return p.n_split == 1 && p.items() >= kUpdateMinItems && p.items() <= step_bwd_blocks(O * K) && K <= kUpdateMaxColumns;
+  if (p.n_split != 1 || p.items() < kUpdateMinItems || p.items() > step_bwd_blocks(O * K) || K > kUpdateMaxColumns) return false;
+  const int64_t rounds = (p.items() + 255) / 256;
+  const int least = p.kind == KIND_M64 && !with_dx ? 12 : p.kind == KIND_L64 && rounds > 2 ? 14 : 13;
+  if (rounds > 1 && p.items() * 16 < rounds * 256 * least) return false;
+  return !(with_dx && p.kind == KIND_L64 && p.items() < 192 && T >= 1408 && !gemm_tn_usable(O, K, T));
+}
+bool gemm_dx_before_dw(int64_t O, int64_t K, int64_t T) {
+  const int64_t Tp = padded_tokens(T);
+  const Plan p = plan_gemm(GemmDims{O, K, Tp, Tp, Tp}, true, kEpiF32);
+  return (p.kind == KIND_L64 || p.kind == KIND_M64) && !(K > 2 * O && T * O >= (int64_t)1 << 23);
 }
 
 template <typename WT>
@@ -1597,25 +1618,46 @@ static hipError_t run_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bo
 
 hipError_t launch_gemm_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bool tn, bool fill_device, const StepBwdArgs& a,
                                  hipStream_t st) {
-  if (!gemm_dw_updates(d.M, d.N, d.Kd) || d.lda % 8 != 0 || d.ldb % 8 != 0) return hipErrorInvalidValue;
+  if (plan_gemm(GemmDims{d.M, d.N, padded_tokens(d.Kd), 0, 0}, true, kEpiF32).n_split != 1 || d.N > kUpdateMaxColumns || d.lda % 8 != 0 ||
+      d.ldb % 8 != 0)
+    return hipErrorInvalidValue;
   return a.w_bf16 ? run_dw_update<bf16_t>(A, B, d, tn, fill_device, a, st) : run_dw_update<float>(A, B, d, tn, fill_device, a, st);
 }
 
+// 256 x 256 tiles become 192-wide ones where these need fewer rounds of the compute units, weighted by the tile's area, as in
+// gemm_tn_tiles
+static int gram_update_tiles(int64_t O, int64_t K, Plan* p) {
+  *p = plan_gemm(GemmDims{O, K, K, K, K}, true, kEpiGram);
+  const int tiles = p->kind != KIND_L64 ? 1 : fewest_rounds(O, K, 1);
+  if (tiles == 2) p->tiles_m = ceil_div(O, 192);
+  if (tiles == 3) p->tiles_n = ceil_div(K, 192);
+  return tiles;
+}
+
 bool gemm_gram_updates(int64_t O, int64_t K) {
-  const Plan p = plan_gemm(GemmDims{O, K, K, K, K}, true, kEpiGram);
-  return p.n_split == 1 && O * K >= kGramUpdateMin && K <= kUpdateMaxColumns && 2 * p.items() <= step_bwd_blocks(O * K);
+  Plan p;
+  const int tiles = gram_update_tiles(O, K, &p);
+  if (p.n_split != 1 || O * K < kGramUpdateMin || K > kUpdateMaxColumns || 2 * p.items() > step_bwd_blocks(O * K)) return false;
+  // The update on the units that the tiles occupy against one on all of them (time over that of two launches; share of the rounds' places
+  // in brackets).  One round on 192-wide tiles, which the product alone would be faster on: 0.83-0.95.  On 256x128, by their weights:
+  // 8192x544 1.04, 5376x880 1.04, 4992x1024 0.99, 5120x1280 0.94.  Otherwise from 0.9 on: (0.78) 7168x1792 1.06, (0.88) 14336x896 1.08,
+  // (0.90) 5136x2688 0.98, (0.94) 7680x1920 0.96, (1) 8192x2048 0.88; in several rounds (0.73) 5696x2976 1.09, (0.82) 6720x3712 1.05,
+  // (0.87) 5760x3648 1.00, (0.91) 4368x6464 1.00, (0.94) 7168x4736 0.95; on 128x128 (1) 2048x2048 0.96, (0.94) 1408x5632 0.90 -- but not
+  // where the product is most of it: 8128x5712 in three rounds 1.02, 8192x8192 in four 1.02 to 1.13
+  const int64_t rounds = (p.items() + 255) / 256;
+  if (rounds == 1 && tiles != 1) return true;
+  if (rounds == 1 && p.kind == KIND_M64) return O * K >= (int64_t)5 << 20;
+  return p.items() * 10 >= rounds * 256 * 9 && rounds <= (p.kind == KIND_L64 && tiles == 1 ? 2 : 3);
 }
 
 template <typename WT>
 static hipError_t run_gram_update(const bf16_t* delta, const bf16_t* gram, const GemmDims& d, const GramOperands& g, StepBwdArgs a,
                                   hipStream_t st) {
-  const Plan p = plan_gemm(d, true, kEpiGram);
-  // 192-wide tiles where these need fewer rounds of the compute units, weighted by the tile's area, as in gemm_tn_tiles.  Alone they
-  // are worth 20 of 241 us on 2048x6144; beside other streams 256x256 tiles would be faster (seven Gram-form jobs on three streams:
-  // 12.0 k steps/s on those, 11.0 k this way, 11.0 k with the pass over V on its own)
-  const int tiles = p.kind != KIND_L64 ? 1 : fewest_rounds(d.M, d.N, 1);
-  const int tm = tiles == 2 ? ceil_div(d.M, 192) : p.tiles_m, tn = tiles == 3 ? ceil_div(d.N, 192) : p.tiles_n;
-  a.n_mse = (int64_t)tm * tn;
+  // 192-wide tiles are worth 20 of 241 us on 2048x6144 alone; beside other streams 256x256 tiles would be faster (seven Gram-form jobs
+  // on three streams: 12.0 k steps/s on those, 11.0 k this way, 11.0 k with the pass over V on its own)
+  Plan p;
+  const int tiles = gram_update_tiles(d.M, d.N, &p), tm = p.tiles_m, tn = p.tiles_n;
+  a.n_mse = p.items();
   const EpiStep<WT, true> e{step_update(a), g, 0.0f, 1.0f, 0.0, 0.0, true, 0.0};
   if (tiles == 1) return run(delta, gram, d, p, e, st);
   const int ksteps = static_cast<int>((d.Kd + DBK64 - 1) / DBK64);
@@ -1661,7 +1703,8 @@ int gemm_tn_tiles(int64_t M, int64_t N, int64_t T, bool fill_device) {
   const Plan p = plan_gemm(GemmDims{M, N, T, T, T}, true, kEpiF32);
   if (p.kind != KIND_L64) return 0;
   if (!fill_device) return 1;
-  return fewest_rounds(M, N, p.n_split, gemm_dw_updates(M, N, T) ? step_bwd_blocks(M * N) : INT64_MAX);
+  const int64_t slots = step_bwd_blocks(M * N);   // of a product that updates V, one a work item
+  return fewest_rounds(M, N, p.n_split, p.n_split == 1 && p.items() <= slots ? slots : INT64_MAX);
 }
 bool gemm_tn_usable(int64_t M, int64_t N, int64_t T) { return gemm_tn_tiles(M, N, T, false) != 0; }
 

@@ -231,7 +231,8 @@ hipError_t launch_gemm_f32_tn(const bf16_t* A, const bf16_t* B, GemmDims d, floa
                               hipStream_t st);
 // The dW product of a step that ends in the pass over V (StepBwdArgs; its G, n_split and split_stride are not used): where the plan
 // does not split it.  A, B as for launch_gemm_f32_tn (tn) or launch_gemm_f32
-bool gemm_dw_updates(int64_t O, int64_t K, int64_t Tp);
+bool gemm_dw_updates(int64_t O, int64_t K, int64_t T, bool with_dx);
+bool gemm_dx_before_dw(int64_t O, int64_t K, int64_t T);   // ... and in such a step with dX, whether dX comes first
 hipError_t launch_gemm_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, bool tn, bool fill_device, const StepBwdArgs& a,
                                  hipStream_t st);
 // The same for the Gram form's product (a.delta_next must not be delta); partials: one double per work item

@@ -106,7 +106,8 @@ VARIANT_SHAPES = [
     (12288, 192, 640), (14336, 560, 64), (48, 2064, 4096), (64, 2064, 4096), (160, 2064, 4096), (432, 2064, 4096),
     (14336, 640, 192), (14336, 528, 512), (14336, 560, 512), (14336, 560, 640),                                     # dY token-major
     (520, 4096, 16384), (4104, 1280, 8192),                                                                         # dX on W_q^T
-    (12288, 5584, 64), (12288, 5616, 64), (12288, 6144, 64),                  # Gram form: 256x256, too many tiles to end in the pass over V
+    (8256, 1360, 64), (8256, 1392, 64), (8256, 1408, 64), (7552, 560, 64),            # Gram form: a pass over V of its own, 256x256, 256x128
+    (3072, 5584, 64), (3072, 5584, 300), (6144, 4112, 64), (6144, 4112, 192),         # dW: likewise, whole, 256x128 and 256x256
 ]
 
 BY_NAME = {c.name: c for c in STEP_CASES + GRAM_CASES}

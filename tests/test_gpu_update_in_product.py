@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 DW = [(1056, 656, 64, False), (648, 2816, 64, False), (648, 5408, 64, False), (7176, 1088, 65, False), (7176, 1088, 64, False),
       (7176, 1088, 64, True), (6224, 1808, 64, True), (5120, 20480, 64, True)]
 # M64, S64, then L64: 256x256, 192x256, 256x192; contractions that end inside a slice and that do not
-GRAM = [(6496, 656), (3912, 1088), (6496, 1232), (6496, 1808), (7176, 1664), (7176, 1088), (6632, 1232), (7040, 1664), (8128, 1376),
-        (8280, 1392)]
+GRAM = [(8872, 592), (8432, 624), (8200, 640), (6496, 1232), (8192, 512), (8256, 1552), (8256, 1584), (8256, 1600), (7176, 1088), (6632, 1232),
+        (7040, 1664), (8128, 1376)]
 
 
 def _layer(O, K, T, dtype):
@@ -45,7 +45,8 @@ def _steps(step, V0, prepared, betas=(BETA, 13.0, 14.5)):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("O,K,T,alone", DW)
 def test_weight_gradient_that_updates_v(O, K, T, alone, dtype):
-    assert fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)[3] == 1 and fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T) == fb.FORM_UPDATES_V
+    assert fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)[3] == 1
+    assert fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T) == fb.FORM_UPDATES_V | fb.FORM_UPDATES_V_WITH_DX
     W, X, Y, sg, scales, V0, gen = _layer(O, K, T, dtype)
     Xt, C, icodes, H, c_norm2 = faar.faar_layer_prepare(W, sg, scales, X, Y, gradient_constant=True)
     alpha = 1.0 / (T * O)
@@ -74,6 +75,24 @@ def test_weight_gradient_that_updates_v(O, K, T, alone, dtype):
                 assert torch.allclose(a, b, rtol=2e-7, atol=0.0), (k, a, b)
             else:
                 assert torch.equal(a, b), k
+
+
+@pytest.mark.parametrize("T", [64, 65])
+def test_input_gradient_in_the_place_of_the_activations(T):
+    """dX comes before the product that updates V where that is faster, but not where it would overwrite an operand of it."""
+    O, K = 7176, 1088
+    W, X, Y, sg, scales, V0, gen = _layer(O, K, T, torch.bfloat16)
+    Xt, C, icodes = faar.faar_layer_prepare(W, sg, scales, X, Y)
+    dY = (1e-3 * torch.randn((T, O), generator=gen, device="cuda")).to(torch.bfloat16)
+    ws = faar.layer_step_workspace(O, K, T, chained=True)
+    runs = []
+    for in_place in (False, True):
+        x, state = X.clone(), [V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)]
+        dX = x if in_place else torch.empty_like(x)
+        faar.faar_layer_step(W, sg, scales, *state, x, Xt, C, icodes, BETA, LAMBDA, 1.0 / (T * O), *ADAM, 1,
+                             torch.zeros(3, dtype=torch.float32, device="cuda"), ws, dY_ext=dY, dX=dX)
+        runs.append([*state, dX])
+    assert all(torch.equal(a, b) for a, b in zip(*runs))
 
 
 def _distance_from_64_bits(O, K, T, alone):

@@ -165,7 +165,7 @@ def test_products_that_update_v_have_a_slot_for_every_work_item():
     rows = [96, 800, 2560, 5120, 6144, 6656, 8192, 10240, 14592, 16640, 17920, 18432, 20480, 24576, 65536]
     seen = set()
     for O, K, T in itertools.product(rows + [8 * n for n in range(600, 2600, 37)], [r // 16 * 16 for r in rows], [64, 512, 2048, 8192, 16384]):
-        if O * K > 2 ** 28 or O * K * T > 2 ** 42 or fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T) != fb.FORM_UPDATES_V:
+        if O * K > 2 ** 28 or O * K * T > 2 ** 42 or not fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T):
             continue
         slots = min(2048, -(-O * K // 2048))
         _, bm, bn, split = fb.faar_gemm_plan(fb.K_GEMM_DW, O, K, T)
@@ -177,6 +177,24 @@ def test_products_that_update_v_have_a_slot_for_every_work_item():
                 assert -(-O // bm) * -(-K // bn) <= slots, (O, K, T, alone)
                 seen.add((alone, tiles))
     assert seen == {(False, 1), (True, 1), (True, 2), (True, 3)}
+
+
+def test_forms_are_taken_where_they_were_measured_to_be_faster():
+    """On both sides of the lines that the rules draw: shapes that took longer in one launch, with the update inside a product, or
+    with it on fewer compute units."""
+    form = fb.faar_gemm_form
+    for O, K in [(2048, 2112), (4352, 1024), (4096, 1088), (8192, 544), (3584, 3584), (7168, 1792), (5696, 2976), (8128, 5712), (8192, 8192)]:
+        assert form(fb.K_GEMM_GRAM, O, K, 1) == 0, (O, K)
+    for O, K in [(2048, 2048), (2048, 6144), (6144, 2048), (2560, 2560), (3072, 3072), (4096, 4096), (2048, 8192), (7168, 4736)]:
+        assert form(fb.K_GEMM_GRAM, O, K, 1) == fb.FORM_UPDATES_V, (O, K)
+    both = fb.FORM_UPDATES_V | fb.FORM_UPDATES_V_WITH_DX
+    for O, K, T, want in [(4208, 7760, 1920, 0), (5440, 6576, 3136, 0), (5760, 7344, 704, 0), (2432, 4048, 3062, fb.FORM_UPDATES_V),
+                          (2816, 5968, 324, 0), (4480, 4224, 1984, fb.FORM_UPDATES_V), (1728, 5952, 1234, both), (3072, 3072, 4096, both),
+                          (6144, 2048, 8192, both), (2048, 8192, 4096, both), (4096, 6784, 704, both)]:
+        assert form(fb.K_GEMM_DW, O, K, T) == want, (O, K, T)
+    for O, K, T, want in [(64, 1024, 16, 0), (256, 512, 32, 0), (256, 384, 64, 0), (256, 320, 96, 0), (256, 256, 192, 0), (256, 256, 128, 4),
+                          (1024, 128, 256, 4), (256, 320, 64, 4)]:
+        assert form(fb.K_GEMM_RESIDUAL, O, K, T) == want, (O, K, T)
 
 
 STAGES = {"L64": 2, "M64": 3, "S64": 4, "N64": 6}      # slices the ring of a tile shape holds
@@ -205,11 +223,12 @@ def _gram_instantiation(O, K):
     return x
 
 
-def _dw_instantiations(O, K, T, alone, nt=True):
-    """The dW product on transposed operands (nt: where a step of the caller's takes them) and on the token-major ones."""
+def _dw_instantiations(O, K, T, alone, nt=True, with_dx=False):
+    """The dW product on transposed operands (nt: a step of the caller's takes them also where the token-major ones would do) and on the
+    token-major ones, in a step that produces dX or in one that does not."""
     x = _instantiation("dw", fb.K_GEMM_DW, (T + 63) // 64 * 64, O, K, T)
     tiles = fb.faar_dw_token_major(O, K, T, alone)
-    if fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T) & fb.FORM_UPDATES_V:
+    if fb.faar_gemm_form(fb.K_GEMM_DW, O, K, T) & (fb.FORM_UPDATES_V_WITH_DX if with_dx else fb.FORM_UPDATES_V):
         assert x[2] == "one"
         if nt or not tiles:
             yield ("update", x[1])
@@ -236,9 +255,11 @@ def _instantiations(O, K, T, chained=True, forward=True, alone=(False,), own_dx=
         yield _walk("rows" if fb.faar_dw_token_major(O, K, T) else "perturbation", fb.K_GEMM_RESIDUAL_H, K, O, K, T)
     if not small or chained and own_dx:
         yield _instantiation("residual", fb.K_GEMM_RESIDUAL, K, O, K, T)
-    if not small or chained:
-        for a in alone:
+    for a in alone:
+        if not small:
             yield from _dw_instantiations(O, K, T, a)
+        if chained:
+            yield from _dw_instantiations(O, K, T, a, own_dx, True)
     yield _instantiation("c", fb.K_GEMM_C, K, O, K, T)
     yield _gram_instantiation(O, K)
     if chained:
@@ -273,7 +294,8 @@ def test_every_gemm_instantiation_is_compared_with_an_oracle():
     for shape in VARIANT_SHAPES:
         covered.update(_instantiations(*shape))
     for O, K, T, alone in UPDATE_DW:
-        covered.update(_dw_instantiations(O, K, T, alone, nt=False))
+        covered.update(_dw_instantiations(O, K, T, alone, False))
+        covered.update(_dw_instantiations(O, K, T, alone, False, True))
     covered.update(_gram_instantiation(O, K) for O, K in UPDATE_GRAM)
     covered.update(x for O, K, T in SMALL_SHAPES for x in _instantiations(O, K, T, False, False) if x[0] == "small")
     covered.update(_walk("forward", fb.K_GEMM_FWD, K, O, K, T) for O, K, T in WALKED_FORWARD)
