@@ -52,29 +52,40 @@ def test_weight_gradient_that_updates_v(O, K, T, alone, dtype):
     alpha = 1.0 / (T * O)
     dY = (1e-3 * torch.randn((T, O), generator=gen, device="cuda")).to(torch.bfloat16)
 
-    def step(chained, ws, V, m, u, beta, t, losses, nxt, ready):
+    def step(chained, own, ws, V, m, u, beta, t, losses, nxt, ready):
         dX = torch.empty((T, K), dtype=torch.bfloat16, device="cuda") if chained else None
         faar.faar_layer_step(W, sg, scales, V, m, u, X, Xt, C, icodes, beta, LAMBDA, alpha, *ADAM, t, losses, ws,
-                             dY_ext=dY if chained else None, dX=dX, beta_next=nxt, forward_ready=ready, H=H, c_norm2=c_norm2,
+                             dY_ext=dY if chained and not own else None, dX=dX, beta_next=nxt, forward_ready=ready, H=H, c_norm2=c_norm2,
                              whole_device=alone)
         return [dX] if chained else []
 
-    for chained in (False, True):
+    delta = faar.faar_softquant_fwd_bwd(W, sg, scales, V0, BETA, emit_delta=True)[0].double()
+    for chained, own in ((False, False), (True, False), (True, True)):      # own: dX of the step's own gradient
         ws = faar.layer_step_workspace(O, K, T, chained=chained)
         V, m, u = V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)
-        step(chained, ws, V, m, u, BETA, 1, torch.zeros(3, device="cuda"), 0.0, False)
-        if chained:
+        step(chained, own, ws, V, m, u, BETA, 1, torch.zeros(3, device="cuda"), 0.0, False)
+        if own:
+            c = C.flatten()[:(T + 3) // 4 * 4 * O].view(-1, O, 4).permute(0, 2, 1).reshape(-1, O).double()[:T]
+            G = _mm(_bf16(2.0 * alpha * (_mm(X.double(), delta.T) - c)).T, X.double())
+        elif chained:
             G = _mm(dY.double().T, X.double())
         else:
-            delta = faar.faar_softquant_fwd_bwd(W, sg, scales, V0, BETA, emit_delta=True)[0].double()
             G = _mm(_bf16(2.0 * alpha * _mm(X.double(), delta.T)).T, X.double()) - 2.0 * alpha * H.view(O, K).double()
         _check_gradient(m, G, W, sg, scales, V0)
-        runs = [_steps(lambda *a: step(chained, ws, *a), V0, prepared) for prepared in (False, True)]
+        runs = [_steps(lambda *a: step(chained, own, ws, *a), V0, prepared) for prepared in (False, True)]
         for k, (a, b) in enumerate(zip(*runs)):
             if a.dtype == torch.float32 and a.numel() == 3:      # the same terms, added up in other groups
                 assert torch.allclose(a, b, rtol=2e-7, atol=0.0), (k, a, b)
             else:
                 assert torch.equal(a, b), k
+        # told of another step's forward: NaN losses, nothing touched, and no forward is left for anyone
+        state = [V0.clone(), torch.zeros_like(V0), torch.zeros_like(V0)]
+        step(chained, own, ws, *state, BETA, 5, torch.zeros(3, device="cuda"), 13.0, False)
+        snap = [x.clone() for x in state]
+        for t in (7, 6):
+            bad = torch.zeros(3, dtype=torch.float32, device="cuda")
+            step(chained, own, ws, *state, 13.0, t, bad, 0.0, True)
+            assert bool(torch.isnan(bad).all()) and all(torch.equal(x, y) for x, y in zip(state, snap))
 
 
 @pytest.mark.parametrize("T", [64, 65])
