@@ -174,7 +174,8 @@ int faar_gemm_plan(int which, int64_t O, int64_t K, int64_t T, int32_t* out);
  * and no dX, FAAR_K_GEMM_DX for an operand W_q as faar_layer_step prepares it.  Pure host function. */
 enum {
   FAAR_FORM_UPDATES_V = 1,    /* FAAR_K_GEMM_DW, FAAR_K_GEMM_GRAM: the product ends in the pass over V (FAAR_K_BWD_ADAM); the
-                               * Gram form's is then on 192-wide tiles where these need fewer rounds of the compute units */
+                               * Gram form's is then on 192-wide tiles where these need fewer rounds of the compute units
+                               * and its contraction is not long */
   FAAR_FORM_WALKS_TILES = 2,  /* 256 workgroups walk the tiles of the plan */
   FAAR_FORM_WHOLE_STEP = 4,   /* the whole step is one launch: nothing of the plan applies */
   FAAR_FORM_UPDATES_V_WITH_DX = 16,  /* FAAR_K_GEMM_DW: the same in a step that produces dX (FAAR_FORM_UPDATES_V: in one that does not) */

@@ -1387,7 +1387,7 @@ struct Plan {
 // instead of 175 us on them, single-stream steps of layers 768 to 2304 wide 3-5 % less.  They move more bytes a flop, which costs
 // where other streams use those units: seven linears on three streams 1.3-4.1 % more, three Gram-form jobs of 2304x2304 12 %, of
 // 2048x6144 7 %.  So only the token-major dW GEMM of a step that is said to be alone takes them, gemm_tn_tiles, and the Gram-form
-// product that ends in the pass over V, which saves as much as they cost there, gram_update_tiles.)
+// product that ends in the pass over V, as long as that saves what they cost there, gram_update_tiles.)
 struct EpiCost { float read_bytes, write_bytes; };  // per output element
 
 constexpr double kSliceUs[KINDS] = {1.666, 1.104, 0.66, 0.42};
@@ -1625,10 +1625,14 @@ hipError_t launch_gemm_dw_update(const bf16_t* A, const bf16_t* B, GemmDims d, b
 }
 
 // 256 x 256 tiles become 192-wide ones where these need fewer rounds of the compute units, weighted by the tile's area, as in
-// gemm_tn_tiles
+// gemm_tn_tiles -- up to contractions over which they lose more beside other streams than the update saves (time over that of two
+// launches, one job / two / three side by side: 192x256 tiles 2880x4352 0.92 / 1.00 / 0.99, 2688x4608 0.91 / 1.00 / 0.99, 2048x5120
+// 0.98 / 1.02 / 1.03, 2304x5376 0.89 / 0.97 / 1.02, 7168x4736 0.94 / 1.04 / 1.01; 256x192 5888x2112 0.93 / 1.00 / 0.98, 4608x2688
+// 0.94 / 0.96 / 0.99, 4096x3072 0.93 / 1.03 / 1.03, 2048x6144 0.92 / 1.05 / 1.05)
 static int gram_update_tiles(int64_t O, int64_t K, Plan* p) {
   *p = plan_gemm(GemmDims{O, K, K, K, K}, true, kEpiGram);
-  const int tiles = p->kind != KIND_L64 ? 1 : fewest_rounds(O, K, 1);
+  const int fewest = p->kind != KIND_L64 ? 1 : fewest_rounds(O, K, 1);
+  const int tiles = fewest == 2 && K > 4608 ? 1 : fewest == 3 && K > 2688 ? 1 : fewest;
   if (tiles == 2) p->tiles_m = ceil_div(O, 192);
   if (tiles == 3) p->tiles_n = ceil_div(K, 192);
   return tiles;
@@ -1646,6 +1650,10 @@ bool gemm_gram_updates(int64_t O, int64_t K) {
   // where the product is most of it: 8128x5712 in three rounds 1.02, 8192x8192 in four 1.02 to 1.13
   const int64_t rounds = (p.items() + 255) / 256;
   if (rounds == 1 && tiles != 1) return true;
+  // where these would fill one round and the contraction is too long for them, on 256x256 tiles: level alone, and faster beside other
+  // streams, which use the units that are left (as above: 2048x6144 1.00 / 0.95 / 0.94, 1536x8192 0.96 / 0.94 / 0.93, 2304x5376 1.01 /
+  // 0.94 / 0.95; not of shorter ones, 4096x3072 1.05 / 0.93 / 0.94)
+  if (rounds == 1 && p.kind == KIND_L64 && K >= 5120 && p.items() >= 176 && fewest_rounds(O, K, 1) != 1) return true;
   if (rounds == 1 && p.kind == KIND_M64) return O * K >= (int64_t)5 << 20;
   return p.items() * 10 >= rounds * 256 * 9 && rounds <= (p.kind == KIND_L64 && tiles == 1 ? 2 : 3);
 }
@@ -1653,8 +1661,6 @@ bool gemm_gram_updates(int64_t O, int64_t K) {
 template <typename WT>
 static hipError_t run_gram_update(const bf16_t* delta, const bf16_t* gram, const GemmDims& d, const GramOperands& g, StepBwdArgs a,
                                   hipStream_t st) {
-  // 192-wide tiles are worth 20 of 241 us on 2048x6144 alone; beside other streams 256x256 tiles would be faster (seven Gram-form jobs
-  // on three streams: 12.0 k steps/s on those, 11.0 k this way, 11.0 k with the pass over V on its own)
   Plan p;
   const int tiles = gram_update_tiles(d.M, d.N, &p), tm = p.tiles_m, tn = p.tiles_n;
   a.n_mse = p.items();

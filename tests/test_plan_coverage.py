@@ -183,9 +183,11 @@ def test_forms_are_taken_where_they_were_measured_to_be_faster():
     """On both sides of the lines that the rules draw: shapes that took longer in one launch, with the update inside a product, or
     with it on fewer compute units."""
     form = fb.faar_gemm_form
-    for O, K in [(2048, 2112), (4352, 1024), (4096, 1088), (8192, 544), (3584, 3584), (7168, 1792), (5696, 2976), (8128, 5712), (8192, 8192)]:
+    for O, K in [(2048, 2112), (4352, 1024), (4096, 1088), (8192, 544), (3584, 3584), (7168, 1792), (5696, 2976), (8128, 5712), (8192, 8192),
+                 (4096, 3072), (2048, 5120), (7168, 4736)]:
         assert form(fb.K_GEMM_GRAM, O, K, 1) == 0, (O, K)
-    for O, K in [(2048, 2048), (2048, 6144), (6144, 2048), (2560, 2560), (3072, 3072), (4096, 4096), (2048, 8192), (7168, 4736)]:
+    for O, K in [(2048, 2048), (2048, 6144), (6144, 2048), (2560, 2560), (3072, 3072), (4096, 4096), (2048, 8192), (2304, 5376), (2688, 4608),
+                 (4608, 2688)]:
         assert form(fb.K_GEMM_GRAM, O, K, 1) == fb.FORM_UPDATES_V, (O, K)
     both = fb.FORM_UPDATES_V | fb.FORM_UPDATES_V_WITH_DX
     for O, K, T, want in [(4208, 7760, 1920, 0), (5440, 6576, 3136, 0), (5760, 7344, 704, 0), (2432, 4048, 3062, fb.FORM_UPDATES_V),
@@ -210,9 +212,11 @@ def _instantiation(epilogue, which, contraction, O, K, T):
 
 
 def _widths(O, K):
-    """The tile of a Gram-form product that ends in the pass over V, where the plan says 256x256: rounds of 256 units, by area."""
+    """The tile of a Gram-form product that ends in the pass over V, where the plan says 256x256: rounds of 256 units, by area, and
+    192-wide ones up to the contraction that their limit is."""
     cost = {(bm, bn): -(-(-(-O // bm) * -(-K // bn)) // 256) * bm * bn for bm, bn in ((256, 256), (192, 256), (256, 192))}
-    return min(cost, key=lambda t: (cost[t], t != (256, 256), t != (192, 256)))
+    tile = min(cost, key=lambda t: (cost[t], t != (256, 256), t != (192, 256)))
+    return tile if K <= {(256, 256): K, (192, 256): 4608, (256, 192): 2688}[tile] else (256, 256)
 
 
 def _gram_instantiation(O, K):
