@@ -11,7 +11,7 @@ LIB_PATH = os.path.join(HERE, "libfaar.so")
 SOURCES = ["faar_api.hip", "faar_elementwise.hip", "faar_gemm.hip", "faar_small.hip", "faar_stage2.hip", "faar_block.hip", "faar_attention.hip"]
 
 # -ffp-contract=off: the decision arithmetic must round once per operation (bit-exact parity).
-# packed-fp32 ops are disabled for the test machines.
+# packed-fp32 ops are off: some of their forms have given wrong results on this hardware.
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

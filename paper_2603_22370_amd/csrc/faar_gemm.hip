@@ -245,8 +245,8 @@ struct GramOperands {
 // are on their way while it works on its 8.  The losses of the step, whose partial sums are complete, are added up by workgroup 0.
 // Whole steps, us: 6144x2048 at 8192 tokens, alone 422.8 -> 396.5; 8192x2048 at 4096 346.5 -> 312; 2048x8192 at 4096 in a chain
 // 472 -> 446; 1024x2048 at 512 38.1 -> 34.5; seven linears on three streams 6.92 -> 6.78 ms.
-// kGram: the same for delta * gram (EpiGram), on the buffer of W_q - W that the next step's does not go to.  2048x6144: 241 -> 221 on
-// 256x192 tiles, 6144x2048 144 -> 132, 4096x4096 236 -> 212, 8192x2048 187 -> 164.
+// kGram: the same for delta * gram (EpiGram), on the buffer of W_q - W that the next step's does not go to.  6144x2048 145 -> 132 on
+// 192x256 tiles, 4096x4096 236 -> 212, 8192x2048 187 -> 164; 2048x6144 level alone, three jobs side by side 217 -> 203.
 template <typename WT, bool kGram = false>
 struct EpiStep {
   static constexpr bool kWarm = false;

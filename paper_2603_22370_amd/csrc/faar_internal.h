@@ -20,7 +20,8 @@ inline int64_t padded_tokens(int64_t T) { return round_up(T, 64); }
 // that follows.  The guard slot in the workspace holds kTagWords tag words followed by one verdict word: the first
 // kernel of a step either produces a fresh forward (verdict 1) or compares the stored tag with the one its caller
 // implies (verdict = equal), and in both cases clears the tag; the kernel that updates V reads the verdict, and
-// writes the tag of the next step's forward when it produces one.
+// writes the tag of the next step's forward when it produces one.  Where the first kernel is also the one that updates V, all of
+// its workgroups compare, and the one that arrives last (kArrivals) clears or replaces the tag.
 constexpr int kTagWords = 12;
 constexpr int kArrivals = kTagWords + 1;   // word of the slot in which a launch counts the workgroups that are done; 0 between launches
 struct ForwardTag { uint32_t w[kTagWords]; };
